@@ -5,6 +5,46 @@ using namespace he_bf16;
 
 namespace {
 
+// A wavefront's share of the scoring head, NA column blocks x MJ row blocks from row m0 and column n0 on.  The logits
+// never leave the registers: per row, the soft-max partials of the wavefront's 32 NA vocabulary entries (slice `part` of
+// the row) and, if the row's next token is among them, its logit.
+template <int NA, int MJ>
+__device__ __forceinline__ void score_tile(const Epi& p, const f32x16 (&acc)[NA][MJ], int m0, int n0, int part, int lane) {
+    const int nl = n0 + 4 * (lane >> 5);
+#pragma unroll
+    for (int j = 0; j < MJ; ++j) {
+        const int m = m0 + j * 32 + (lane & 31);
+        int tgt = -1;
+        if (m < p.M && m % p.S != p.S - 1) {
+            tgt = p.ids[m + 1];
+            tgt = tgt < 0 ? 0 : (tgt >= p.N ? p.N - 1 : tgt);  // clamped like the embedding's ids
+        }
+        float mx = -INFINITY;
+#pragma unroll
+        for (int i = 0; i < NA; ++i)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const int n = nl + i * 32 + 8 * (r >> 2) + (r & 3);
+                const float z = n < p.N ? acc[i][j][r] : -INFINITY;
+                mx = fmaxf(mx, z);
+                if (n == tgt) p.sc_tgt[m] = z;
+            }
+        mx = fmaxf(mx, __shfl_xor(mx, 32));
+        float sum = 0.f;
+        if (mx > -INFINITY) {
+#pragma unroll
+            for (int i = 0; i < NA; ++i)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    const int n = nl + i * 32 + 8 * (r >> 2) + (r & 3);
+                    sum += expf((n < p.N ? acc[i][j][r] : -INFINITY) - mx);
+                }
+        }
+        sum += __shfl_xor(sum, 32);
+        if (lane < 32 && m < p.M) p.sc_stats[(size_t)m * p.sc_parts + part] = make_float2(mx, sum);
+    }
+}
+
 // ----------------------------------------------------------------- tiled GEMM (prompt pass)
 //
 // 256 (n) x 128 (m) output tile per workgroup, four wavefronts in a 2x2 grid of
@@ -65,7 +105,7 @@ __global__ __launch_bounds__(256, (PAIR && MW == 2) ? 2 : 1) void gemm_tiled_ker
     const int tm = first_m + (lin % gsize) % gm, tn = (lin % gsize) / gm;
 
     const int wn = wave & 1, wm = wave >> 1;  // this wavefront's 128 (n) x 32 MW (m) sub-tile
-    const int cur_len = epilogue_len<MODE>(p);
+    [[maybe_unused]] const int cur_len = epilogue_len<MODE>(p);
     f32x16 acc[4][MW];
 #pragma unroll
     for (int i = 0; i < 4; ++i)
@@ -190,52 +230,7 @@ __global__ __launch_bounds__(256, (PAIR && MW == 2) ? 2 : 1) void gemm_tiled_ker
             mma_ops(opb);
         }
     }
-    if (MODE == MODE_SCORE) {
-        // The logits never leave the registers: per row, the soft-max partials of this wavefront's
-        // 128 vocabulary entries and, if the row's next token is among them, its logit.
-#pragma unroll
-        for (int j = 0; j < MW; ++j) {
-            const int m = tm * TMR + (wm * MW + j) * 32 + (lane & 31);
-            int tgt = -1;
-            if (m < p.M && m % p.S != p.S - 1) {
-                tgt = p.ids[m + 1];
-                tgt = tgt < 0 ? 0 : (tgt >= p.N ? p.N - 1 : tgt);  // clamped like the embedding's ids
-            }
-            float mx = -INFINITY;
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const int n = tn * TN + (wn * 4 + i) * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-                    const float z = n < p.N ? acc[i][j][r] : -INFINITY;
-                    acc[i][j][r] = z;
-                    mx = fmaxf(mx, z);
-                    if (n == tgt) p.sc_tgt[m] = z;
-                }
-            mx = fmaxf(mx, __shfl_xor(mx, 32));
-            float sum = 0.f;
-            if (mx > -INFINITY) {
-#pragma unroll
-                for (int i = 0; i < 4; ++i)
-#pragma unroll
-                    for (int r = 0; r < 16; ++r) sum += expf(acc[i][j][r] - mx);
-            }
-            sum += __shfl_xor(sum, 32);
-            if (lane < 32 && m < p.M) p.sc_stats[(size_t)m * p.sc_parts + tn * 2 + wn] = make_float2(mx, sum);
-        }
-        return;
-    }
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < MW; ++j) {
-            const int m = tm * TMR + (wm * MW + j) * 32 + (lane & 31);
-            const int nb = tn * TN + (wn * 4 + i) * 32 + 4 * (lane >> 5);
-#pragma unroll
-            for (int q = 0; q < 4; ++q)
-                epilogue4<MODE>(p, m, nb + 8 * q, ks, acc[i][j][q * 4 + 0], acc[i][j][q * 4 + 1], acc[i][j][q * 4 + 2],
-                                acc[i][j][q * 4 + 3], epilogue_bias<MODE>(p, nb + 8 * q), cur_len);
-        }
+    score_tile<4, MW>(p, acc, tm * TMR + wm * 32 * MW, tn * TN + wn * 128, tn * 2 + wn, lane);
 }
 
 // ----------------------------------------------------------------- 256 x 256 tiles (prompt and scoring passes)
@@ -268,6 +263,93 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ void store16(void* dst, u32x4 v) { *reinterpret_cast<u32x4*>(dst) = v; }
 __device__ __forceinline__ void store16(void* dst, float a, float b, float c, float d) {
     *reinterpret_cast<f32x4*>(dst) = f32x4{a, b, c, d};
+}
+
+// A wavefront's results, NA column blocks x MJ row blocks of 32 x 32 accumulators from row m0 and column n0 on.
+template <int MODE, int NA, int MJ>
+__device__ __forceinline__ void store_tile(const Epi& p, const u32x4* __restrict__ bias8, const f32x16 (&acc)[NA][MJ], int m0,
+                                           int n0, int ks, int cur_len, int lane) {
+    // Epilogue.  The CU runs nothing else meanwhile, so it is written out per mode with everything that depends on
+    // the row alone (sequence, cache position, row base address) computed once per 32-row block and everything
+    // that depends on the column alone wave-uniform (the generic per-quad form recomputes both, with run-time
+    // integer divisions, for each of a lane's 64 quads: 22 us per tile for FC1, 44 us for QKV, against 130 us of
+    // matrix instructions).  N is a multiple of 32 here, so a 32-column block is inside or outside as a whole.
+    const int hh = lane >> 5;
+#pragma unroll
+    for (int j = 0; j < MJ; ++j) {
+        const int m = m0 + j * 32 + (lane & 31);
+        if (m >= p.M) continue;
+        size_t row = 0;       // MODE_STORE: float index of (m, 4 hh); BIAS_RELU: 16-byte slot of (m, k half hh) in
+                              // the first block of its row of blocks; QKV: float index into q
+        size_t kvrow = 0;     // QKV: half index of (sequence, head 0, position, 0) inside one (layer, k|v) plane
+        bool append = true;   // QKV: the row is a token (not padding): its key and value go into the cache
+        if (MODE == MODE_STORE) {
+            row = (size_t)ks * p.out_split + (size_t)m * p.N + 4 * hh;
+        } else if (MODE == MODE_BIAS_RELU) {
+            row = (size_t)(m >> 5) * (p.N >> 4) * 64 + 32 * hh + (m & 31);
+        } else {
+            row = (size_t)m * p.H + 4 * hh;
+            const int b = row_seq(p.st, m, p.S), r = m % p.S;
+            int t = cur_len + r;
+            if (cur_len < 0) {  // sequences of different lengths; padding rows append nothing
+                const int tr = r - row_pad(p.st, b);
+                append = tr >= 0;
+                t = seq_len(p.st, b) + tr;
+            }
+            kvrow = ((size_t)b * p.n_heads * p.max_seq + t) * p.d;
+        }
+#pragma unroll
+        for (int i = 0; i < NA; ++i) {
+            const int n32 = n0 + i * 32;  // wave-uniform
+            if (n32 >= p.N) continue;
+            if (MODE == MODE_STORE) {
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    store16(p.out + row + n32 + 8 * q, acc[i][j][q * 4 + 0], acc[i][j][q * 4 + 1], acc[i][j][q * 4 + 2],
+                            acc[i][j][q * 4 + 3]);
+            } else if (MODE == MODE_BIAS_RELU) {
+                u32x4* ob = p.out_blocks + row + (size_t)(n32 >> 4) * 64;
+                uint2 h4[4];
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const u32x4 b8 = bias8[(n32 >> 3) + q];  // wave-uniform address: a scalar load
+                    const uint2 bb = hh ? make_uint2(b8.z, b8.w) : make_uint2(b8.x, b8.y);
+                    const float v0 = fmaxf(acc[i][j][q * 4 + 0] + bf_lo(bb.x), 0.f), v1 = fmaxf(acc[i][j][q * 4 + 1] + bf_hi(bb.x), 0.f);
+                    const float v2 = fmaxf(acc[i][j][q * 4 + 2] + bf_lo(bb.y), 0.f), v3 = fmaxf(acc[i][j][q * 4 + 3] + bf_hi(bb.y), 0.f);
+                    h4[q] = make_uint2(pack2(v0, v1), pack2(v2, v3));
+                }
+#pragma unroll
+                for (int qq = 0; qq < 2; ++qq) store16(ob + qq * 64, join_halves(h4[2 * qq], h4[2 * qq + 1]));
+            } else {
+                const int part = n32 >= 2 * p.H ? 2 : (n32 >= p.H ? 1 : 0);  // query, key or value columns (uniform)
+                half_t* kvcol = nullptr;
+                if (part) {
+                    const int c32 = n32 - part * p.H, head = c32 / p.d;
+                    kvcol = p.kv + (((size_t)(p.layer * 2 + (part - 1)) * p.max_batch) * p.n_heads + head) * p.max_seq * (size_t)p.d +
+                            (c32 - head * p.d);
+                }
+                uint2 h4[4];
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const u32x4 b8 = bias8[(n32 >> 3) + q];
+                    const uint2 bb = hh ? make_uint2(b8.z, b8.w) : make_uint2(b8.x, b8.y);
+                    const float v0 = acc[i][j][q * 4 + 0] + bf_lo(bb.x), v1 = acc[i][j][q * 4 + 1] + bf_hi(bb.x);
+                    const float v2 = acc[i][j][q * 4 + 2] + bf_lo(bb.y), v3 = acc[i][j][q * 4 + 3] + bf_hi(bb.y);
+                    if (!part)
+                        store16(p.out + row + n32 + 8 * q, v0 * p.qscale, v1 * p.qscale, v2 * p.qscale, v3 * p.qscale);
+                    else
+                        h4[q] = make_uint2(pack2(v0, v1), pack2(v2, v3));
+                }
+                if (part) {  // (uniform) keys / values: eight halves of a row per lane
+#pragma unroll
+                    for (int qq = 0; qq < 2; ++qq) {
+                        const u32x4 v8 = join_halves(h4[2 * qq], h4[2 * qq + 1]);
+                        if (append) store16(kvcol + kvrow + 8 * (2 * qq + hh), v8);
+                    }
+                }
+            }
+        }
+    }
 }
 
 // One matrix instruction with the accumulator tile pinned to a register file: the accumulation registers (VG =
@@ -455,87 +537,166 @@ __global__ __launch_bounds__(256, 1) void gemm_tiled256_kernel(const u32x4* __re
         mma_all(opb);
     }
     if constexpr (NA > 4) asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");  // the last matrix instructions' results are in
-    // Epilogue.  The CU runs nothing else meanwhile, so it is written out per mode with everything that depends on
-    // the row alone (sequence, cache position, row base address) computed once per 32-row block and everything
-    // that depends on the column alone wave-uniform (the generic per-quad form recomputes both, with run-time
-    // integer divisions, for each of a lane's 64 quads: 22 us per tile for FC1, 44 us for QKV, against 130 us of
-    // matrix instructions).  N is a multiple of 32 here, so a 32-column block is inside or outside as a whole.
-    const int hh = lane >> 5;
+    store_tile<MODE, NA, 4>(p, bias8, acc, tm * BM + wm * 128, tn * BN + wn * 32 * NA, ks, cur_len, lane);
+}
+
+// ----------------------------------------------------------------- 256 x 64..192 tiles on a deep ring (few rows)
+//
+// Prompt passes of too few rows to give every CU a 256 x 256 tile, and the wide decode steps.  What bounds these is not
+// the matrix cores but how fast one CU pulls operands in: about 64 KB can be outstanding per CU whatever the ring's depth,
+// a weight block takes 1.3 us from HBM and an activation block 0.45 us out of L2, so a stage (two k-blocks: 16 KiB of
+// weights, 4 MW KiB of activations) takes 0.33 / 0.39 / 0.43 us for MW = 1 / 2 / 3, and a launch is fast when it has
+// a workgroup on every CU.  Hence: tiles of 64 MW rows so that few rows are padding, each cut into k ranges until the
+// CUs are covered (ring_plan), and as many stages in flight as LDS holds (8 / 6 / 5).  The schedule is the big
+// kernel's -- LDS reads and copies dealt out behind the matrix instructions, a bare workgroup barrier per stage -- with
+// one difference: a slot is refilled behind the barrier of its own stage (every wavefront waits for its own LDS reads
+// before it), so all but one of the slots are in flight.
+// Measured (weights from HBM, one k range per tile -> the planned ranges; the kernel before this, four stages, one
+// range): 250 x 4096 x 16384: 269 -> 203 -> 45 us; 250 x 16384 x 4096: 79 -> 64 -> 44; 96 x 5120 x 20480: 52 (eight
+// ranges) -> 44 (twelve); 768 x 12288 x 4096: 150 -> 76 (192-row tiles, one range).
+template <int MW> struct RingShape {
+    static constexpr int TM = 64 * MW;                       // rows of X per tile
+    static constexpr int SB = (8 + 2 * MW) * 2;              // blocks per stage (two k-blocks)
+    static constexpr int NST = 160 / SB < 8 ? 160 / SB : 8;  // stages that fit into 160 KiB
+    static constexpr int CW = SB / 4;                        // copies per wavefront and stage
+};
+
+// s_waitcnt vmcnt(N) lgkmcnt(0)
+template <int N>
+__device__ __forceinline__ void wait_vmcnt_lgkm0() {
+    __builtin_amdgcn_s_waitcnt((N & 0xF) | ((N >> 4) << 14) | (0x7 << 4));
+}
+
+template <int MODE, int MW>
+__global__ __launch_bounds__(256, 1) void gemm_ring_kernel(const u32x4* __restrict__ Wp, const u32x4* __restrict__ X,
+                                                           const u32x4* __restrict__ bias8, int KB, int NT32, int MT32,
+                                                           int tiles_n, int tiles_m, int ksplit, Epi p) {
+    typedef RingShape<MW> Sh;
+    constexpr int SB = Sh::SB, NST = Sh::NST, CW = Sh::CW;
+    constexpr int NM = 4 * MW, NR = 4 + MW;  // matrix instructions, LDS reads per wavefront and k-block
+    static_assert((NST - 1) * CW <= 63, "the wait counter holds every copy in flight");
+    __shared__ u32x4 ring[NST][SB][64];  // block c of a stage: W row-tile c / 2, k-block c % 2; from 16 on X row-tile (c - 16) / 2
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    // A contiguous run of items per XCD; the row tiles of one (column tile, k range) are neighbours and share its weights
+    const int nitem = tiles_n * tiles_m * ksplit, per_xcd = (nitem + 7) / 8;
+    const int item = (blockIdx.x % 8) * per_xcd + blockIdx.x / 8;
+    if (item >= nitem) return;
+    const int tm = item % tiles_m, rest = item / tiles_m;
+    const int tn = rest % tiles_n, ks = rest / tiles_n;
+    const int wn = wave & 1, wm = wave >> 1;  // this wavefront's 128 (n) x 32 MW (m) sub-tile
+    const int cur_len = epilogue_len<MODE>(p);
+    f32x16 acc[4][MW];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        const int m = tm * BM + (wm * 4 + j) * 32 + (lane & 31);
-        if (m >= p.M) continue;
-        size_t row = 0;       // MODE_STORE: float index of (m, 4 hh); BIAS_RELU: 16-byte slot of (m, k half hh) in
-                              // the first block of its row of blocks; QKV: float index into q
-        size_t kvrow = 0;     // QKV: half index of (sequence, head 0, position, 0) inside one (layer, k|v) plane
-        bool append = true;   // QKV: the row is a token (not padding): its key and value go into the cache
-        if (MODE == MODE_STORE) {
-            row = (size_t)ks * p.out_split + (size_t)m * p.N + 4 * hh;
-        } else if (MODE == MODE_BIAS_RELU) {
-            row = (size_t)(m >> 5) * (p.N >> 4) * 64 + 32 * hh + (m & 31);
-        } else {
-            row = (size_t)m * p.H + 4 * hh;
-            const int b = row_seq(p.st, m, p.S), r = m % p.S;
-            int t = cur_len + r;
-            if (cur_len < 0) {  // sequences of different lengths; padding rows append nothing
-                const int tr = r - row_pad(p.st, b);
-                append = tr >= 0;
-                t = seq_len(p.st, b) + tr;
-            }
-            kvrow = ((size_t)b * p.n_heads * p.max_seq + t) * p.d;
-        }
+    for (int i = 0; i < 4; ++i)
 #pragma unroll
-        for (int i = 0; i < NA; ++i) {
-            const int n32 = tn * BN + (wn * NA + i) * 32;  // wave-uniform
-            if (n32 >= p.N) continue;
-            if (MODE == MODE_STORE) {
+        for (int j = 0; j < MW; ++j) acc[i][j] = f32x16{};
+    const int nst_all = KB / 2;  // KB is even (K % 32 == 0)
+    const int st0 = (int)((long)ks * nst_all / ksplit);
+    const int nstage = (int)((long)(ks + 1) * nst_all / ksplit) - st0;
+    const u32x4* src[CW];  // row-tiles past the matrix: the last one (computed, never stored)
 #pragma unroll
-                for (int q = 0; q < 4; ++q)
-                    store16(p.out + row + n32 + 8 * q, acc[i][j][q * 4 + 0], acc[i][j][q * 4 + 1], acc[i][j][q * 4 + 2],
-                            acc[i][j][q * 4 + 3]);
-            } else if (MODE == MODE_BIAS_RELU) {
-                u32x4* ob = p.out_blocks + row + (size_t)(n32 >> 4) * 64;
-                uint2 h4[4];
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const u32x4 b8 = bias8[(n32 >> 3) + q];  // wave-uniform address: a scalar load
-                    const uint2 bb = hh ? make_uint2(b8.z, b8.w) : make_uint2(b8.x, b8.y);
-                    const float v0 = fmaxf(acc[i][j][q * 4 + 0] + bf_lo(bb.x), 0.f), v1 = fmaxf(acc[i][j][q * 4 + 1] + bf_hi(bb.x), 0.f);
-                    const float v2 = fmaxf(acc[i][j][q * 4 + 2] + bf_lo(bb.y), 0.f), v3 = fmaxf(acc[i][j][q * 4 + 3] + bf_hi(bb.y), 0.f);
-                    h4[q] = make_uint2(pack2(v0, v1), pack2(v2, v3));
-                }
-#pragma unroll
-                for (int qq = 0; qq < 2; ++qq) store16(ob + qq * 64, join_halves(h4[2 * qq], h4[2 * qq + 1]));
-            } else {
-                const int part = n32 >= 2 * p.H ? 2 : (n32 >= p.H ? 1 : 0);  // query, key or value columns (uniform)
-                half_t* kvcol = nullptr;
-                if (part) {
-                    const int c32 = n32 - part * p.H, head = c32 / p.d;
-                    kvcol = p.kv + (((size_t)(p.layer * 2 + (part - 1)) * p.max_batch) * p.n_heads + head) * p.max_seq * (size_t)p.d +
-                            (c32 - head * p.d);
-                }
-                uint2 h4[4];
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const u32x4 b8 = bias8[(n32 >> 3) + q];
-                    const uint2 bb = hh ? make_uint2(b8.z, b8.w) : make_uint2(b8.x, b8.y);
-                    const float v0 = acc[i][j][q * 4 + 0] + bf_lo(bb.x), v1 = acc[i][j][q * 4 + 1] + bf_hi(bb.x);
-                    const float v2 = acc[i][j][q * 4 + 2] + bf_lo(bb.y), v3 = acc[i][j][q * 4 + 3] + bf_hi(bb.y);
-                    if (!part)
-                        store16(p.out + row + n32 + 8 * q, v0 * p.qscale, v1 * p.qscale, v2 * p.qscale, v3 * p.qscale);
-                    else
-                        h4[q] = make_uint2(pack2(v0, v1), pack2(v2, v3));
-                }
-                if (part) {  // (uniform) keys / values: eight halves of a row per lane
-#pragma unroll
-                    for (int qq = 0; qq < 2; ++qq) {
-                        const u32x4 v8 = join_halves(h4[2 * qq], h4[2 * qq + 1]);
-                        if (append) store16(kvcol + kvrow + 8 * (2 * qq + hh), v8);
-                    }
-                }
-            }
-        }
+    for (int q = 0; q < CW; ++q) {
+        const int c = wave * CW + q;
+        const bool isw = c < 16;
+        const int rt = isw ? min(tn * 8 + (c >> 1), NT32 - 1) : min(tm * 2 * MW + ((c - 16) >> 1), MT32 - 1);
+        src[q] = (isw ? Wp : X) + ((size_t)rt * KB + (size_t)st0 * 2 + (c & 1)) * 64 + lane;
     }
+    auto copy1 = [&](int st, int slot, int q) { load_block_to_lds(src[q] + (size_t)st * 128, &ring[slot][wave * CW + q][0]); };
+    struct Ops { u32x4 a[4], b[MW]; };
+    // LDS read q of a k-block, in the order the matrix instructions first need the operands: a0, b0 .., a1, a2, a3
+    auto read1 = [&](Ops& o, int slot, int j, int q) {
+        if (q == 0) o.a[0] = ring[slot][wn * 8 + j][lane];
+        else if (q <= MW) o.b[q - 1] = ring[slot][16 + (wm * MW + q - 1) * 2 + j][lane];
+        else o.a[q - MW] = ring[slot][(wn * 4 + q - MW) * 2 + j][lane];
+    };
+    auto mma1 = [&](const Ops& o, int n) { acc[n / MW][n % MW] = mfma_f16(o.a[n / MW], o.b[n % MW], acc[n / MW][n % MW]); };
+    // Two reads behind each matrix instruction until all are out, then the copies, spread over the remaining ones.
+    constexpr int R2 = (NR + 1) / 2 < NM - 1 ? (NR + 1) / 2 : NM - 1;
+    constexpr int C2 = (CW + 1) / 2;  // copies of a stage that go out in the second half of a loop trip; the rest in the next first half
+    auto read_behind = [](int q) { return q / 2 < NM - 1 ? q / 2 : NM - 1; };
+    auto copy_behind = [](int q, int n) { return R2 + q * (NM - R2) / n; };
+    auto barrier = []() {  // the bare instruction: the waits before it say what it orders
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    // this wavefront's LDS reads are done, and its copies of all but the `later` youngest stages have landed
+    auto wait_stage = [&](int later) {
+        if (later >= NST - 1) wait_vmcnt_lgkm0<(NST - 1) * CW>();
+        else if (NST > 7 && later == 6) wait_vmcnt_lgkm0<6 * CW <= 63 ? 6 * CW : 0>();
+        else if (NST > 6 && later == 5) wait_vmcnt_lgkm0<5 * CW <= 63 ? 5 * CW : 0>();
+        else if (NST > 5 && later == 4) wait_vmcnt_lgkm0<4 * CW>();
+        else if (later == 3) wait_vmcnt_lgkm0<3 * CW>();
+        else if (later == 2) wait_vmcnt_lgkm0<2 * CW>();
+        else if (later == 1) wait_vmcnt_lgkm0<CW>();
+        else wait_vmcnt_lgkm0<0>();
+    };
+    const int n_pro = min(NST, nstage);
+    for (int st = 0; st < n_pro; ++st)
+#pragma unroll
+        for (int q = 0; q < CW; ++q) copy1(st, st, q);
+    wait_stage(n_pro - 1);
+    barrier();
+    Ops opa, opb;
+#pragma unroll
+    for (int q = 0; q < NR; ++q) read1(opa, 0, 0, q);
+    int s = 0, slot = 0;             // the stage in use and its slot
+    int late = 0, late_slot = 0;     // the stage whose last copies are still to be requested
+    for (; s + NST < nstage; ++s) {  // steady state: stages s+1 .. s+NST-1 are in flight
+        const int nslot = slot + 1 == NST ? 0 : slot + 1;
+        const bool have_late = s > 0;
+#pragma unroll
+        for (int n = 0; n < NM; ++n) {
+            mma1(opa, n);
+#pragma unroll
+            for (int q = 0; q < NR; ++q)
+                if (read_behind(q) == n) read1(opb, slot, 1, q);
+            if (have_late) {
+#pragma unroll
+                for (int q = C2; q < CW; ++q)
+                    if (copy_behind(q - C2, CW - C2) == n) copy1(late, late_slot, q);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        wait_vmcnt_lgkm0<(NST - 2) * CW>();  // stage s+1 has landed, this stage's slot has been read: by everybody behind the barrier
+        barrier();
+        late = s + NST; late_slot = slot;
+#pragma unroll
+        for (int n = 0; n < NM; ++n) {
+            mma1(opb, n);
+#pragma unroll
+            for (int q = 0; q < NR; ++q)
+                if (read_behind(q) == n) read1(opa, nslot, 0, q);
+#pragma unroll
+            for (int q = 0; q < C2; ++q)
+                if (copy_behind(q, C2) == n) copy1(late, late_slot, q);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        slot = nslot;
+    }
+    if (s > 0) {
+#pragma unroll
+        for (int q = C2; q < CW; ++q) copy1(late, late_slot, q);
+    }
+    for (; s < nstage; ++s) {  // the last stages: everything has been requested
+        const int nslot = slot + 1 == NST ? 0 : slot + 1;
+#pragma unroll
+        for (int q = 0; q < NR; ++q) read1(opb, slot, 1, q);
+#pragma unroll
+        for (int n = 0; n < NM; ++n) mma1(opa, n);
+        if (s + 1 < nstage) {
+            wait_stage(nstage - 2 - s);
+            barrier();
+#pragma unroll
+            for (int q = 0; q < NR; ++q) read1(opa, nslot, 0, q);
+        }
+#pragma unroll
+        for (int n = 0; n < NM; ++n) mma1(opb, n);
+        slot = nslot;
+    }
+    if constexpr (MODE == MODE_SCORE) score_tile<4, MW>(p, acc, tm * Sh::TM + wm * 32 * MW, tn * 256 + wn * 128, tn * 2 + wn, lane);
+    else store_tile<MODE, 4, MW>(p, bias8, acc, tm * Sh::TM + wm * 32 * MW, tn * 256 + wn * 128, ks, cur_len, lane);
 }
 
 // One wavefront per scored row: log-sum-exp over the vocabulary slices in slice order, then
@@ -560,6 +721,7 @@ __global__ __launch_bounds__(256) void score_reduce_kernel(const float2* __restr
 
 // Many rows (a prompt or scoring pass): 256 x 256 tiles, one workgroup per CU, once there are enough of them to
 // give every CU one.
+constexpr int kMaxTiledKSplit = 16;
 static int g_tiled_cus_override = 0;  // a planner query's CU count
 static int tiled_cus() { return g_tiled_cus_override > 0 ? g_tiled_cus_override : num_cus(); }
 static bool use_big_tile(int M, int N) {
@@ -593,45 +755,63 @@ static BigPlan big_plan(int M, int N, int KB, bool may_cut) {
     return best;
 }
 
-// split_col: with a k-split on the big tiles, the first column whose tiles are cut into k ranges (0: all of them);
-// tile_na: their width as planned by the caller (0: plan here, no cut)
-template <int MODE>
-void launch_tiled(hipStream_t s, const void* Wp, const void* Xhi, int KB, int N, int M, const Epi& p, int ksplit = 1,
-                  int split_col = 0, int tile_na = 0) {
-    const int NT32 = (N + 31) / 32, MT32 = (M + 31) / 32;
-    // (the scoring head's epilogue keeps a soft-max over all of a wavefront's accumulators: it does not fit next to 16 of them)
-    const bool big = MODE != MODE_SCORE && use_big_tile(M, N);
-    const int TM = big ? 256 : 128;
-    const int tiles_n = (N + TN - 1) / TN, tiles_m = (M + TM - 1) / TM;
-    const int nitem = tiles_n * tiles_m * ksplit;
-    const int grid = ((nitem + 7) / 8) * 8;
-    if constexpr (MODE != MODE_SCORE) {
-        if (big) {
-            // (the bias through a pointer of its own: declared never to alias the outputs, its values can be fetched
-            // with scalar loads, which do not queue behind the epilogue's stores)
-            const int na = tile_na ? tile_na : big_plan(M, N, KB, false).na;
-            const int bn = 64 * na, tn_big = (N + bn - 1) / bn;
-            const int split_tn = ksplit > 1 ? split_col / bn : tn_big;  // without a k-split every tile is whole
-            const int whole = split_tn * tiles_m, cutn = (tn_big - split_tn) * tiles_m * ksplit;
-            const int grid2 = (whole + 7) / 8 * 8 + (cutn + 7) / 8 * 8;
-            if (na == 5)
-                gemm_tiled256_kernel<MODE, 5><<<grid2, 256, 0, s>>>((const u32x4*)Wp, (const u32x4*)Xhi, (const u32x4*)p.bias,
-                                                                    KB, NT32, MT32, tn_big, tiles_m, ksplit, split_tn, p);
-            else
-                gemm_tiled256_kernel<MODE, 4><<<grid2, 256, 0, s>>>((const u32x4*)Wp, (const u32x4*)Xhi, (const u32x4*)p.bias,
-                                                                    KB, NT32, MT32, tn_big, tiles_m, ksplit, split_tn, p);
-            return;
+// How a GEMM of too few rows or tiles for whole rounds of big tiles is cut: tiles of 256 columns x 64 mw rows (mw = 1, 2, 3:
+// the ring kernel; 4: the big one, which at 5 takes 320 columns), every tile in ks k ranges.  One workgroup per CU, so
+// a launch costs its rounds of ramp plus stages, and on top of that: the weights' way from HBM, writing the partial
+// sums (fused = false: of a GEMM whose consumer, a LayerNorm, adds them up and pays for reading them), and, for an
+// epilogue that needs the whole sum (fused), the pass of finish_kernel.  Microseconds fitted to launches of M = 96 ..
+// 768 rows and the 1.3B .. 13B matrices (uncontended stages 0.33 / 0.39 / 0.43 / 0.53 / 0.68 us; a second, partly empty
+// round: 4096 x 4096 and 768 rows, 240 workgroups 33.6 us, 288: 54.1).
+struct RingPlan { int mw, ks; };
+static RingPlan ring_plan(int M, int N, int KB, bool fused, size_t capacity_floats) {
+    constexpr double kStage[5] = {0.33, 0.39, 0.43, 0.53, 0.68}, kRamp[5] = {6.0, 7.0, 8.5, 12.0, 14.0};
+    const long cus = tiled_cus(), stages = KB / 2;
+    const double sums = 4.0 * M * N / 5e6, weights = 32.0 * N * KB / 14e6;
+    RingPlan best{2, 1};
+    double best_cost = 1e30;
+    for (int mw = 1; mw <= 5; ++mw) {
+        const int tm = mw < 4 ? 64 * mw : 256, tn = mw < 5 ? 256 : 320;
+        const long tiles = (long)((N + tn - 1) / tn) * ((M + tm - 1) / tm);
+        for (int ks = 1; ks <= kMaxTiledKSplit; ++ks) {
+            if (ks > 1 && (stages / ks < 4 || (size_t)ks * M * N > capacity_floats)) break;
+            const double rounds = (double)((tiles * ks + cus - 1) / cus);
+            double cost = rounds * (kRamp[mw - 1] + (double)((stages + ks - 1) / ks) * kStage[mw - 1]) + weights;
+            if (!fused) cost += 2.0 * ks * sums;
+            else if (ks > 1) cost += 2.0 * ks * sums + 5.0;
+            if (cost < best_cost) {
+                best_cost = cost;
+                best = RingPlan{mw, ks};
+            }
         }
     }
-    // two workgroups per CU once there are that many (their k ranges must hold an even number of k-blocks
-    // each: that ring alternates two register sets)
-    const bool pair = nitem >= 2 * num_cus() && KB % (2 * ksplit) == 0;
-    if (pair)
-        gemm_tiled_kernel<MODE, 1, 2><<<grid, 256, 0, s>>>((const u32x4*)Wp, (const u32x4*)Xhi, KB, NT32, MT32, tiles_n,
-                                                           tiles_m, ksplit, p);
-    else
-        gemm_tiled_kernel<MODE, 0, 2><<<grid, 256, 0, s>>>((const u32x4*)Wp, (const u32x4*)Xhi, KB, NT32, MT32, tiles_n,
-                                                           tiles_m, ksplit, p);
+    return best;
+}
+
+// tile: 1 .. 3 the ring kernel with 64 tile rows, 4 / 5 the big tiles.  Columns from split_col on are cut into ksplit k
+// ranges (with one range none are; the ring kernel cuts every tile).
+template <int MODE>
+void launch_tiled(hipStream_t s, const void* Wp, const void* Xhi, int KB, int N, int M, const Epi& p, int tile, int ksplit,
+                  int split_col) {
+    const int NT32 = (N + 31) / 32, MT32 = (M + 31) / 32;
+    // (the bias through a pointer of its own: declared never to alias the outputs, its values can be fetched
+    // with scalar loads, which do not queue behind the epilogue's stores)
+    const u32x4 *W = (const u32x4*)Wp, *X = (const u32x4*)Xhi, *bias8 = (const u32x4*)p.bias;
+    if (tile < 4) {
+        const int tiles_n = (N + 255) / 256, tiles_m = (M + 64 * tile - 1) / (64 * tile);
+        const int grid = (tiles_n * tiles_m * ksplit + 7) / 8 * 8;
+        if (tile == 1) gemm_ring_kernel<MODE, 1><<<grid, 256, 0, s>>>(W, X, bias8, KB, NT32, MT32, tiles_n, tiles_m, ksplit, p);
+        else if (tile == 2) gemm_ring_kernel<MODE, 2><<<grid, 256, 0, s>>>(W, X, bias8, KB, NT32, MT32, tiles_n, tiles_m, ksplit, p);
+        else gemm_ring_kernel<MODE, 3><<<grid, 256, 0, s>>>(W, X, bias8, KB, NT32, MT32, tiles_n, tiles_m, ksplit, p);
+        return;
+    }
+    if constexpr (MODE != MODE_SCORE) {
+        const int bn = 64 * tile, tiles_n = (N + bn - 1) / bn, tiles_m = (M + BM - 1) / BM;
+        const int split_tn = ksplit > 1 ? split_col / bn : tiles_n;  // without a k-split every tile is whole
+        const int whole = split_tn * tiles_m, cutn = (tiles_n - split_tn) * tiles_m * ksplit;
+        const int grid = (whole + 7) / 8 * 8 + (cutn + 7) / 8 * 8;
+        if (tile == 5) gemm_tiled256_kernel<MODE, 5><<<grid, 256, 0, s>>>(W, X, bias8, KB, NT32, MT32, tiles_n, tiles_m, ksplit, split_tn, p);
+        else gemm_tiled256_kernel<MODE, 4><<<grid, 256, 0, s>>>(W, X, bias8, KB, NT32, MT32, tiles_n, tiles_m, ksplit, split_tn, p);
+    }
 }
 
 // After a k-split MODE_STORE GEMM whose epilogue needs the whole sum: adds the partial sums in split
@@ -643,9 +823,14 @@ __global__ __launch_bounds__(256) void finish_kernel(const float* __restrict__ p
     if (idx >= (size_t)p.M * quads) return;
     const int m = (int)(idx / quads), n0 = (int)(idx % quads) * 4;
     float4 v = *reinterpret_cast<const float4*>(part + (size_t)m * p.N + n0);
-    for (int k = 1; k < ksplit; ++k) {
-        const float4 y = *reinterpret_cast<const float4*>(part + (size_t)k * split + (size_t)m * p.N + n0);
-        v.x += y.x; v.y += y.y; v.z += y.z; v.w += y.w;
+    for (int k0 = 1; k0 < ksplit; k0 += 4) {  // in split order, four loads on their way at a time
+        float4 y[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+            y[k] = *reinterpret_cast<const float4*>(part + (size_t)min(k0 + k, ksplit - 1) * split + (size_t)m * p.N + n0);
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+            if (k0 + k < ksplit) { v.x += y[k].x; v.y += y[k].y; v.z += y[k].z; v.w += y[k].w; }
     }
     epilogue4<MODE>(p, m, n0, 0, v.x, v.y, v.z, v.w, epilogue_bias<MODE>(p, n0), epilogue_len<MODE>(p));
 }
@@ -654,87 +839,64 @@ __global__ __launch_bounds__(256) void finish_kernel(const float* __restrict__ p
 
 // ------------------------------------------------------------------ launchers
 
-void bf16_gemm_tiled(hipStream_t s, int mode, const void* Wp, const void* Xhi, int M, int N, int K,
-                     const bf16_gemm_args& a) {
-    const Epi p = make_epi(M, N, a);
-    if (mode == EPI_STORE) launch_tiled<MODE_STORE>(s, Wp, Xhi, K / 16, N, M, p);
-    else if (mode == EPI_BIAS_RELU) launch_tiled<MODE_BIAS_RELU>(s, Wp, Xhi, K / 16, N, M, p);
-    else launch_tiled<MODE_QKV>(s, Wp, Xhi, K / 16, N, M, p);
+// Floats of scratch the k ranges of a few-row GEMM can make use of: at most a round of tiles' sums (256 tiles of
+// 256 x 256), and never more than kMaxTiledKSplit sets of the matrix.
+size_t bf16_tiled_scratch_floats(int rows, int widest) {
+    return std::min((size_t)256 * 256 * 256, (size_t)kMaxTiledKSplit * rows * widest);
 }
 
-int bf16_tiled_ksplit(int M, int N, int K) {
-    const int tiles = ((N + TN - 1) / TN) * ((M + 127) / 128), stages = K / 16 / TiledShape<0, 2>::KSTAGE;
-    int ks = num_cus() / tiles;
-    if (ks > 8) ks = 8;
-    while (ks > 1 && stages / ks < 8) --ks;  // keep the ring worth filling
-    return ks < 1 ? 1 : ks;
-}
-
-// Many-row MODE_STORE GEMMs (out-projection and FC2 of a prompt pass): the tiles come in rounds of two per
-// CU, and a last round that is partly empty costs as much as a full one (1280 tiles on 256 CUs: three rounds
-// for the work of two and a half).  Cutting every tile into ks k ranges makes the rounds shorter and the
-// last one fuller; the price is ks sets of partial sums for the following LayerNorm to add.
-int bf16_tiled_store_ksplit(int M, int N, int K, size_t capacity_floats) {
-    const bool big = use_big_tile(M, N);
-    const long slots = (big ? 1L : 2L) * tiled_cus(), tiles = (long)((N + TN - 1) / TN) * ((M + (big ? 255 : 127)) / (big ? 256 : 128));
-    const int KB = K / 16;
-    if (tiles < slots || KB % 2) return 1;
-    int best = 1;
-    double best_cost = (double)((tiles + slots - 1) / slots);  // in units of one full-K tile
-    for (int ks = 2; ks <= 4; ++ks) {
-        if (KB % (2 * ks) || KB / ks < 8 * TiledShape<1, 2>::NSTG || (size_t)ks * M * N > capacity_floats) continue;
-        const double cost = (double)((tiles * ks + slots - 1) / slots) / ks * (1.0 + 0.02 * ks);
-        if (cost < 0.95 * best_cost) { best_cost = cost; best = ks; }
+// Out-projection and FC2 (the following LayerNorm adds the partial sums): which tile, *ks k ranges for the tiles of
+// columns >= *split_col and one for the columns before.  With enough rows and columns for rounds of big tiles
+// these come whole first, in rounds of one per CU, and the cut ones fill the last, shorter round: 640 tiles of 256
+// columns on 256 CUs are two rounds of whole tiles and one of 256 half tiles, with a second set of partial sums for a
+// fifth of the columns only (and 512 tiles of 320 columns are two rounds with nothing to cut).  With fewer, ring_plan
+// cuts every tile.
+void bf16_tiled_store_plan(int M, int N, int K, size_t capacity_floats, int* tile, int* ks, int* split_col) {
+    if (use_big_tile(M, N)) {
+        const BigPlan g = big_plan(M, N, K / 16, (size_t)2 * M * N <= capacity_floats);
+        *tile = g.na; *ks = g.ks; *split_col = g.split_col;
+        return;
     }
-    return best;
-}
-
-// The same decision for the big tiles, which can cut the tiles of the last columns only: *split_col is the first
-// column whose tiles are cut into *ks k ranges (0: all; columns before it get one whole-k sum), *na the tiles' width
-// in 64 columns.  The whole tiles come first, in rounds of one per CU, and the cut ones fill the last, shorter round:
-// 640 tiles of 256 columns on 256 CUs are two rounds of whole tiles and one of 256 half tiles, with a second set of
-// partial sums for a fifth of the columns only (and 512 tiles of 320 columns are two rounds with nothing to cut).
-// Other tile shapes: bf16_tiled_store_ksplit, every tile cut.
-void bf16_tiled_store_split(int M, int N, int K, size_t capacity_floats, int* ks, int* split_col, int* na) {
-    *ks = bf16_tiled_store_ksplit(M, N, K, capacity_floats);
-    *split_col = 0;
-    *na = 0;
-    if (!use_big_tile(M, N)) return;
-    const BigPlan g = big_plan(M, N, K / 16, (size_t)2 * M * N <= capacity_floats);
-    *ks = g.ks;
-    *split_col = g.split_col;
-    *na = g.na;
+    const RingPlan g = ring_plan(M, N, K / 16, false, capacity_floats);
+    *tile = g.mw; *ks = g.ks; *split_col = 0;
 }
 
 void bf16_tiled_plan_query(int M, int N, int K, int may_cut, size_t capacity_floats, int cus, int* tile_cols, int* ks,
                            int* split_col) {
     g_tiled_cus_override = cus;
     *tile_cols = 0; *ks = 1; *split_col = 0;
+    const size_t room = capacity_floats ? capacity_floats : (size_t)-1;
     if (use_big_tile(M, N)) {
-        const bool room = capacity_floats == 0 || (size_t)2 * M * N <= capacity_floats;
-        const BigPlan g = big_plan(M, N, K / 16, may_cut && room);
+        const BigPlan g = big_plan(M, N, K / 16, may_cut && (size_t)2 * M * N <= room);
         *tile_cols = 64 * g.na; *ks = g.ks; *split_col = g.split_col;
     } else if (may_cut) {
-        *ks = bf16_tiled_store_ksplit(M, N, K, capacity_floats ? capacity_floats : (size_t)-1);
+        *ks = ring_plan(M, N, K / 16, false, room).ks;
     }
     g_tiled_cus_override = 0;
 }
 
-void bf16_gemm_tiled_ksplit(hipStream_t s, int mode, const void* Wp, const void* Xhi, int M, int N, int K,
-                            int ksplit, float* part, size_t part_split, const bf16_gemm_args& a) {
-    if (ksplit == 1 && mode != EPI_STORE) {  // the tiles alone fill the chip: the epilogue runs in the GEMM
-        bf16_gemm_tiled(s, mode, Wp, Xhi, M, N, K, a);
+void bf16_gemm_tiled_store(hipStream_t s, const void* Wp, const void* Xhi, int M, int N, int K, float* part, int tile, int ks,
+                           int split_col) {
+    bf16_gemm_args a;
+    a.out = part; a.out_split = (size_t)M * N;
+    launch_tiled<MODE_STORE>(s, Wp, Xhi, K / 16, N, M, make_epi(M, N, a), tile, ks, split_col);
+}
+
+void bf16_gemm_tiled(hipStream_t s, int mode, const void* Wp, const void* Xhi, int M, int N, int K, const bf16_gemm_args& a,
+                     float* part, size_t part_floats) {
+    const Epi p = make_epi(M, N, a);
+    RingPlan g{0, 1};
+    if (use_big_tile(M, N)) g.mw = big_plan(M, N, K / 16, false).na;
+    else g = ring_plan(M, N, K / 16, true, part_floats);
+    if (g.ks == 1) {  // the epilogue runs in the GEMM
+        if (mode == EPI_BIAS_RELU) launch_tiled<MODE_BIAS_RELU>(s, Wp, Xhi, K / 16, N, M, p, g.mw, 1, 0);
+        else launch_tiled<MODE_QKV>(s, Wp, Xhi, K / 16, N, M, p, g.mw, 1, 0);
         return;
     }
-    bf16_gemm_args st = a;
-    st.out = part; st.out_split = part_split;
-    const Epi ps = make_epi(M, N, st);
-    launch_tiled<MODE_STORE>(s, Wp, Xhi, K / 16, N, M, ps, ksplit, a.split_col, a.tile_na);
-    if (mode == EPI_STORE) return;  // the consumer (a LayerNorm) adds the partial sums
-    const Epi p = make_epi(M, N, a);
+    bf16_gemm_tiled_store(s, Wp, Xhi, M, N, K, part, g.mw, g.ks, 0);
     const unsigned grid = (unsigned)(((size_t)M * (N / 4) + 255) / 256);
-    if (mode == EPI_BIAS_RELU) finish_kernel<MODE_BIAS_RELU><<<grid, 256, 0, s>>>(part, ksplit, part_split, p);
-    else finish_kernel<MODE_QKV><<<grid, 256, 0, s>>>(part, ksplit, part_split, p);
+    if (mode == EPI_BIAS_RELU) finish_kernel<MODE_BIAS_RELU><<<grid, 256, 0, s>>>(part, g.ks, (size_t)M * N, p);
+    else finish_kernel<MODE_QKV><<<grid, 256, 0, s>>>(part, g.ks, (size_t)M * N, p);
 }
 
 int bf16_score_parts(int V) { return 2 * ((V + TN - 1) / TN); }
@@ -743,7 +905,13 @@ void bf16_score_head(hipStream_t s, const void* Wp, const void* Xhi, int M, int 
                      const int32_t* ids, float* stats, float* tgt, float* out) {
     Epi p{};
     p.M = M; p.N = V; p.S = S; p.ids = ids; p.sc_stats = (float2*)stats; p.sc_tgt = tgt; p.sc_parts = bf16_score_parts(V);
-    launch_tiled<MODE_SCORE>(s, Wp, Xhi, K / 16, V, M, p);
+    const int NT32 = (V + 31) / 32, MT32 = (M + 31) / 32, KB = K / 16;
+    const int tiles_n = (V + TN - 1) / TN, tiles_m = (M + 127) / 128, tiles = tiles_n * tiles_m;
+    if (tiles >= 2 * num_cus())  // two workgroups per CU
+        gemm_tiled_kernel<MODE_SCORE, 1, 2><<<(tiles + 7) / 8 * 8, 256, 0, s>>>((const u32x4*)Wp, (const u32x4*)Xhi, KB, NT32, MT32,
+                                                                               tiles_n, tiles_m, 1, p);
+    else
+        launch_tiled<MODE_SCORE>(s, Wp, Xhi, KB, V, M, p, M <= 64 ? 1 : 2, 1, 0);
     score_reduce_kernel<<<(M + 3) / 4, 256, 0, s>>>((const float2*)stats, tgt, p.sc_parts, M, S, out);
 }
 

@@ -138,9 +138,14 @@ __global__ __launch_bounds__(THREADS) void ln_row_kernel(float* __restrict__ r, 
             const int i = threadIdx.x + j * THREADS;
             if (i >= nq) continue;
             float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
-            for (int k = 0; k < ksplit; ++k) {  // fixed order: the sum does not depend on scheduling
-                const float4 y = *reinterpret_cast<const float4*>(part + (size_t)k * part_split + src * H + 4 * i);
-                acc.x += y.x; acc.y += y.y; acc.z += y.z; acc.w += y.w;
+            for (int k0 = 0; k0 < ksplit; k0 += 4) {  // fixed order: the sum does not depend on scheduling
+                float4 y[4];  // four loads on their way at a time
+#pragma unroll
+                for (int k = 0; k < 4; ++k)
+                    y[k] = *reinterpret_cast<const float4*>(part + (size_t)min(k0 + k, ksplit - 1) * part_split + src * H + 4 * i);
+#pragma unroll
+                for (int k = 0; k < 4; ++k)
+                    if (k0 + k < ksplit) { acc.x += y[k].x; acc.y += y[k].y; acc.z += y[k].z; acc.w += y[k].w; }
             }
             const uint2 pb = *reinterpret_cast<const uint2*>(pbias + 4 * i);
             v[j].x += acc.x + bf_lo(pb.x);

@@ -37,7 +37,8 @@ struct he_engine {
     int* exps_tmp = nullptr;
     Tiled scratch{nullptr, nullptr, nullptr, nullptr};
     float *part = nullptr, *stats = nullptr;
-    size_t part_floats = 0;  // capacity of `part`
+    size_t part_floats = 0;        // capacity of `part` the decode plans count on
+    size_t tiled_part_floats = 0;  // ... and all of it (the many-row GEMMs' k ranges)
     int* stats_idx = nullptr;
     // decode rows: LayerNorms folded into the GEMMs around them
     float *cvec = nullptr;     // per layer W gamma, W beta for wqkv (2 x 3H) and w1 (2 x F), then the LM head's (2 x V), padded to 32
@@ -93,7 +94,7 @@ namespace {
 struct Sizes {
     size_t kv, rowsH, rowsF, xf, logits, gen, total;
     // bf16 path
-    size_t tiled_layer, tiled_lm, ablk, hblk, xfblk, part, stats, stats_idx, cvec, ln_stats, ln_counters, score_stats, tail;
+    size_t tiled_layer, tiled_lm, ablk, hblk, xfblk, part, tiled_part, stats, stats_idx, cvec, ln_stats, ln_counters, score_stats, tail;
 };
 
 bool is_fast(const he_config& c) { return c.dtype == HE_BF16 && c.impl == 0; }
@@ -157,6 +158,8 @@ Sizes sizes_of(const he_config& c) {
     const size_t mrow = c.max_batch > 32 ? ((size_t)kMaxKSplit * c.max_batch * wide + c.hidden - 1) / c.hidden : 0;
     const size_t prow = std::max(std::max(rows, drow), mrow);
     s.part = prow * H * sizeof(float);
+    // the many-row GEMMs cut their tiles into k ranges where these alone do not fill the chip
+    s.tiled_part = std::max(s.part, bf16_tiled_scratch_floats((int)rows, (int)wide) * sizeof(float));
     const size_t ntile = (size_t)(c.vocab + 31) / 32;
     s.stats = (size_t)c.max_batch * ntile * 4 * sizeof(float);
     s.stats_idx = (size_t)c.max_batch * ntile * sizeof(int);
@@ -175,7 +178,7 @@ Sizes sizes_of(const he_config& c) {
                    wide * sizeof(int);
     }
     s.total += 2 * s.rowsH /* resid, q */ + (c.weights_tiled || c.weights_fp8 ? 0 : (size_t)c.n_layers * s.tiled_layer + s.tiled_lm) +
-               2 * s.ablk + s.hblk + s.xfblk + s.part + s.stats + s.stats_idx;
+               2 * s.ablk + s.hblk + s.xfblk + s.tiled_part + s.stats + s.stats_idx;
     return s;
 }
 
@@ -269,9 +272,9 @@ void pass_tiled_bf16(he_engine* e, const int32_t* d_ids, int id_stride, int B, i
     const size_t split = (size_t)M * H;
     // k ranges per tile of the two GEMMs whose partial sums the next LayerNorm adds, and the first column whose
     // tiles are cut at all
-    int kso, sco, nao, ks2, sc2, na2;
-    bf16_tiled_store_split(M, H, H, e->part_floats, &kso, &sco, &nao);
-    bf16_tiled_store_split(M, H, F, e->part_floats, &ks2, &sc2, &na2);
+    int kso, sco, tlo, ks2, sc2, tl2;
+    bf16_tiled_store_plan(M, H, H, e->tiled_part_floats, &tlo, &kso, &sco);
+    bf16_tiled_store_plan(M, H, F, e->tiled_part_floats, &tl2, &ks2, &sc2);
     int pend_ks = 1, pend_sc = 0;
     for (int l = 0; l < c.n_layers; ++l) {
         const he_layer_weights& lw = e->layers[l];
@@ -279,16 +282,14 @@ void pass_tiled_bf16(he_engine* e, const int32_t* d_ids, int id_stride, int B, i
         bf16_ln(s, e->resid, pend, pend_ks, split, pend_b, lw.ln1_g, lw.ln1_b, e->ablk, M, H, c.ln_eps, 1, 0, 1, pend_sc);
         bf16_gemm_args a = base;
         a.layer = l; a.bias = lw.bqkv; a.out = e->qbuf; a.kv = e->kv; a.qscale = 1.0f / sqrtf((float)e->d);
-        bf16_gemm_tiled(s, EPI_QKV, tw.wqkv, e->ablk, M, 3 * H, H, a);
+        bf16_gemm_tiled(s, EPI_QKV, tw.wqkv, e->ablk, M, 3 * H, H, a, e->part, e->tiled_part_floats);
         if (l == c.n_layers - 1 && !full) break;
         bf16_attn(s, e->qbuf, e->kv, e->oblk, e->st, M, Sp, l, H, c.n_heads, c.max_batch, c.max_seq_len);
-        a = base; a.split_col = sco; a.tile_na = nao;
-        bf16_gemm_tiled_ksplit(s, EPI_STORE, tw.wo, e->oblk, M, H, H, kso, e->part, split, a);
+        bf16_gemm_tiled_store(s, tw.wo, e->oblk, M, H, H, e->part, tlo, kso, sco);
         bf16_ln(s, e->resid, e->part, kso, split, lw.bo, lw.ln2_g, lw.ln2_b, e->ablk, M, H, c.ln_eps, 1, 0, 1, sco);
         a = base; a.bias = lw.b1; a.out_blocks = e->hblk;
-        bf16_gemm_tiled(s, EPI_BIAS_RELU, tw.w1, e->ablk, M, F, H, a);
-        a = base; a.split_col = sc2; a.tile_na = na2;
-        bf16_gemm_tiled_ksplit(s, EPI_STORE, tw.w2, e->hblk, M, H, F, ks2, e->part, split, a);
+        bf16_gemm_tiled(s, EPI_BIAS_RELU, tw.w1, e->ablk, M, F, H, a, e->part, e->tiled_part_floats);
+        bf16_gemm_tiled_store(s, tw.w2, e->hblk, M, H, F, e->part, tl2, ks2, sc2);
         pend = e->part; pend_b = lw.b2; pend_ks = ks2; pend_sc = sc2;
     }
     if (pend_bias) *pend_bias = pend_b;
@@ -496,52 +497,51 @@ void pass_decode_wide_bf16(he_engine* e, const int32_t* d_ids, int id_stride, in
     base.max_seq = c.max_seq_len;
     plain_embed(s, 1, d_ids, id_stride, e->w.tok_emb, e->w.pos_emb, e->resid, e->st, B, 1, H, c.vocab, c.pos_offset);
     const float* pend = nullptr;
-    int pend_ks = 0;
+    int pend_ks = 0, pend_sc = 0;
     const void* pend_b = nullptr;
     const size_t split = (size_t)B * H;
-    const int ksq = bf16_tiled_ksplit(B, 3 * H, H), kso = bf16_tiled_ksplit(B, H, H);
-    const int ks1 = bf16_tiled_ksplit(B, F, H), ks2 = bf16_tiled_ksplit(B, H, F);
+    int kso, sco, tlo, ks2, sc2, tl2;
+    bf16_tiled_store_plan(B, H, H, e->tiled_part_floats, &tlo, &kso, &sco);
+    bf16_tiled_store_plan(B, H, F, e->tiled_part_floats, &tl2, &ks2, &sc2);
     for (int l = 0; l < c.n_layers; ++l) {
         const he_layer_weights& lw = e->layers[l];
         const he_engine::Tiled tw = layer_blocks(e, l);
         {
             LaunchTimer t(e, HE_K_LAYERNORM);
-            bf16_ln(s, e->resid, pend, pend_ks, split, pend_b, lw.ln1_g, lw.ln1_b, e->ablk, B, H, c.ln_eps, 1, 0, 1);
+            bf16_ln(s, e->resid, pend, pend_ks, split, pend_b, lw.ln1_g, lw.ln1_b, e->ablk, B, H, c.ln_eps, 1, 0, 1, pend_sc);
         }
         bf16_gemm_args a = base;
         a.layer = l; a.bias = lw.bqkv; a.out = e->qbuf; a.kv = e->kv; a.qscale = 1.0f / sqrtf((float)e->d);
         {
             LaunchTimer t(e, HE_K_QKV);
-            bf16_gemm_tiled_ksplit(s, EPI_QKV, tw.wqkv, e->ablk, B, 3 * H, H, ksq, e->part, (size_t)B * 3 * H, a);
+            bf16_gemm_tiled(s, EPI_QKV, tw.wqkv, e->ablk, B, 3 * H, H, a, e->part, e->tiled_part_floats);
         }
         {
             LaunchTimer t(e, HE_K_ATTENTION);
             bf16_attn(s, e->qbuf, e->kv, e->oblk, e->st, B, 1, l, H, c.n_heads, c.max_batch, c.max_seq_len);
         }
-        a = base;
         {
             LaunchTimer t(e, HE_K_OUT_PROJ);
-            bf16_gemm_tiled_ksplit(s, EPI_STORE, tw.wo, e->oblk, B, H, H, kso, e->part, split, a);
+            bf16_gemm_tiled_store(s, tw.wo, e->oblk, B, H, H, e->part, tlo, kso, sco);
         }
         {
             LaunchTimer t(e, HE_K_LAYERNORM);
-            bf16_ln(s, e->resid, e->part, kso, split, lw.bo, lw.ln2_g, lw.ln2_b, e->ablk, B, H, c.ln_eps, 1, 0, 1);
+            bf16_ln(s, e->resid, e->part, kso, split, lw.bo, lw.ln2_g, lw.ln2_b, e->ablk, B, H, c.ln_eps, 1, 0, 1, sco);
         }
         a = base; a.bias = lw.b1; a.out_blocks = e->hblk;
         {
             LaunchTimer t(e, HE_K_FC1);
-            bf16_gemm_tiled_ksplit(s, EPI_BIAS_RELU, tw.w1, e->ablk, B, F, H, ks1, e->part, (size_t)B * F, a);
+            bf16_gemm_tiled(s, EPI_BIAS_RELU, tw.w1, e->ablk, B, F, H, a, e->part, e->tiled_part_floats);
         }
-        a = base;
         {
             LaunchTimer t(e, HE_K_FC2);
-            bf16_gemm_tiled_ksplit(s, EPI_STORE, tw.w2, e->hblk, B, H, F, ks2, e->part, split, a);
+            bf16_gemm_tiled_store(s, tw.w2, e->hblk, B, H, F, e->part, tl2, ks2, sc2);
         }
-        pend = e->part; pend_ks = ks2; pend_b = lw.b2;
+        pend = e->part; pend_ks = ks2; pend_sc = sc2; pend_b = lw.b2;
     }
     {
         LaunchTimer t(e, HE_K_LAYERNORM);
-        bf16_ln(s, e->resid, pend, pend_ks, split, pend_b, e->w.lnf_g, e->w.lnf_b, e->xfblk, B, H, c.ln_eps, 1, 0, 0);
+        bf16_ln(s, e->resid, pend, pend_ks, split, pend_b, e->w.lnf_g, e->w.lnf_b, e->xfblk, B, H, c.ln_eps, 1, 0, 0, pend_sc);
     }
     {
         LaunchTimer t(e, HE_K_LM_HEAD);
@@ -819,7 +819,8 @@ he_status he_create(const he_config* cfg, const he_weights* weights, he_engine**
             A(&e->lm_tiled, z.tiled_lm);
         }
         A(&e->ablk, z.ablk); A(&e->oblk, z.ablk); A(&e->hblk, z.hblk); A(&e->xfblk, z.xfblk);
-        A(&e->part, z.part); e->part_floats = z.part / sizeof(float); A(&e->stats, z.stats); A(&e->stats_idx, z.stats_idx);
+        A(&e->part, z.tiled_part); e->part_floats = z.part / sizeof(float); e->tiled_part_floats = z.tiled_part / sizeof(float);
+        A(&e->stats, z.stats); A(&e->stats_idx, z.stats_idx);
         A(&e->cvec, z.cvec); A(&e->ln_stats, z.ln_stats); A(&e->ln_counters, z.ln_counters);
         A(&e->score_stats, z.score_stats); A(&e->score_tgt, z.gen); A(&e->tail_buf, z.tail);
     }
@@ -1321,14 +1322,13 @@ he_status he_kernel_sweep(he_engine* e, int kernel_class, int reps) {
                 if (e->w8) return fail(e, HE_ERR_STATE, "he_kernel_sweep: with 8-bit weights only for batches up to 32");
                 if (kernel_class == HE_K_FC1) {
                     a.bias = e->layers[l].b1; a.out_blocks = e->hblk;
-                    bf16_gemm_tiled_ksplit(e->stream, EPI_BIAS_RELU, e->tiled[l].w1, e->ablk, B, F, H,
-                                           bf16_tiled_ksplit(B, F, H), e->part, (size_t)B * F, a);
-                } else if (kernel_class == HE_K_FC2) {
-                    bf16_gemm_tiled_ksplit(e->stream, EPI_STORE, e->tiled[l].w2, e->hblk, B, H, F,
-                                           bf16_tiled_ksplit(B, H, F), e->part, split, a);
+                    bf16_gemm_tiled(e->stream, EPI_BIAS_RELU, e->tiled[l].w1, e->ablk, B, F, H, a, e->part, e->tiled_part_floats);
                 } else {
-                    bf16_gemm_tiled_ksplit(e->stream, EPI_STORE, e->tiled[l].wo, e->oblk, B, H, H,
-                                           bf16_tiled_ksplit(B, H, H), e->part, split, a);
+                    const bool fc2 = kernel_class == HE_K_FC2;
+                    int ks, sc, tl;
+                    bf16_tiled_store_plan(B, H, fc2 ? F : H, e->tiled_part_floats, &tl, &ks, &sc);
+                    bf16_gemm_tiled_store(e->stream, fc2 ? e->tiled[l].w2 : e->tiled[l].wo, fc2 ? e->hblk : e->oblk, B, H,
+                                          fc2 ? F : H, e->part, tl, ks, sc);
                 }
                 continue;
             }

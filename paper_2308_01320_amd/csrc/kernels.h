@@ -46,8 +46,6 @@ struct bf16_gemm_args {
     const void* bias = nullptr;      // bf16 [N]
     float* out = nullptr;            // EPI_STORE: partials [ksplit][M][N]; EPI_QKV: q [M][H]
     size_t out_split = 0;            // elements between k-splits
-    int split_col = 0;               // EPI_STORE on the big tiles with a k-split: first column that has one
-    int tile_na = 0;                 // ... and the tiles' width as bf16_tiled_store_split planned it
     size_t out_capacity = 0;         // EPI_STORE_LN: floats `out` can hold (0 = not checked)
     void* out_blocks = nullptr;      // EPI_BIAS_RELU: tiled half output
     void* kv = nullptr;              // EPI_QKV
@@ -98,23 +96,21 @@ void bf16_wvec(hipStream_t s, const void* Wp, int N, int K, const void* gamma, c
 // X: the activations as tiled half blocks; ksplit is ignored (the plan decides)
 void bf16_gemm_skinny(hipStream_t s, int mode, const void* Wp, const void* X, int M, int N, int K, int ksplit,
                       const bf16_gemm_args& a);
-// many rows (prompt pass)
-void bf16_gemm_tiled(hipStream_t s, int mode, const void* Wp, const void* X, int M, int N, int K, const bf16_gemm_args& a);
-// a decode step of more than 32 rows: the same tiles, cut into k ranges so that they fill the chip.  The
-// partial sums go to part [ksplit][M][N]; for EPI_STORE the caller's LayerNorm adds them, for the other
-// modes a second kernel adds them and applies the epilogue.
-int bf16_tiled_ksplit(int M, int N, int K);
-// k ranges per tile for a many-row MODE_STORE GEMM whose tiles do not come out in whole rounds of one per CU
-// (1 if they do, or if ks x M x N partial sums do not fit capacity_floats)
-int bf16_tiled_store_ksplit(int M, int N, int K, size_t capacity_floats);
-// ... and for the 256 x 256 tiles: *ks k ranges for the tiles of columns >= *split_col, one for the columns before
-// (*na: the tiles' width in 64 columns, to be handed on in bf16_gemm_args.tile_na; 0 for other tile shapes)
-void bf16_tiled_store_split(int M, int N, int K, size_t capacity_floats, int* ks, int* split_col, int* na);
+// Many rows (prompt and scoring passes, wide decode steps): EPI_BIAS_RELU or EPI_QKV.  part: scratch of part_floats
+// floats for the k ranges' sums where the tiles alone do not fill the chip (a second kernel then adds them and applies
+// the epilogue).
+void bf16_gemm_tiled(hipStream_t s, int mode, const void* Wp, const void* X, int M, int N, int K, const bf16_gemm_args& a,
+                     float* part, size_t part_floats);
+// The GEMMs whose partial sums the following LayerNorm adds (out-projection, FC2): the plan -- tile shape, *ks k ranges for
+// the columns >= *split_col, one for the columns before -- and the launch: part [ks][M][N]
+void bf16_tiled_store_plan(int M, int N, int K, size_t capacity_floats, int* tile, int* ks, int* split_col);
+void bf16_gemm_tiled_store(hipStream_t s, const void* Wp, const void* X, int M, int N, int K, float* part, int tile, int ks,
+                           int split_col);
+// floats of scratch these can make use of for passes of up to `rows` rows and matrices of up to `widest` rows
+size_t bf16_tiled_scratch_floats(int rows, int widest);
 // The plan of a many-row GEMM for a planner query (cus: compute units to plan for, 0 = the current device's)
 void bf16_tiled_plan_query(int M, int N, int K, int may_cut, size_t capacity_floats, int cus, int* tile_cols, int* ks,
                            int* split_col);
-void bf16_gemm_tiled_ksplit(hipStream_t s, int mode, const void* Wp, const void* X, int M, int N, int K, int ksplit,
-                            float* part, size_t part_split, const bf16_gemm_args& a);
 // ---- 8-bit weight storage: E4M3 codes with one power-of-two scale per row
 size_t fp8_units_bytes(int rows, int K);  // codes in the half-tile kernel's units: [rows/16][K/64][64 lanes][16 bytes]
 void fp8_row_exponents(hipStream_t s, const void* src, int R, int K, int* exps, float* scales);  // e[n], 2^e[n]

@@ -1,0 +1,53 @@
+"""GPU parity of the prompt and scoring passes of few rows (the deep-ring GEMM): row counts at the edges of its 64-, 128- and
+192-row tiles and of the 32-row blocks, column counts that end inside a 256-column tile, k ranges of different lengths, and
+wide decode steps, each against the oracle."""
+import numpy as np
+import pytest
+
+from oracle import opt_oracle as O
+from paper_2308_01320_amd import binding, synth
+from tests import util
+
+pytestmark = pytest.mark.gpu
+
+BF16_TOL, MARGIN = 2e-2, 1e-2
+
+
+@pytest.mark.parametrize("B,S", [(1, 33), (1, 64), (1, 65), (2, 64), (3, 43), (1, 191), (4, 48), (1, 193), (5, 51), (3, 86), (9, 64)])
+@pytest.mark.parametrize("H,nh,F", [(320, 5, 1344), (1024, 8, 2112)])
+def test_prompt_rows_at_tile_edges(H, nh, F, B, S):
+    d = synth.ModelDims("x", 2, H, nh, F, 300, 256, B, S, 2, "bf16", "greedy")
+    w = synth.make_weights(d, seed=5)
+    prompts = synth.make_prompts(d, seed=6)
+    want = util.oracle_run(d, util.weights_f64(w), prompts, 2, "greedy", 1.0, seed=3)
+    eng = util.make_engine(d, w)
+    got = util.engine_teacher_forced(eng, prompts, want["ids"], 2, binding.sampling("greedy", 1.0, 3))
+    eng.he_destroy()
+    util.compare(got, want, BF16_TOL, MARGIN)
+
+
+@pytest.mark.parametrize("B", [65, 96, 129, 200])
+def test_wide_decode_rows(B):
+    d = synth.ModelDims("x", 2, 1024, 8, 4096, 300, 64, B, 3, 3, "bf16", "greedy")
+    w = synth.make_weights(d, seed=5)
+    prompts = synth.make_prompts(d, seed=6)
+    want = util.oracle_run(d, util.weights_f64(w), prompts, 3, "greedy", 1.0, seed=3)
+    eng = util.make_engine(d, w)
+    got = util.engine_teacher_forced(eng, prompts, want["ids"], 3, binding.sampling("greedy", 1.0, 3))
+    eng.he_destroy()
+    util.compare(got, want, BF16_TOL, MARGIN)
+
+
+@pytest.mark.parametrize("B,T", [(1, 17), (1, 64), (2, 33), (3, 64)])
+def test_score_few_rows(B, T):
+    import torch
+    d = synth.ModelDims("x", 1, 256, 4, 512, 1111, 128, B, T, 1, "bf16", "greedy")
+    w = synth.make_weights(d, seed=3)
+    ids = synth.make_prompts(d, seed=4, batch=B, prompt_len=T)
+    eng = util.make_engine(d, w, max_batch=B, max_seq_len=T)
+    got = eng.he_score(torch.from_numpy(ids).cuda())
+    torch.cuda.synchronize()
+    got = got.cpu().numpy()
+    eng.he_destroy()
+    want = O.score(util.weights_f64(w), ids, d.n_heads, eps=d.ln_eps, pos_offset=d.pos_offset)
+    assert float(np.abs(got - want).max()) <= BF16_TOL
