@@ -21,7 +21,7 @@ struct he_engine {
     std::vector<void*> allocs;  // everything the engine owns on the device
     void* kv = nullptr;
     he_dev_state* st = nullptr;
-    float *resid = nullptr, *abuf = nullptr, *qbuf = nullptr, *obuf = nullptr, *ybuf = nullptr, *hbuf = nullptr;
+    float *resid = nullptr, *abuf = nullptr, *qbuf = nullptr, *obuf = nullptr, *hbuf = nullptr;
     float *xf = nullptr, *logits = nullptr, *gen_lp = nullptr;
     int32_t *cur_ids = nullptr, *gen_ids = nullptr;
 
@@ -141,7 +141,7 @@ Sizes sizes_of(const he_config& c) {
     s.gen = rows * sizeof(float);
     s.total = s.kv + s.logits + 2 * s.gen + c.max_batch * sizeof(int32_t) + he_dev_state_bytes(c.max_batch);
     if (!is_fast(c)) {
-        s.total += 5 * s.rowsH + s.rowsF + s.xf;
+        s.total += 4 * s.rowsH + s.rowsF + s.xf;
         return s;
     }
     const int H = c.hidden, F = c.ffn;
@@ -629,6 +629,26 @@ void tile_weights(he_engine* e) {
     bf16_wvec(e->stream, e->lm_tiled, c.vocab, H, e->w.lnf_g, e->w.lnf_b, v.c1, v.c2);
 }
 
+// Plain kernels: every layer over the M = B*S rows of the residual stream, in place.
+void plain_layers(he_engine* e, int M, int S) {
+    const he_config& c = e->cfg;
+    hipStream_t s = e->stream;
+    const int H = c.hidden, F = c.ffn, bf = e->bf16;
+    auto gemm = [&](const float* A, const void* W, const void* bias, int N, int K, int epi, float* out, int l, const plain_ln_args* ln) {
+        plain_gemm(s, bf, A, W, bias, M, N, K, epi, out, e->kv, e->st, S, l, H, c.n_heads, c.max_batch, c.max_seq_len,
+                   1.0f / sqrtf((float)e->d), ln, e->abuf);
+    };
+    for (int l = 0; l < c.n_layers; ++l) {
+        const he_layer_weights& lw = e->layers[l];
+        const plain_ln_args ln1{lw.ln1_g, lw.ln1_b, c.ln_eps, 1, 0}, ln2{lw.ln2_g, lw.ln2_b, c.ln_eps, 1, 0};
+        gemm(e->resid, lw.wqkv, lw.bqkv, 3 * H, H, EPI_QKV, e->qbuf, l, &ln1);
+        plain_attn(s, bf, e->qbuf, e->kv, e->obuf, e->st, M, S, l, H, c.n_heads, c.max_batch, c.max_seq_len);
+        gemm(e->obuf, lw.wo, lw.bo, H, H, EPI_RESID, e->resid, l, nullptr);
+        gemm(e->resid, lw.w1, lw.b1, F, H, EPI_BIAS_RELU, e->hbuf, l, &ln2);
+        gemm(e->hbuf, lw.w2, lw.b2, H, F, EPI_RESID, e->resid, l, nullptr);
+    }
+}
+
 // One pass of the decoder over M = B*S new rows (S = prompt length, or 1 for a
 // decode step) followed by the LM head on each sequence's last row and sampling.
 he_status run_forward(he_engine* e, const int32_t* d_ids, int B, int S, int32_t* ids_out, float* lp_out,
@@ -636,32 +656,15 @@ he_status run_forward(he_engine* e, const int32_t* d_ids, int B, int S, int32_t*
     if (e->fast) return run_forward_bf16(e, d_ids, B, S, ids_out, lp_out, out_stride, out_at_step, d_logits_opt);
     const he_config& c = e->cfg;
     hipStream_t s = e->stream;
-    const int M = B * S, H = c.hidden, F = c.ffn, bf = e->bf16;
-    const float qscale = 1.0f / sqrtf((float)e->d);
+    const int M = B * S, H = c.hidden, bf = e->bf16;
 
     plain_embed(s, bf, d_ids, S, e->w.tok_emb, e->w.pos_emb, e->resid, e->st, M, S, H, c.vocab, c.pos_offset);
-    const float* pend_y = nullptr;  // GEMM output not yet added to the residual stream
-    const void* pend_b = nullptr;
-    for (int l = 0; l < c.n_layers; ++l) {
-        const he_layer_weights& lw = e->layers[l];
-        plain_ln(s, bf, e->resid, pend_y, pend_b, lw.ln1_g, lw.ln1_b, e->abuf, M, H, c.ln_eps, 1, 0, 1);
-        plain_gemm(s, bf, e->abuf, lw.wqkv, lw.bqkv, M, 3 * H, H, EPI_QKV, e->qbuf, e->kv, e->st, S, l, H, c.n_heads,
-                   c.max_batch, c.max_seq_len, qscale);
-        plain_attn(s, bf, e->qbuf, e->kv, e->obuf, e->st, M, S, l, H, c.n_heads, c.max_batch, c.max_seq_len);
-        plain_gemm(s, bf, e->obuf, lw.wo, nullptr, M, H, H, EPI_STORE, e->ybuf, nullptr, e->st, S, l, H, c.n_heads,
-                   c.max_batch, c.max_seq_len, 1.f);
-        plain_ln(s, bf, e->resid, e->ybuf, lw.bo, lw.ln2_g, lw.ln2_b, e->abuf, M, H, c.ln_eps, 1, 0, 1);
-        plain_gemm(s, bf, e->abuf, lw.w1, lw.b1, M, F, H, EPI_BIAS_RELU, e->hbuf, nullptr, e->st, S, l, H, c.n_heads,
-                   c.max_batch, c.max_seq_len, 1.f);
-        plain_gemm(s, bf, e->hbuf, lw.w2, nullptr, M, H, F, EPI_STORE, e->ybuf, nullptr, e->st, S, l, H, c.n_heads,
-                   c.max_batch, c.max_seq_len, 1.f);
-        pend_y = e->ybuf;
-        pend_b = lw.b2;
-    }
+    plain_layers(e, M, S);
     // final LayerNorm on each sequence's last row only
-    plain_ln(s, bf, e->resid, pend_y, pend_b, e->w.lnf_g, e->w.lnf_b, e->xf, B, H, c.ln_eps, S, S - 1, 0);
     float* logits = d_logits_opt ? d_logits_opt : e->logits;
-    plain_lm_head(s, bf, e->xf, e->w.lm_head, logits, B, H, c.vocab);
+    const plain_ln_args lnf{e->w.lnf_g, e->w.lnf_b, c.ln_eps, S, S - 1};
+    plain_gemm(s, bf, e->resid, e->w.lm_head, nullptr, B, c.vocab, H, EPI_STORE, logits, nullptr, e->st, S, 0, H, c.n_heads,
+               c.max_batch, c.max_seq_len, 1.f, &lnf, e->xf);
     launch_sample(s, logits, B, c.vocab, e->st, ids_out, lp_out, out_stride, out_at_step, e->cur_ids);
     if (e->ragged_gen) launch_ragged_post(s, e->st, ids_out, lp_out, e->cur_ids, out_stride, B);
     launch_advance_state(s, e->st, S, 1);
@@ -787,7 +790,7 @@ he_status he_create(const he_config* cfg, const he_weights* weights, he_engine**
     A(&e->resid, z.rowsH); A(&e->qbuf, z.rowsH);
     A(&e->logits, z.logits);
     if (!e->fast) {
-        A(&e->abuf, z.rowsH); A(&e->obuf, z.rowsH); A(&e->ybuf, z.rowsH);
+        A(&e->abuf, z.rowsH); A(&e->obuf, z.rowsH);
         A(&e->hbuf, z.rowsF);
         A(&e->xf, z.xf);
     } else {
@@ -1147,7 +1150,7 @@ he_status he_score(he_engine* e, const int32_t* d_ids, int B, int T, float* d_ou
     if (rc != HE_OK) return rc;
     const he_config& c = e->cfg;
     hipStream_t s = e->stream;
-    const int M = B * T, H = c.hidden, F = c.ffn, V = c.vocab;
+    const int M = B * T, H = c.hidden, V = c.vocab;
     if (e->fast) {
         const void* pend_b = nullptr;
         int pend_ks = 1, pend_sc = 0;
@@ -1157,31 +1160,14 @@ he_status he_score(he_engine* e, const int32_t* d_ids, int B, int T, float* d_ou
         bf16_score_head(s, e->lm_tiled, e->ablk, M, T, V, H, d_ids, e->score_stats, e->score_tgt, d_out_logprobs);
     } else {
         const int bf = e->bf16;
-        const float qscale = 1.0f / sqrtf((float)e->d);
         plain_embed(s, bf, d_ids, T, e->w.tok_emb, e->w.pos_emb, e->resid, e->st, M, T, H, V, c.pos_offset);
-        const float* pend_y = nullptr;
-        const void* pend_b = nullptr;
-        for (int l = 0; l < c.n_layers; ++l) {
-            const he_layer_weights& lw = e->layers[l];
-            plain_ln(s, bf, e->resid, pend_y, pend_b, lw.ln1_g, lw.ln1_b, e->abuf, M, H, c.ln_eps, 1, 0, 1);
-            plain_gemm(s, bf, e->abuf, lw.wqkv, lw.bqkv, M, 3 * H, H, EPI_QKV, e->qbuf, e->kv, e->st, T, l, H, c.n_heads,
-                       c.max_batch, c.max_seq_len, qscale);
-            plain_attn(s, bf, e->qbuf, e->kv, e->obuf, e->st, M, T, l, H, c.n_heads, c.max_batch, c.max_seq_len);
-            plain_gemm(s, bf, e->obuf, lw.wo, nullptr, M, H, H, EPI_STORE, e->ybuf, nullptr, e->st, T, l, H, c.n_heads,
-                       c.max_batch, c.max_seq_len, 1.f);
-            plain_ln(s, bf, e->resid, e->ybuf, lw.bo, lw.ln2_g, lw.ln2_b, e->abuf, M, H, c.ln_eps, 1, 0, 1);
-            plain_gemm(s, bf, e->abuf, lw.w1, lw.b1, M, F, H, EPI_BIAS_RELU, e->hbuf, nullptr, e->st, T, l, H, c.n_heads,
-                       c.max_batch, c.max_seq_len, 1.f);
-            plain_gemm(s, bf, e->hbuf, lw.w2, nullptr, M, H, F, EPI_STORE, e->ybuf, nullptr, e->st, T, l, H, c.n_heads,
-                       c.max_batch, c.max_seq_len, 1.f);
-            pend_y = e->ybuf;
-            pend_b = lw.b2;
-        }
+        plain_layers(e, M, T);
         // final LayerNorm of every row into abuf, then the LM head max_batch rows at a time
-        plain_ln(s, bf, e->resid, pend_y, pend_b, e->w.lnf_g, e->w.lnf_b, e->abuf, M, H, c.ln_eps, 1, 0, 0);
+        plain_ln(s, bf, e->resid, plain_ln_args{e->w.lnf_g, e->w.lnf_b, c.ln_eps, 1, 0}, e->abuf, M, H);
         for (int r0 = 0; r0 < M; r0 += c.max_batch) {
             const int n = M - r0 < c.max_batch ? M - r0 : c.max_batch;
-            plain_lm_head(s, bf, e->abuf + (size_t)r0 * H, e->w.lm_head, e->logits, n, H, V);
+            plain_gemm(s, bf, e->abuf + (size_t)r0 * H, e->w.lm_head, nullptr, n, V, H, EPI_STORE, e->logits, nullptr, e->st, T, 0, H,
+                       c.n_heads, c.max_batch, c.max_seq_len, 1.f);
             plain_score_rows(s, e->logits, d_ids, r0, n, T, V, d_out_logprobs);
         }
     }

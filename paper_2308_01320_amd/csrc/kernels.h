@@ -5,19 +5,21 @@
 
 struct he_dev_state;
 
-enum { EPI_STORE = 0, EPI_BIAS_RELU = 1, EPI_QKV = 2, EPI_STORE_LN = 3 };
+enum { EPI_STORE = 0, EPI_BIAS_RELU = 1, EPI_QKV = 2, EPI_STORE_LN = 3, EPI_RESID = 4 };
 
 // ---- plain kernels (kernels_plain.hip): float activations, row-major; bf16 != 0 selects bf16 storage
 void plain_embed(hipStream_t s, int bf16, const int32_t* ids, int id_stride, const void* tok, const void* pos, float* x,
                  const he_dev_state* st, int M, int S, int H, int V, int pos_offset);
-void plain_ln(hipStream_t s, int bf16, float* r, const float* y, const void* ybias, const void* g, const void* b,
-              float* a, int rows, int H, float eps, int in_mul, int in_add, int writeback);
+// LayerNorm of rows m*in_mul + in_add of the residual stream
+struct plain_ln_args { const void *gamma, *beta; float eps; int in_mul, in_add; };
+void plain_ln(hipStream_t s, int bf16, const float* r, const plain_ln_args& ln, float* a, int rows, int H);
+// epi: EPI_STORE, EPI_BIAS_RELU, EPI_QKV, or EPI_RESID (out += the product + bias).  ln: A is the residual stream, normalised on
+// the way in (scratch [M][K] is used when there are many rows)
 void plain_gemm(hipStream_t s, int bf16, const float* A, const void* W, const void* bias, int M, int N, int K, int epi,
                 float* out, void* kv, const he_dev_state* st, int S, int layer, int H, int n_heads, int max_batch,
-                int max_seq, float qscale);
+                int max_seq, float qscale, const plain_ln_args* ln = nullptr, float* scratch = nullptr);
 void plain_attn(hipStream_t s, int bf16, const float* q, const void* kv, float* o, const he_dev_state* st, int M, int S,
                 int layer, int H, int n_heads, int max_batch, int max_seq);
-void plain_lm_head(hipStream_t s, int bf16, const float* xf, const void* W, float* logits, int B, int H, int V);
 // rows row0 .. row0+n-1 of the M = B*S positions, given their logits [n][V]: out[b][t] = log_softmax(z)[ids[m+1]]
 void plain_score_rows(hipStream_t s, const float* logits, const int32_t* ids, int row0, int n, int S, int V, float* out);
 

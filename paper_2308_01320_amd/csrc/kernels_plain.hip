@@ -47,119 +47,238 @@ __global__ void embed_kernel(const int32_t* __restrict__ ids, int id_stride, con
         x[(size_t)m * H + i] = ld_f32(tok, (size_t)id * H + i) + ld_f32(pos, p * H + i);
 }
 
-// Row `row = m*in_mul + in_add` of the residual stream: r += y + bias (when y is given,
-// written back when writeback), then a[m,:] = LayerNorm(r).
+// a[m,:] = LayerNorm of row m*in_mul + in_add of the residual stream.  (Many rows; a few are normalised inside the GEMM.)
 template <typename ST>
-__global__ void ln_kernel(float* __restrict__ r, const float* __restrict__ y, const ST* __restrict__ ybias,
-                          const ST* __restrict__ gamma, const ST* __restrict__ beta, float* __restrict__ a, int H,
-                          float eps, int in_mul, int in_add, int writeback) {
+__global__ void ln_kernel(const float* __restrict__ r, const ST* __restrict__ gamma, const ST* __restrict__ beta,
+                          float* __restrict__ a, int H, float eps, int in_mul, int in_add) {
     __shared__ float red[8];
     const int m = blockIdx.x;
-    const size_t row = (size_t)m * in_mul + in_add;
-    float* rr = r + row * H;
+    const float* rr = r + ((size_t)m * in_mul + in_add) * H;
     float s = 0.f;
-    for (int i = threadIdx.x; i < H; i += blockDim.x) {
-        float v = rr[i];
-        if (y) v += y[row * H + i] + ld_f32(ybias, i);
-        if (y && writeback) rr[i] = v;
-        a[(size_t)m * H + i] = v;  // staged; normalised below
-        s += v;
-    }
+    for (int i = threadIdx.x; i < H; i += blockDim.x) s += rr[i];
     const float mean = block_sum(s, red) / H;
     float q = 0.f;
     for (int i = threadIdx.x; i < H; i += blockDim.x) {
-        const float dlt = a[(size_t)m * H + i] - mean;
+        const float dlt = rr[i] - mean;
         q += dlt * dlt;
     }
     const float rstd = 1.0f / sqrtf(block_sum(q, red) / H + eps);
-    for (int i = threadIdx.x; i < H; i += blockDim.x) {
-        const float v = a[(size_t)m * H + i];
-        a[(size_t)m * H + i] = (v - mean) * rstd * ld_f32(gamma, i) + ld_f32(beta, i);
-    }
+    for (int i = threadIdx.x; i < H; i += blockDim.x)
+        a[(size_t)m * H + i] = (rr[i] - mean) * rstd * ld_f32(gamma, i) + ld_f32(beta, i);
 }
 
-// C[m,n] = sum_k A[m,k] W[n,k]; 64x64 tile, 4x4 outputs per thread, K staged 16 at a time.
+// ----------------------------------------------------------------- GEMM
+//
+// C[m,n] = sum_k A[m,k] W[n,k] in float on the matrix cores (16x16x4: 4 KFLOP per wavefront and four k, float operands and
+// accumulators).  A wavefront holds T x T tiles of 16 x 16; lane l loads W[n0 + l%16][k .. k+3] and A[m0 + l%16][k .. k+3], k = 16 step + 4 (l/16),
+// 16 bytes each, and instruction i of a step multiplies element i of both: the four lane groups' k values differ, but
+// by the same rule on both sides.  No LDS staging: the models of this path are small and their rows come out of L2.
+// What bounds it is the length of the dependent chain -- a launch, a load or two, a few matrix instructions -- so the k
+// range is split over KW wavefronts of a workgroup (partial sums added in wavefront order through LDS) and the few rows
+// of a decode step go 16 columns to a workgroup.  Measured on 4 rows (float, captured decode step): the 256 x 256 and
+// 256 x 1024 matrices together 139 -> 9.8 us, 768 x 256 with its LayerNorm 40 -> 6.1; the kernel before this gave a 64 x 64
+// tile to a workgroup and walked k alone.
+//   few rows (at most 64):      T = 1, KW = 8: 16 columns x 16 rows per workgroup, LayerNorm of the rows folded in
+//   many tiles (from 256 on):   T = 2, KW = 1: 64 x 64 per workgroup of four wavefronts
+//   else:                       T = 2, KW = 8: 32 x 32 per workgroup
+// VEC: K is a multiple of four and the rows are aligned for 16-byte loads (8-byte ones for bf16 storage).
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
+template <bool VEC>
+__device__ __forceinline__ f32x4 load_k4(const float* row, int k, int K) {
+    if (VEC) return k < K ? *reinterpret_cast<const f32x4*>(row + k) : f32x4{0.f, 0.f, 0.f, 0.f};
+    f32x4 v = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+        if (k + i < K) v[i] = row[k + i];
+    return v;
+}
+template <bool VEC>
+__device__ __forceinline__ f32x4 load_k4(const bf16_t* row, int k, int K) {
+    f32x4 v = {0.f, 0.f, 0.f, 0.f};
+    if (VEC) {
+        if (k < K) {
+            const uint2 w = *reinterpret_cast<const uint2*>(row + k);
+            v = f32x4{__uint_as_float(w.x << 16), __uint_as_float(w.x & 0xFFFF0000u), __uint_as_float(w.y << 16),
+                      __uint_as_float(w.y & 0xFFFF0000u)};
+        }
+        return v;
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+        if (k + i < K) v[i] = bf16_to_f32(row[k + i]);
+    return v;
+}
+
+struct PlainGemm {
+    int M, N, K, epi;
+    float* out;
+    float* kv;
+    const he_dev_state* st;
+    int S, layer, H, n_heads, max_batch, max_seq;
+    float qscale;
+    float eps;           // folded LayerNorm: row m of A is row m*in_mul + in_add of the residual stream, not normalised
+    int in_mul, in_add;
+    int vec_out;         // four consecutive outputs may be stored at once
+};
+
 template <typename ST>
-__global__ void gemm_kernel(const float* __restrict__ A, const ST* __restrict__ W, const ST* __restrict__ bias, int M,
-                            int N, int K, int epi, float* __restrict__ out, float* __restrict__ kv,
-                            const he_dev_state* __restrict__ st, int S, int layer, int H, int n_heads, int max_batch,
-                            int max_seq, float qscale) {
-    __shared__ float As[16][65];
-    __shared__ float Ws[16][65];
-    const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
-    const int m0 = blockIdx.y * 64, n0 = blockIdx.x * 64;
-    float acc[4][4] = {};
-    for (int k0 = 0; k0 < K; k0 += 16) {
-        for (int i = threadIdx.x; i < 64 * 16; i += kThreads) {
-            const int r = i >> 4, c = i & 15;
-            As[c][r] = (m0 + r < M && k0 + c < K) ? A[(size_t)(m0 + r) * K + k0 + c] : 0.f;
-            Ws[c][r] = (n0 + r < N && k0 + c < K) ? ld_f32(W, (size_t)(n0 + r) * K + k0 + c) : 0.f;
+__device__ __forceinline__ void plain_epilogue4(const PlainGemm& p, const ST* __restrict__ bias, int m, int n0, f32x4 v) {
+    if (m >= p.M) return;
+    const int nv = min(4, p.N - n0);
+    if (p.epi != EPI_STORE)
+        for (int i = 0; i < nv; ++i) v[i] += ld_f32(bias, n0 + i);
+    float* dst = p.out + (size_t)m * p.N + n0;
+    if (p.epi == EPI_BIAS_RELU) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) v[i] = fmaxf(v[i], 0.f);
+    } else if (p.epi == EPI_RESID) {
+        for (int i = 0; i < nv; ++i) v[i] = dst[i] + v[i];
+    } else if (p.epi == EPI_QKV) {  // q scaled to `out`, k and v appended to the cache (H and the head dimension are multiples of 8)
+        const int d = p.H / p.n_heads;
+        if (n0 < p.H) {
+            dst = p.out + (size_t)m * p.H + n0;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) v[i] *= p.qscale;
+        } else if (n0 < p.N) {
+            const int which = n0 >= 2 * p.H, c = n0 - (which ? 2 * p.H : p.H);
+            const int b = row_seq(p.st, m, p.S), tr = m % p.S - row_pad(p.st, b);
+            if (tr < 0) return;  // padding rows append nothing
+            dst = p.kv + kv_index(p.layer, which, b, c / d, seq_len(p.st, b) + tr, p.max_batch, p.n_heads, p.max_seq, d) + (c % d);
         }
-        __syncthreads();
-#pragma unroll
-        for (int c = 0; c < 16; ++c) {
-            float av[4], wv[4];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) { av[i] = As[c][ty * 4 + i]; wv[i] = Ws[c][tx * 4 + i]; }
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) acc[i][j] = fmaf(av[i], wv[j], acc[i][j]);
-        }
-        __syncthreads();
     }
-    const int d = H / n_heads;
-    for (int i = 0; i < 4; ++i) {
-        const int m = m0 + ty * 4 + i;
-        if (m >= M) continue;
-        for (int j = 0; j < 4; ++j) {
-            const int n = n0 + tx * 4 + j;
-            if (n >= N) continue;
-            float v = acc[i][j];
-            if (epi == EPI_STORE) {
-                out[(size_t)m * N + n] = v;
-            } else if (epi == EPI_BIAS_RELU) {
-                v += ld_f32(bias, n);
-                out[(size_t)m * N + n] = v > 0.f ? v : 0.f;
-            } else {  // EPI_QKV: q scaled to `out`, k and v appended to the cache at cur_len + t
-                v += ld_f32(bias, n);
-                if (n < H) {
-                    out[(size_t)m * H + n] = v * qscale;
-                } else {
-                    const int which = (n >= 2 * H), c = n - (which ? 2 * H : H);
-                    const int b = m / S, tr = m % S - row_pad(st, b);  // padding rows append nothing
-                    if (tr >= 0)
-                        st_val(kv, kv_index(layer, which, b, c / d, seq_len(st, b) + tr, max_batch, n_heads, max_seq, d) + (c % d), v);
-                }
-            }
-        }
+    if (p.vec_out && nv == 4) {
+        *reinterpret_cast<f32x4*>(dst) = v;
+    } else {
+        for (int i = 0; i < nv; ++i) dst[i] = v[i];
     }
 }
 
-// One block per (row m, head h): scores over keys 0..cur_len+t, softmax, weighted sum of values.
-__global__ void attn_kernel(const float* __restrict__ q, const float* __restrict__ kv, float* __restrict__ o,
-                            const he_dev_state* __restrict__ st, int S, int layer, int H, int n_heads, int max_batch,
-                            int max_seq) {
-    extern __shared__ float smem[];
+template <typename ST, int T, int KW, int WN, int WM, bool VEC, bool LN>
+__global__ __launch_bounds__(64 * KW * WN * WM) void gemm_kernel(const float* __restrict__ A, const ST* __restrict__ W,
+                                                                 const ST* __restrict__ bias, const ST* __restrict__ gamma,
+                                                                 const ST* __restrict__ beta, PlainGemm p) {
+    static_assert(!LN || (T == 1 && WM == 1), "the folded LayerNorm knows one 16-row tile");
+    constexpr int U = T == 1 ? 4 : 2;  // steps of 16 k requested together
+    __shared__ float red[KW > 1 ? KW : 1][T * T][4][64];
+    __shared__ float smean[16], srstd[16];
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, l16 = lane & 15, kq = 4 * (lane >> 4);
+    const int kw = wave % KW, wn = (wave / KW) % WN, wm = wave / (KW * WN);
+    const int n0 = (blockIdx.x * WN + wn) * 16 * T, m0 = (blockIdx.y * WM + wm) * 16 * T;
+    const int steps = (p.K + 15) / 16;
+    const int s0 = kw * steps / KW, s1 = (kw + 1) * steps / KW;
+    const ST* wr[T];
+    const float* ar[T];
+#pragma unroll
+    for (int t = 0; t < T; ++t) {  // rows past the end: the last one (computed, never stored)
+        wr[t] = W + (size_t)min(n0 + 16 * t + l16, p.N - 1) * p.K;
+        const size_t m = min(m0 + 16 * t + l16, p.M - 1);
+        ar[t] = A + (LN ? m * p.in_mul + p.in_add : m) * p.K;
+    }
+    f32x4 acc[T][T];
+#pragma unroll
+    for (int i = 0; i < T; ++i)
+#pragma unroll
+        for (int j = 0; j < T; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    f32x4 w[U][T], a[U][T], g[U], be[U];
+    auto load = [&](int s) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int k = s + u < s1 ? 16 * (s + u) + kq : p.K;  // (past this wavefront's range: zeros)
+#pragma unroll
+            for (int t = 0; t < T; ++t) {
+                w[u][t] = load_k4<VEC>(wr[t], k, p.K);
+                a[u][t] = load_k4<VEC>(ar[t], k, p.K);
+            }
+            if (LN) { g[u] = load_k4<VEC>(gamma, k, p.K); be[u] = load_k4<VEC>(beta, k, p.K); }
+        }
+    };
+    load(s0);
+    float mean = 0.f, rstd = 0.f;
+    if (LN) {  // mean and 1/sqrt(var + eps) of the tile's rows, a wavefront per row
+        for (int r = wave; r < 16 && m0 + r < p.M; r += KW * WN) {
+            const float* row = A + ((size_t)(m0 + r) * p.in_mul + p.in_add) * p.K;
+            float s = 0.f;
+            for (int k = lane; k < p.K; k += 64) s += row[k];
+            for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o);
+            const float mu = s / p.K;
+            float q = 0.f;
+            for (int k = lane; k < p.K; k += 64) { const float dlt = row[k] - mu; q += dlt * dlt; }
+            for (int o = 32; o > 0; o >>= 1) q += __shfl_xor(q, o);
+            if (lane == 0) { smean[r] = mu; srstd[r] = 1.0f / sqrtf(q / p.K + p.eps); }
+        }
+        __syncthreads();
+        const int r = min(l16, min(16, p.M - m0) - 1);
+        mean = smean[r]; rstd = srstd[r];
+    }
+    for (int s = s0; s < s1; s += U) {
+        if (s > s0) load(s);
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (LN) a[u][0] = (a[u][0] - mean) * rstd * g[u] + be[u];
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+#pragma unroll
+                for (int i = 0; i < T; ++i)
+#pragma unroll
+                    for (int j = 0; j < T; ++j)
+                        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(w[u][i][e], a[u][j][e], acc[i][j], 0, 0, 0);
+        }
+    }
+    if (KW > 1) {
+#pragma unroll
+        for (int i = 0; i < T; ++i)
+#pragma unroll
+            for (int j = 0; j < T; ++j)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) red[kw][i * T + j][r][lane] = acc[i][j][r];
+        __syncthreads();
+        for (int t = kw; t < T * T; t += KW) {
+            f32x4 v = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int x = 0; x < KW; ++x)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) v[r] += red[x][t][r][lane];
+            plain_epilogue4(p, bias, m0 + 16 * (t % T) + l16, n0 + 16 * (t / T) + kq, v);
+        }
+    } else {
+#pragma unroll
+        for (int i = 0; i < T; ++i)
+#pragma unroll
+            for (int j = 0; j < T; ++j) plain_epilogue4(p, bias, m0 + 16 * j + l16, n0 + 16 * i + kq, acc[i][j]);
+    }
+}
+
+// One block per (row m, head h): scores over keys 0..cur_len+t, softmax, weighted sum of values.  16 lanes share a key
+// (four of its dimensions at a time); a thread of the second part owns four output dimensions of a share of the keys.
+__global__ __launch_bounds__(256) void attn_kernel(const float* __restrict__ q, const float* __restrict__ kv,
+                                                   float* __restrict__ o, const he_dev_state* __restrict__ st, int S, int layer,
+                                                   int H, int n_heads, int max_batch, int max_seq) {
+    extern __shared__ __align__(16) float smem[];
     __shared__ float red[8];
-    const int d = H / n_heads;
-    float* qs = smem;      // [d]
-    float* sc = smem + d;  // [max_seq]
+    const int d = H / n_heads, d4 = d / 4;  // (d is a multiple of 8)
+    f32x4* part = reinterpret_cast<f32x4*>(smem);  // [256] partial outputs
+    float* sc = smem + 4 * 256;                    // [max_seq] scores, then probabilities
     const int m = blockIdx.x, h = blockIdx.y;
     const int b = m / S, nkeys = seq_len(st, b) + (m % S) - row_pad(st, b) + 1;
     if (nkeys <= 0 || seq_done(st, b)) {  // a padding row, or a sequence that has ended: nothing reads this output
         for (int e = threadIdx.x; e < d; e += blockDim.x) o[(size_t)m * H + h * d + e] = 0.f;
         return;
     }
-    const float* Kp = kv + kv_index(layer, 0, b, h, 0, max_batch, n_heads, max_seq, d);
-    const float* Vp = kv + kv_index(layer, 1, b, h, 0, max_batch, n_heads, max_seq, d);
-    for (int e = threadIdx.x; e < d; e += blockDim.x) qs[e] = q[(size_t)m * H + h * d + e];
-    __syncthreads();
+    const f32x4* Q = reinterpret_cast<const f32x4*>(q + (size_t)m * H + h * d);
+    const f32x4* Kp = reinterpret_cast<const f32x4*>(kv + kv_index(layer, 0, b, h, 0, max_batch, n_heads, max_seq, d));
+    const f32x4* Vp = reinterpret_cast<const f32x4*>(kv + kv_index(layer, 1, b, h, 0, max_batch, n_heads, max_seq, d));
+    const int sub = threadIdx.x & 15;
     float mx = -INFINITY;
-    for (int j = threadIdx.x; j < nkeys; j += blockDim.x) {
+    for (int j = threadIdx.x >> 4; j < nkeys; j += 16) {
         float s = 0.f;
-        for (int e = 0; e < d; ++e) s = fmaf(qs[e], ld_f32(Kp, (size_t)j * d + e), s);
-        sc[j] = s;
+        for (int e = sub; e < d4; e += 16) {
+            const f32x4 a = Q[e], c = Kp[(size_t)j * d4 + e];
+            s = fmaf(a[0], c[0], s); s = fmaf(a[1], c[1], s); s = fmaf(a[2], c[2], s); s = fmaf(a[3], c[3], s);
+        }
+#pragma unroll
+        for (int x = 1; x < 16; x <<= 1) s += __shfl_xor(s, x);
+        if (sub == 0) sc[j] = s;
         mx = fmaxf(mx, s);
     }
     mx = block_max(mx, red);
@@ -170,34 +289,22 @@ __global__ void attn_kernel(const float* __restrict__ q, const float* __restrict
         sum += p;
     }
     sum = block_sum(sum, red);  // also orders the sc[] writes before the reads below
-    for (int e = threadIdx.x; e < d; e += blockDim.x) {
-        float acc = 0.f;
-        for (int j = 0; j < nkeys; ++j) acc = fmaf(sc[j], ld_f32(Vp, (size_t)j * d + e), acc);
-        o[(size_t)m * H + h * d + e] = acc / sum;
+    const int parts = 256 / d4, e = threadIdx.x % d4, part0 = threadIdx.x / d4;  // (d <= 256: at least four shares of the keys)
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+    if (part0 < parts) {
+        for (int j = part0; j < nkeys; j += parts) {
+            const f32x4 v = Vp[(size_t)j * d4 + e];
+            const float p = sc[j];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) acc[i] = fmaf(p, v[i], acc[i]);
+        }
+        part[threadIdx.x] = acc;
     }
-}
-
-// logits[b,v] = sum_k xf[b,k] Wlm[v,k]: one wave per vocabulary row, all batch rows at once.
-template <typename ST>
-__global__ void lm_head_kernel(const float* __restrict__ xf, const ST* __restrict__ W, float* __restrict__ logits,
-                               int B, int H, int V) {
-    const int v = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
-    const int lane = threadIdx.x & 63;
-    if (v >= V) return;
-    for (int b0 = 0; b0 < B; b0 += 8) {
-        float acc[8] = {};
-        for (int k = lane; k < H; k += 64) {
-            const float w = ld_f32(W, (size_t)v * H + k);
-#pragma unroll
-            for (int i = 0; i < 8; ++i)
-                if (b0 + i < B) acc[i] = fmaf(w, xf[(size_t)(b0 + i) * H + k], acc[i]);
-        }
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            float a = acc[i];
-            for (int o = 32; o > 0; o >>= 1) a += __shfl_xor(a, o);
-            if (lane == 0 && b0 + i < B) logits[(size_t)(b0 + i) * V + v] = a;
-        }
+    __syncthreads();
+    if ((int)threadIdx.x < d4) {
+        f32x4 t = part[threadIdx.x];
+        for (int x = 1; x < parts; ++x) t += part[threadIdx.x + x * d4];
+        reinterpret_cast<f32x4*>(o + (size_t)m * H + h * d)[threadIdx.x] = t / sum;
     }
 }
 
@@ -376,41 +483,65 @@ void plain_embed(hipStream_t s, int bf16, const int32_t* ids, int id_stride, con
     else plain_embed_t<float>(s, ids, id_stride, tok, pos, x, st, M, S, H, V, pos_offset);
 }
 
-void plain_ln(hipStream_t s, int bf16, float* r, const float* y, const void* ybias, const void* g, const void* b,
-              float* a, int rows, int H, float eps, int in_mul, int in_add, int writeback) {
+void plain_ln(hipStream_t s, int bf16, const float* r, const plain_ln_args& ln, float* a, int rows, int H) {
     if (bf16)
-        ln_kernel<bf16_t><<<rows, kThreads, 0, s>>>(r, y, (const bf16_t*)ybias, (const bf16_t*)g, (const bf16_t*)b, a,
-                                                    H, eps, in_mul, in_add, writeback);
+        ln_kernel<bf16_t><<<rows, kThreads, 0, s>>>(r, (const bf16_t*)ln.gamma, (const bf16_t*)ln.beta, a, H, ln.eps, ln.in_mul,
+                                                    ln.in_add);
     else
-        ln_kernel<float><<<rows, kThreads, 0, s>>>(r, y, (const float*)ybias, (const float*)g, (const float*)b, a, H,
-                                                   eps, in_mul, in_add, writeback);
+        ln_kernel<float><<<rows, kThreads, 0, s>>>(r, (const float*)ln.gamma, (const float*)ln.beta, a, H, ln.eps, ln.in_mul,
+                                                   ln.in_add);
+}
+
+// rows up to which the LayerNorm is folded into the GEMM: every workgroup of 16 columns then normalises its 16 rows for itself
+constexpr int kFewRows = 64;
+
+template <typename ST, bool VEC>
+static void launch_gemm(hipStream_t s, const float* A, const ST* W, const ST* bias, const plain_ln_args* ln, const PlainGemm& p) {
+    const ST *gamma = ln ? (const ST*)ln->gamma : nullptr, *beta = ln ? (const ST*)ln->beta : nullptr;
+    if (p.M <= kFewRows) {
+        const dim3 grid((p.N + 15) / 16, (p.M + 15) / 16);
+        if (ln) gemm_kernel<ST, 1, 8, 1, 1, VEC, true><<<grid, 512, 0, s>>>(A, W, bias, gamma, beta, p);
+        else gemm_kernel<ST, 1, 8, 1, 1, VEC, false><<<grid, 512, 0, s>>>(A, W, bias, gamma, beta, p);
+        return;
+    }
+    const dim3 big((p.N + 63) / 64, (p.M + 63) / 64);
+    if (big.x * big.y >= 256)
+        gemm_kernel<ST, 2, 1, 2, 2, VEC, false><<<big, 256, 0, s>>>(A, W, bias, gamma, beta, p);
+    else
+        gemm_kernel<ST, 2, 8, 1, 1, VEC, false><<<dim3((p.N + 31) / 32, (p.M + 31) / 32), 512, 0, s>>>(A, W, bias, gamma, beta, p);
+}
+
+template <typename ST>
+static void plain_gemm_t(hipStream_t s, const float* A, const void* W, const void* bias, const plain_ln_args* ln, float* scratch,
+                         PlainGemm& p) {
+    if (ln && p.M > kFewRows) {
+        plain_ln(s, sizeof(ST) == 2, A, *ln, scratch, p.M, p.K);
+        A = scratch;
+        ln = nullptr;
+    }
+    // the engine's activations are aligned; the caller's matrices and vectors may start anywhere, and rows follow one another
+    auto at = [](const void* q) { return (uintptr_t)q % (4 * sizeof(ST)) == 0; };
+    p.vec_out = p.N % 4 == 0 && (uintptr_t)p.out % 16 == 0;
+    const bool vec = p.K % 4 == 0 && at(W) && (!ln || (at(ln->gamma) && at(ln->beta)));
+    if (ln) { p.eps = ln->eps; p.in_mul = ln->in_mul; p.in_add = ln->in_add; }
+    if (vec) launch_gemm<ST, true>(s, A, (const ST*)W, (const ST*)bias, ln, p);
+    else launch_gemm<ST, false>(s, A, (const ST*)W, (const ST*)bias, ln, p);
 }
 
 void plain_gemm(hipStream_t s, int bf16, const float* A, const void* W, const void* bias, int M, int N, int K, int epi,
                 float* out, void* kv, const he_dev_state* st, int S, int layer, int H, int n_heads, int max_batch,
-                int max_seq, float qscale) {
-    dim3 grid((N + 63) / 64, (M + 63) / 64);
-    if (bf16)
-        gemm_kernel<bf16_t><<<grid, kThreads, 0, s>>>(A, (const bf16_t*)W, (const bf16_t*)bias, M, N, K, epi, out,
-                                                      (float*)kv, st, S, layer, H, n_heads, max_batch, max_seq,
-                                                      qscale);
-    else
-        gemm_kernel<float><<<grid, kThreads, 0, s>>>(A, (const float*)W, (const float*)bias, M, N, K, epi, out,
-                                                     (float*)kv, st, S, layer, H, n_heads, max_batch, max_seq, qscale);
+                int max_seq, float qscale, const plain_ln_args* ln, float* scratch) {
+    PlainGemm p{M, N, K, epi, out, (float*)kv, st, S, layer, H, n_heads, max_batch, max_seq, qscale, 0.f, 1, 0, 0};
+    if (bf16) plain_gemm_t<bf16_t>(s, A, W, bias, ln, scratch, p);
+    else plain_gemm_t<float>(s, A, W, bias, ln, scratch, p);
 }
 
 void plain_attn(hipStream_t s, int bf16, const float* q, const void* kv, float* o, const he_dev_state* st, int M, int S,
                 int layer, int H, int n_heads, int max_batch, int max_seq) {
     dim3 grid(M, n_heads);
-    const size_t shm = (size_t)(H / n_heads + max_seq) * sizeof(float);
+    const size_t shm = (size_t)(4 * 256 + max_seq) * sizeof(float);
     (void)bf16;  // the plain kernels keep keys and values as floats whatever the weights' type
-    attn_kernel<<<grid, 128, shm, s>>>(q, (const float*)kv, o, st, S, layer, H, n_heads, max_batch, max_seq);
-}
-
-void plain_lm_head(hipStream_t s, int bf16, const float* xf, const void* W, float* logits, int B, int H, int V) {
-    const int grid = (V + 3) / 4;
-    if (bf16) lm_head_kernel<bf16_t><<<grid, kThreads, 0, s>>>(xf, (const bf16_t*)W, logits, B, H, V);
-    else lm_head_kernel<float><<<grid, kThreads, 0, s>>>(xf, (const float*)W, logits, B, H, V);
+    attn_kernel<<<grid, 256, shm, s>>>(q, (const float*)kv, o, st, S, layer, H, n_heads, max_batch, max_seq);
 }
 
 // one workgroup per row: log-sum-exp of the row's logits, then the next token's log-probability

@@ -328,3 +328,21 @@ def test_pretiled_weights_give_identical_results():
     torch.cuda.synchronize()
     assert torch.equal(a, b) and torch.equal(al, bl)
     e0.he_destroy(); e1.he_destroy()
+
+
+@pytest.mark.parametrize("L,H,nh,F,V,B,S,G", [
+    (2, 96, 3, 77, 101, 3, 5, 3),       # odd ffn and vocabulary: element-wise loads and stores
+    (1, 136, 17, 24, 64, 1, 1, 2),      # head dimension 8, one row
+    (2, 200, 1, 300, 333, 17, 4, 3),    # head dimension 200, a second 16-row tile, a k range that ends inside a step
+    (1, 256, 4, 1024, 900, 5, 13, 2),   # 65 prompt rows: one more than the few-row kernel takes
+    (1, 512, 8, 2048, 500, 9, 29, 2),   # 64 x 64 tiles with row and column remainders
+])
+def test_f32_gemm_variants(L, H, nh, F, V, B, S, G):
+    d = synth.ModelDims("x", L, H, nh, F, V, 128, B, S, G, "f32", "greedy")
+    w = synth.make_weights(d, seed=5)
+    prompts = synth.make_prompts(d, seed=6)
+    want = util.oracle_run(d, util.weights_f64(w), prompts, G, "greedy", 1.0, seed=3)
+    eng = util.make_engine(d, w)
+    got = util.engine_teacher_forced(eng, prompts, want["ids"], G, binding.sampling("greedy", 1.0, 3))
+    eng.he_destroy()
+    util.compare(got, want, 1e-5, 1e-4)  # logits of order one: a few hundred float roundings
