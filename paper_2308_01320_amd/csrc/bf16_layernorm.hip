@@ -245,35 +245,55 @@ __global__ __launch_bounds__(64) void embed_ln_kernel(const int32_t* __restrict_
     if (lane == 0) stats[((size_t)(m >> 5) * groups + g) * 32 + (m & 31)] = make_float2(mean, q2);
 }
 
-// c1[n] = sum_k W[n][k] gamma[k], c2[n] = sum_k W[n][k] beta[k] from the tiled weights: one
-// wavefront per 32-row tile (lane = row and k half), float accumulation in k order.
-__global__ __launch_bounds__(256) void wvec_kernel(const u32x4* __restrict__ Wp, int KB, int n_tiles,
-                                                   const bf16_t* __restrict__ gamma, const bf16_t* __restrict__ beta,
-                                                   float* __restrict__ c1, float* __restrict__ c2) {
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int tile = blockIdx.x * 4 + wave;
-    if (tile >= n_tiles) return;
+// c1[n] = sum_k W[n][k] gamma[k], c2[n] = sum_k W[n][k] beta[k] from the tiled weights: a workgroup per 32-row tile (lane =
+// row and k half), its eight wavefronts each with a share of k, float accumulation in k order, the shares' sums added in
+// wavefront order.  Bound by reading the matrix once; four blocks on their way per wavefront.  (A wavefront per tile, one
+// block at a time, as before: 16384 x 4096 136 -> 38 us.)
+constexpr int kWvecWaves = 8;
+__global__ __launch_bounds__(64 * kWvecWaves) void wvec_kernel(const u32x4* __restrict__ Wp, int KB,
+                                                               const bf16_t* __restrict__ gamma,
+                                                               const bf16_t* __restrict__ beta, float* __restrict__ c1,
+                                                               float* __restrict__ c2) {
+    __shared__ float red[2][kWvecWaves][32];
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, tile = blockIdx.x;
+    const int kb0 = wave * KB / kWvecWaves, kb1 = (wave + 1) * KB / kWvecWaves;
     const u32x4* w = Wp + (size_t)tile * KB * 64 + lane;
     float a1 = 0.f, a2 = 0.f;
-    for (int kb = 0; kb < KB; ++kb) {
-        const u32x4 wv = w[(size_t)kb * 64];
-        const int k0 = kb * 16 + (lane >> 5) * 8;
-        const u32x4 gv = *reinterpret_cast<const u32x4*>(gamma + k0), bv = *reinterpret_cast<const u32x4*>(beta + k0);
-        const uint32_t ww[4] = {wv.x, wv.y, wv.z, wv.w}, gg[4] = {gv.x, gv.y, gv.z, gv.w}, bb[4] = {bv.x, bv.y, bv.z, bv.w};
+    constexpr int U = 4;
+    for (int kb = kb0; kb < kb1; kb += U) {
+        u32x4 wv[U], gv[U], bv[U];
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const float w0 = half_lo(ww[j]), w1 = half_hi(ww[j]);
-            a1 = fmaf(w0, bf_lo(gg[j]), a1);
-            a1 = fmaf(w1, bf_hi(gg[j]), a1);
-            a2 = fmaf(w0, bf_lo(bb[j]), a2);
-            a2 = fmaf(w1, bf_hi(bb[j]), a2);
+        for (int u = 0; u < U; ++u) {
+            const int k = min(kb + u, kb1 - 1);
+            wv[u] = __builtin_nontemporal_load(w + (size_t)k * 64);
+            gv[u] = *reinterpret_cast<const u32x4*>(gamma + k * 16 + (lane >> 5) * 8);
+            bv[u] = *reinterpret_cast<const u32x4*>(beta + k * 16 + (lane >> 5) * 8);
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (kb + u >= kb1) break;
+            const uint32_t ww[4] = {wv[u].x, wv[u].y, wv[u].z, wv[u].w}, gg[4] = {gv[u].x, gv[u].y, gv[u].z, gv[u].w};
+            const uint32_t bb[4] = {bv[u].x, bv[u].y, bv[u].z, bv[u].w};
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const float w0 = half_lo(ww[j]), w1 = half_hi(ww[j]);
+                a1 = fmaf(w0, bf_lo(gg[j]), a1);
+                a1 = fmaf(w1, bf_hi(gg[j]), a1);
+                a2 = fmaf(w0, bf_lo(bb[j]), a2);
+                a2 = fmaf(w1, bf_hi(bb[j]), a2);
+            }
         }
     }
     a1 += __shfl_xor(a1, 32);
     a2 += __shfl_xor(a2, 32);
-    if (lane < 32) {  // rows past the matrix are zero blocks: their entries come out zero
-        c1[tile * 32 + lane] = a1;
-        c2[tile * 32 + lane] = a2;
+    if (lane < 32) { red[0][wave][lane] = a1; red[1][wave][lane] = a2; }
+    __syncthreads();
+    if (threadIdx.x < 64) {  // rows past the matrix are zero blocks: their entries come out zero
+        const int which = threadIdx.x >> 5, r = threadIdx.x & 31;
+        float t = 0.f;
+#pragma unroll
+        for (int x = 0; x < kWvecWaves; ++x) t += red[which][x][r];
+        (which ? c2 : c1)[tile * 32 + r] = t;
     }
 }
 
@@ -306,9 +326,7 @@ void bf16_embed_ln(hipStream_t s, const int32_t* ids, int id_stride, const void*
 }
 
 void bf16_wvec(hipStream_t s, const void* Wp, int N, int K, const void* gamma, const void* beta, float* c1, float* c2) {
-    const int n_tiles = (N + 31) / 32;
-    wvec_kernel<<<(n_tiles + 3) / 4, 256, 0, s>>>((const u32x4*)Wp, K / 16, n_tiles, (const bf16_t*)gamma,
-                                                  (const bf16_t*)beta, c1, c2);
+    wvec_kernel<<<(N + 31) / 32, 64 * kWvecWaves, 0, s>>>((const u32x4*)Wp, K / 16, (const bf16_t*)gamma, (const bf16_t*)beta, c1, c2);
 }
 
 void bf16_ln(hipStream_t s, float* r, const float* part, int ksplit, size_t part_split, const void* pbias,

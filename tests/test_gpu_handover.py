@@ -149,3 +149,17 @@ def test_arena_release_and_acquire():
         torch.cuda.synchronize()
         assert torch.equal(ids0, ids1) and torch.equal(lp0, lp1) and torch.equal(sc0, sc1)
     eng.he_destroy()
+
+
+@pytest.mark.parametrize("rows,cols,rank", [(1, 16, 1), (33, 48, 3), (65, 80, 5), (64, 32, 2), (130, 272, 17), (95, 160, 33)])
+def test_merged_matrix_bit_exact_at_tile_edges(rows, cols, rank):
+    """Row counts around 32 and 64, column counts that are odd multiples of 16 and end inside a workgroup's columns."""
+    import torch
+    rng = np.random.default_rng(rows)
+    bf = synth.round_to_bf16
+    W, A, B = bf(rng.normal(0, 0.05, (rows, cols))), bf(rng.normal(0, 0.05, (rank, cols))), bf(rng.normal(0, 0.05, (rows, rank)))
+    dev = lambda x: torch.from_numpy(np.ascontiguousarray(x, np.float32)).cuda().to(torch.bfloat16).contiguous()
+    got = binding.he_tile_matrix_lora(dev(W), dev(A), dev(B), 0.625)
+    want = binding.he_tile_matrix(dev(O.merge_lora(W, A, B, 0.625)))
+    torch.cuda.synchronize()
+    assert torch.equal(got, want)
