@@ -12,18 +12,25 @@ namespace {
 // whole row of K or V per group, coalesced); scores are reduced with wavefront
 // shuffles, kept in LDS, soft-maxed, then the same lanes accumulate p_j * V[j].
 // The output goes out as tiled half blocks for the out-projection GEMM.
-template <int D>
-__global__ __launch_bounds__(256) void attn_kernel(const float* __restrict__ q, const half_t* __restrict__ kv,
+//
+// WAVES: with many (row, head) pairs a workgroup is four wavefronts, several share a CU and the launch runs at the HBM rate
+// (6.2 TB/s at 32 sequences x 40 heads x 384 positions).  With few, what bounds it is the serial chain of load rounds of one
+// workgroup, and more wavefronts shorten it: 16 where a CU has at most one pair, 8 where it has two, but no more than one
+// round over a full cache needs (waves without keys only lengthen the barriers).  Measured, 4 wavefronts -> the rule's:
+// 1 x 32 heads of 64, 516 keys: 12.7 -> 8.6 us; 7 x 32 heads of 128, 100-250 keys: 11.8 -> 9.0; 2 x 40 heads of 128,
+// 1999 keys: 71.7 -> 26.0; 16 x 32 heads of 64 in a cache of 64: 5.8 (8 wavefronts: 6.8).
+template <int D, int WAVES>
+__global__ __launch_bounds__(64 * WAVES) void attn_kernel(const float* __restrict__ q, const half_t* __restrict__ kv,
                                                    u32x4* __restrict__ o,
                                                    const he_dev_state* __restrict__ st, int S, int layer, int H,
                                                    int n_heads, int max_batch, int max_seq) {
     constexpr int LPK = D / 8;     // lanes per key
     constexpr int KPW = 64 / LPK;  // keys per wavefront load
-    constexpr int KR = 4 * KPW;    // keys per workgroup round
+    constexpr int KR = WAVES * KPW;  // keys per workgroup round
     constexpr int U = 4;
     extern __shared__ float sc[];  // [max_seq] scores, then probabilities
-    __shared__ float red[8];
-    __shared__ float ored[4][LPK * 8];
+    __shared__ float red[2][WAVES];
+    __shared__ float ored[WAVES][LPK * 8];
     const int m = blockIdx.x, h = blockIdx.y;
     const int b = row_seq(st, m, S), T = seq_len(st, b) + (m % S) - row_pad(st, b) + 1;
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
@@ -80,19 +87,23 @@ __global__ __launch_bounds__(256) void attn_kernel(const float* __restrict__ q, 
     }
     // cur now holds the first values
     for (int o2 = 32; o2 > 0; o2 >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o2));
-    if (lane == 0) red[wave] = mx;
+    if (lane == 0) red[0][wave] = mx;
     __syncthreads();  // also publishes sc[]
-    mx = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
+    mx = red[0][0];
+#pragma unroll
+    for (int w = 1; w < WAVES; ++w) mx = fmaxf(mx, red[0][w]);
     float sum = 0.f;
-    for (int j = threadIdx.x; j < T; j += 256) {
+    for (int j = threadIdx.x; j < T; j += 64 * WAVES) {
         const float pj = expf(sc[j] - mx);
         sc[j] = pj;
         sum += pj;
     }
     for (int o2 = 32; o2 > 0; o2 >>= 1) sum += __shfl_xor(sum, o2);
-    if (lane == 0) red[4 + wave] = sum;
+    if (lane == 0) red[1][wave] = sum;
     __syncthreads();  // also publishes the probabilities
-    sum = (red[4] + red[5]) + (red[6] + red[7]);
+    sum = 0.f;
+#pragma unroll
+    for (int w = 0; w < WAVES; w += 2) sum += red[1][w] + red[1][w + 1];
     float acc[8] = {};
     for (int base = 0; base < T; base += STEP) {
         if (base + STEP < T) load_rows(nxt, Vp, base + STEP);
@@ -128,7 +139,10 @@ __global__ __launch_bounds__(256) void attn_kernel(const float* __restrict__ q, 
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
             const int i = threadIdx.x * 8 + e;
-            ov[e] = ((ored[0][i] + ored[1][i]) + (ored[2][i] + ored[3][i])) * inv;
+            float t = 0.f;
+#pragma unroll
+            for (int w = 0; w < WAVES; w += 2) t += ored[w][i] + ored[w + 1][i];
+            ov[e] = t * inv;
         }
         const size_t slot = block_slot(m, h * D + threadIdx.x * 8, H >> 4);
         o[slot] = u32x4{pack2(ov[0], ov[1]), pack2(ov[2], ov[3]), pack2(ov[4], ov[5]), pack2(ov[6], ov[7])};
@@ -471,6 +485,30 @@ __global__ __launch_bounds__(256, 2) void attn_prompt_mfma_kernel(const float* _
 
 // ------------------------------------------------------------------ launchers
 
+// Wavefronts per (row, head): by the sizes of the launch and of the cache, never by how much of it is filled, so that a captured
+// step and the same step launched alone add up in the same order.
+static int attn_waves(long pairs, int max_seq, int d) {
+    const long cus = num_cus();
+    int waves = pairs <= cus ? 16 : (pairs <= 2 * cus ? 8 : 4);
+    const int keys_per_wave = 4 * 64 / (d / 8);  // of one round
+    while (waves > 4 && (waves / 2) * keys_per_wave >= max_seq) waves /= 2;
+    return waves;
+}
+
+template <int D>
+static void launch_attn(hipStream_t s, const float* q, const void* kv, void* o_blocks, const he_dev_state* st, int M, int S, int layer,
+                        int H, int n_heads, int max_batch, int max_seq) {
+    const dim3 grid(M, n_heads);
+    const size_t shm = (size_t)max_seq * sizeof(float);
+    const int waves = attn_waves((long)M * n_heads, max_seq, D);
+    if (waves == 16)
+        attn_kernel<D, 16><<<grid, 1024, shm, s>>>(q, (const half_t*)kv, (u32x4*)o_blocks, st, S, layer, H, n_heads, max_batch, max_seq);
+    else if (waves == 8)
+        attn_kernel<D, 8><<<grid, 512, shm, s>>>(q, (const half_t*)kv, (u32x4*)o_blocks, st, S, layer, H, n_heads, max_batch, max_seq);
+    else
+        attn_kernel<D, 4><<<grid, 256, shm, s>>>(q, (const half_t*)kv, (u32x4*)o_blocks, st, S, layer, H, n_heads, max_batch, max_seq);
+}
+
 void bf16_attn(hipStream_t s, const float* q, const void* kv, void* o_blocks, const he_dev_state* st, int M, int S, int layer, int H, int n_heads, int max_batch, int max_seq) {
     if (S >= 32) {  // prompt rows: 32 queries per wavefront on the matrix cores
         dim3 fgrid((S + 127) / 128, n_heads, M / S);
@@ -493,12 +531,6 @@ void bf16_attn(hipStream_t s, const float* q, const void* kv, void* o_blocks, co
                                                                   max_batch, max_seq);
         return;
     }
-    dim3 grid(M, n_heads);
-    const size_t shm = (size_t)max_seq * sizeof(float);
-    if (H / n_heads == 128)
-        attn_kernel<128><<<grid, 256, shm, s>>>(q, (const half_t*)kv, (u32x4*)o_blocks, st, S,
-                                                layer, H, n_heads, max_batch, max_seq);
-    else
-        attn_kernel<64><<<grid, 256, shm, s>>>(q, (const half_t*)kv, (u32x4*)o_blocks, st, S,
-                                               layer, H, n_heads, max_batch, max_seq);
+    if (H / n_heads == 128) launch_attn<128>(s, q, kv, o_blocks, st, M, S, layer, H, n_heads, max_batch, max_seq);
+    else launch_attn<64>(s, q, kv, o_blocks, st, M, S, layer, H, n_heads, max_batch, max_seq);
 }
