@@ -241,18 +241,8 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_skinny_kernel(const u32x4* __
     __shared__ float red[WAVES][NT][16][64];
     __shared__ float lnp[WAVES * 4 * 32];  // folded LayerNorm: the wavefronts' partial sums of the row statistics
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    int bx = blockIdx.x, mt = blockIdx.y;
-    if (MODE == MODE_LMHEAD && gridDim.y > 1) {
-        // Several 32-row slices each stream the whole matrix.  Workgroups go round the XCDs by index: the slices
-        // of one group of tiles are placed on ONE XCD, next to each other in dispatch order, so that they run
-        // side by side and all but the first of them find the weights in that XCD's L2 (the grid's x is padded
-        // to a multiple of eight for this).
-        const int lid = blockIdx.y * gridDim.x + blockIdx.x, span = 8 * gridDim.y;
-        bx = (lid / span) * 8 + (lid % span) % 8;
-        mt = (lid % span) / 8;
-        if (bx >= (n_tiles + NT - 1) / NT) return;  // the whole workgroup
-    }
-    const int grp = bx / ksplit, ks = bx % ksplit;
+    const int mt = blockIdx.y;
+    const int grp = blockIdx.x / ksplit, ks = blockIdx.x % ksplit;
     const int parts = ksplit * WAVES, part = ks * WAVES + wave;
     const int kb0 = (int)(((long)part * KB) / parts), kb1 = (int)(((long)(part + 1) * KB) / parts);
     constexpr bool FOLDABLE = MODE == MODE_BIAS_RELU || MODE == MODE_QKV || MODE == MODE_LMHEAD;
@@ -294,12 +284,38 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_skinny_kernel(const u32x4* __
     f32x16 acc[NT];
 #pragma unroll
     for (int t = 0; t < NT; ++t) acc[t] = f32x16{};
+    // LM head with sampling: the noise of this thread's own outputs (a Philox block and two logarithms each, 11 of a
+    // 50272 x 5120 head's 97 us when formed at the end, 5 of 92 here) is formed between the load rounds, while the vector units are idle,
+    // and waits in the part of LDS that takes the accumulators after the loop.
+    constexpr int NOISE = MODE == MODE_LMHEAD ? ITEMS * 4 : 0;
+    [[maybe_unused]] float* nz = &red[0][0][0][0] + threadIdx.x;
+    [[maybe_unused]] uint32_t nz_step = 0, nz_seq = 0, nz_k0 = 0, nz_k1 = 0;
+    [[maybe_unused]] bool gumbel = false;
+    [[maybe_unused]] int nz_next = 0, nz_per_round = 0;
     int n = kb1 - kb0;
+    auto noise_round = [&](int count) {
+        if constexpr (MODE == MODE_LMHEAD) {
+            for (int c = 0; c < count && nz_next < NOISE; ++c, ++nz_next) {
+                const int item = wave + (nz_next >> 2) * WAVES;
+                const int vid = (grp * NT + (item >> 2)) * 32 + 8 * (item & 3) + 4 * (lane >> 5) + (nz_next & 3);
+                nz[nz_next * WAVES * 64] = gumbel_from_word(philox_word0((uint32_t)vid, nz_step, nz_seq, nz_k0, nz_k1));
+            }
+        }
+    };
+    auto noise_setup = [&](int blocks) {
+        if constexpr (MODE == MODE_LMHEAD) {
+            gumbel = p.st->mode == 1;
+            nz_step = (uint32_t)p.st->step; nz_k0 = p.st->seed_lo; nz_k1 = p.st->seed_hi;
+            nz_seq = (uint32_t)row_seq(p.st, min(mt * 32 + (lane & 31), p.M - 1), 1);  // the noise is keyed by the sequence, not by its row
+            nz_per_round = gumbel ? (NOISE * U + blocks - 1) / max(blocks, 1) : 0;
+        }
+    };
     if (n >= U) {
         SkinnyRegs<NT, U> ra;
         skinny_load<NT, U>(ra, w, xh);
         n -= U;
         request_epilogue_operands();
+        noise_setup(n);
         // the statistics are used once the second round is on its way as well (first trip peeled off
         // the loop: a test inside it cost the loop its schedule)
         if (n >= U) {
@@ -316,18 +332,31 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_skinny_kernel(const u32x4* __
             SkinnyRegs<NT, U> rb;
             skinny_load<NT, U>(rb, w, xh);
             n -= U;
+            noise_round(nz_per_round);
             skinny_mma<NT, U>(ra, acc);
             ra = rb;
         }
         skinny_mma<NT, U>(ra, acc);
     } else {
         request_epilogue_operands();
+        noise_setup(0);
         if (fold) ln_partial<WAVES>(lnl, p, mt, wave, lane, lnp);
     }
     for (; n > 0; --n) {
         SkinnyRegs<NT, 1> r1;
         skinny_load<NT, 1>(r1, w, xh);
         skinny_mma<NT, 1>(r1, acc);
+    }
+    [[maybe_unused]] float noise[ITEMS][4];
+    if constexpr (MODE == MODE_LMHEAD) {
+        if (gumbel) {
+            noise_round(NOISE);
+#pragma unroll
+            for (int i = 0; i < ITEMS; ++i)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) noise[i][r] = nz[(i * 4 + r) * WAVES * 64];
+            __syncthreads();
+        }
     }
 #pragma unroll
     for (int t = 0; t < NT; ++t)
@@ -375,48 +404,62 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_skinny_kernel(const u32x4* __
                                         32.f * (float)min(NT, n_tiles - grp * NT), v, mrow, n0, live, rslot);
         return;
     }
-    float (*zt)[32][33] = reinterpret_cast<float (*)[32][33]>(&red[0][0][0][0]);  // logits tiles reuse the LDS
-    if (MODE == MODE_LMHEAD) __syncthreads();                                      // once every partial is read
+    if constexpr (MODE != MODE_LMHEAD) {
 #pragma unroll
-    for (int i = 0; i < ITEMS; ++i) {
-        const int item = wave + i * WAVES, t = item >> 2, tile = grp * NT + t;
-        const int nl = 8 * (item & 3) + 4 * (lane >> 5);  // first of this lane's four rows inside the tile
-        if (item >= NT * 4) continue;
-        if (MODE != MODE_LMHEAD) {
-            if (tile < n_tiles) epilogue4<MODE>(p, m, tile * 32 + nl, ks, v[i][0], v[i][1], v[i][2], v[i][3], bias_w[i], cur_len);
-        } else {
-#pragma unroll
-            for (int r = 0; r < 4; ++r) zt[t][nl + r][lane & 31] = v[i][r];
+        for (int i = 0; i < ITEMS; ++i) {
+            const int item = wave + i * WAVES, tile = grp * NT + (item >> 2);
+            if (item < NT * 4 && tile < n_tiles)
+                epilogue4<MODE>(p, m, tile * 32 + 8 * (item & 3) + 4 * (lane >> 5), ks, v[i][0], v[i][1], v[i][2], v[i][3], bias_w[i], cur_len);
         }
-    }
-    if (MODE == MODE_LMHEAD) {
-        // logits tiles -> per-(row, tile) softmax and arg-max partials
-        __syncthreads();
-        for (int i0 = threadIdx.x; i0 < NT * 32; i0 += WAVES * 64) {
-            const int t = i0 >> 5, mm = mt * 32 + (i0 & 31), tile = grp * NT + t;
-            if (mm >= p.M || tile >= n_tiles) continue;
-            const int mode = p.st->mode, step = p.st->step;
-            const uint32_t seq = (uint32_t)row_seq(p.st, mm, 1);  // the noise is keyed by the sequence, not by its row
-            const float temp = p.st->temperature;
-            const uint32_t k0 = p.st->seed_lo, k1 = p.st->seed_hi;
-            float mx = -INFINITY, best = -INFINITY, bestz = 0.f;
-            int besti = 0x7FFFFFFF;
-            const int nv = min(32, p.N - tile * 32);
-            for (int i = 0; i < nv; ++i) {
-                const float z = zt[t][i][i0 & 31];
-                const int vid = tile * 32 + i;
-                if (p.logits) p.logits[(size_t)mm * p.N + vid] = z;
+    } else {
+        // Soft-max and arg-max partials per (row, workgroup).  All of a thread's outputs belong to one row: reduced in its
+        // registers, with the lane 32 away, then over the wavefronts.
+        __shared__ float4 part[WAVES][32];
+        __shared__ int part_idx[WAVES][32];
+        const float temp = p.st->temperature;
+        float mx = -INFINITY, best = -INFINITY, bestz = 0.f;
+        int besti = 0x7FFFFFFF;
+#pragma unroll
+        for (int i = 0; i < ITEMS; ++i) {
+            const int item = wave + i * WAVES, tile = grp * NT + (item >> 2);
+            const int n0 = tile * 32 + 8 * (item & 3) + 4 * (lane >> 5);  // ascending in i
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                if (item >= NT * 4 || n0 + r >= p.N) { v[i][r] = -INFINITY; continue; }
+                const float z = v[i][r];
+                if (p.logits && m < p.M) p.logits[(size_t)m * p.N + n0 + r] = z;
                 mx = fmaxf(mx, z);
-                float s = z;
-                if (mode == 1)
-                    s = z / temp + gumbel_from_word(philox_word0((uint32_t)vid, (uint32_t)step, seq, k0, k1));
-                if (s > best) { best = s; besti = vid; bestz = z; }  // ascending ids: strict > keeps the lowest
+                const float s = gumbel ? z / temp + noise[i][r] : z;
+                if (s > best) { best = s; besti = n0 + r; bestz = z; }  // strict: the lowest id of equals
             }
-            float sum = 0.f;
-            for (int i = 0; i < nv; ++i) sum += expf(zt[t][i][i0 & 31] - mx);
-            float* sp = p.stats + ((size_t)mm * p.n_tiles + tile) * 4;
-            sp[0] = mx; sp[1] = sum; sp[2] = best; sp[3] = bestz;
-            p.stats_idx[(size_t)mm * p.n_tiles + tile] = besti;
+        }
+        auto take_better = [&](float s, int id, float z) {
+            if (s > best || (s == best && id < besti)) { best = s; besti = id; bestz = z; }
+        };
+        mx = fmaxf(mx, __shfl_xor(mx, 32));
+        take_better(__shfl_xor(best, 32), __shfl_xor(besti, 32), __shfl_xor(bestz, 32));
+        float sum = 0.f;
+        if (mx > -INFINITY) {
+#pragma unroll
+            for (int i = 0; i < ITEMS; ++i)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) sum += expf(v[i][r] - mx);
+        }
+        sum += __shfl_xor(sum, 32);
+        if (lane < 32) { part[wave][lane] = make_float4(mx, sum, best, bestz); part_idx[wave][lane] = besti; }
+        __syncthreads();
+        if (threadIdx.x < 32 && m < p.M) {
+            float4 e[WAVES];
+#pragma unroll
+            for (int x = 0; x < WAVES; ++x) { e[x] = part[x][lane]; mx = fmaxf(mx, e[x].x); }
+            sum = 0.f;
+#pragma unroll
+            for (int x = 0; x < WAVES; ++x) {
+                if (e[x].x > -INFINITY) sum += e[x].y * expf(e[x].x - mx);
+                take_better(e[x].z, part_idx[x][lane], e[x].w);
+            }
+            reinterpret_cast<float4*>(p.stats)[(size_t)m * p.n_tiles + grp] = make_float4(mx, sum, best, bestz);
+            p.stats_idx[(size_t)m * p.n_tiles + grp] = besti;
         }
     }
 }
@@ -686,7 +729,7 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_half_kernel(const u32x4* __re
     }
 }
 
-// One block per sequence: combines the LM-head tile partials in tile order
+// One block per sequence: combines the LM-head partials of the workgroups (or wavefronts) in their order
 // (deterministic), writes token id and its untempered log-probability.
 __global__ void lm_reduce_kernel(const float* __restrict__ stats, const int* __restrict__ stats_idx, int n_tiles,
                                  const he_dev_state* __restrict__ st, int32_t* __restrict__ ids_out,
@@ -762,7 +805,6 @@ void launch_skinny_nt(hipStream_t s, const void* Wp, const void* Xhi, int KB, in
                       int m_tiles, int ksplit, const Epi& p) {
     constexpr int U = HE_SKINNY_U(NT);
     dim3 grid(((n_tiles + NT - 1) / NT) * ksplit, m_tiles);
-    if (MODE == MODE_LMHEAD && m_tiles > 1) grid.x = (grid.x + 7) / 8 * 8;  // see the kernel: slices of a tile group share an XCD
     // What bounds a wavefront is its serial chain of load rounds (K/16 blocks / wavefronts / U
     // rounds, about 1.7 us each under load): eight wavefronts halve the chain when K leaves each
     // of them two rounds (and their accumulators still fit in LDS for the final reduction).
@@ -1110,16 +1152,24 @@ void bf16_gemm_skinny(hipStream_t s, int mode, const void* Wp, const void* Xhi, 
     }
 }
 
+// (up to 32 rows: one per workgroup of at least one 32-wide tile; more: one per wavefront of a 256-wide tile)
+int bf16_lm_parts_max(int V) { return std::max((V + 31) / 32, 2 * ((V + 255) / 256)); }
+
 void bf16_lm_head(hipStream_t s, const void* Wp, const void* Xhi, int B, int V, int K,
                   const he_dev_state* st, float* logits_opt, float* stats, int* stats_idx, int32_t* ids_out,
                   float* lp_out, int out_stride, int out_at_step, int32_t* cur_ids, const bf16_gemm_args* fold) {
-    Epi p{};
-    if (fold) p = make_epi(B, V, *fold);
-    p.M = B; p.N = V; p.st = st; p.logits = logits_opt; p.stats = stats; p.stats_idx = stats_idx;
-    p.n_tiles = (V + 31) / 32;
-    const int m_tiles = (B + 31) / 32;
-    launch_skinny<MODE_LMHEAD>(s, Wp, Xhi, K / 16, p.n_tiles, m_tiles, skinny_nt_fused(p.n_tiles, m_tiles), 1, p);
-    lm_reduce_kernel<<<B, 256, 0, s>>>(stats, stats_idx, p.n_tiles, st, ids_out, lp_out, out_stride, out_at_step,
+    int parts;  // soft-max partials per row
+    if (B > 32) {
+        parts = bf16_lm_head_tiles(s, Wp, Xhi, B, V, K, fold, st, logits_opt, stats, stats_idx);
+    } else {
+        Epi p{};
+        if (fold) p = make_epi(B, V, *fold);
+        const int tiles = (V + 31) / 32, nt = skinny_nt_fused(tiles, 1);
+        p.M = B; p.N = V; p.st = st; p.logits = logits_opt; p.stats = stats; p.stats_idx = stats_idx;
+        p.n_tiles = parts = (tiles + nt - 1) / nt;  // one per workgroup
+        launch_skinny<MODE_LMHEAD>(s, Wp, Xhi, K / 16, tiles, 1, nt, 1, p);
+    }
+    lm_reduce_kernel<<<B, 256, 0, s>>>(stats, stats_idx, parts, st, ids_out, lp_out, out_stride, out_at_step,
                                        cur_ids);
 }
 

@@ -45,6 +45,71 @@ __device__ __forceinline__ void score_tile(const Epi& p, const f32x16 (&acc)[NA]
     }
 }
 
+// A wavefront's share of the LM head of a decode step of more than 32 rows, 4 column blocks x MJ row blocks from row m0 and
+// column n0 on: per row, soft-max partials of its 128 logits, the best score (with the sampler's noise) and its id, and
+// the logits themselves where the caller wants them.  fold: mean and 1/sqrt(var + eps) of the lane's row of each block;
+// zl: 64 x 64 floats of LDS of the wavefront's own.
+template <int MJ>
+__device__ __forceinline__ void lm_head_tile(const Epi& p, const f32x16 (&acc)[4][MJ], const float2 (&fold)[MJ], int m0, int n0, int part,
+                                             int lane, float* zl) {
+    const int hh = lane >> 5;
+    const int mode = p.st->mode, step = p.st->step;
+    const float temp = p.st->temperature;
+    const uint32_t k0 = p.st->seed_lo, k1 = p.st->seed_hi;
+    const bool folded = p.ln_stats != nullptr;
+#pragma unroll
+    for (int j = 0; j < MJ; ++j) {
+        if (m0 + j * 32 < p.M) {  // (wave-uniform)
+            const int m = m0 + j * 32 + (lane & 31);
+            const uint32_t seq = (uint32_t)row_seq(p.st, min(m, p.M - 1), 1);  // the noise is keyed by the sequence, not by its row
+            float mx = -INFINITY;
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const int nq = n0 + i * 32 + 8 * q + 4 * hh;
+                    float4 c1 = make_float4(0.f, 0.f, 0.f, 0.f), c2 = c1;
+                    if (folded && nq < p.N) {  // (c1 and c2 are padded to whole 32s)
+                        c1 = *reinterpret_cast<const float4*>(p.c1 + nq);
+                        c2 = *reinterpret_cast<const float4*>(p.c2 + nq);
+                    }
+                    const float c1v[4] = {c1.x, c1.y, c1.z, c1.w}, c2v[4] = {c2.x, c2.y, c2.z, c2.w};
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        float v = acc[i][j][4 * q + e];
+                        if (folded) v = fold[j].y * (v - fold[j].x * c1v[e]) + c2v[e];
+                        if (nq + e >= p.N) v = -INFINITY;
+                        else if (p.logits && m < p.M) p.logits[(size_t)m * p.N + nq + e] = v;
+                        zl[(i * 16 + 4 * q + e) * 64 + lane] = v;  // (read back by this lane only)
+                        mx = fmaxf(mx, v);
+                    }
+                }
+            mx = fmaxf(mx, __shfl_xor(mx, 32));
+            // the sampler's noise is some forty multiplications per logit: a loop of its own, short enough to stay in the
+            // instruction cache (written out 64 times over it is not)
+            float best = -INFINITY, bestz = 0.f, sum = 0.f;
+            int besti = 0x7FFFFFFF;
+#pragma unroll 4
+            for (int x = 0; x < 64; ++x) {
+                const float v = zl[x * 64 + lane];
+                const int n = n0 + (x >> 4) * 32 + 8 * ((x >> 2) & 3) + 4 * hh + (x & 3);
+                if (mx > -INFINITY) sum += expf(v - mx);
+                float s = v;
+                if (mode == 1) s = v / temp + gumbel_from_word(philox_word0((uint32_t)n, (uint32_t)step, seq, k0, k1));
+                if (n < p.N && s > best) { best = s; besti = n; bestz = v; }  // ascending ids: strict > keeps the lowest
+            }
+            sum += __shfl_xor(sum, 32);
+            const float os = __shfl_xor(best, 32), oz = __shfl_xor(bestz, 32);
+            const int oi = __shfl_xor(besti, 32);
+            if (os > best || (os == best && oi < besti)) { best = os; besti = oi; bestz = oz; }
+            if (hh == 0 && m < p.M) {
+                reinterpret_cast<float4*>(p.stats)[(size_t)m * p.n_tiles + part] = make_float4(mx, sum, best, bestz);
+                p.stats_idx[(size_t)m * p.n_tiles + part] = besti;
+            }
+        }
+    }
+}
+
 // ----------------------------------------------------------------- tiled GEMM (prompt pass)
 //
 // 256 (n) x 128 (m) output tile per workgroup, four wavefronts in a 2x2 grid of
@@ -584,7 +649,14 @@ __global__ __launch_bounds__(256, 1) void gemm_ring_kernel(const u32x4* __restri
     const int tm = item % tiles_m, rest = item / tiles_m;
     const int tn = rest % tiles_n, ks = rest / tiles_n;
     const int wn = wave & 1, wm = wave >> 1;  // this wavefront's 128 (n) x 32 MW (m) sub-tile
-    const int cur_len = epilogue_len<MODE>(p);
+    [[maybe_unused]] const int cur_len = epilogue_len<MODE>(p);
+    [[maybe_unused]] LnLoads lnl[2 * MW];  // LM head with the final LayerNorm folded in: this wavefront's share of the rows' statistics
+    if constexpr (MODE == MODE_LMHEAD) {
+        if (p.ln_stats) {
+#pragma unroll
+            for (int x = 0; x < 2 * MW; ++x) ln_issue<4>(lnl[x], p, min(tm * 2 * MW + x, MT32 - 1), wave, lane);
+        }
+    }
     f32x16 acc[4][MW];
 #pragma unroll
     for (int i = 0; i < 4; ++i)
@@ -695,7 +767,24 @@ __global__ __launch_bounds__(256, 1) void gemm_ring_kernel(const u32x4* __restri
         for (int n = 0; n < NM; ++n) mma1(opb, n);
         slot = nslot;
     }
-    if constexpr (MODE == MODE_SCORE) score_tile<4, MW>(p, acc, tm * Sh::TM + wm * 32 * MW, tn * 256 + wn * 128, tn * 2 + wn, lane);
+    if constexpr (MODE == MODE_LMHEAD) {
+        float2 fold[MW];
+#pragma unroll
+        for (int j = 0; j < MW; ++j) fold[j] = make_float2(0.f, 1.f);
+        float* lds = reinterpret_cast<float*>(&ring[0][0][0]);  // the ring is free: statistics and logits go through it
+        __syncthreads();
+        if (p.ln_stats) {
+            float* lnp = lds + 4 * 64 * 64;
+#pragma unroll
+            for (int x = 0; x < 2 * MW; ++x)
+                ln_partial<4>(lnl[x], p, min(tm * 2 * MW + x, MT32 - 1), wave, lane, lnp + x * 4 * 4 * 32);
+            __syncthreads();
+#pragma unroll
+            for (int j = 0; j < MW; ++j) fold[j] = ln_finish<4>(lnp + (wm * MW + j) * 4 * 4 * 32, lane & 31, p);
+        }
+        lm_head_tile<MW>(p, acc, fold, tm * Sh::TM + wm * 32 * MW, tn * 256 + wn * 128, tn * 2 + wn, lane,
+                         lds + wave * 64 * 64);
+    } else if constexpr (MODE == MODE_SCORE) score_tile<4, MW>(p, acc, tm * Sh::TM + wm * 32 * MW, tn * 256 + wn * 128, tn * 2 + wn, lane);
     else store_tile<MODE, 4, MW>(p, bias8, acc, tm * Sh::TM + wm * 32 * MW, tn * 256 + wn * 128, ks, cur_len, lane);
 }
 
@@ -763,13 +852,13 @@ static BigPlan big_plan(int M, int N, int KB, bool may_cut) {
 // 768 rows and the 1.3B .. 13B matrices (uncontended stages 0.33 / 0.39 / 0.43 / 0.53 / 0.68 us; a second, partly empty
 // round: 4096 x 4096 and 768 rows, 240 workgroups 33.6 us, 288: 54.1).
 struct RingPlan { int mw, ks; };
-static RingPlan ring_plan(int M, int N, int KB, bool fused, size_t capacity_floats) {
+static RingPlan ring_plan(int M, int N, int KB, bool fused, size_t capacity_floats, int max_mw = 5) {
     constexpr double kStage[5] = {0.33, 0.39, 0.43, 0.53, 0.68}, kRamp[5] = {6.0, 7.0, 8.5, 12.0, 14.0};
     const long cus = tiled_cus(), stages = KB / 2;
     const double sums = 4.0 * M * N / 5e6, weights = 32.0 * N * KB / 14e6;
     RingPlan best{2, 1};
     double best_cost = 1e30;
-    for (int mw = 1; mw <= 5; ++mw) {
+    for (int mw = 1; mw <= max_mw; ++mw) {
         const int tm = mw < 4 ? 64 * mw : 256, tn = mw < 5 ? 256 : 320;
         const long tiles = (long)((N + tn - 1) / tn) * ((M + tm - 1) / tm);
         for (int ks = 1; ks <= kMaxTiledKSplit; ++ks) {
@@ -804,7 +893,7 @@ void launch_tiled(hipStream_t s, const void* Wp, const void* Xhi, int KB, int N,
         else gemm_ring_kernel<MODE, 3><<<grid, 256, 0, s>>>(W, X, bias8, KB, NT32, MT32, tiles_n, tiles_m, ksplit, p);
         return;
     }
-    if constexpr (MODE != MODE_SCORE) {
+    if constexpr (MODE != MODE_SCORE && MODE != MODE_LMHEAD) {
         const int bn = 64 * tile, tiles_n = (N + bn - 1) / bn, tiles_m = (M + BM - 1) / BM;
         const int split_tn = ksplit > 1 ? split_col / bn : tiles_n;  // without a k-split every tile is whole
         const int whole = split_tn * tiles_m, cutn = (tiles_n - split_tn) * tiles_m * ksplit;
@@ -851,13 +940,13 @@ size_t bf16_tiled_scratch_floats(int rows, int widest) {
 // columns on 256 CUs are two rounds of whole tiles and one of 256 half tiles, with a second set of partial sums for a
 // fifth of the columns only (and 512 tiles of 320 columns are two rounds with nothing to cut).  With fewer, ring_plan
 // cuts every tile.
-void bf16_tiled_store_plan(int M, int N, int K, size_t capacity_floats, int* tile, int* ks, int* split_col) {
+void bf16_tiled_store_plan(int M, int N, int K, size_t capacity_floats, int* tile, int* ks, int* split_col, bool few_rows_whole) {
     if (use_big_tile(M, N)) {
         const BigPlan g = big_plan(M, N, K / 16, (size_t)2 * M * N <= capacity_floats);
         *tile = g.na; *ks = g.ks; *split_col = g.split_col;
         return;
     }
-    const RingPlan g = ring_plan(M, N, K / 16, false, capacity_floats);
+    const RingPlan g = ring_plan(M, N, K / 16, false, few_rows_whole ? 0 : capacity_floats);
     *tile = g.mw; *ks = g.ks; *split_col = 0;
 }
 
@@ -897,6 +986,20 @@ void bf16_gemm_tiled(hipStream_t s, int mode, const void* Wp, const void* Xhi, i
     const unsigned grid = (unsigned)(((size_t)M * (N / 4) + 255) / 256);
     if (mode == EPI_BIAS_RELU) finish_kernel<MODE_BIAS_RELU><<<grid, 256, 0, s>>>(part, g.ks, (size_t)M * N, p);
     else finish_kernel<MODE_QKV><<<grid, 256, 0, s>>>(part, g.ks, (size_t)M * N, p);
+}
+
+// The LM head of a decode step of more than 32 rows: the matrix is streamed once for all of them (the weight-streaming
+// kernel takes 32 rows at a time and rereads it: 96 rows of 50272 x 5120 took 222 us, this 151, of which 23 are the noise).  Returns the soft-max
+// partials per row.
+int bf16_lm_head_tiles(hipStream_t s, const void* Wp, const void* X, int M, int V, int K, const bf16_gemm_args* fold, const he_dev_state* st,
+                       float* logits_opt, float* stats, int* stats_idx) {
+    Epi p{};
+    if (fold) p = make_epi(M, V, *fold);
+    p.M = M; p.N = V; p.st = st; p.logits = logits_opt; p.stats = stats; p.stats_idx = stats_idx;
+    p.n_tiles = 2 * ((V + 255) / 256);
+    const RingPlan g = ring_plan(M, V, K / 16, true, 0, 3);  // no scratch: whole k ranges
+    launch_tiled<MODE_LMHEAD>(s, Wp, X, K / 16, V, M, p, g.mw, 1, 0);
+    return p.n_tiles;
 }
 
 int bf16_score_parts(int V) { return 2 * ((V + TN - 1) / TN); }

@@ -160,7 +160,7 @@ Sizes sizes_of(const he_config& c) {
     s.part = prow * H * sizeof(float);
     // the many-row GEMMs cut their tiles into k ranges where these alone do not fill the chip
     s.tiled_part = std::max(s.part, bf16_tiled_scratch_floats((int)rows, (int)wide) * sizeof(float));
-    const size_t ntile = (size_t)(c.vocab + 31) / 32;
+    const size_t ntile = (size_t)bf16_lm_parts_max(c.vocab);  // soft-max partials of a row's LM head
     s.stats = (size_t)c.max_batch * ntile * 4 * sizeof(float);
     s.stats_idx = (size_t)c.max_batch * ntile * sizeof(int);
     const size_t vpad = ((size_t)c.vocab + 31) / 32 * 32, mtiles = ((size_t)c.max_batch + 31) / 32;
@@ -272,9 +272,12 @@ void pass_tiled_bf16(he_engine* e, const int32_t* d_ids, int id_stride, int B, i
     const size_t split = (size_t)M * H;
     // k ranges per tile of the two GEMMs whose partial sums the next LayerNorm adds, and the first column whose
     // tiles are cut at all
+    // A scoring pass of few rows keeps every sum whole: a sequence scores the same alone and in a batch of whole rounds of
+    // big tiles, to the last bit wherever those have no k ranges either (1.7e-3 apart with them, activations being rounded)
+    const size_t room = full ? 0 : e->tiled_part_floats;
     int kso, sco, tlo, ks2, sc2, tl2;
-    bf16_tiled_store_plan(M, H, H, e->tiled_part_floats, &tlo, &kso, &sco);
-    bf16_tiled_store_plan(M, H, F, e->tiled_part_floats, &tl2, &ks2, &sc2);
+    bf16_tiled_store_plan(M, H, H, e->tiled_part_floats, &tlo, &kso, &sco, full);
+    bf16_tiled_store_plan(M, H, F, e->tiled_part_floats, &tl2, &ks2, &sc2, full);
     int pend_ks = 1, pend_sc = 0;
     for (int l = 0; l < c.n_layers; ++l) {
         const he_layer_weights& lw = e->layers[l];
@@ -282,13 +285,13 @@ void pass_tiled_bf16(he_engine* e, const int32_t* d_ids, int id_stride, int B, i
         bf16_ln(s, e->resid, pend, pend_ks, split, pend_b, lw.ln1_g, lw.ln1_b, e->ablk, M, H, c.ln_eps, 1, 0, 1, pend_sc);
         bf16_gemm_args a = base;
         a.layer = l; a.bias = lw.bqkv; a.out = e->qbuf; a.kv = e->kv; a.qscale = 1.0f / sqrtf((float)e->d);
-        bf16_gemm_tiled(s, EPI_QKV, tw.wqkv, e->ablk, M, 3 * H, H, a, e->part, e->tiled_part_floats);
+        bf16_gemm_tiled(s, EPI_QKV, tw.wqkv, e->ablk, M, 3 * H, H, a, e->part, room);
         if (l == c.n_layers - 1 && !full) break;
         bf16_attn(s, e->qbuf, e->kv, e->oblk, e->st, M, Sp, l, H, c.n_heads, c.max_batch, c.max_seq_len);
         bf16_gemm_tiled_store(s, tw.wo, e->oblk, M, H, H, e->part, tlo, kso, sco);
         bf16_ln(s, e->resid, e->part, kso, split, lw.bo, lw.ln2_g, lw.ln2_b, e->ablk, M, H, c.ln_eps, 1, 0, 1, sco);
         a = base; a.bias = lw.b1; a.out_blocks = e->hblk;
-        bf16_gemm_tiled(s, EPI_BIAS_RELU, tw.w1, e->ablk, M, F, H, a, e->part, e->tiled_part_floats);
+        bf16_gemm_tiled(s, EPI_BIAS_RELU, tw.w1, e->ablk, M, F, H, a, e->part, room);
         bf16_gemm_tiled_store(s, tw.w2, e->hblk, M, H, F, e->part, tl2, ks2, sc2);
         pend = e->part; pend_b = lw.b2; pend_ks = ks2; pend_sc = sc2;
     }

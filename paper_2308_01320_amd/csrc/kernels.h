@@ -105,7 +105,9 @@ void bf16_gemm_tiled(hipStream_t s, int mode, const void* Wp, const void* X, int
                      float* part, size_t part_floats);
 // The GEMMs whose partial sums the following LayerNorm adds (out-projection, FC2): the plan -- tile shape, *ks k ranges for
 // the columns >= *split_col, one for the columns before -- and the launch: part [ks][M][N]
-void bf16_tiled_store_plan(int M, int N, int K, size_t capacity_floats, int* tile, int* ks, int* split_col);
+// (few_rows_whole: passes of too few rows for rounds of big tiles get one k range)
+void bf16_tiled_store_plan(int M, int N, int K, size_t capacity_floats, int* tile, int* ks, int* split_col,
+                           bool few_rows_whole = false);
 void bf16_gemm_tiled_store(hipStream_t s, const void* Wp, const void* X, int M, int N, int K, float* part, int tile, int ks,
                            int split_col);
 // floats of scratch these can make use of for passes of up to `rows` rows and matrices of up to `widest` rows
@@ -125,6 +127,11 @@ void bf16_lm_head(hipStream_t s, const void* Wp, const void* X, int B, int V, in
                   const he_dev_state* st, float* logits_opt, float* stats, int* stats_idx, int32_t* ids_out,
                   float* lp_out, int out_stride, int out_at_step, int32_t* cur_ids,
                   const bf16_gemm_args* fold = nullptr);
+// partials per row that any form of the LM head leaves, at most
+int bf16_lm_parts_max(int V);
+// ... of more than 32 rows (bf16_lm_head calls it): soft-max and arg-max partials into stats / stats_idx; returns how many per row
+int bf16_lm_head_tiles(hipStream_t s, const void* Wp, const void* X, int M, int V, int K, const bf16_gemm_args* fold, const he_dev_state* st,
+                       float* logits_opt, float* stats, int* stats_idx);
 // LM head over all M = B*S positions fused with log-softmax and the gather of each position's next
 // token: out [B][S-1]; stats [M][bf16_score_parts(V)][2] and tgt [M] are scratch
 int bf16_score_parts(int V);

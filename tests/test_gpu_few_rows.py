@@ -65,3 +65,18 @@ def test_decode_attention_wavefront_counts(B, S, max_seq, H, nh):
     got = util.engine_teacher_forced(eng, prompts, want["ids"], 4, binding.sampling("greedy", 1.0, 3))
     eng.he_destroy()
     util.compare(got, want, BF16_TOL, MARGIN)
+
+
+@pytest.mark.parametrize("B", [1, 17, 32, 33, 65, 100, 130])
+@pytest.mark.parametrize("V,H", [(31, 64), (257, 128), (2500, 512), (9000, 64)])
+def test_lm_head_sampled_rows_and_vocabularies(B, V, H):
+    """The sampler's noise formed between the load rounds (at most 32 rows) or behind the product (more), vocabularies that end
+    inside a 32-wide tile, and a k range too short for a load round."""
+    d = synth.ModelDims("x", 1, H, H // 64, 2 * H, V, 64, B, 2, 3, "bf16", "gumbel")
+    w = synth.make_weights(d, seed=5)
+    prompts = synth.make_prompts(d, seed=6)
+    want = util.oracle_run(d, util.weights_f64(w), prompts, 3, "gumbel", 0.9, seed=3)
+    eng = util.make_engine(d, w)
+    got = util.engine_teacher_forced(eng, prompts, want["ids"], 3, binding.sampling("gumbel", 0.9, 3))
+    eng.he_destroy()
+    util.compare(got, want, BF16_TOL, MARGIN)
