@@ -624,15 +624,41 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_half_kernel(const u32x4* __re
         for (int s2 = 0; s2 < MT; ++s2) ln_partial<WAVES>(lnl[s2], p, mt + s2, wave, lane, lnp[s2]);
     };
     int n = kp1 - kp0;
+    // Where every workgroup's ranges begin at multiples of 32 KiB and more (they do at these widths), workgroups that walk
+    // them in step ask the same memory channels at the same time.  With ROTATE each starts its rounds at another one and
+    // wraps around: 8-bit 16384 x 4096 19.0 -> 14.9 us, 20480 x 5120 21.9 -> 20.0, 4096 x 16384 (four ranges) 22.7 ->
+    // 18.6, 16-bit 4096 x 16384 (two) 28.9 -> 26.9.  The 16-bit GEMMs with one range lose by it (16384 x 4096 27.2 -> 29.8).
+    constexpr bool ROTATE = W8 || MODE == MODE_STORE_LN;
+    constexpr int WSTEP = W8 ? 64 : 128;
+    const int rounds = n / U;
+    int round = 0;  // the round the pointers are at
+    auto move = [&](int by) {
+#pragma unroll
+        for (int t = 0; t < HT; ++t) w[t] += by * U * WSTEP;
+        xh += by * U * KU * 128;
+    };
+    if (ROTATE && rounds > 0) {
+        round = (int)(blockIdx.x * 5u % (unsigned)rounds);
+        move(round);
+    }
+    auto next_round = [&]() {
+        if (ROTATE) {
+            const bool wrap = ++round == rounds;
+            move(wrap ? -rounds : 0);
+            round = wrap ? 0 : round;
+        }
+    };
     if (n >= U) {
         HalfRegs<HT, U, W8, MH> ra;
         half_load<HT, U, W8, MH>(ra, w, xh, xstride);
+        next_round();
         n -= U;
         request_epilogue_operands();
         // the statistics are used once the second round is on its way as well (first trip peeled off the loop)
         if (n >= U) {
             HalfRegs<HT, U, W8, MH> rb;
             half_load<HT, U, W8, MH>(rb, w, xh, xstride);
+            next_round();
             n -= U;
             if (fold) ln_partials();
             half_mma<HT, U, W8, MH>(ra, acc);
@@ -643,6 +669,7 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_half_kernel(const u32x4* __re
         while (n >= U) {
             HalfRegs<HT, U, W8, MH> rb;
             half_load<HT, U, W8, MH>(rb, w, xh, xstride);
+            next_round();
             n -= U;
             half_mma<HT, U, W8, MH>(ra, acc);
             ra = rb;
@@ -652,6 +679,7 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_half_kernel(const u32x4* __re
         request_epilogue_operands();
         if (fold) ln_partials();
     }
+    if (ROTATE && rounds > 0) move(rounds - round);  // the blocks behind the last whole round
     for (; n > 0; --n) {
         HalfRegs<HT, 1, W8, MH> r1;
         half_load<HT, 1, W8, MH>(r1, w, xh, xstride);
@@ -1042,19 +1070,25 @@ static GemmPlan plan_fused_w8(int N) {
     return GemmPlan{true, ht < 1 ? 1 : ht, 1};
 }
 
+// The k-split GEMMs with 8-bit weights: the cost of store_cost_us with a byte per weight, 0.75 us per split (fitted to launches of
+// the 1.3B, 6.7B and 13B shapes: 5120 x 20480, 32 rows: five units x four splits 23.7 us, four x three 24.2, ten x eight,
+// the balance-only choice before this, 28.4; 5120 x 5120: four x three 11.0, five x four 12.3).
 static GemmPlan plan_store_w8(int N, int K, size_t capacity) {
     const int n_half = N / 16, kq = K / 64, cus = plan_cus();
     GemmPlan g{true, kHalfMax, 1};
     double best = 1e30;
     for (int ht = kHalfMax; ht >= 1; --ht) {
         const int groups = (n_half + ht - 1) / ht;
-        int ks = cus / groups;
-        if (ks < 1) ks = 1;
-        if (ks > 8) ks = 8;
-        while (ks > 1 && kq / (ks * 4) < 4) --ks;  // at least four 64-wide steps per wavefront
-        if (capacity && (size_t)groups * ks * (size_t)(2 * ht + 7) * 256 > capacity) continue;
-        const double load = (double)ht * 16 / ks * (groups * ks > cus ? (double)(groups * ks + cus - 1) / cus : 1.0);
-        if (load < best * 0.999) { best = load; g = GemmPlan{true, ht, ks}; }
+        for (int ks = 1; ks <= 8; ++ks) {
+            if (ks > 1 && (groups * ks > cus || kq / (ks * 4) < 4)) break;  // at least four 64-wide steps per wavefront
+            if (capacity && (size_t)groups * ks * (size_t)(2 * ht + 7) * 256 > capacity) break;
+            const int wgs = groups * ks, items = (2 * ht + (ht <= 4 ? 7 : 3)) / (ht <= 4 ? 8 : 4);
+            const double idle = wgs < cus ? 1.0 - (double)wgs / cus : 0.0;
+            const double per_cu = (double)K / ks * (16.0 * ht + 64.0) / 48e3 * ((wgs + cus - 1) / cus);
+            const double hbm = (double)N * K / 6.5e6 * (1.0 + 0.5 * idle);
+            const double cost = std::max(per_cu, hbm) + 0.2 * items + 0.75 * ks;
+            if (cost < best * 0.999) { best = cost; g = GemmPlan{true, ht, ks}; }
+        }
     }
     return g;
 }
