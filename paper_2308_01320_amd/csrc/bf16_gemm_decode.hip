@@ -758,11 +758,11 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_half_kernel(const u32x4* __re
 }
 
 // One block per sequence: combines the LM-head partials of the workgroups (or wavefronts) in their order
-// (deterministic), writes token id and its untempered log-probability.
+// (deterministic), writes token id and its untempered log-probability; advance: the step ends here.
 __global__ void lm_reduce_kernel(const float* __restrict__ stats, const int* __restrict__ stats_idx, int n_tiles,
-                                 const he_dev_state* __restrict__ st, int32_t* __restrict__ ids_out,
+                                 he_dev_state* st, int32_t* __restrict__ ids_out,
                                  float* __restrict__ lp_out, int out_stride, int out_at_step,
-                                 int32_t* __restrict__ cur_ids) {
+                                 int32_t* __restrict__ cur_ids, int advance) {
     __shared__ float smx[4], ssum[4], sbest[4], sz[4];
     __shared__ int sidx[4];
     const int b = blockIdx.x, wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
@@ -801,6 +801,7 @@ __global__ void lm_reduce_kernel(const float* __restrict__ stats, const int* __r
         lp_out[at] = bz - (mx + logf(sum));
         if (cur_ids) cur_ids[q] = bi;
     }
+    if (advance) advance_state_by_last(st, 1, 1);
 }
 
 // Launch shapes are sized for the current device's CU count, or for the count a planner query names.
@@ -1190,8 +1191,8 @@ void bf16_gemm_skinny(hipStream_t s, int mode, const void* Wp, const void* Xhi, 
 int bf16_lm_parts_max(int V) { return std::max((V + 31) / 32, 2 * ((V + 255) / 256)); }
 
 void bf16_lm_head(hipStream_t s, const void* Wp, const void* Xhi, int B, int V, int K,
-                  const he_dev_state* st, float* logits_opt, float* stats, int* stats_idx, int32_t* ids_out,
-                  float* lp_out, int out_stride, int out_at_step, int32_t* cur_ids, const bf16_gemm_args* fold) {
+                  he_dev_state* st, float* logits_opt, float* stats, int* stats_idx, int32_t* ids_out,
+                  float* lp_out, int out_stride, int out_at_step, int32_t* cur_ids, bool advance, const bf16_gemm_args* fold) {
     int parts;  // soft-max partials per row
     if (B > 32) {
         parts = bf16_lm_head_tiles(s, Wp, Xhi, B, V, K, fold, st, logits_opt, stats, stats_idx);
@@ -1204,6 +1205,6 @@ void bf16_lm_head(hipStream_t s, const void* Wp, const void* Xhi, int B, int V, 
         launch_skinny<MODE_LMHEAD>(s, Wp, Xhi, K / 16, tiles, 1, nt, 1, p);
     }
     lm_reduce_kernel<<<B, 256, 0, s>>>(stats, stats_idx, parts, st, ids_out, lp_out, out_stride, out_at_step,
-                                       cur_ids);
+                                       cur_ids, advance ? 1 : 0);
 }
 

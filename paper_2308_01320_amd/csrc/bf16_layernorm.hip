@@ -208,10 +208,11 @@ __global__ __launch_bounds__(THREADS) void ln_row_kernel(float* __restrict__ r, 
 // (column group, row), four columns per lane (gw <= 256).
 __global__ __launch_bounds__(64) void embed_ln_kernel(const int32_t* __restrict__ ids, int id_stride,
                                                       const bf16_t* __restrict__ tok, const bf16_t* __restrict__ pos,
-                                                      const he_dev_state* __restrict__ st, int V, int pos_offset,
+                                                      he_dev_state* __restrict__ st, int V, int pos_offset,
                                                       int H, int gw, int groups, const bf16_t* __restrict__ gamma,
                                                       float* __restrict__ r, u32x4* __restrict__ xb,
-                                                      float2* __restrict__ stats) {
+                                                      float2* __restrict__ stats, he_step_sampling sp) {
+    if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) store_sampling(st, sp);
     const int g = blockIdx.x, m = blockIdx.y, lane = threadIdx.x;
     const int b = row_seq(st, m, 1);  // one row per running sequence here
     int id = ids[(size_t)b * id_stride];
@@ -317,12 +318,12 @@ void bf16_gather_last_rows(hipStream_t s, const float* r, const float* q, float*
 }
 
 void bf16_embed_ln(hipStream_t s, const int32_t* ids, int id_stride, const void* tok, const void* pos,
-                   const he_dev_state* st, int B, int H, int V, int pos_offset, int gw, const void* gamma, float* r,
-                   void* x_blocks, float* stats) {
+                   he_dev_state* st, int B, int H, int V, int pos_offset, int gw, const void* gamma, float* r,
+                   void* x_blocks, float* stats, const he_step_sampling& sp) {
     const int groups = (H + gw - 1) / gw;
     embed_ln_kernel<<<dim3(groups, B), 64, 0, s>>>(ids, id_stride, (const bf16_t*)tok, (const bf16_t*)pos, st, V,
                                                    pos_offset, H, gw, groups, (const bf16_t*)gamma, r,
-                                                   (u32x4*)x_blocks, (float2*)stats);
+                                                   (u32x4*)x_blocks, (float2*)stats, sp);
 }
 
 void bf16_wvec(hipStream_t s, const void* Wp, int N, int K, const void* gamma, const void* beta, float* c1, float* c2) {

@@ -19,7 +19,8 @@ struct he_dev_state {
     int max_batch;
     int eos_id, pad_id;  // end-of-sequence stop (eos_id < 0: none) and the filler written after it
     int n_active;      // sequences that have not produced eos_id yet
-    int reserved[5];
+    int arrivals;      // workgroups of the step's last kernel that are done with this state (zero between launches)
+    int reserved[4];
     // [0 .. max_batch): cached positions of sequence b;  [max_batch .. 2 max_batch): left padding of
     // the rows now going through the model (0 outside a prompt pass);  [2 .. 3 max_batch): 1 once the
     // sequence has produced eos_id;  [3 .. 4 max_batch): tokens produced so far;  [4 .. 5 max_batch): the
@@ -43,6 +44,42 @@ __device__ __forceinline__ bool seq_done(const he_dev_state* st, int b) {
 __device__ __forceinline__ int row_seq(const he_dev_state* st, int m, int S) {
     if (S != 1) return m / S;
     return st->ragged ? st->seq[4 * st->max_batch + m] : m;
+}
+
+// Sampling parameters that come with a step: stored by its first kernel, which does not read them.
+struct he_step_sampling { int set, mode; float temperature; uint32_t seed_lo, seed_hi; };
+__device__ __forceinline__ void store_sampling(he_dev_state* st, const he_step_sampling& sp) {
+    if (sp.set) { st->mode = sp.mode; st->temperature = sp.temperature; st->seed_lo = sp.seed_lo; st->seed_hi = sp.seed_hi; }
+}
+
+// End of a pass that fed `tokens` rows per sequence (padding included) and sampled `steps` tokens; by a whole workgroup.
+__device__ __forceinline__ void advance_state(he_dev_state* st, int tokens, int steps) {
+    if (st->ragged) {
+        const int mb = st->max_batch;
+        for (int b = threadIdx.x; b < mb; b += blockDim.x) {
+            if (!st->seq[2 * mb + b]) st->seq[b] += tokens - st->seq[mb + b];
+            st->seq[mb + b] = 0;
+        }
+    }
+    if (threadIdx.x == 0) {
+        st->cur_len += tokens;
+        st->step += steps;
+    }
+}
+// The same at the end of a kernel of many workgroups (a launch of its own for these few words costs 5 us): each counts itself
+// in once it has used what it read of the state -- the values went into addresses of stores that were issued before --
+// and whoever is last advances it.  All threads call it.
+__device__ __forceinline__ void advance_state_by_last(he_dev_state* st, int tokens, int steps) {
+    __shared__ int last;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+        last = __hip_atomic_fetch_add(&st->arrivals, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (int)gridDim.x - 1;
+    }
+    __syncthreads();
+    if (!last) return;
+    advance_state(st, tokens, steps);
+    if (threadIdx.x == 0) __hip_atomic_store(&st->arrivals, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 __device__ __forceinline__ float bf16_to_f32(bf16_t v) { return __uint_as_float(((uint32_t)v) << 16); }

@@ -66,6 +66,7 @@ struct he_engine {
     float lora_scale = 0.f;
     bool arena_released = false;
     size_t kv_bytes = 0;
+    he_step_sampling next_sampling{};  // set: the next pass's first kernel stores it in the device state
     bool ragged_gen = false;   // he_generate_ragged is running: sampling is followed by the end-token bookkeeping
     int* host_active = nullptr;  // pinned: sequences still generating, read back every few steps
     int last_rows = 0;           // rows of the last decode step of the last he_generate / he_generate_ragged
@@ -187,6 +188,13 @@ he_status fail(he_engine* e, he_status code, const std::string& msg) {
     return code;
 }
 
+// what the next pass's first kernel is to store; handed out once
+he_step_sampling take_sampling(he_engine* e) {
+    const he_step_sampling sp = e->next_sampling;
+    e->next_sampling.set = 0;
+    return sp;
+}
+
 he_status check_hip(he_engine* e, hipError_t r, const char* what) {
     if (r == hipSuccess) return HE_OK;
     return fail(e, HE_ERR_DEVICE, std::string(what) + ": " + hipGetErrorString(r));
@@ -266,7 +274,7 @@ void pass_tiled_bf16(he_engine* e, const int32_t* d_ids, int id_stride, int B, i
     bf16_gemm_args base;
     base.st = e->st; base.S = Sp; base.H = H; base.n_heads = c.n_heads; base.max_batch = c.max_batch;
     base.max_seq = c.max_seq_len;
-    plain_embed(s, 1, d_ids, id_stride, e->w.tok_emb, e->w.pos_emb, e->resid, e->st, M, Sp, H, c.vocab, c.pos_offset);
+    plain_embed(s, 1, d_ids, id_stride, e->w.tok_emb, e->w.pos_emb, e->resid, e->st, M, Sp, H, c.vocab, c.pos_offset, take_sampling(e));
     const float* pend = nullptr;  // GEMM output not yet added to the residual stream
     const void* pend_b = nullptr;
     const size_t split = (size_t)M * H;
@@ -321,6 +329,13 @@ CVec cvec_lm(const he_engine* e) {
     return {p, p + vpad};
 }
 
+// After the sampling kernel, which has advanced the device state itself unless he_generate_ragged's bookkeeping comes first.
+void end_step(he_engine* e, int tokens, int32_t* ids_out, float* lp_out, int out_stride, int B) {
+    if (!e->ragged_gen) return;
+    launch_ragged_post(e->stream, e->st, ids_out, lp_out, e->cur_ids, out_stride, B);
+    launch_advance_state(e->stream, e->st, tokens, 1);
+}
+
 // bf16 path, one new token per sequence (a decode step, or the last prompt token):
 // weight-streaming GEMMs, attention over the cache, LM head
 // fused with log-softmax and sampling.
@@ -357,7 +372,7 @@ void pass_decode_bf16(he_engine* e, const int32_t* d_ids, int id_stride, int B, 
         LaunchTimer t(e, HE_K_LAYERNORM);
         const bool last = L == 0;
         bf16_embed_ln(s, d_ids, id_stride, e->w.tok_emb, e->w.pos_emb, e->st, B, H, c.vocab, c.pos_offset, gw2,
-                      last ? e->w.lnf_g : e->layers[0].ln1_g, e->resid, last ? e->xfblk : e->ablk, e->ln_stats);
+                      last ? e->w.lnf_g : e->layers[0].ln1_g, e->resid, last ? e->xfblk : e->ablk, e->ln_stats, take_sampling(e));
     }
     for (int l = 0; l < L; ++l) {
         const he_layer_weights& lw = e->layers[l];
@@ -403,11 +418,10 @@ void pass_decode_bf16(he_engine* e, const int32_t* d_ids, int id_stride, int B, 
         bf16_gemm_args a = base;
         fold(a, gw2, cvec_lm(e));
         bf16_lm_head(s, e->lm_tiled, e->xfblk, B, c.vocab, H, e->st, d_logits_opt, e->stats, e->stats_idx,
-                     ids_out, lp_out, out_stride, out_at_step, e->cur_ids, &a);
+                     ids_out, lp_out, out_stride, out_at_step, e->cur_ids, !e->ragged_gen, &a);
     }
     { LaunchTimer t(e, HE_K_EMPTY); }
-    if (e->ragged_gen) launch_ragged_post(s, e->st, ids_out, lp_out, e->cur_ids, out_stride, B);
-    launch_advance_state(s, e->st, 1, 1);
+    end_step(e, 1, ids_out, lp_out, out_stride, B);
     e->cur_len += 1;
     e->step += 1;
 }
@@ -478,11 +492,10 @@ void pass_last_token_bf16(he_engine* e, int B, int S, int32_t* ids_out, float* l
         a = base;
         fold(a, gw2, cvec_lm(e));
         bf16_lm_head(s, e->lm_tiled, e->xfblk, B, c.vocab, H, e->st, d_logits_opt, e->stats, e->stats_idx, ids_out, lp_out,
-                     out_stride, out_at_step, e->cur_ids, &a);
+                     out_stride, out_at_step, e->cur_ids, !e->ragged_gen, &a);
     }
     { LaunchTimer t(e, HE_K_EMPTY); }
-    if (e->ragged_gen) launch_ragged_post(s, e->st, ids_out, lp_out, e->cur_ids, out_stride, B);
-    launch_advance_state(s, e->st, 1, 1);
+    end_step(e, 1, ids_out, lp_out, out_stride, B);
     e->cur_len += 1;
     e->step += 1;
 }
@@ -498,7 +511,7 @@ void pass_decode_wide_bf16(he_engine* e, const int32_t* d_ids, int id_stride, in
     bf16_gemm_args base;
     base.st = e->st; base.S = 1; base.H = H; base.n_heads = c.n_heads; base.max_batch = c.max_batch;
     base.max_seq = c.max_seq_len;
-    plain_embed(s, 1, d_ids, id_stride, e->w.tok_emb, e->w.pos_emb, e->resid, e->st, B, 1, H, c.vocab, c.pos_offset);
+    plain_embed(s, 1, d_ids, id_stride, e->w.tok_emb, e->w.pos_emb, e->resid, e->st, B, 1, H, c.vocab, c.pos_offset, take_sampling(e));
     const float* pend = nullptr;
     int pend_ks = 0, pend_sc = 0;
     const void* pend_b = nullptr;
@@ -549,11 +562,10 @@ void pass_decode_wide_bf16(he_engine* e, const int32_t* d_ids, int id_stride, in
     {
         LaunchTimer t(e, HE_K_LM_HEAD);
         bf16_lm_head(s, e->lm_tiled, e->xfblk, B, c.vocab, H, e->st, d_logits_opt, e->stats, e->stats_idx,
-                     ids_out, lp_out, out_stride, out_at_step, e->cur_ids);
+                     ids_out, lp_out, out_stride, out_at_step, e->cur_ids, !e->ragged_gen);
     }
     { LaunchTimer t(e, HE_K_EMPTY); }
-    if (e->ragged_gen) launch_ragged_post(s, e->st, ids_out, lp_out, e->cur_ids, out_stride, B);
-    launch_advance_state(s, e->st, 1, 1);
+    end_step(e, 1, ids_out, lp_out, out_stride, B);
     e->cur_len += 1;
     e->step += 1;
 }
@@ -661,16 +673,15 @@ he_status run_forward(he_engine* e, const int32_t* d_ids, int B, int S, int32_t*
     hipStream_t s = e->stream;
     const int M = B * S, H = c.hidden, bf = e->bf16;
 
-    plain_embed(s, bf, d_ids, S, e->w.tok_emb, e->w.pos_emb, e->resid, e->st, M, S, H, c.vocab, c.pos_offset);
+    plain_embed(s, bf, d_ids, S, e->w.tok_emb, e->w.pos_emb, e->resid, e->st, M, S, H, c.vocab, c.pos_offset, take_sampling(e));
     plain_layers(e, M, S);
     // final LayerNorm on each sequence's last row only
     float* logits = d_logits_opt ? d_logits_opt : e->logits;
     const plain_ln_args lnf{e->w.lnf_g, e->w.lnf_b, c.ln_eps, S, S - 1};
     plain_gemm(s, bf, e->resid, e->w.lm_head, nullptr, B, c.vocab, H, EPI_STORE, logits, nullptr, e->st, S, 0, H, c.n_heads,
                c.max_batch, c.max_seq_len, 1.f, &lnf, e->xf);
-    launch_sample(s, logits, B, c.vocab, e->st, ids_out, lp_out, out_stride, out_at_step, e->cur_ids);
-    if (e->ragged_gen) launch_ragged_post(s, e->st, ids_out, lp_out, e->cur_ids, out_stride, B);
-    launch_advance_state(s, e->st, S, 1);
+    launch_sample(s, logits, B, c.vocab, e->st, ids_out, lp_out, out_stride, out_at_step, e->cur_ids, e->ragged_gen ? 0 : S);
+    end_step(e, S, ids_out, lp_out, out_stride, B);
     e->cur_len += S;
     e->step += 1;
     return check_hip(e, hipGetLastError(), "kernel launch");
@@ -983,7 +994,7 @@ he_status he_decode_step(he_engine* e, const int32_t* d_in_ids, const he_samplin
     if (e->cur_len == 0 || e->batch == 0) return fail(e, HE_ERR_STATE, "he_decode_step: no prompt has been prefilled");
     if (e->cur_len + 1 > e->cfg.max_seq_len) return fail(e, HE_ERR_CAPACITY, "he_decode_step: KV cache is full");
     if (e->cur_len + 1 > e->cfg.max_positions) return fail(e, HE_ERR_CAPACITY, "he_decode_step: position table exhausted");
-    launch_set_state(e->stream, e->st, 0, 0, 0, sampling->mode, sampling->temperature, sampling->seed);
+    e->next_sampling = {1, sampling->mode, sampling->temperature, (uint32_t)(sampling->seed & 0xFFFFFFFFu), (uint32_t)(sampling->seed >> 32)};
     return run_forward(e, d_in_ids, e->batch, 1, d_next_ids, d_logprobs, 1, 0, d_logits_opt);
 }
 
@@ -1040,7 +1051,7 @@ he_status he_decode_step_static(he_engine* e, const int32_t* d_in_ids, const he_
     const size_t zero_words = (L.stats - L.ln_stats) / sizeof(uint32_t);
     zero_words_kernel<<<(unsigned)std::min<size_t>((zero_words + 255) / 256, 64), 256, 0, e->stream>>>(
         (uint32_t*)(base + L.ln_stats), zero_words);
-    launch_set_state(e->stream, e->st, 0, 0, 0, sampling->mode, sampling->temperature, sampling->seed);
+    e->next_sampling = {1, sampling->mode, sampling->temperature, (uint32_t)(sampling->seed & 0xFFFFFFFFu), (uint32_t)(sampling->seed >> 32)};
     // the step itself: the same launches as he_decode_step, one by one, with the five scratch pointers swapped
     float *part = e->part, *ln_stats = e->ln_stats, *stats = e->stats;
     int *ln_counters = e->ln_counters, *stats_idx = e->stats_idx;
@@ -1163,7 +1174,7 @@ he_status he_score(he_engine* e, const int32_t* d_ids, int B, int T, float* d_ou
         bf16_score_head(s, e->lm_tiled, e->ablk, M, T, V, H, d_ids, e->score_stats, e->score_tgt, d_out_logprobs);
     } else {
         const int bf = e->bf16;
-        plain_embed(s, bf, d_ids, T, e->w.tok_emb, e->w.pos_emb, e->resid, e->st, M, T, H, V, c.pos_offset);
+        plain_embed(s, bf, d_ids, T, e->w.tok_emb, e->w.pos_emb, e->resid, e->st, M, T, H, V, c.pos_offset, take_sampling(e));
         plain_layers(e, M, T);
         // final LayerNorm of every row into abuf, then the LM head max_batch rows at a time
         plain_ln(s, bf, e->resid, plain_ln_args{e->w.lnf_g, e->w.lnf_b, c.ln_eps, 1, 0}, e->abuf, M, H);

@@ -4,12 +4,13 @@
 #include <stdint.h>
 
 struct he_dev_state;
+struct he_step_sampling;
 
 enum { EPI_STORE = 0, EPI_BIAS_RELU = 1, EPI_QKV = 2, EPI_STORE_LN = 3, EPI_RESID = 4 };
 
 // ---- plain kernels (kernels_plain.hip): float activations, row-major; bf16 != 0 selects bf16 storage
 void plain_embed(hipStream_t s, int bf16, const int32_t* ids, int id_stride, const void* tok, const void* pos, float* x,
-                 const he_dev_state* st, int M, int S, int H, int V, int pos_offset);
+                 he_dev_state* st, int M, int S, int H, int V, int pos_offset, const he_step_sampling& sp);
 // LayerNorm of rows m*in_mul + in_add of the residual stream
 struct plain_ln_args { const void *gamma, *beta; float eps; int in_mul, in_add; };
 void plain_ln(hipStream_t s, int bf16, const float* r, const plain_ln_args& ln, float* a, int rows, int H);
@@ -24,8 +25,9 @@ void plain_attn(hipStream_t s, int bf16, const float* q, const void* kv, float* 
 void plain_score_rows(hipStream_t s, const float* logits, const int32_t* ids, int row0, int n, int S, int V, float* out);
 
 // ---- shared small kernels
-void launch_sample(hipStream_t s, const float* logits, int B, int V, const he_dev_state* st, int32_t* ids_out,
-                   float* lp_out, int out_stride, int out_at_step, int32_t* cur_ids);
+// advance > 0: the pass fed that many tokens per sequence and ends here (else launch_advance_state follows)
+void launch_sample(hipStream_t s, const float* logits, int B, int V, he_dev_state* st, int32_t* ids_out,
+                   float* lp_out, int out_stride, int out_at_step, int32_t* cur_ids, int advance);
 void launch_set_state(hipStream_t s, he_dev_state* st, int cur_len, int step, int set_pos, int mode, float temperature,
                       uint64_t seed);
 void launch_advance_state(hipStream_t s, he_dev_state* st, int tokens, int steps);
@@ -89,8 +91,8 @@ void bf16_store_footprint(int M, int N, int K, size_t capacity, int w8, int cus,
 // units per workgroup, k-splits; store != 0 for the k-split GEMMs
 void bf16_plan_query(int M, int N, int K, int store, size_t capacity, int cus, int* unit_rows, int* per_wg, int* ks);
 void bf16_embed_ln(hipStream_t s, const int32_t* ids, int id_stride, const void* tok, const void* pos,
-                   const he_dev_state* st, int B, int H, int V, int pos_offset, int gw, const void* gamma, float* r,
-                   void* x_blocks, float* stats);
+                   he_dev_state* st, int B, int H, int V, int pos_offset, int gw, const void* gamma, float* r,
+                   void* x_blocks, float* stats, const he_step_sampling& sp);
 // rows b*S + S-1 of r and q ([B*S][H] floats) -> rows b of r_out and q_out ([B][H])
 void bf16_gather_last_rows(hipStream_t s, const float* r, const float* q, float* r_out, float* q_out, int B, int S, int H);
 void bf16_wvec(hipStream_t s, const void* Wp, int N, int K, const void* gamma, const void* beta, float* c1, float* c2);
@@ -123,9 +125,10 @@ void fp8_quant_units(hipStream_t s, const void* src, const int* exps, void* unit
 // units -> half 32x16 blocks (what the tiled GEMMs read)
 void fp8_dequant_units(hipStream_t s, const void* units, const float* scales, void* dst_blocks, int R, int K);
 void bf16_store_plan_w8(int N, int K, size_t capacity, int* group_cols, int* ks);
+// advance: the step ends here (else launch_advance_state follows)
 void bf16_lm_head(hipStream_t s, const void* Wp, const void* X, int B, int V, int K,
-                  const he_dev_state* st, float* logits_opt, float* stats, int* stats_idx, int32_t* ids_out,
-                  float* lp_out, int out_stride, int out_at_step, int32_t* cur_ids,
+                  he_dev_state* st, float* logits_opt, float* stats, int* stats_idx, int32_t* ids_out,
+                  float* lp_out, int out_stride, int out_at_step, int32_t* cur_ids, bool advance,
                   const bf16_gemm_args* fold = nullptr);
 // partials per row that any form of the LM head leaves, at most
 int bf16_lm_parts_max(int V);

@@ -7,6 +7,17 @@
 namespace {
 
 constexpr int kThreads = 256;
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
+// four consecutive values, aligned
+__device__ __forceinline__ f32x4 load4(const float* p) { return *reinterpret_cast<const f32x4*>(p); }
+__device__ __forceinline__ f32x4 load4(const bf16_t* p) {
+    const uint2 w = *reinterpret_cast<const uint2*>(p);
+    return f32x4{__uint_as_float(w.x << 16), __uint_as_float(w.x & 0xFFFF0000u), __uint_as_float(w.y << 16), __uint_as_float(w.y & 0xFFFF0000u)};
+}
+// the caller's tables and vectors may start anywhere
+template <typename ST>
+bool aligned4(const void* q) { return (uintptr_t)q % (4 * sizeof(ST)) == 0; }
 
 __device__ __forceinline__ float block_sum(float v, float* red) {
     for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
@@ -31,20 +42,27 @@ __device__ __forceinline__ float block_max(float v, float* red) {
 }
 
 // Row m = b*S + t:  x[m,:] = tok_emb[ids[b*id_stride + t],:] + pos_emb[cur_len + t + pos_offset,:]
-template <typename ST>
-__global__ void embed_kernel(const int32_t* __restrict__ ids, int id_stride, const ST* __restrict__ tok,
-                             const ST* __restrict__ pos, float* __restrict__ x, const he_dev_state* __restrict__ st,
-                             int S, int H, int V, int pos_offset) {
+// VEC: H is a multiple of four and the tables are aligned for four values at a time (96 rows of 5120: 11.2 -> 6.8 us).
+template <typename ST, bool VEC>
+__global__ __launch_bounds__(256) void embed_kernel(const int32_t* __restrict__ ids, int id_stride, const ST* __restrict__ tok,
+                                                    const ST* __restrict__ pos, float* __restrict__ x, he_dev_state* __restrict__ st,
+                                                    int S, int H, int V, int pos_offset, he_step_sampling sp) {
+    if (blockIdx.x == 0 && threadIdx.x == 0) store_sampling(st, sp);
     const int m = blockIdx.x, b = row_seq(st, m, S), t = m % S - row_pad(st, b);
-    if (t < 0) {  // a padding row: not a token, nothing downstream uses it
-        for (int i = threadIdx.x; i < H; i += blockDim.x) x[(size_t)m * H + i] = 0.f;
-        return;
-    }
+    const bool token = t >= 0;  // else a padding row: zeros, nothing downstream uses it
     int id = ids[(size_t)b * id_stride + (m % S)];
     id = id < 0 ? 0 : (id >= V ? V - 1 : id);  // out-of-range ids are clamped, never read out of bounds
-    const size_t p = (size_t)(seq_len(st, b) + t + pos_offset);
-    for (int i = threadIdx.x; i < H; i += blockDim.x)
-        x[(size_t)m * H + i] = ld_f32(tok, (size_t)id * H + i) + ld_f32(pos, p * H + i);
+    const size_t p = token ? (size_t)(seq_len(st, b) + t + pos_offset) : 0;
+    if (VEC) {
+        for (int i = threadIdx.x * 4; i < H; i += blockDim.x * 4) {
+            f32x4 v = {0.f, 0.f, 0.f, 0.f};
+            if (token) v = load4(tok + (size_t)id * H + i) + load4(pos + p * H + i);
+            *reinterpret_cast<f32x4*>(x + (size_t)m * H + i) = v;
+        }
+    } else {
+        for (int i = threadIdx.x; i < H; i += blockDim.x)
+            x[(size_t)m * H + i] = token ? ld_f32(tok, (size_t)id * H + i) + ld_f32(pos, p * H + i) : 0.f;
+    }
 }
 
 // a[m,:] = LayerNorm of row m*in_mul + in_add of the residual stream.  (Many rows; a few are normalised inside the GEMM.)
@@ -82,31 +100,16 @@ __global__ void ln_kernel(const float* __restrict__ r, const ST* __restrict__ ga
 //   many tiles (from 256 on):   T = 2, KW = 1: 64 x 64 per workgroup of four wavefronts
 //   else:                       T = 2, KW = 8: 32 x 32 per workgroup
 // VEC: K is a multiple of four and the rows are aligned for 16-byte loads (8-byte ones for bf16 storage).
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-
-template <bool VEC>
-__device__ __forceinline__ f32x4 load_k4(const float* row, int k, int K) {
-    if (VEC) return k < K ? *reinterpret_cast<const f32x4*>(row + k) : f32x4{0.f, 0.f, 0.f, 0.f};
-    f32x4 v = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-        if (k + i < K) v[i] = row[k + i];
-    return v;
-}
-template <bool VEC>
-__device__ __forceinline__ f32x4 load_k4(const bf16_t* row, int k, int K) {
+template <bool VEC, typename ST>
+__device__ __forceinline__ f32x4 load_k4(const ST* row, int k, int K) {
     f32x4 v = {0.f, 0.f, 0.f, 0.f};
     if (VEC) {
-        if (k < K) {
-            const uint2 w = *reinterpret_cast<const uint2*>(row + k);
-            v = f32x4{__uint_as_float(w.x << 16), __uint_as_float(w.x & 0xFFFF0000u), __uint_as_float(w.y << 16),
-                      __uint_as_float(w.y & 0xFFFF0000u)};
-        }
+        if (k < K) v = load4(row + k);
         return v;
     }
 #pragma unroll
     for (int i = 0; i < 4; ++i)
-        if (k + i < K) v[i] = bf16_to_f32(row[k + i]);
+        if (k + i < K) v[i] = ld_f32(row, k + i);
     return v;
 }
 
@@ -310,9 +313,10 @@ __global__ __launch_bounds__(256) void attn_kernel(const float* __restrict__ q, 
 
 // One block per sequence: token = argmax of z (greedy) or of z/temperature + Gumbel noise, ties
 // to the lowest id; logprob = z[token] - logsumexp(z).
-__global__ void sample_kernel(const float* __restrict__ logits, int V, const he_dev_state* __restrict__ st,
+// advance > 0: the pass fed that many tokens per sequence and ends here.
+__global__ void sample_kernel(const float* __restrict__ logits, int V, he_dev_state* st,
                               int32_t* __restrict__ ids_out, float* __restrict__ lp_out, int out_stride,
-                              int out_at_step, int32_t* __restrict__ cur_ids) {
+                              int out_at_step, int32_t* __restrict__ cur_ids, int advance) {
     __shared__ float red[8];
     __shared__ float bs[kThreads / 64];
     __shared__ int bi[kThreads / 64];
@@ -348,6 +352,7 @@ __global__ void sample_kernel(const float* __restrict__ logits, int V, const he_
         lp_out[at] = z[besti] - (mx + logf(sum));
         if (cur_ids) cur_ids[b] = besti;
     }
+    if (advance) advance_state_by_last(st, advance, 1);
 }
 
 __global__ void set_state_kernel(he_dev_state* st, int cur_len, int step, int set_pos, int mode, float temperature,
@@ -361,7 +366,7 @@ __global__ void init_state_kernel(he_dev_state* st, int max_batch) {
     for (int i = threadIdx.x; i < max_batch; i += blockDim.x) st->seq[4 * max_batch + i] = i;
     if (threadIdx.x == 0) {
         st->cur_len = 0; st->step = 0; st->mode = 0; st->temperature = 1.f; st->seed_lo = st->seed_hi = 0u;
-        st->ragged = 0; st->max_batch = max_batch; st->eos_id = -1; st->pad_id = 0; st->n_active = 0;
+        st->ragged = 0; st->max_batch = max_batch; st->eos_id = -1; st->pad_id = 0; st->n_active = 0; st->arrivals = 0;
     }
 }
 
@@ -381,20 +386,7 @@ __global__ void set_ragged_kernel(he_dev_state* st, const int32_t* __restrict__ 
     if (threadIdx.x == 0) { st->ragged = 1; st->eos_id = eos_id; st->pad_id = pad_id; st->n_active = B; }
 }
 
-// End of a pass that fed `tokens` rows per sequence (padding included) and sampled `steps` tokens.
-__global__ void advance_state_kernel(he_dev_state* st, int tokens, int steps) {
-    if (st->ragged) {
-        const int mb = st->max_batch;
-        for (int b = threadIdx.x; b < mb; b += blockDim.x) {
-            if (!st->seq[2 * mb + b]) st->seq[b] += tokens - st->seq[mb + b];
-            st->seq[mb + b] = 0;
-        }
-    }
-    if (threadIdx.x == 0) {
-        st->cur_len += tokens;
-        st->step += steps;
-    }
-}
+__global__ void advance_state_kernel(he_dev_state* st, int tokens, int steps) { advance_state(st, tokens, steps); }
 
 // he_generate_ragged, after a step's sampling: a sequence that has ended keeps producing the
 // filler (log-probability 0); one that has just produced eos_id ends here.
@@ -474,13 +466,16 @@ __global__ void copy_out_kernel(const int32_t* __restrict__ ids, const float* __
 
 template <typename ST>
 static void plain_embed_t(hipStream_t s, const int32_t* ids, int id_stride, const void* tok, const void* pos,
-                          float* x, const he_dev_state* st, int M, int S, int H, int V, int pos_offset) {
-    embed_kernel<ST><<<M, kThreads, 0, s>>>(ids, id_stride, (const ST*)tok, (const ST*)pos, x, st, S, H, V, pos_offset);
+                          float* x, he_dev_state* st, int M, int S, int H, int V, int pos_offset, const he_step_sampling& sp) {
+    if (H % 4 == 0 && aligned4<ST>(tok) && aligned4<ST>(pos))
+        embed_kernel<ST, true><<<M, kThreads, 0, s>>>(ids, id_stride, (const ST*)tok, (const ST*)pos, x, st, S, H, V, pos_offset, sp);
+    else
+        embed_kernel<ST, false><<<M, kThreads, 0, s>>>(ids, id_stride, (const ST*)tok, (const ST*)pos, x, st, S, H, V, pos_offset, sp);
 }
 void plain_embed(hipStream_t s, int bf16, const int32_t* ids, int id_stride, const void* tok, const void* pos, float* x,
-                 const he_dev_state* st, int M, int S, int H, int V, int pos_offset) {
-    if (bf16) plain_embed_t<bf16_t>(s, ids, id_stride, tok, pos, x, st, M, S, H, V, pos_offset);
-    else plain_embed_t<float>(s, ids, id_stride, tok, pos, x, st, M, S, H, V, pos_offset);
+                 he_dev_state* st, int M, int S, int H, int V, int pos_offset, const he_step_sampling& sp) {
+    if (bf16) plain_embed_t<bf16_t>(s, ids, id_stride, tok, pos, x, st, M, S, H, V, pos_offset, sp);
+    else plain_embed_t<float>(s, ids, id_stride, tok, pos, x, st, M, S, H, V, pos_offset, sp);
 }
 
 void plain_ln(hipStream_t s, int bf16, const float* r, const plain_ln_args& ln, float* a, int rows, int H) {
@@ -519,10 +514,9 @@ static void plain_gemm_t(hipStream_t s, const float* A, const void* W, const voi
         A = scratch;
         ln = nullptr;
     }
-    // the engine's activations are aligned; the caller's matrices and vectors may start anywhere, and rows follow one another
-    auto at = [](const void* q) { return (uintptr_t)q % (4 * sizeof(ST)) == 0; };
+    // (the engine's activations are aligned)
     p.vec_out = p.N % 4 == 0 && (uintptr_t)p.out % 16 == 0;
-    const bool vec = p.K % 4 == 0 && at(W) && (!ln || (at(ln->gamma) && at(ln->beta)));
+    const bool vec = p.K % 4 == 0 && aligned4<ST>(W) && (!ln || (aligned4<ST>(ln->gamma) && aligned4<ST>(ln->beta)));
     if (ln) { p.eps = ln->eps; p.in_mul = ln->in_mul; p.in_add = ln->in_add; }
     if (vec) launch_gemm<ST, true>(s, A, (const ST*)W, (const ST*)bias, ln, p);
     else launch_gemm<ST, false>(s, A, (const ST*)W, (const ST*)bias, ln, p);
@@ -580,9 +574,9 @@ void plain_score_rows(hipStream_t s, const float* logits, const int32_t* ids, in
     score_rows_kernel<<<n, kThreads, 0, s>>>(logits, ids, row0, S, V, out);
 }
 
-void launch_sample(hipStream_t s, const float* logits, int B, int V, const he_dev_state* st, int32_t* ids_out,
-                   float* lp_out, int out_stride, int out_at_step, int32_t* cur_ids) {
-    sample_kernel<<<B, kThreads, 0, s>>>(logits, V, st, ids_out, lp_out, out_stride, out_at_step, cur_ids);
+void launch_sample(hipStream_t s, const float* logits, int B, int V, he_dev_state* st, int32_t* ids_out,
+                   float* lp_out, int out_stride, int out_at_step, int32_t* cur_ids, int advance) {
+    sample_kernel<<<B, kThreads, 0, s>>>(logits, V, st, ids_out, lp_out, out_stride, out_at_step, cur_ids, advance);
 }
 
 void launch_set_state(hipStream_t s, he_dev_state* st, int cur_len, int step, int set_pos, int mode, float temperature,
