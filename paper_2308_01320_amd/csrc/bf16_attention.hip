@@ -326,32 +326,91 @@ __global__ __launch_bounds__(256) void attn_prompt_kernel(const float* __restric
 // scores of query lane%32 in that lane's 16 accumulators (online soft-max needs one exchange
 // with lane^32), and O^T = V^T P^T accumulates that query's output column, so the soft-max
 // rescaling is a per-lane scalar.  Q and P enter the MFMA as two half terms (hi + lo).  The
-// keys of a PV step are taken in the order the score accumulators already hold them; the V^T
-// operand is gathered in that order from the staged rows with 16-bit LDS reads.
+// keys of a PV step are taken in the order the score accumulators already hold them.
+//
+// 32 matrix instructions per tile and wavefront (1024 cycles; head dimension 128) set the pace only if nothing else
+// takes longer.  V is transposed on its way into LDS -- a thread brings eight dimensions of two consecutive keys and writes
+// eight words -- so that an operand of V^T is two 8-byte reads (reading it out of untransposed rows took 64 16-bit reads per
+// tile and wavefront, and the LDS pipe was the bottleneck); its pitch of 18 words puts both the writes (16 keys pairs x 4
+// dimension groups) and the reads (32 dimensions) on all banks.  Two buffers: one barrier per tile.  The scores come out
+// in units of log2 (log2 e is multiplied into Q), so a probability is one subtraction and the hardware's 2^x.
+// Measured: 2 x 1999 queries, 40 heads of 128: 405 -> 390 us with the above, -> 230 with the order of the workgroups below;
+// 32 x 512, 32 heads of 64: 183 -> 174 -> 126; 32 x 256, 40 heads of 128: 132 -> 131 -> 121 (of which reading q in float,
+// K and V and writing the output take 76).
 template <int D>
 __global__ __launch_bounds__(256, 2) void attn_prompt_mfma_kernel(const float* __restrict__ q,
                                                                const half_t* __restrict__ kv, u32x4* __restrict__ o,
                                                                const he_dev_state* __restrict__ st, int S, int layer,
-                                                               int H, int n_heads, int max_batch, int max_seq) {
+                                                               int H, int n_heads, int max_batch, int max_seq, int batch) {
     constexpr int KBD = D / 16;      // k-blocks over the head dimension
     constexpr int DB = D / 32;       // 32-wide blocks of output dimensions
     constexpr int KPITCH = D + 8;    // halves per K row in LDS (16 bytes of padding)
-    __shared__ __align__(16) half_t ks[32 * KPITCH];
-    __shared__ __align__(16) half_t vs[32 * KPITCH];
-    const int h = blockIdx.y, b = blockIdx.z;
+    constexpr int VPITCH = 36;       // halves per V^T row: 32 keys and 8 bytes of padding
+    __shared__ __align__(16) half_t ks[2][32 * KPITCH];
+    __shared__ __align__(16) half_t vt[2][D * VPITCH];
+    // Workgroups go round the XCDs by index, and one of late queries has many times the keys of one of early ones: with the
+    // query blocks along the grid an XCD got the same blocks of every (sequence, head), and the launch waited for the XCD
+    // with the last ones (up to 1.6 times the mean).  Here a (sequence, head) belongs to one XCD, and the blocks go out
+    // longest first.
+    const int qblocks = (S + 127) / 128, pairs = batch * n_heads, per_xcd = (pairs + 7) / 8, slot = blockIdx.x >> 3;
+    const int pair = (slot % per_xcd) * 8 + (blockIdx.x & 7), qblock = qblocks - 1 - slot / per_xcd;
+    if (pair >= pairs) return;  // the whole workgroup
+    const int h = pair % n_heads, b = pair / n_heads;
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int j = lane & 31, hh = lane >> 5;
     const int cur = seq_len(st, b) - row_pad(st, b);  // cache position of row 0: negative while rows are padding
     const int T = cur + S;                          // keys in the cache once this pass is stored
-    const int t0 = (blockIdx.x * 4 + wave) * 32;    // this wavefront's first query
+    const int t0 = (qblock * 4 + wave) * 32;        // this wavefront's first query
     const bool live = t0 < S;
     const int qpos = max(cur + t0 + j, 0);          // last key this lane's query may see (a padding row looks at key 0)
-    const int wg_last = min(T - 1, cur + min(S, (int)(blockIdx.x * 4 + 4) * 32) - 1);
+    const int wg_last = min(T - 1, cur + min(S, (qblock * 4 + 4) * 32) - 1);
     const int n_tiles = wg_last / 32 + 1;
     const int my_last_tile = live ? min(T - 1, cur + t0 + 31) / 32 : -1;
 
+    const half_t* Kg = kv + kv_index(layer, 0, b, h, 0, max_batch, n_heads, max_seq, D);
+    const half_t* Vg = kv + kv_index(layer, 1, b, h, 0, max_batch, n_heads, max_seq, D);
+    // A tile's K and V rows are requested one tile ahead and wait in registers while the tile before
+    // them is multiplied, so that their latency is not paid between two barriers.
+    constexpr int NI = 32 * (D / 8) / 256;  // 16-byte pieces of K per thread and tile
+    const bool has_v = (int)threadIdx.x < 2 * D;  // V: keys 2 vp, 2 vp + 1, dimensions 8 vc .. 8 vc + 7
+    const int vp = threadIdx.x & 15, vc = threadIdx.x >> 4;
+    u32x4 kreg[NI], vreg[2];
+    auto request_tile = [&](int kt) {
+#pragma unroll
+        for (int n = 0; n < NI; ++n) {
+            const int c = threadIdx.x + n * 256;
+            const int key = c / (D / 8), d0 = (c % (D / 8)) * 8, kabs = kt * 32 + key;
+            kreg[n] = u32x4{0u, 0u, 0u, 0u};
+            if (kabs < T) kreg[n] = *reinterpret_cast<const u32x4*>(Kg + (size_t)kabs * D + d0);
+        }
+#pragma unroll
+        for (int n = 0; n < 2; ++n) {
+            const int kabs = kt * 32 + 2 * vp + n;
+            vreg[n] = u32x4{0u, 0u, 0u, 0u};
+            if (has_v && kabs < T) vreg[n] = *reinterpret_cast<const u32x4*>(Vg + (size_t)kabs * D + vc * 8);
+        }
+    };
+    auto store_tile = [&](int buf) {
+#pragma unroll
+        for (int n = 0; n < NI; ++n) {
+            const int c = threadIdx.x + n * 256;
+            *reinterpret_cast<u32x4*>(&ks[buf][(c / (D / 8)) * KPITCH + (c % (D / 8)) * 8]) = kreg[n];
+        }
+        if (has_v) {
+            const uint32_t a[4] = {vreg[0].x, vreg[0].y, vreg[0].z, vreg[0].w}, c[4] = {vreg[1].x, vreg[1].y, vreg[1].z, vreg[1].w};
+            uint32_t* dst = reinterpret_cast<uint32_t*>(&vt[buf][0]) + vc * 8 * (VPITCH / 2) + vp;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {  // (key 2 vp, key 2 vp + 1) of dimensions 2 e and 2 e + 1
+                dst[(2 * e) * (VPITCH / 2)] = (a[e] & 0xFFFFu) | (c[e] << 16);
+                dst[(2 * e + 1) * (VPITCH / 2)] = (a[e] >> 16) | (c[e] & 0xFFFF0000u);
+            }
+        }
+    };
+    if (n_tiles > 0) request_tile(0);
+
     u32x4 qhi[KBD], qlo[KBD];
     {
+        constexpr float kLog2e = 1.44269504f;
         const bool ok = t0 + j < S;
         const float* qp = q + (size_t)(b * S + (ok ? t0 + j : 0)) * H + h * D + hh * 8;
 #pragma unroll
@@ -362,107 +421,80 @@ __global__ __launch_bounds__(256, 2) void attn_prompt_mfma_kernel(const float* _
                 c = *reinterpret_cast<const float4*>(qp + kb * 16 + 4);
             }
             uint32_t h0, h1, h2, h3, l0, l1, l2, l3;
-            split2(a.x, a.y, h0, l0); split2(a.z, a.w, h1, l1); split2(c.x, c.y, h2, l2); split2(c.z, c.w, h3, l3);
+            split2(a.x * kLog2e, a.y * kLog2e, h0, l0); split2(a.z * kLog2e, a.w * kLog2e, h1, l1);
+            split2(c.x * kLog2e, c.y * kLog2e, h2, l2); split2(c.z * kLog2e, c.w * kLog2e, h3, l3);
             qhi[kb] = u32x4{h0, h1, h2, h3};
             qlo[kb] = u32x4{l0, l1, l2, l3};
         }
     }
-    const half_t* Kg = kv + kv_index(layer, 0, b, h, 0, max_batch, n_heads, max_seq, D);
-    const half_t* Vg = kv + kv_index(layer, 1, b, h, 0, max_batch, n_heads, max_seq, D);
     f32x16 oacc[DB];
 #pragma unroll
     for (int i = 0; i < DB; ++i) oacc[i] = f32x16{};
     float m_run = -INFINITY, l_run = 0.f;
-
-    // A tile's K and V rows are requested one tile ahead and wait in registers while the tile before
-    // them is multiplied, so that their latency is not paid between two barriers.
-    constexpr int NI = 32 * (D / 8) / 256;  // 16-byte pieces of K (and of V) per thread and tile
-    u32x4 kreg[NI], vreg[NI];
-    auto request_tile = [&](int kt) {
-#pragma unroll
-        for (int n = 0; n < NI; ++n) {
-            const int c = threadIdx.x + n * 256;
-            const int key = c / (D / 8), d0 = (c % (D / 8)) * 8, kabs = kt * 32 + key;
-            kreg[n] = vreg[n] = u32x4{0u, 0u, 0u, 0u};
-            if (kabs < T) {
-                kreg[n] = *reinterpret_cast<const u32x4*>(Kg + (size_t)kabs * D + d0);
-                vreg[n] = *reinterpret_cast<const u32x4*>(Vg + (size_t)kabs * D + d0);
-            }
-        }
-    };
-    request_tile(0);
+    if (n_tiles > 0) {
+        store_tile(0);
+        if (n_tiles > 1) request_tile(1);
+    }
+    __syncthreads();
     for (int kt = 0; kt < n_tiles; ++kt) {
-        __syncthreads();  // the previous tile has been consumed
-        // stage the K and V rows as they are (a padded pitch keeps the reads below off each other's banks)
+        const int buf = kt & 1;
+        if (kt <= my_last_tile) {  // (else wholly above the diagonal for this wavefront; uniform per wavefront)
+            f32x16 sacc = f32x16{};
 #pragma unroll
-        for (int n = 0; n < NI; ++n) {
-            const int c = threadIdx.x + n * 256;
-            const int key = c / (D / 8), d0 = (c % (D / 8)) * 8;
-            *reinterpret_cast<u32x4*>(&ks[key * KPITCH + d0]) = kreg[n];
-            *reinterpret_cast<u32x4*>(&vs[key * KPITCH + d0]) = vreg[n];
-        }
-        __syncthreads();
-        if (kt + 1 < n_tiles) request_tile(kt + 1);
-        if (kt > my_last_tile) continue;  // wholly above the diagonal for this wavefront (uniform per wavefront)
-        // two accumulators (one per term of Q), so that consecutive MFMAs do not wait for each other's result
-        f32x16 sacc = f32x16{}, sacc_lo = f32x16{};
-#pragma unroll
-        for (int kb = 0; kb < KBD; ++kb) {
-            const u32x4 kblk = *reinterpret_cast<const u32x4*>(&ks[j * KPITCH + kb * 16 + hh * 8]);
-            sacc = mfma_f16(kblk, qhi[kb], sacc);
-            sacc_lo = mfma_f16(kblk, qlo[kb], sacc_lo);
-        }
-#pragma unroll
-        for (int r = 0; r < 16; ++r) sacc[r] += sacc_lo[r];
-        float mx = -INFINITY;
-        if (kt * 32 + 31 > cur + t0) {  // the tile reaches past the first query's last key: mask per query
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int kabs = kt * 32 + 8 * (r >> 2) + 4 * hh + (r & 3);
-                if (kabs > qpos) sacc[r] = -INFINITY;
+            for (int kb = 0; kb < KBD; ++kb) {
+                const u32x4 kblk = *reinterpret_cast<const u32x4*>(&ks[buf][j * KPITCH + kb * 16 + hh * 8]);
+                sacc = mfma_f16(kblk, qlo[kb], sacc);
+                sacc = mfma_f16(kblk, qhi[kb], sacc);
             }
-        }
+            float mx = -INFINITY;
+            if (kt * 32 + 31 > cur + t0) {  // the tile reaches past the first query's last key: mask per query
 #pragma unroll
-        for (int r = 0; r < 16; ++r) mx = fmaxf(mx, sacc[r]);
-        mx = fmaxf(mx, __shfl_xor(mx, 32));
-        const float m_new = fmaxf(m_run, mx);  // finite from the first tile on: key 0 is visible to every query
-        // the hardware's exponential (2^(x log2 e), a few ulp): the library routine's ~20 instructions per
-        // value were more work per tile than its matrix products
-        const float alpha = __expf(m_run - m_new);
-        float psum = 0.f;
-        float pr[16];
-#pragma unroll
-        for (int r = 0; r < 16; ++r) { pr[r] = __expf(sacc[r] - m_new); psum += pr[r]; }
-        l_run = l_run * alpha + psum;
-        if (__any(m_new != m_run)) {  // no query of this wavefront met a larger score: nothing to rescale
-#pragma unroll
-            for (int i = 0; i < DB; ++i)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) oacc[i][r] *= alpha;
-        }
-        m_run = m_new;
-#pragma unroll
-        for (int s2 = 0; s2 < 2; ++s2) {
-            uint32_t ph[4], pl[4];
-#pragma unroll
-            for (int x = 0; x < 4; ++x) split2(pr[8 * s2 + 2 * x], pr[8 * s2 + 2 * x + 1], ph[x], pl[x]);
-            const u32x4 phi = u32x4{ph[0], ph[1], ph[2], ph[3]}, plo = u32x4{pl[0], pl[1], pl[2], pl[3]};
-#pragma unroll
-            for (int i = 0; i < DB; ++i) {
-                // V^T operand: this lane's output dimension, the eight keys in the order the score
-                // accumulators hold them (16-bit reads down a column of the staged rows: the 32 lanes of
-                // a half read 64 consecutive bytes, the two halves sit 16 banks apart)
-                const half_t* vcol = &vs[(s2 * 16 + 4 * hh) * KPITCH + i * 32 + j];
-                uint32_t vw[4];
-#pragma unroll
-                for (int x = 0; x < 4; ++x) {
-                    const int k0 = 8 * (x >> 1) + 2 * (x & 1);  // element 2x of the operand; 2x+1 is the next key
-                    vw[x] = (uint32_t)vcol[k0 * KPITCH] | ((uint32_t)vcol[(k0 + 1) * KPITCH] << 16);
+                for (int r = 0; r < 16; ++r) {
+                    const int kabs = kt * 32 + 8 * (r >> 2) + 4 * hh + (r & 3);
+                    if (kabs > qpos) sacc[r] = -INFINITY;
                 }
-                const u32x4 vblk = u32x4{vw[0], vw[1], vw[2], vw[3]};
-                oacc[i] = mfma_f16(vblk, phi, oacc[i]);
-                oacc[i] = mfma_f16(vblk, plo, oacc[i]);
             }
+#pragma unroll
+            for (int r = 0; r < 16; ++r) mx = fmaxf(mx, sacc[r]);
+            mx = fmaxf(mx, __shfl_xor(mx, 32));
+            const float m_new = fmaxf(m_run, mx);  // finite from the first tile on: key 0 is visible to every query
+            const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);
+            float psum = 0.f;
+            float pr[16];
+#pragma unroll
+            for (int r = 0; r < 16; ++r) { pr[r] = __builtin_amdgcn_exp2f(sacc[r] - m_new); psum += pr[r]; }
+            l_run = l_run * alpha + psum;
+            if (__any(m_new != m_run)) {  // no query of this wavefront met a larger score: nothing to rescale
+#pragma unroll
+                for (int i = 0; i < DB; ++i)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) oacc[i][r] *= alpha;
+            }
+            m_run = m_new;
+#pragma unroll
+            for (int s2 = 0; s2 < 2; ++s2) {
+                uint32_t ph[4], pl[4];
+#pragma unroll
+                for (int x = 0; x < 4; ++x) split2(pr[8 * s2 + 2 * x], pr[8 * s2 + 2 * x + 1], ph[x], pl[x]);
+                const u32x4 phi = u32x4{ph[0], ph[1], ph[2], ph[3]}, plo = u32x4{pl[0], pl[1], pl[2], pl[3]};
+                u32x4 vblk[DB];
+#pragma unroll
+                for (int i = 0; i < DB; ++i) {
+                    // V^T operand: this lane's output dimension, the eight keys in the order the score accumulators hold them
+                    const half_t* vrow = &vt[buf][(i * 32 + j) * VPITCH + s2 * 16 + 4 * hh];
+                    const uint2 v0 = *reinterpret_cast<const uint2*>(vrow), v1 = *reinterpret_cast<const uint2*>(vrow + 8);
+                    vblk[i] = u32x4{v0.x, v0.y, v1.x, v1.y};
+                }
+#pragma unroll
+                for (int i = 0; i < DB; ++i) oacc[i] = mfma_f16(vblk[i], plo, oacc[i]);
+#pragma unroll
+                for (int i = 0; i < DB; ++i) oacc[i] = mfma_f16(vblk[i], phi, oacc[i]);
+            }
+        }
+        if (kt + 1 < n_tiles) {
+            store_tile(buf ^ 1);  // (everybody has left that buffer: the barrier that opened this tile)
+            if (kt + 2 < n_tiles) request_tile(kt + 2);
+            __syncthreads();
         }
     }
     if (!live || t0 + j >= S) return;
@@ -511,13 +543,14 @@ static void launch_attn(hipStream_t s, const float* q, const void* kv, void* o_b
 
 void bf16_attn(hipStream_t s, const float* q, const void* kv, void* o_blocks, const he_dev_state* st, int M, int S, int layer, int H, int n_heads, int max_batch, int max_seq) {
     if (S >= 32) {  // prompt rows: 32 queries per wavefront on the matrix cores
-        dim3 fgrid((S + 127) / 128, n_heads, M / S);
+        const int batch = M / S;
+        const unsigned fgrid = (unsigned)((S + 127) / 128) * ((batch * n_heads + 7) / 8) * 8;
         if (H / n_heads == 128)
             attn_prompt_mfma_kernel<128><<<fgrid, 256, 0, s>>>(q, (const half_t*)kv, (u32x4*)o_blocks, st, S, layer, H, n_heads,
-                                                               max_batch, max_seq);
+                                                               max_batch, max_seq, batch);
         else
             attn_prompt_mfma_kernel<64><<<fgrid, 256, 0, s>>>(q, (const half_t*)kv, (u32x4*)o_blocks, st, S, layer, H, n_heads,
-                                                              max_batch, max_seq);
+                                                              max_batch, max_seq, batch);
         return;
     }
     const size_t prompt_shm = (size_t)QB * max_seq * sizeof(float);

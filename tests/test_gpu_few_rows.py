@@ -80,3 +80,23 @@ def test_lm_head_sampled_rows_and_vocabularies(B, V, H):
     got = util.engine_teacher_forced(eng, prompts, want["ids"], 3, binding.sampling("gumbel", 0.9, 3))
     eng.he_destroy()
     util.compare(got, want, BF16_TOL, MARGIN)
+
+
+@pytest.mark.parametrize("B,S,H,nh", [(1, 32, 128, 2), (3, 129, 192, 3), (2, 257, 256, 2), (5, 400, 640, 5)])
+def test_prompt_attention_blocks_and_pairs(B, S, H, nh):
+    """Query blocks of 128 with remainders, (sequence, head) pairs that do not divide over the eight XCDs, both head dimensions,
+    lengths that differ (rows of padding, blocks of nothing but padding)."""
+    import torch
+    d = synth.ModelDims("x", 2, H, nh, 2 * H, 300, 512, B, S, 2, "bf16", "greedy")
+    w = synth.make_weights(d, seed=5)
+    prompts = synth.make_prompts(d, seed=6)
+    lens = np.array([max(1, (S * (b + 1)) // B - (b % 2)) for b in range(B)], np.int32)
+    eng = util.make_engine(d, w)
+    _, lp, lg = eng.he_prefill_ragged(torch.from_numpy(prompts).cuda(), torch.from_numpy(lens).cuda(), binding.sampling("greedy"), True)
+    torch.cuda.synchronize()
+    got = lg.cpu().numpy()
+    eng.he_destroy()
+    w64 = util.weights_f64(w)
+    for b in range(B):
+        one = util.oracle_run(d, w64, prompts[b:b + 1, S - lens[b]:], 1, "greedy")
+        assert float(np.abs(got[b] - one["logits"][0, 0]).max()) <= BF16_TOL, b
