@@ -188,6 +188,9 @@ he_status fail(he_engine* e, he_status code, const std::string& msg) {
     return code;
 }
 
+he_step_sampling step_sampling(const he_sampling& sp) {
+    return {1, sp.mode, sp.temperature, (uint32_t)(sp.seed & 0xFFFFFFFFu), (uint32_t)(sp.seed >> 32)};
+}
 // what the next pass's first kernel is to store; handed out once
 he_step_sampling take_sampling(he_engine* e) {
     const he_step_sampling sp = e->next_sampling;
@@ -266,7 +269,7 @@ he_engine::Tiled layer_blocks(he_engine* e, int l) {
 // With `full` (the scoring pass) every layer is completed and the last FC2's output is left
 // pending, as k-split partial sums plus *pend_bias, for the final LayerNorm.
 void pass_tiled_bf16(he_engine* e, const int32_t* d_ids, int id_stride, int B, int Sp, bool full = false,
-                     const void** pend_bias = nullptr, int* pend_ksplit = nullptr, int advance = -1,
+                     const void** pend_bias = nullptr, int* pend_ksplit = nullptr, bool last_token_follows = false,
                      int* pend_split_col = nullptr) {
     const he_config& c = e->cfg;
     hipStream_t s = e->stream;
@@ -306,9 +309,9 @@ void pass_tiled_bf16(he_engine* e, const int32_t* d_ids, int id_stride, int B, i
     if (pend_bias) *pend_bias = pend_b;
     if (pend_ksplit) *pend_ksplit = pend_ks;
     if (pend_split_col) *pend_split_col = pend_sc;
-    if (advance < 0) advance = Sp;  // (the caller that finishes the last token itself advances by one row less)
-    launch_advance_state(s, e->st, advance, 0);
-    e->cur_len += advance;
+    if (last_token_follows) return;  // (pass_last_token_bf16 advances the state on its way)
+    launch_advance_state(s, e->st, Sp, 0);
+    e->cur_len += Sp;
 }
 
 // Where the vectors W gamma (c1) and W beta (c2) of the GEMMs that follow a LayerNorm live.
@@ -430,8 +433,8 @@ void pass_decode_bf16(he_engine* e, const int32_t* d_ids, int id_stride, int B, 
 // left of that layer, for each sequence's LAST token only -- attention over the cache, out-projection, FC1, FC2
 // on the weight-streaming kernels -- then the LM head and sampling.  (The last token used to take the whole
 // decode-shaped pass, streaming all layers' weights once more: one decode step's time per prompt pass.)
-// On entry the device state still counts the last token as not cached (cur_len = S - 1), as in a decode step
-// after its QKV projection.
+// From its first kernel on the device state counts the last token as not cached (cur_len = S - 1), as in a decode
+// step after its QKV projection.
 void pass_last_token_bf16(he_engine* e, int B, int S, int32_t* ids_out, float* lp_out, int out_stride, int out_at_step,
                           float* d_logits_opt) {
     const he_config& c = e->cfg;
@@ -450,7 +453,8 @@ void pass_last_token_bf16(he_engine* e, int B, int S, int32_t* ids_out, float* l
     }
     const size_t split = (size_t)B * H;
     float *r_last = e->tail_buf, *q_last = e->tail_buf + (size_t)c.max_batch * H;
-    bf16_gather_last_rows(s, e->resid, e->qbuf, r_last, q_last, B, S, H);
+    bf16_gather_last_rows(s, e->resid, e->qbuf, r_last, q_last, B, S, H, e->st, S - 1);
+    e->cur_len += S - 1;
     const he_layer_weights& lw = e->layers[l];
     const he_engine::Tiled& tw = e->tiled[l];
     const Scales sc = e->w8 ? scales_of(e, l) : Scales{nullptr, nullptr, nullptr, nullptr};
@@ -579,7 +583,7 @@ he_status run_forward_bf16(he_engine* e, const int32_t* d_ids, int B, int S, int
     if (S > 1 && e->cfg.n_layers > 0 && !wide_decode(e, B)) {
         // every prompt token through the tiled GEMMs up to the last layer's keys and values, then the rest of
         // that layer for the last tokens alone
-        pass_tiled_bf16(e, d_ids, S, B, S, false, nullptr, nullptr, S - 1);
+        pass_tiled_bf16(e, d_ids, S, B, S, false, nullptr, nullptr, true);
         pass_last_token_bf16(e, B, S, ids_out, lp_out, out_stride, out_at_step, d_logits_opt);
         return check_hip(e, hipGetLastError(), "kernel launch");
     }
@@ -947,10 +951,9 @@ he_status he_reset(he_engine* e) {
     if (!e) return HE_ERR_INVALID_ARG;
     e->cur_len = 0; e->step = 0; e->batch = 0;
     e->ragged_gen = false;
-    launch_set_state(e->stream, e->st, 0, 0, 1, 0, 1.f, 0);
-    // the arrival counters of the k-split GEMMs clear themselves; after a launch that failed half-way they
-    // may not have, so a reset clears them too (outside any captured graph)
-    if (e->ln_counters) (void)hipMemsetAsync(e->ln_counters, 0, sizes_of(e->cfg).ln_counters, e->stream);
+    // (the arrival counters of the k-split GEMMs clear themselves; after a launch that failed half-way they may not
+    // have, so a reset clears them too)
+    launch_reset_state(e->stream, e->st, e->ln_counters, e->ln_counters ? (int)(sizes_of(e->cfg).ln_counters / sizeof(int)) : 0);
     return check_hip(e, hipGetLastError(), "he_reset");
 }
 
@@ -970,7 +973,7 @@ static he_status prefill_impl(he_engine* e, const char* who, const int32_t* d_pr
     if (e->cur_len != 0) return fail(e, HE_ERR_STATE, w + ": cache is not empty (call he_reset)");
     e->batch = B;
     e->step = 0;
-    launch_set_state(e->stream, e->st, 0, 0, 1, sampling->mode, sampling->temperature, sampling->seed);
+    e->next_sampling = step_sampling(*sampling);  // (positions and step number are zero: the cache is empty since a reset)
     if (ragged) launch_set_ragged(e->stream, e->st, d_prompt_lens, B, S, -1, 0);
     return run_forward(e, d_prompt_ids, B, S, d_next_ids, d_logprobs, 1, 0, d_logits_opt);
 }
@@ -994,7 +997,7 @@ he_status he_decode_step(he_engine* e, const int32_t* d_in_ids, const he_samplin
     if (e->cur_len == 0 || e->batch == 0) return fail(e, HE_ERR_STATE, "he_decode_step: no prompt has been prefilled");
     if (e->cur_len + 1 > e->cfg.max_seq_len) return fail(e, HE_ERR_CAPACITY, "he_decode_step: KV cache is full");
     if (e->cur_len + 1 > e->cfg.max_positions) return fail(e, HE_ERR_CAPACITY, "he_decode_step: position table exhausted");
-    e->next_sampling = {1, sampling->mode, sampling->temperature, (uint32_t)(sampling->seed & 0xFFFFFFFFu), (uint32_t)(sampling->seed >> 32)};
+    e->next_sampling = step_sampling(*sampling);
     return run_forward(e, d_in_ids, e->batch, 1, d_next_ids, d_logprobs, 1, 0, d_logits_opt);
 }
 
@@ -1051,7 +1054,7 @@ he_status he_decode_step_static(he_engine* e, const int32_t* d_in_ids, const he_
     const size_t zero_words = (L.stats - L.ln_stats) / sizeof(uint32_t);
     zero_words_kernel<<<(unsigned)std::min<size_t>((zero_words + 255) / 256, 64), 256, 0, e->stream>>>(
         (uint32_t*)(base + L.ln_stats), zero_words);
-    e->next_sampling = {1, sampling->mode, sampling->temperature, (uint32_t)(sampling->seed & 0xFFFFFFFFu), (uint32_t)(sampling->seed >> 32)};
+    e->next_sampling = step_sampling(*sampling);
     // the step itself: the same launches as he_decode_step, one by one, with the five scratch pointers swapped
     float *part = e->part, *ln_stats = e->ln_stats, *stats = e->stats;
     int *ln_counters = e->ln_counters, *stats_idx = e->stats_idx;
@@ -1083,7 +1086,7 @@ static he_status generate_impl(he_engine* e, const char* who, const int32_t* d_p
     he_status rc = he_reset(e);
     if (rc != HE_OK) return rc;
     e->batch = B;
-    launch_set_state(e->stream, e->st, 0, 0, 1, sampling->mode, sampling->temperature, sampling->seed);
+    e->next_sampling = step_sampling(*sampling);
     if (ragged) {
         launch_set_ragged(e->stream, e->st, d_prompt_lens, B, S, eos_id, pad_id);
         launch_fill_gen(e->stream, e->gen_ids, e->gen_lp, B * G, e->st);  // steps never run stay filler
@@ -1168,7 +1171,7 @@ he_status he_score(he_engine* e, const int32_t* d_ids, int B, int T, float* d_ou
     if (e->fast) {
         const void* pend_b = nullptr;
         int pend_ks = 1, pend_sc = 0;
-        pass_tiled_bf16(e, d_ids, T, B, T, true, &pend_b, &pend_ks, -1, &pend_sc);
+        pass_tiled_bf16(e, d_ids, T, B, T, true, &pend_b, &pend_ks, false, &pend_sc);
         bf16_ln(s, e->resid, c.n_layers ? e->part : nullptr, pend_ks, (size_t)M * H, pend_b, e->w.lnf_g, e->w.lnf_b, e->ablk,
                 M, H, c.ln_eps, 1, 0, 0, pend_sc);
         bf16_score_head(s, e->lm_tiled, e->ablk, M, T, V, H, d_ids, e->score_stats, e->score_tgt, d_out_logprobs);

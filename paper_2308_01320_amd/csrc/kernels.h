@@ -28,8 +28,8 @@ void plain_score_rows(hipStream_t s, const float* logits, const int32_t* ids, in
 // advance > 0: the pass fed that many tokens per sequence and ends here (else launch_advance_state follows)
 void launch_sample(hipStream_t s, const float* logits, int B, int V, he_dev_state* st, int32_t* ids_out,
                    float* lp_out, int out_stride, int out_at_step, int32_t* cur_ids, int advance);
-void launch_set_state(hipStream_t s, he_dev_state* st, int cur_len, int step, int set_pos, int mode, float temperature,
-                      uint64_t seed);
+// empty cache, greedy sampling, n_counters arrival counters cleared
+void launch_reset_state(hipStream_t s, he_dev_state* st, int* counters, int n_counters);
 void launch_advance_state(hipStream_t s, he_dev_state* st, int tokens, int steps);
 void launch_init_state(hipStream_t s, he_dev_state* st, int max_batch);
 // sequences of different lengths: B left-padded rows of S entries, lens[b] of them tokens
@@ -93,8 +93,9 @@ void bf16_plan_query(int M, int N, int K, int store, size_t capacity, int cus, i
 void bf16_embed_ln(hipStream_t s, const int32_t* ids, int id_stride, const void* tok, const void* pos,
                    he_dev_state* st, int B, int H, int V, int pos_offset, int gw, const void* gamma, float* r,
                    void* x_blocks, float* stats, const he_step_sampling& sp);
-// rows b*S + S-1 of r and q ([B*S][H] floats) -> rows b of r_out and q_out ([B][H])
-void bf16_gather_last_rows(hipStream_t s, const float* r, const float* q, float* r_out, float* q_out, int B, int S, int H);
+// rows b*S + S-1 of r and q ([B*S][H] floats) -> rows b of r_out and q_out ([B][H]); the state advances by `advance` tokens
+void bf16_gather_last_rows(hipStream_t s, const float* r, const float* q, float* r_out, float* q_out, int B, int S, int H, he_dev_state* st,
+                           int advance);
 void bf16_wvec(hipStream_t s, const void* Wp, int N, int K, const void* gamma, const void* beta, float* c1, float* c2);
 // rows in slices of 32 (a decode step of up to 32 sequences): EPI_BIAS_RELU, EPI_QKV or EPI_STORE_LN;
 // X: the activations as tiled half blocks; ksplit is ignored (the plan decides)

@@ -355,10 +355,14 @@ __global__ void sample_kernel(const float* __restrict__ logits, int V, he_dev_st
     if (advance) advance_state_by_last(st, advance, 1);
 }
 
-__global__ void set_state_kernel(he_dev_state* st, int cur_len, int step, int set_pos, int mode, float temperature,
-                                 uint32_t seed_lo, uint32_t seed_hi) {
-    if (set_pos) { st->cur_len = cur_len; st->step = step; st->ragged = 0; }
-    st->mode = mode; st->temperature = temperature; st->seed_lo = seed_lo; st->seed_hi = seed_hi;
+// Empty cache, greedy sampling; the arrival counters of the k-split GEMMs (null: none) cleared with it.
+__global__ __launch_bounds__(256) void reset_state_kernel(he_dev_state* st, int* __restrict__ counters, int n_counters) {
+    const int i = blockIdx.x * 256 + threadIdx.x;
+    if (i == 0) {
+        st->cur_len = 0; st->step = 0; st->ragged = 0;
+        st->mode = 0; st->temperature = 1.f; st->seed_lo = st->seed_hi = 0u;
+    }
+    if (i < n_counters) counters[i] = 0;
 }
 
 __global__ void init_state_kernel(he_dev_state* st, int max_batch) {
@@ -579,10 +583,8 @@ void launch_sample(hipStream_t s, const float* logits, int B, int V, he_dev_stat
     sample_kernel<<<B, kThreads, 0, s>>>(logits, V, st, ids_out, lp_out, out_stride, out_at_step, cur_ids, advance);
 }
 
-void launch_set_state(hipStream_t s, he_dev_state* st, int cur_len, int step, int set_pos, int mode, float temperature,
-                      uint64_t seed) {
-    set_state_kernel<<<1, 1, 0, s>>>(st, cur_len, step, set_pos, mode, temperature, (uint32_t)(seed & 0xFFFFFFFFu),
-                                     (uint32_t)(seed >> 32));
+void launch_reset_state(hipStream_t s, he_dev_state* st, int* counters, int n_counters) {
+    reset_state_kernel<<<(n_counters + 255) / 256 + (n_counters == 0), 256, 0, s>>>(st, counters, n_counters);
 }
 
 void launch_init_state(hipStream_t s, he_dev_state* st, int max_batch) { init_state_kernel<<<1, 256, 0, s>>>(st, max_batch); }
