@@ -346,7 +346,7 @@ he_status he_arrival_counters_nonzero(he_engine* e, int* nonzero);
 
 /* Test hook, host logic only: how a GEMM of a prompt or scoring pass (M rows, [N, K] weights) is cut into tiles on
  * `cus` compute units (0 = the current device's count, 256 if there is none).  *tile_cols: columns of a tile (256 or
- * 320 with 256 rows; 0 if the pass is too small for these tiles and takes the 256 x 128 ones); *ksplit, *split_col:
+ * 320 with 256 rows; 0 if the pass is too small for whole rounds of these and is cut by tiles of 64 to 256 rows); *ksplit, *split_col:
  * with may_cut (the out-projection and FC2, whose partial sums the following LayerNorm adds; scratch_floats floats
  * of scratch, 0 = unlimited), the tiles of columns >= *split_col are cut into *ksplit k ranges (1: none are). */
 he_status he_plan_prompt_gemm(int M, int N, int K, int may_cut, size_t scratch_floats, int cus, int* tile_cols,

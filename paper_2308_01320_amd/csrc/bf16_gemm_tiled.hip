@@ -110,197 +110,118 @@ __device__ __forceinline__ void lm_head_tile(const Epi& p, const f32x16 (&acc)[4
     }
 }
 
-// ----------------------------------------------------------------- tiled GEMM (prompt pass)
+// ----------------------------------------------------------------- 256 x 128 tiles, two workgroups per CU (scoring head)
 //
 // 256 (n) x 128 (m) output tile per workgroup, four wavefronts in a 2x2 grid of
-// 128x64 sub-tiles (4x2 MFMA tiles each: 8 LDS operand reads feed 16 MFMAs per
+// 128x64 sub-tiles (4x2 MFMA tiles each: 6 LDS operand reads feed 8 MFMAs per
 // k-block).  Operands arrive as 1 KiB blocks whose layout is the lane order, so
 // they are moved global -> LDS directly (global_load_lds, 16 bytes per lane, no
-// staging registers) into a ring of stages; loads run several stages (about 3000
-// MFMA cycles) ahead of the arithmetic, which is what it takes to cover an L2 /
-// infinity-cache round trip; one barrier per stage.
-//
-// Two ring shapes.  PAIR = 0: four stages of two k-blocks (128 KiB), one workgroup per CU -- for launches
-// with fewer tiles than CUs (few rows; the k-split GEMMs of a wide decode step).  PAIR = 1: five stages of
-// one k-block (80 KiB) and at most 256 registers, so that TWO workgroups share a CU: while one of them
-// sits at its barrier, waits for operands or writes its results, the other one's MFMAs keep the matrix
-// cores busy (one workgroup per CU left them idle 40-50 % of the time, and a 256-row tile that moves a
-// quarter less operand data per flop, but fits only once, still 39 %).
-
+// staging registers) into a ring of five stages of one k-block (80 KiB); one barrier per stage.
+// At most 256 registers, so that TWO workgroups share a CU: while one of them sits at its barrier, waits
+// for operands or reduces its logits (13 us of a 256 x 256 tile's 72 at 2048 columns of k: the big tile's kernel with this
+// epilogue took as long), the other one's MFMAs keep the matrix cores busy.
 constexpr int TN = 256;
-constexpr int TNB = TN / 32;   // 32-row operand blocks on the n side
-// MW: 32-row m blocks per wavefront (2: a 128-row m tile; 4: a 256-row m tile whose 16 accumulator tiles take a
-// wavefront's whole register file, so one workgroup per CU)
-template <int PAIR, int MW> struct TiledShape {
-    static constexpr int TMB = 2 * MW;                 // 32-row operand blocks on the m side
-    static constexpr int TMR = TMB * 32;               // rows of the m tile
-    static constexpr int KSTAGE = PAIR ? 1 : 2;        // k-blocks (16 values of k each) per stage
-    static constexpr int NSTG = PAIR ? (MW == 4 ? 8 : 5) : 4;  // ring depth
-    static constexpr int STAGE_BLOCKS = (TNB + TMB) * KSTAGE;
-};
+constexpr int TNB = TN / 32;  // 32-row operand blocks on the n side
+constexpr int TMB = 4;        // ... and on the m side
+constexpr int NSTG = 5;       // ring depth
 
-template <int MODE, int PAIR, int MW>
-__global__ __launch_bounds__(256, (PAIR && MW == 2) ? 2 : 1) void gemm_tiled_kernel(const u32x4* __restrict__ Wp, const u32x4* __restrict__ Xhi,
-                                                         int KB, int NT32, int MT32,
-                                                         int tiles_n, int tiles_m, int ksplit, Epi p) {
-    // ring[stage][block][lane]; blocks of a stage: W tile i, k-block j at KSTAGE i + j; X tile i at KSTAGE (TNB + i) + j
-    typedef TiledShape<PAIR, MW> Shape;
-    constexpr int TMB = Shape::TMB, TMR = Shape::TMR, NSTG = Shape::NSTG;
-    constexpr int KSTAGE = Shape::KSTAGE;
-    constexpr int STAGE_BLOCKS = Shape::STAGE_BLOCKS;
-    __shared__ u32x4 ring[NSTG][STAGE_BLOCKS][64];
+__global__ __launch_bounds__(256, 2) void gemm_score_kernel(const u32x4* __restrict__ Wp, const u32x4* __restrict__ Xhi, int KB, int NT32,
+                                                            int MT32, int tiles_n, int tiles_m, Epi p) {
+    __shared__ u32x4 ring[NSTG][TNB + TMB][64];  // ring[stage][block][lane]: W row-tiles, then X row-tiles
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     // XCD-aware order: consecutive workgroups land on different XCDs, so give each XCD a
-    // contiguous run of tiles; within a run, tiles sharing an m panel are neighbours.  With few
-    // rows (a decode step of a large batch) the tiles alone do not fill the chip: each is then cut
-    // into ksplit k ranges (MODE_STORE only; the partial sums go to separate slots).
-    const int nblk = tiles_n * tiles_m;
-    const int nitem = nblk * ksplit;
-    const int per_xcd = (nitem + 7) / 8;
-    const int item = (blockIdx.x % 8) * per_xcd + blockIdx.x / 8;
-    if (item >= nitem) return;
-    // PAIR: k range after k range, so that the tiles an XCD works on at once still share their panels;
-    // the few tiles of a wide decode step: all k ranges of a tile next to each other
-    const int lin = PAIR ? item % nblk : item / ksplit, ks = PAIR ? item / nblk : item % ksplit;
-    const int GROUP = 8;  // m-tiles per super-row: the tiles an XCD works on at once (8 x 4, or 8 x 8 when two share
-                          // a CU) use the same few W and X panels
+    // contiguous run of tiles; within a run, tiles sharing an m panel are neighbours.
+    const int nitem = tiles_n * tiles_m, per_xcd = (nitem + 7) / 8;
+    const int lin = (blockIdx.x % 8) * per_xcd + blockIdx.x / 8;
+    if (lin >= nitem) return;
+    constexpr int GROUP = 8;  // m-tiles per super-row: the 8 x 8 tiles an XCD works on at once use the same few W and X panels
     const int gsize = GROUP * tiles_n;
     const int g = lin / gsize, first_m = g * GROUP;
     const int gm = min(GROUP, tiles_m - first_m);
     const int tm = first_m + (lin % gsize) % gm, tn = (lin % gsize) / gm;
-
-    const int wn = wave & 1, wm = wave >> 1;  // this wavefront's 128 (n) x 32 MW (m) sub-tile
-    [[maybe_unused]] const int cur_len = epilogue_len<MODE>(p);
-    f32x16 acc[4][MW];
+    const int wn = wave & 1, wm = wave >> 1;  // this wavefront's 128 (n) x 64 (m) sub-tile
+    f32x16 acc[4][2];
 #pragma unroll
     for (int i = 0; i < 4; ++i)
 #pragma unroll
-        for (int j = 0; j < MW; ++j) acc[i][j] = f32x16{};
-
-    // this wavefront brings in W row-tiles 2w, 2w+1 and XW row-tiles of X per k-block
-    constexpr int XW = TMB / 4;
+        for (int j = 0; j < 2; ++j) acc[i][j] = f32x16{};
+    // this wavefront brings in W row-tiles 2w, 2w+1 and X row-tile w per k-block
     const u32x4* wsrc[2];
 #pragma unroll
     for (int i = 0; i < 2; ++i) wsrc[i] = Wp + (size_t)min(tn * TNB + wave * 2 + i, NT32 - 1) * KB * 64 + lane;
-    const u32x4 *hsrc[XW];
-#pragma unroll
-    for (int x = 0; x < XW; ++x) {
-        const int xrt = min(tm * TMB + wave * XW + x, MT32 - 1);
-        hsrc[x] = Xhi + (size_t)xrt * KB * 64 + lane;
-    }
-    const int nst_all = KB / KSTAGE;  // KB is even (K % 32 == 0)
-    const int st0 = (int)((long)ks * nst_all / ksplit);
-    const int nstage = (int)((long)(ks + 1) * nst_all / ksplit) - st0;  // this workgroup's stages: st0 .. st0+nstage-1
-    {
-        const size_t skip = (size_t)st0 * KSTAGE * 64;
-        wsrc[0] += skip; wsrc[1] += skip;
-#pragma unroll
-        for (int x = 0; x < XW; ++x) hsrc[x] += skip;
-    }
+    const u32x4* hsrc = Xhi + (size_t)min(tm * TMB + wave, MT32 - 1) * KB * 64 + lane;
+    const int nstage = KB;  // (even: K is a multiple of 32)
     auto issue = [&](int st) {
         u32x4 (*slot)[64] = ring[st % NSTG];
-#pragma unroll
-        for (int j = 0; j < KSTAGE; ++j) {
-            const size_t off = ((size_t)st * KSTAGE + j) * 64;
-            load_block_to_lds(wsrc[0] + off, &slot[(wave * 2 + 0) * KSTAGE + j][0]);
-            load_block_to_lds(wsrc[1] + off, &slot[(wave * 2 + 1) * KSTAGE + j][0]);
-#pragma unroll
-            for (int x = 0; x < XW; ++x) load_block_to_lds(hsrc[x] + off, &slot[(TNB + wave * XW + x) * KSTAGE + j][0]);
-        }
+        const size_t off = (size_t)st * 64;
+        load_block_to_lds(wsrc[0] + off, &slot[wave * 2 + 0][0]);
+        load_block_to_lds(wsrc[1] + off, &slot[wave * 2 + 1][0]);
+        load_block_to_lds(hsrc + off, &slot[TNB + wave][0]);
     };
-    constexpr int kLoadsPerStage = (2 + XW) * KSTAGE;  // per wavefront
-    // operand registers of one k-block: 4 weight blocks, MW activation tiles
-    struct Ops { u32x4 a[4], b[MW]; };
-    auto read_ops = [&](Ops& o, int st, int j) {
+    constexpr int kLoadsPerStage = 3;  // per wavefront
+    // operand registers of one k-block: 4 weight blocks, 2 activation tiles
+    struct Ops { u32x4 a[4], b[2]; };
+    auto read_ops = [&](Ops& o, int st) {
         u32x4 (*slot)[64] = ring[st % NSTG];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) o.a[i] = slot[(wn * 4 + i) * KSTAGE + j][lane];
+        for (int i = 0; i < 4; ++i) o.a[i] = slot[wn * 4 + i][lane];
 #pragma unroll
-        for (int i = 0; i < MW; ++i) o.b[i] = slot[(TNB + wm * MW + i) * KSTAGE + j][lane];
+        for (int i = 0; i < 2; ++i) o.b[i] = slot[TNB + wm * 2 + i][lane];
     };
     auto mma_ops = [&](const Ops& o) {
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
 #pragma unroll
-            for (int jj = 0; jj < MW; ++jj) acc[i][jj] = mfma_f16(o.a[i], o.b[jj], acc[i][jj]);
+            for (int jj = 0; jj < 2; ++jj) acc[i][jj] = mfma_f16(o.a[i], o.b[jj], acc[i][jj]);
         }
-    };
-    // Stage st is usable once this wavefront's own loads of it have landed (at most the loads of the
-    // stages issued after it may still be outstanding) and every other wavefront says the same.
-    auto stage_ready = [&](int st, int last_issued) {
-        const int later = min(last_issued, nstage - 1) - st;  // 0 .. NSTG-2
-        if (later >= 4) wait_vmcnt<4 * kLoadsPerStage>();
-        else if (later == 3) wait_vmcnt<3 * kLoadsPerStage>();
-        else if (later == 2) wait_vmcnt<2 * kLoadsPerStage>();
-        else if (later == 1) wait_vmcnt<kLoadsPerStage>();
-        else wait_vmcnt<0>();
-        __syncthreads();
     };
 #pragma unroll
     for (int st = 0; st < NSTG - 1; ++st)
         if (st < nstage) issue(st);
-    // Two operand register sets, used in turn.  No set is ever copied into the other: a copy would
-    // have to wait for the LDS reads it copies, in the middle of the MFMAs.  A stage's slot is
-    // refilled behind the barrier that every wavefront passes only after its MFMAs of that stage.
+    // Two operand register sets, used in turn: even stages from A, odd ones from B.  No set is ever copied into the
+    // other: a copy would have to wait for the LDS reads it copies, in the middle of the MFMAs.  A stage's slot is
+    // refilled behind the barrier that every wavefront passes only after its MFMAs of that stage.  In the steady
+    // state a stage is opened while the NSTG-3 stages issued after it are still in flight, and the slot just finished
+    // with is refilled.
     Ops opa, opb;
-    if constexpr (KSTAGE == 2) {
-        // first k-block of a stage from A while B loads, second from B while A loads from the next
-        // stage; the barrier that opens stage s+1 sits before the last k-block of stage s
-        stage_ready(0, NSTG - 2);
-        read_ops(opa, 0, 0);
-        for (int s = 0; s < nstage; ++s) {
-            read_ops(opb, s, KSTAGE - 1);
-            mma_ops(opa);
-            if (s + 1 < nstage) {
-                stage_ready(s + 1, s + NSTG - 2);
-                if (s + NSTG - 1 < nstage) issue(s + NSTG - 1);
-                read_ops(opa, s + 1, 0);
-            }
-            mma_ops(opb);
-        }
-    } else {
-        // One k-block per stage, an even number of stages (the launcher sees to that): even stages
-        // from A, odd ones from B.  In the steady state a stage is opened while the NSTG-3 stages
-        // issued after it are still in flight, and the slot just finished with is refilled.
-        constexpr int kAhead = (NSTG - 3) * kLoadsPerStage;
-        int s = 0;
-        if (nstage > NSTG) {  // then the prologue has issued NSTG-1 stages
-            wait_vmcnt<(NSTG - 2) * kLoadsPerStage>();
+    constexpr int kAhead = (NSTG - 3) * kLoadsPerStage;
+    int s = 0;
+    if (nstage > NSTG) {  // then the prologue has issued NSTG-1 stages
+        wait_vmcnt<(NSTG - 2) * kLoadsPerStage>();
+        __syncthreads();
+        read_ops(opa, 0);
+        for (; s + NSTG < nstage; s += 2) {
+            wait_vmcnt<kAhead>();
             __syncthreads();
-            read_ops(opa, 0, 0);
-            for (; s + NSTG < nstage; s += 2) {
-                wait_vmcnt<kAhead>();
-                __syncthreads();
-                issue(s + NSTG - 1);
-                read_ops(opb, s + 1, 0);
-                mma_ops(opa);
-                wait_vmcnt<kAhead>();
-                __syncthreads();
-                issue(s + NSTG);
-                read_ops(opa, s + 2, 0);
-                mma_ops(opb);
-            }
-        }
-        // the last stages: issue the one that may still be missing (into the slot of stage s-1, which
-        // every wavefront has left once it is past the barrier), then one wait covers them all
-        __syncthreads();
-        if (s + NSTG - 1 < nstage) issue(s + NSTG - 1);
-        wait_vmcnt<0>();
-        __syncthreads();
-        if (s == 0) read_ops(opa, 0, 0);
-        for (; s < nstage; s += 2) {
-            read_ops(opb, s + 1, 0);
+            issue(s + NSTG - 1);
+            read_ops(opb, s + 1);
             mma_ops(opa);
-            if (s + 2 < nstage) read_ops(opa, s + 2, 0);
+            wait_vmcnt<kAhead>();
+            __syncthreads();
+            issue(s + NSTG);
+            read_ops(opa, s + 2);
             mma_ops(opb);
         }
     }
-    score_tile<4, MW>(p, acc, tm * TMR + wm * 32 * MW, tn * TN + wn * 128, tn * 2 + wn, lane);
+    // the last stages: issue the one that may still be missing (into the slot of stage s-1, which
+    // every wavefront has left once it is past the barrier), then one wait covers them all
+    __syncthreads();
+    if (s + NSTG - 1 < nstage) issue(s + NSTG - 1);
+    wait_vmcnt<0>();
+    __syncthreads();
+    if (s == 0) read_ops(opa, 0);
+    for (; s < nstage; s += 2) {
+        read_ops(opb, s + 1);
+        mma_ops(opa);
+        if (s + 2 < nstage) read_ops(opa, s + 2);
+        mma_ops(opb);
+    }
+    score_tile<4, 2>(p, acc, (tm * TMB + wm * 2) * 32, tn * TN + wn * 128, tn * 2 + wn, lane);
 }
 
 // ----------------------------------------------------------------- 256 x 256 tiles (prompt and scoring passes)
 //
-// With one half term per activation the 256 x 128 tile above no longer keeps the matrix cores busy: it pulls
+// With one half term per activation a 256 x 128 tile no longer keeps the matrix cores busy: it pulls
 // 12 KiB of operands out of L2 for every 32 matrix instructions, and at eight rounds of 512 tiles on 256 CUs that
 // is 10 TB/s -- what the L2s deliver.  This kernel takes 16 KiB for 64: a 256 x 256 tile per workgroup, four
 // wavefronts with a 128 x 128 sub-tile each (16 accumulator tiles: the whole accumulator file, so one workgroup
@@ -808,11 +729,11 @@ __global__ __launch_bounds__(256) void score_reduce_kernel(const float2* __restr
 }
 
 
-// Many rows (a prompt or scoring pass): 256 x 256 tiles, one workgroup per CU, once there are enough of them to
-// give every CU one.
-constexpr int kMaxTiledKSplit = 16;
+constexpr int kMaxTiledKSplit = 16;  // k ranges a tile of a few-row GEMM is cut into at most
 static int g_tiled_cus_override = 0;  // a planner query's CU count
 static int tiled_cus() { return g_tiled_cus_override > 0 ? g_tiled_cus_override : num_cus(); }
+// Many rows (a prompt or scoring pass): 256 x 256 tiles, one workgroup per CU, once there are enough of them to
+// give every CU one.
 static bool use_big_tile(int M, int N) {
     return M >= 1024 && (long)((N + TN - 1) / TN) * ((M + 255) / 256) >= tiled_cus();
 }
@@ -1011,8 +932,7 @@ void bf16_score_head(hipStream_t s, const void* Wp, const void* Xhi, int M, int 
     const int NT32 = (V + 31) / 32, MT32 = (M + 31) / 32, KB = K / 16;
     const int tiles_n = (V + TN - 1) / TN, tiles_m = (M + 127) / 128, tiles = tiles_n * tiles_m;
     if (tiles >= 2 * num_cus())  // two workgroups per CU
-        gemm_tiled_kernel<MODE_SCORE, 1, 2><<<(tiles + 7) / 8 * 8, 256, 0, s>>>((const u32x4*)Wp, (const u32x4*)Xhi, KB, NT32, MT32,
-                                                                               tiles_n, tiles_m, 1, p);
+        gemm_score_kernel<<<(tiles + 7) / 8 * 8, 256, 0, s>>>((const u32x4*)Wp, (const u32x4*)Xhi, KB, NT32, MT32, tiles_n, tiles_m, p);
     else
         launch_tiled<MODE_SCORE>(s, Wp, Xhi, KB, V, M, p, M <= 64 ? 1 : 2, 1, 0);
     score_reduce_kernel<<<(M + 3) / 4, 256, 0, s>>>((const float2*)stats, tgt, p.sc_parts, M, S, out);
