@@ -163,7 +163,10 @@ he_status he_refresh_weights(he_engine* e);
  * Fills the KV cache for positions 0..S-1 and samples generation step 0 from
  * the last position's logits z:  d_next_ids [B] int32, d_logprobs [B] float
  * = log_softmax(z)[id] (untempered).  d_logits_opt, if not NULL, receives z
- * as [B, V] float. */
+ * as [B, V] float.  The pass puts the engine's device-side position and step
+ * number at the start itself: captured into a HIP graph (alone or with decode
+ * steps behind it) it can be replayed any number of times, he_prefill_ragged
+ * likewise; the host-side checks see the capture only. */
 he_status he_prefill(he_engine* e, const int32_t* d_prompt_ids, int B, int S, const he_sampling* sampling,
                      int32_t* d_next_ids, float* d_logprobs, float* d_logits_opt);
 

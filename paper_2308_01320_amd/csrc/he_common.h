@@ -46,10 +46,14 @@ __device__ __forceinline__ int row_seq(const he_dev_state* st, int m, int S) {
     return st->ragged ? st->seq[4 * st->max_batch + m] : m;
 }
 
-// Sampling parameters that come with a step: stored by its first kernel, which does not read them.
-struct he_step_sampling { int set, mode; float temperature; uint32_t seed_lo, seed_hi; };
+// Sampling parameters that come with a step: stored by its first kernel, which does not read them.  start: the step is a
+// prompt pass over sequences of one length, which begins at position 0 and generation step 0 whatever the state holds (a
+// captured pass is replayed with the state its last replay left); its first kernel stores that as well and, because its other
+// workgroups may look before or after, reads nothing of the state.  (Ragged passes: set_ragged_kernel.)
+struct he_step_sampling { int set, mode; float temperature; uint32_t seed_lo, seed_hi; int start; };
 __device__ __forceinline__ void store_sampling(he_dev_state* st, const he_step_sampling& sp) {
     if (sp.set) { st->mode = sp.mode; st->temperature = sp.temperature; st->seed_lo = sp.seed_lo; st->seed_hi = sp.seed_hi; }
+    if (sp.start) { st->cur_len = 0; st->step = 0; st->ragged = 0; }
 }
 
 // End of a pass that fed `tokens` rows per sequence (padding included) and sampled `steps` tokens; by a whole workgroup.

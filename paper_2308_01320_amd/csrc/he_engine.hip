@@ -188,13 +188,13 @@ he_status fail(he_engine* e, he_status code, const std::string& msg) {
     return code;
 }
 
-he_step_sampling step_sampling(const he_sampling& sp) {
-    return {1, sp.mode, sp.temperature, (uint32_t)(sp.seed & 0xFFFFFFFFu), (uint32_t)(sp.seed >> 32)};
+he_step_sampling step_sampling(const he_sampling& sp, bool start = false) {
+    return {1, sp.mode, sp.temperature, (uint32_t)(sp.seed & 0xFFFFFFFFu), (uint32_t)(sp.seed >> 32), start ? 1 : 0};
 }
 // what the next pass's first kernel is to store; handed out once
 he_step_sampling take_sampling(he_engine* e) {
     const he_step_sampling sp = e->next_sampling;
-    e->next_sampling.set = 0;
+    e->next_sampling.set = e->next_sampling.start = 0;
     return sp;
 }
 
@@ -973,7 +973,7 @@ static he_status prefill_impl(he_engine* e, const char* who, const int32_t* d_pr
     if (e->cur_len != 0) return fail(e, HE_ERR_STATE, w + ": cache is not empty (call he_reset)");
     e->batch = B;
     e->step = 0;
-    e->next_sampling = step_sampling(*sampling);  // (positions and step number are zero: the cache is empty since a reset)
+    e->next_sampling = step_sampling(*sampling, !ragged);  // (ragged: launch_set_ragged puts the state at the start)
     if (ragged) launch_set_ragged(e->stream, e->st, d_prompt_lens, B, S, -1, 0);
     return run_forward(e, d_prompt_ids, B, S, d_next_ids, d_logprobs, 1, 0, d_logits_opt);
 }

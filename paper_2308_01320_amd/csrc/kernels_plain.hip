@@ -48,11 +48,11 @@ __global__ __launch_bounds__(256) void embed_kernel(const int32_t* __restrict__ 
                                                     const ST* __restrict__ pos, float* __restrict__ x, he_dev_state* __restrict__ st,
                                                     int S, int H, int V, int pos_offset, he_step_sampling sp) {
     if (blockIdx.x == 0 && threadIdx.x == 0) store_sampling(st, sp);
-    const int m = blockIdx.x, b = row_seq(st, m, S), t = m % S - row_pad(st, b);
+    const int m = blockIdx.x, b = sp.start ? m / S : row_seq(st, m, S), t = m % S - (sp.start ? 0 : row_pad(st, b));
     const bool token = t >= 0;  // else a padding row: zeros, nothing downstream uses it
     int id = ids[(size_t)b * id_stride + (m % S)];
     id = id < 0 ? 0 : (id >= V ? V - 1 : id);  // out-of-range ids are clamped, never read out of bounds
-    const size_t p = token ? (size_t)(seq_len(st, b) + t + pos_offset) : 0;
+    const size_t p = token ? (size_t)((sp.start ? 0 : seq_len(st, b)) + t + pos_offset) : 0;
     if (VEC) {
         for (int i = threadIdx.x * 4; i < H; i += blockDim.x * 4) {
             f32x4 v = {0.f, 0.f, 0.f, 0.f};
@@ -387,7 +387,10 @@ __global__ void set_ragged_kernel(he_dev_state* st, const int32_t* __restrict__ 
         st->seq[3 * mb + b] = 0;
         st->seq[4 * mb + b] = b;
     }
-    if (threadIdx.x == 0) { st->ragged = 1; st->eos_id = eos_id; st->pad_id = pad_id; st->n_active = B; }
+    if (threadIdx.x == 0) {
+        st->cur_len = 0; st->step = 0;  // (a replay of a captured pass finds what the last one left)
+        st->ragged = 1; st->eos_id = eos_id; st->pad_id = pad_id; st->n_active = B;
+    }
 }
 
 __global__ void advance_state_kernel(he_dev_state* st, int tokens, int steps) { advance_state(st, tokens, steps); }
