@@ -343,9 +343,12 @@ typedef struct {
 he_status he_decode_scratch_account(const he_config* cfg, int B, int which, int cus, he_scratch_account* out);
 
 /* Test hook: waits for the engine's stream, then counts the engine's arrival counters that are not zero.  Every
- * k-split launch leaves its counters at zero for the next one (its last workgroup clears them), and he_reset
- * clears them all: between calls the answer is 0.  bf16, impl 0 only. */
+ * k-split launch leaves its counters at zero for the next one (its last workgroup clears them), the last kernel of a
+ * step does the same with the one that decides who advances the device state, and he_reset clears them all: between
+ * calls the answer is 0.  he_arrival_counters_set leaves `value` in all of them, as launches that failed half-way might:
+ * he_reset has to come before the next pass.  bf16, impl 0 only. */
 he_status he_arrival_counters_nonzero(he_engine* e, int* nonzero);
+he_status he_arrival_counters_set(he_engine* e, int value);
 
 /* Test hook, host logic only: how a GEMM of a prompt or scoring pass (M rows, [N, K] weights) is cut into tiles on
  * `cus` compute units (0 = the current device's count, 256 if there is none).  *tile_cols: columns of a tile (256 or

@@ -129,6 +129,8 @@ def lib() -> C.CDLL:
     L.he_decode_scratch_account.argtypes = [C.POINTER(he_config), C.c_int, C.c_int, C.c_int, C.POINTER(he_scratch_account)]
     L.he_arrival_counters_nonzero.restype = C.c_int
     L.he_arrival_counters_nonzero.argtypes = [vp, C.POINTER(C.c_int)]
+    L.he_arrival_counters_set.restype = C.c_int
+    L.he_arrival_counters_set.argtypes = [vp, C.c_int]
     L.he_last_step_rows.restype = C.c_int
     L.he_last_step_rows.argtypes = [vp]
     L.he_plan_prompt_gemm.restype = C.c_int
@@ -150,7 +152,7 @@ EXPORTS = ("he_workspace_bytes", "he_create", "he_refresh_weights", "he_prefill"
            "he_tile_matrix", "he_score", "he_prefill_ragged",
            "he_generate_ragged", "he_refresh_weights_lora", "he_release_arena", "he_acquire_arena",
            "he_tile_matrix_lora", "he_plan_decode_gemm", "he_fp8_quantize_rows", "he_decode_step_static",
-           "he_decode_scratch_account", "he_arrival_counters_nonzero", "he_last_step_rows",
+           "he_decode_scratch_account", "he_arrival_counters_nonzero", "he_arrival_counters_set", "he_last_step_rows",
            "he_plan_prompt_gemm")
 
 KERNEL_CLASSES = ("layernorm", "qkv", "attention", "out_proj", "fc1", "fc2", "lm_head", "empty")
@@ -329,6 +331,9 @@ class Engine:
         n = C.c_int()
         self._check(lib().he_arrival_counters_nonzero(self.handle, C.byref(n)))
         return n.value
+
+    def he_arrival_counters_set(self, value: int):
+        self._check(lib().he_arrival_counters_set(self.handle, value))
 
     def he_kernel_sweep(self, kernel_class: str, reps: int = 1):
         self._check(lib().he_kernel_sweep(self.handle, KERNEL_CLASSES.index(kernel_class), reps))

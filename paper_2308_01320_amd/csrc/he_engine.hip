@@ -951,8 +951,8 @@ he_status he_reset(he_engine* e) {
     if (!e) return HE_ERR_INVALID_ARG;
     e->cur_len = 0; e->step = 0; e->batch = 0;
     e->ragged_gen = false;
-    // (the arrival counters of the k-split GEMMs clear themselves; after a launch that failed half-way they may not
-    // have, so a reset clears them too)
+    // (the arrival counters of the k-split GEMMs and of the step's last kernel clear themselves; after a launch that failed
+    // half-way they may not have, so a reset clears them too)
     launch_reset_state(e->stream, e->st, e->ln_counters, e->ln_counters ? (int)(sizes_of(e->cfg).ln_counters / sizeof(int)) : 0);
     return check_hip(e, hipGetLastError(), "he_reset");
 }
@@ -1296,14 +1296,26 @@ he_status he_arrival_counters_nonzero(he_engine* e, int* nonzero) {
     if (!e || !nonzero) return HE_ERR_INVALID_ARG;
     if (!e->fast || !e->ln_counters) return fail(e, HE_ERR_STATE, "he_arrival_counters_nonzero: bf16 path only");
     const size_t n = sizes_of(e->cfg).ln_counters / sizeof(int);
-    std::vector<int> host(n);
+    std::vector<int> host(n + 1);
     hipError_t r = hipStreamSynchronize(e->stream);
     if (r == hipSuccess) r = hipMemcpy(host.data(), e->ln_counters, n * sizeof(int), hipMemcpyDeviceToHost);
+    if (r == hipSuccess) r = hipMemcpy(&host[n], &e->st->arrivals, sizeof(int), hipMemcpyDeviceToHost);
     if (r != hipSuccess) return check_hip(e, r, "he_arrival_counters_nonzero");
     int c = 0;
     for (int v : host) c += v != 0;
     *nonzero = c;
     return HE_OK;
+}
+
+he_status he_arrival_counters_set(he_engine* e, int value) {
+    if (!e) return HE_ERR_INVALID_ARG;
+    if (!e->fast || !e->ln_counters) return fail(e, HE_ERR_STATE, "he_arrival_counters_set: bf16 path only");
+    const size_t n = sizes_of(e->cfg).ln_counters / sizeof(int);
+    const std::vector<int> host(n + 1, value);
+    hipError_t r = hipStreamSynchronize(e->stream);
+    if (r == hipSuccess) r = hipMemcpy(e->ln_counters, host.data(), n * sizeof(int), hipMemcpyHostToDevice);
+    if (r == hipSuccess) r = hipMemcpy(&e->st->arrivals, &host[n], sizeof(int), hipMemcpyHostToDevice);
+    return check_hip(e, r, "he_arrival_counters_set");
 }
 
 he_status he_kernel_sweep(he_engine* e, int kernel_class, int reps) {

@@ -355,11 +355,12 @@ __global__ void sample_kernel(const float* __restrict__ logits, int V, he_dev_st
     if (advance) advance_state_by_last(st, advance, 1);
 }
 
-// Empty cache, greedy sampling; the arrival counters of the k-split GEMMs (null: none) cleared with it.
+// Empty cache, greedy sampling; the arrival counters of the k-split GEMMs (null: none) and of the step's last kernel cleared
+// with it.
 __global__ __launch_bounds__(256) void reset_state_kernel(he_dev_state* st, int* __restrict__ counters, int n_counters) {
     const int i = blockIdx.x * 256 + threadIdx.x;
     if (i == 0) {
-        st->cur_len = 0; st->step = 0; st->ragged = 0;
+        st->cur_len = 0; st->step = 0; st->ragged = 0; st->arrivals = 0;
         st->mode = 0; st->temperature = 1.f; st->seed_lo = st->seed_hi = 0u;
     }
     if (i < n_counters) counters[i] = 0;

@@ -219,6 +219,27 @@ def test_generate_graph_replay_matches_step_by_step():
         e.he_destroy()
 
 
+def test_reset_clears_every_arrival_counter():
+    """Counters that a failed launch left behind -- of the k-split hand-off and of the kernel that ends a step -- are gone
+    after he_reset, and the next generation is the one of an untouched engine."""
+    import torch
+    d = synth.ModelDims("x", 2, 1024, 8, 4096, 1000, 64, 5, 9, 6, "bf16", "gumbel")
+    eng = util.make_engine(d, synth.make_weights(d, seed=5))
+    p = torch.from_numpy(synth.make_prompts(d, seed=6)).cuda()
+    s = binding.sampling("gumbel", 1.0, 11)
+    ids0, lp0 = eng.he_generate(p, d.gen_len, s)
+    assert eng.he_arrival_counters_nonzero() == 0
+    eng.he_arrival_counters_set(0x5A5A)
+    assert eng.he_arrival_counters_nonzero() > 1
+    eng.he_reset()
+    assert eng.he_arrival_counters_nonzero() == 0
+    ids1, lp1 = eng.he_generate(p, d.gen_len, s)
+    torch.cuda.synchronize()
+    assert torch.equal(ids0, ids1) and torch.equal(lp0, lp1)
+    assert eng.he_arrival_counters_nonzero() == 0
+    eng.he_destroy()
+
+
 def test_timing_hook_counts_launches():
     import torch
     d = synth.ModelDims("x", 3, 256, 4, 512, 1000, 128, 4, 6, 4, "bf16", "greedy")
