@@ -439,12 +439,11 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_skinny_kernel(const u32x4* __
         mx = fmaxf(mx, __shfl_xor(mx, 32));
         take_better(__shfl_xor(best, 32), __shfl_xor(besti, 32), __shfl_xor(bestz, 32));
         float sum = 0.f;
-        if (mx > -INFINITY) {
+        const float base = mx > -INFINITY ? mx : 0.f;  // (nothing above -inf: ids past the vocabulary add 0, a NaN stays one)
 #pragma unroll
-            for (int i = 0; i < ITEMS; ++i)
+        for (int i = 0; i < ITEMS; ++i)
 #pragma unroll
-                for (int r = 0; r < 4; ++r) sum += expf(v[i][r] - mx);
-        }
+            for (int r = 0; r < 4; ++r) sum += expf(v[i][r] - base);
         sum += __shfl_xor(sum, 32);
         if (lane < 32) { part[wave][lane] = make_float4(mx, sum, best, bestz); part_idx[wave][lane] = besti; }
         __syncthreads();
@@ -455,7 +454,7 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_skinny_kernel(const u32x4* __
             sum = 0.f;
 #pragma unroll
             for (int x = 0; x < WAVES; ++x) {
-                if (e[x].x > -INFINITY) sum += e[x].y * expf(e[x].x - mx);
+                sum += e[x].x > -INFINITY ? e[x].y * expf(e[x].x - mx) : e[x].y;
                 take_better(e[x].z, part_idx[x][lane], e[x].w);
             }
             reinterpret_cast<float4*>(p.stats)[(size_t)m * p.n_tiles + grp] = make_float4(mx, sum, best, bestz);

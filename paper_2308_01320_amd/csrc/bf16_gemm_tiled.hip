@@ -89,11 +89,12 @@ __device__ __forceinline__ void lm_head_tile(const Epi& p, const f32x16 (&acc)[4
             // instruction cache (written out 64 times over it is not)
             float best = -INFINITY, bestz = 0.f, sum = 0.f;
             int besti = 0x7FFFFFFF;
+            const float base = mx > -INFINITY ? mx : 0.f;  // (nothing above -inf: ids past the vocabulary add 0, a NaN stays one)
 #pragma unroll 4
             for (int x = 0; x < 64; ++x) {
                 const float v = zl[x * 64 + lane];
                 const int n = n0 + (x >> 4) * 32 + 8 * ((x >> 2) & 3) + 4 * hh + (x & 3);
-                if (mx > -INFINITY) sum += expf(v - mx);
+                sum += expf(v - base);
                 float s = v;
                 if (mode == 1) s = v / temp + gumbel_from_word(philox_word0((uint32_t)n, (uint32_t)step, seq, k0, k1));
                 if (n < p.N && s > best) { best = s; besti = n; bestz = v; }  // ascending ids: strict > keeps the lowest

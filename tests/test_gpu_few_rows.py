@@ -82,6 +82,25 @@ def test_lm_head_sampled_rows_and_vocabularies(B, V, H):
     util.compare(got, want, BF16_TOL, MARGIN)
 
 
+@pytest.mark.parametrize("B", [4, 40, 70])
+def test_lm_head_nan_slice_reaches_the_logprob(B):
+    """A stretch of the vocabulary whose logits are all NaN: the soft-max over the whole vocabulary is NaN, the chosen token
+    the best of the others."""
+    import torch
+    d = synth.ModelDims("x", 1, 128, 2, 256, 2000, 64, B, 3, 2, "bf16", "greedy")
+    w = binding.upload_weights(synth.make_weights(d, seed=5, tied=False), "bf16")
+    w["lm_head"][512:1024] = float("nan")
+    eng = binding.Engine(binding.make_config(d), w)
+    p = torch.from_numpy(synth.make_prompts(d, seed=6)).cuda()
+    s = binding.sampling("greedy")
+    for ids, lp, lg in (eng.he_prefill(p, s, True), eng.he_decode_step(p[:, 0].contiguous(), s, True)):
+        torch.cuda.synchronize()
+        assert torch.isnan(lg[:, 512:1024]).all() and torch.isfinite(lg[:, :512]).all() and torch.isfinite(lg[:, 1024:]).all()
+        assert torch.isnan(lp).all()
+        assert torch.equal(ids.long(), torch.nan_to_num(lg, nan=-1e30).argmax(1))
+    eng.he_destroy()
+
+
 @pytest.mark.parametrize("B,S,H,nh", [(1, 32, 128, 2), (3, 129, 192, 3), (2, 257, 256, 2), (5, 400, 640, 5)])
 def test_prompt_attention_blocks_and_pairs(B, S, H, nh):
     """Query blocks of 128 with remainders, (sequence, head) pairs that do not divide over the eight XCDs, both head dimensions,
