@@ -82,6 +82,25 @@ def test_lm_head_sampled_rows_and_vocabularies(B, V, H):
     util.compare(got, want, BF16_TOL, MARGIN)
 
 
+def test_prompt_attention_large_queries():
+    """A query component near the end of the half range (49152, against a key component of 2^-13): the two half terms of the
+    prompt attention hold it."""
+    d = synth.ModelDims("x", 2, 128, 2, 256, 300, 64, 2, 40, 1, "bf16", "greedy")
+    w = synth.make_weights(d, seed=5)
+    lw = w["layers"][0]
+    for h in range(2):
+        q, k = 64 * h, 128 + 64 * h
+        lw["wqkv"][k] = 0.0
+        lw["bqkv"][k] = 2.0 ** -13
+        lw["bqkv"][q] = 8 * 49152.0
+    prompts = synth.make_prompts(d, seed=6)
+    want = util.oracle_run(d, util.weights_f64(w), prompts, 1, "greedy", 1.0, seed=3)
+    eng = util.make_engine(d, w)
+    got = util.engine_teacher_forced(eng, prompts, want["ids"], 1, binding.sampling("greedy", 1.0, 3))
+    eng.he_destroy()
+    util.compare(got, want, BF16_TOL, MARGIN)
+
+
 @pytest.mark.parametrize("B", [4, 40, 70])
 def test_lm_head_nan_slice_reaches_the_logprob(B):
     """A stretch of the vocabulary whose logits are all NaN: the soft-max over the whole vocabulary is NaN, the chosen token
