@@ -358,6 +358,18 @@ he_status he_arrival_counters_set(he_engine* e, int value);
 he_status he_plan_prompt_gemm(int M, int N, int K, int may_cut, size_t scratch_floats, int cus, int* tile_cols,
                               int* ksplit, int* split_col);
 
+/* Test hook, host logic only: how the launchers cut a GEMM of a pass of `rows` rows -- a prompt pass, a decode step on the
+ * prompt pass's tiles (more than 64 sequences), with `scoring` a scoring pass -- in an engine created with cfg: which = 0 QKV,
+ * 1 out-projection, 2 FC1, 3 FC2, 4 the LM head of a decode step of `rows` sequences (32 x 32: streamed once per 32 rows)
+ * or, with `scoring`, the scoring head.  The tiles of columns >= split_col come in ksplit k ranges; scratch_floats: what the launch
+ * indexes of the scratch for partial sums, scratch_reserved: what he_create reserves.  cus as in he_plan_prompt_gemm.
+ * bf16, impl 0 only. */
+typedef struct {
+    int tile_rows, tile_cols, ksplit, split_col;
+    size_t scratch_floats, scratch_reserved;
+} he_pass_plan;
+he_status he_plan_pass_gemm(const he_config* cfg, int rows, int which, int scoring, int cus, he_pass_plan* out);
+
 /* Measurement hook: a plain copy kernel (reads `bytes`, writes `bytes`, a multiple of 16,
  * device pointers, on `stream`).  Hardware byte counters (rocprofv3 FETCH_SIZE /
  * WRITE_SIZE) are scaled by what they read for this kernel of known size. */

@@ -57,6 +57,11 @@ class he_sampling(C.Structure):
     _fields_ = [("mode", C.c_int), ("temperature", C.c_float), ("seed", C.c_uint64)]
 
 
+class he_pass_plan(C.Structure):
+    _fields_ = [("tile_rows", C.c_int), ("tile_cols", C.c_int), ("ksplit", C.c_int), ("split_col", C.c_int),
+                ("scratch_floats", C.c_size_t), ("scratch_reserved", C.c_size_t)]
+
+
 class HeError(RuntimeError):
     def __init__(self, status: int, text: str):
         super().__init__(f"{STATUS_NAMES.get(status, status)}: {text}")
@@ -126,6 +131,8 @@ def lib() -> C.CDLL:
     L.he_plan_decode_gemm.argtypes = [C.c_int, C.c_int, C.c_int, C.c_int, C.c_size_t, C.c_int, C.POINTER(C.c_int),
                                       C.POINTER(C.c_int), C.POINTER(C.c_int)]
     L.he_decode_scratch_account.restype = C.c_int
+    L.he_plan_pass_gemm.restype = C.c_int
+    L.he_plan_pass_gemm.argtypes = [C.POINTER(he_config), C.c_int, C.c_int, C.c_int, C.c_int, C.POINTER(he_pass_plan)]
     L.he_decode_scratch_account.argtypes = [C.POINTER(he_config), C.c_int, C.c_int, C.c_int, C.POINTER(he_scratch_account)]
     L.he_arrival_counters_nonzero.restype = C.c_int
     L.he_arrival_counters_nonzero.argtypes = [vp, C.POINTER(C.c_int)]
@@ -153,7 +160,7 @@ EXPORTS = ("he_workspace_bytes", "he_create", "he_refresh_weights", "he_prefill"
            "he_generate_ragged", "he_refresh_weights_lora", "he_release_arena", "he_acquire_arena",
            "he_tile_matrix_lora", "he_plan_decode_gemm", "he_fp8_quantize_rows", "he_decode_step_static",
            "he_decode_scratch_account", "he_arrival_counters_nonzero", "he_arrival_counters_set", "he_last_step_rows",
-           "he_plan_prompt_gemm")
+           "he_plan_prompt_gemm", "he_plan_pass_gemm")
 
 KERNEL_CLASSES = ("layernorm", "qkv", "attention", "out_proj", "fc1", "fc2", "lm_head", "empty")
 
@@ -412,6 +419,18 @@ def he_plan_prompt_gemm(M, N, K, may_cut=False, scratch_floats=0, cus=256):
     if rc != HE_OK:
         raise HeError(rc, "he_plan_prompt_gemm")
     return t.value, k.value, c.value
+
+
+PASS_GEMMS = ("qkv", "out_proj", "fc1", "fc2", "lm_head")
+
+
+def he_plan_pass_gemm(cfg: he_config, rows: int, which: str, scoring=False, cus: int = 256) -> he_pass_plan:
+    """How a GEMM of a pass of `rows` rows is cut in an engine of this configuration; host logic only."""
+    out = he_pass_plan()
+    rc = lib().he_plan_pass_gemm(C.byref(cfg), rows, PASS_GEMMS.index(which), 1 if scoring else 0, cus, C.byref(out))
+    if rc != HE_OK:
+        raise HeError(rc, "he_plan_pass_gemm")
+    return out
 
 
 def he_decode_scratch_account(cfg: he_config, B: int, which: int, cus: int = 256) -> he_scratch_account:

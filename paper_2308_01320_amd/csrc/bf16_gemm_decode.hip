@@ -241,8 +241,18 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_skinny_kernel(const u32x4* __
     __shared__ float red[WAVES][NT][16][64];
     __shared__ float lnp[WAVES * 4 * 32];  // folded LayerNorm: the wavefronts' partial sums of the row statistics
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int mt = blockIdx.y;
-    const int grp = blockIdx.x / ksplit, ks = blockIdx.x % ksplit;
+    int bx = blockIdx.x, mt = blockIdx.y;
+    if (MODE == MODE_LMHEAD && gridDim.y > 1) {
+        // Several 32-row slices each stream the whole matrix.  Workgroups go round the XCDs by index: the slices
+        // of one group of tiles are placed on ONE XCD, next to each other in dispatch order, so that they run
+        // side by side and all but the first of them find the weights in that XCD's L2 (the grid's x is padded
+        // to a multiple of eight for this).
+        const int lid = blockIdx.y * gridDim.x + blockIdx.x, span = 8 * gridDim.y;
+        bx = (lid / span) * 8 + (lid % span) % 8;
+        mt = (lid % span) / 8;
+        if (bx >= (n_tiles + NT - 1) / NT) return;  // the whole workgroup
+    }
+    const int grp = bx / ksplit, ks = bx % ksplit;
     const int parts = ksplit * WAVES, part = ks * WAVES + wave;
     const int kb0 = (int)(((long)part * KB) / parts), kb1 = (int)(((long)(part + 1) * KB) / parts);
     constexpr bool FOLDABLE = MODE == MODE_BIAS_RELU || MODE == MODE_QKV || MODE == MODE_LMHEAD;
@@ -833,6 +843,7 @@ void launch_skinny_nt(hipStream_t s, const void* Wp, const void* Xhi, int KB, in
                       int m_tiles, int ksplit, const Epi& p) {
     constexpr int U = HE_SKINNY_U(NT);
     dim3 grid(((n_tiles + NT - 1) / NT) * ksplit, m_tiles);
+    if (MODE == MODE_LMHEAD && m_tiles > 1) grid.x = (grid.x + 7) / 8 * 8;  // see the kernel: slices of a tile group share an XCD
     // What bounds a wavefront is its serial chain of load rounds (K/16 blocks / wavefronts / U
     // rounds, about 1.7 us each under load): eight wavefronts halve the chain when K leaves each
     // of them two rounds (and their accumulators still fit in LDS for the final reduction).
@@ -1186,22 +1197,40 @@ void bf16_gemm_skinny(hipStream_t s, int mode, const void* Wp, const void* Xhi, 
     }
 }
 
-// (up to 32 rows: one per workgroup of at least one 32-wide tile; more: one per wavefront of a 256-wide tile)
+// Tiles per workgroup of the streamed LM head.  All slices of a group of tiles run on one XCD, so a launch is one round where
+// every XCD's groups times slices fit its CUs (32 here; a launch that only fits the chip as a whole waited for the XCDs that got a
+// group more: 96 rows of 16000 x 5120 +31 us).
+static int lm_stream_nt(int tiles, int slices) {
+    if (slices == 1) return skinny_nt_fused(tiles, 1);
+    const int groups = 8 * std::max(1, plan_cus() / 8 / slices);
+    return (tiles + groups - 1) / groups;
+}
+
+// Whether the LM head of B rows streams the matrix once per 32 rows (gemm_skinny_kernel; slices after the first find it in L2)
+// or takes all rows in 256-wide tiles (gemm_ring_kernel).  A small vocabulary gives the tiles a few workgroups only, each
+// walking the whole of K (2000 ids: eight of 256 CUs); the line is where the 32-wide tiles of all slices no longer fit one
+// round of at most eight per workgroup.  Measured a decode step, streamed / tiled, us, sampled where not said otherwise:
+// K 1024, 64 rows: 2000 ids 50 / 75, 27000 65 / 79 (greedy 62 / 68); 192 rows, greedy: 6000 93 / 100.  K 5120, 64 rows: 12000
+// 156 / 183, 20000 173 / 185 (greedy 173 / 175), 27000 192 / 211, beyond the line 50272 269 / 237; 96 rows: 20000 230 / 249; 160:
+// 12000 257 / 270; 250: 6000 272 / 304.
+bool bf16_lm_head_streams(int B, int V) { return B <= 32 || lm_stream_nt((V + 31) / 32, (B + 31) / 32) <= 8; }
+
+// (streamed: one per workgroup of at least one 32-wide tile; tiled: one per wavefront of a 256-wide tile)
 int bf16_lm_parts_max(int V) { return std::max((V + 31) / 32, 2 * ((V + 255) / 256)); }
 
 void bf16_lm_head(hipStream_t s, const void* Wp, const void* Xhi, int B, int V, int K,
                   he_dev_state* st, float* logits_opt, float* stats, int* stats_idx, int32_t* ids_out,
                   float* lp_out, int out_stride, int out_at_step, int32_t* cur_ids, bool advance, const bf16_gemm_args* fold) {
     int parts;  // soft-max partials per row
-    if (B > 32) {
+    if (!bf16_lm_head_streams(B, V)) {
         parts = bf16_lm_head_tiles(s, Wp, Xhi, B, V, K, fold, st, logits_opt, stats, stats_idx);
     } else {
         Epi p{};
         if (fold) p = make_epi(B, V, *fold);
-        const int tiles = (V + 31) / 32, nt = skinny_nt_fused(tiles, 1);
+        const int tiles = (V + 31) / 32, m_tiles = (B + 31) / 32, nt = lm_stream_nt(tiles, m_tiles);
         p.M = B; p.N = V; p.st = st; p.logits = logits_opt; p.stats = stats; p.stats_idx = stats_idx;
         p.n_tiles = parts = (tiles + nt - 1) / nt;  // one per workgroup
-        launch_skinny<MODE_LMHEAD>(s, Wp, Xhi, K / 16, tiles, 1, nt, 1, p);
+        launch_skinny<MODE_LMHEAD>(s, Wp, Xhi, K / 16, tiles, m_tiles, nt, 1, p);
     }
     lm_reduce_kernel<<<B, 256, 0, s>>>(stats, stats_idx, parts, st, ids_out, lp_out, out_stride, out_at_step,
                                        cur_ids, advance ? 1 : 0);

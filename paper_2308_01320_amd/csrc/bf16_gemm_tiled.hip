@@ -886,6 +886,41 @@ void bf16_tiled_plan_query(int M, int N, int K, int may_cut, size_t capacity_flo
     g_tiled_cus_override = 0;
 }
 
+// QKV and FC1, whose epilogue needs the whole sum: with k ranges finish_kernel applies it.
+static RingPlan fused_plan(int M, int N, int KB, size_t capacity_floats) {
+    if (use_big_tile(M, N)) return RingPlan{big_plan(M, N, KB, false).na, 1};
+    return ring_plan(M, N, KB, true, capacity_floats);
+}
+
+// The LM head's tiles (no scratch: whole k ranges; 192 rows at most to a tile)
+static RingPlan lm_head_plan(int M, int V, int K) { return ring_plan(M, V, K / 16, true, 0, 3); }
+
+// The scoring head: 0 for gemm_score_kernel (two workgroups per CU: from two rounds of its tiles on), else the ring kernel's tile
+static int score_tile(int M, int V) {
+    const long tiles = (long)((V + TN - 1) / TN) * ((M + 127) / 128);
+    return tiles >= 2 * tiled_cus() ? 0 : (M <= 64 ? 1 : 2);
+}
+
+void bf16_pass_plan_query(int use, int M, int N, int K, size_t capacity_floats, int cus, int* tile_rows, int* tile_cols, int* ks,
+                          int* split_col) {
+    g_tiled_cus_override = cus;
+    int tile = 0;
+    *ks = 1; *split_col = 0;
+    if (use == TILED_STORE || use == TILED_STORE_WHOLE) {
+        bf16_tiled_store_plan(M, N, K, capacity_floats, &tile, ks, split_col, use == TILED_STORE_WHOLE);
+    } else if (use == TILED_FUSED) {
+        const RingPlan g = fused_plan(M, N, K / 16, capacity_floats);
+        tile = g.mw; *ks = g.ks;
+    } else if (use == TILED_SCORE_HEAD) {
+        tile = score_tile(M, N);
+    } else {
+        tile = bf16_lm_head_streams(M, N) ? -1 : lm_head_plan(M, N, K).mw;
+    }
+    g_tiled_cus_override = 0;
+    *tile_rows = tile < 0 ? 32 : (tile == 0 ? 128 : (tile < 4 ? 64 * tile : 256));
+    *tile_cols = tile < 0 ? 32 : (tile == 5 ? 320 : 256);
+}
+
 void bf16_gemm_tiled_store(hipStream_t s, const void* Wp, const void* Xhi, int M, int N, int K, float* part, int tile, int ks,
                            int split_col) {
     bf16_gemm_args a;
@@ -896,9 +931,7 @@ void bf16_gemm_tiled_store(hipStream_t s, const void* Wp, const void* Xhi, int M
 void bf16_gemm_tiled(hipStream_t s, int mode, const void* Wp, const void* Xhi, int M, int N, int K, const bf16_gemm_args& a,
                      float* part, size_t part_floats) {
     const Epi p = make_epi(M, N, a);
-    RingPlan g{0, 1};
-    if (use_big_tile(M, N)) g.mw = big_plan(M, N, K / 16, false).na;
-    else g = ring_plan(M, N, K / 16, true, part_floats);
+    const RingPlan g = fused_plan(M, N, K / 16, part_floats);
     if (g.ks == 1) {  // the epilogue runs in the GEMM
         if (mode == EPI_BIAS_RELU) launch_tiled<MODE_BIAS_RELU>(s, Wp, Xhi, K / 16, N, M, p, g.mw, 1, 0);
         else launch_tiled<MODE_QKV>(s, Wp, Xhi, K / 16, N, M, p, g.mw, 1, 0);
@@ -910,17 +943,16 @@ void bf16_gemm_tiled(hipStream_t s, int mode, const void* Wp, const void* Xhi, i
     else finish_kernel<MODE_QKV><<<grid, 256, 0, s>>>(part, g.ks, (size_t)M * N, p);
 }
 
-// The LM head of a decode step of more than 32 rows: the matrix is streamed once for all of them (the weight-streaming
-// kernel takes 32 rows at a time and rereads it: 96 rows of 50272 x 5120 took 222 us, this 151, of which 23 are the noise).  Returns the soft-max
-// partials per row.
+// The LM head of a decode step of more than 32 rows and a large vocabulary (bf16_lm_head_streams): the matrix is read once for all
+// of them (the weight-streaming kernel takes 32 rows at a time and rereads it: 96 rows of 50272 x 5120 took 222 us, this 151, of
+// which 23 are the noise).  Returns the soft-max partials per row.
 int bf16_lm_head_tiles(hipStream_t s, const void* Wp, const void* X, int M, int V, int K, const bf16_gemm_args* fold, const he_dev_state* st,
                        float* logits_opt, float* stats, int* stats_idx) {
     Epi p{};
     if (fold) p = make_epi(M, V, *fold);
     p.M = M; p.N = V; p.st = st; p.logits = logits_opt; p.stats = stats; p.stats_idx = stats_idx;
     p.n_tiles = 2 * ((V + 255) / 256);
-    const RingPlan g = ring_plan(M, V, K / 16, true, 0, 3);  // no scratch: whole k ranges
-    launch_tiled<MODE_LMHEAD>(s, Wp, X, K / 16, V, M, p, g.mw, 1, 0);
+    launch_tiled<MODE_LMHEAD>(s, Wp, X, K / 16, V, M, p, lm_head_plan(M, V, K).mw, 1, 0);
     return p.n_tiles;
 }
 
@@ -931,11 +963,11 @@ void bf16_score_head(hipStream_t s, const void* Wp, const void* Xhi, int M, int 
     Epi p{};
     p.M = M; p.N = V; p.S = S; p.ids = ids; p.sc_stats = (float2*)stats; p.sc_tgt = tgt; p.sc_parts = bf16_score_parts(V);
     const int NT32 = (V + 31) / 32, MT32 = (M + 31) / 32, KB = K / 16;
-    const int tiles_n = (V + TN - 1) / TN, tiles_m = (M + 127) / 128, tiles = tiles_n * tiles_m;
-    if (tiles >= 2 * num_cus())  // two workgroups per CU
+    const int tiles_n = (V + TN - 1) / TN, tiles_m = (M + 127) / 128, tiles = tiles_n * tiles_m, tile = score_tile(M, V);
+    if (tile == 0)
         gemm_score_kernel<<<(tiles + 7) / 8 * 8, 256, 0, s>>>((const u32x4*)Wp, (const u32x4*)Xhi, KB, NT32, MT32, tiles_n, tiles_m, p);
     else
-        launch_tiled<MODE_SCORE>(s, Wp, Xhi, KB, V, M, p, M <= 64 ? 1 : 2, 1, 0);
+        launch_tiled<MODE_SCORE>(s, Wp, Xhi, KB, V, M, p, tile, 1, 0);
     score_reduce_kernel<<<(M + 3) / 4, 256, 0, s>>>((const float2*)stats, tgt, p.sc_parts, M, S, out);
 }
 

@@ -1273,6 +1273,21 @@ he_status he_plan_prompt_gemm(int M, int N, int K, int may_cut, size_t scratch_f
     return HE_OK;
 }
 
+he_status he_plan_pass_gemm(const he_config* cfg, int rows, int which, int scoring, int cus, he_pass_plan* out) {
+    if (!out || check_config(cfg) || check_shape(cfg) || !is_fast(*cfg)) return HE_ERR_INVALID_ARG;
+    if (rows < 1 || (long)rows > (long)cfg->max_batch * cfg->max_seq_len || which < 0 || which > 4 || cus < 0) return HE_ERR_INVALID_ARG;
+    const int H = cfg->hidden, F = cfg->ffn, N[5] = {3 * H, H, F, H, cfg->vocab}, K = which == 3 ? F : H;
+    const bool store = which == 1 || which == 3;
+    const size_t cap = sizes_of(*cfg).tiled_part / sizeof(float);
+    const int use = which == 4 ? (scoring ? TILED_SCORE_HEAD : TILED_LM_HEAD)
+                               : (store ? (scoring ? TILED_STORE_WHOLE : TILED_STORE) : TILED_FUSED);
+    bf16_pass_plan_query(use, rows, N[which], K, scoring && !store ? 0 : cap, cus, &out->tile_rows, &out->tile_cols, &out->ksplit,
+                         &out->split_col);
+    out->scratch_floats = store || out->ksplit > 1 ? (size_t)out->ksplit * rows * N[which] : 0;
+    out->scratch_reserved = cap;
+    return HE_OK;
+}
+
 he_status he_decode_scratch_account(const he_config* cfg, int B, int which, int cus, he_scratch_account* out) {
     if (!out || check_config(cfg) || check_shape(cfg) || !is_fast(*cfg)) return HE_ERR_INVALID_ARG;
     if (B < 1 || B > cfg->max_batch || B > 64 || (which != 0 && which != 1) || cus < 0) return HE_ERR_INVALID_ARG;

@@ -118,6 +118,11 @@ size_t bf16_tiled_scratch_floats(int rows, int widest);
 // The plan of a many-row GEMM for a planner query (cus: compute units to plan for, 0 = the current device's)
 void bf16_tiled_plan_query(int M, int N, int K, int may_cut, size_t capacity_floats, int cus, int* tile_cols, int* ks,
                            int* split_col);
+// What the launchers choose for any of these GEMMs (capacity_floats: the scratch they are given): *tile_rows x *tile_cols tiles
+// (32 x 32: the LM head streamed in slices of 32 rows)
+enum { TILED_STORE = 0, TILED_STORE_WHOLE = 1, TILED_FUSED = 2, TILED_LM_HEAD = 3, TILED_SCORE_HEAD = 4 };
+void bf16_pass_plan_query(int use, int M, int N, int K, size_t capacity_floats, int cus, int* tile_rows, int* tile_cols, int* ks,
+                          int* split_col);
 // ---- 8-bit weight storage: E4M3 codes with one power-of-two scale per row
 size_t fp8_units_bytes(int rows, int K);  // codes in the half-tile kernel's units: [rows/16][K/64][64 lanes][16 bytes]
 void fp8_row_exponents(hipStream_t s, const void* src, int R, int K, int* exps, float* scales);  // e[n], 2^e[n]
@@ -133,7 +138,9 @@ void bf16_lm_head(hipStream_t s, const void* Wp, const void* X, int B, int V, in
                   const bf16_gemm_args* fold = nullptr);
 // partials per row that any form of the LM head leaves, at most
 int bf16_lm_parts_max(int V);
-// ... of more than 32 rows (bf16_lm_head calls it): soft-max and arg-max partials into stats / stats_idx; returns how many per row
+// whether it streams the matrix in slices of 32 rows (host logic)
+bool bf16_lm_head_streams(int B, int V);
+// ... else (bf16_lm_head calls it): soft-max and arg-max partials into stats / stats_idx; returns how many per row
 int bf16_lm_head_tiles(hipStream_t s, const void* Wp, const void* X, int M, int V, int K, const bf16_gemm_args* fold, const he_dev_state* st,
                        float* logits_opt, float* stats, int* stats_idx);
 // LM head over all M = B*S positions fused with log-softmax and the gather of each position's next

@@ -143,6 +143,26 @@ def test_prompt_gemm_plans_fill_the_chip_in_whole_rounds():
         binding.he_plan_prompt_gemm(8192, 100, 64)
 
 
+def test_lm_head_of_a_small_vocabulary_is_streamed():
+    """Up to 32 rows the LM head always streams its matrix; more rows take 256-wide tiles only where the vocabulary makes
+    enough of them for the CUs -- 2000 ids are eight."""
+    import dataclasses
+    d = synth.CONFIGS["opt-13b"]
+
+    def tile(V, H, rows):
+        cfg = binding.make_config(dataclasses.replace(d, vocab=V, hidden=H, n_heads=H // 128), max_batch=256, max_seq_len=64)
+        a = binding.he_plan_pass_gemm(cfg, rows, "lm_head")
+        assert a.ksplit == 1 and a.scratch_floats == 0
+        return a.tile_rows, a.tile_cols
+
+    for H in (1024, 5120):
+        for rows in (1, 32):
+            assert tile(50272, H, rows) == (32, 32)
+        for rows in (33, 64, 100, 192):
+            assert tile(2000, H, rows) == tile(4000, H, rows) == (32, 32)
+            assert tile(50272, H, rows) == ({1: 64, 2: 128, 3: 192}[(rows + 63) // 64], 256)
+
+
 def test_ksplit_hand_off_stays_inside_what_he_create_reserves():
     """The invariant the k-split hand-off of the decode out-projection / FC2 rests on.  Partial sums cross
     workgroups inside one launch through scratch, every (column group, row slice, split) in words of its own, with

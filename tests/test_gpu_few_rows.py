@@ -1,6 +1,8 @@
 """GPU parity of the prompt and scoring passes of few rows (the deep-ring GEMM): row counts at the edges of its 64-, 128- and
 192-row tiles and of the 32-row blocks, column counts that end inside a 256-column tile, k ranges of different lengths, and
 wide decode steps, each against the oracle."""
+import functools
+
 import numpy as np
 import pytest
 
@@ -67,13 +69,22 @@ def test_decode_attention_wavefront_counts(B, S, max_seq, H, nh):
     util.compare(got, want, BF16_TOL, MARGIN)
 
 
-@pytest.mark.parametrize("B", [1, 17, 32, 33, 65, 100, 130])
-@pytest.mark.parametrize("V,H", [(31, 64), (257, 128), (2500, 512), (9000, 64)])
-def test_lm_head_sampled_rows_and_vocabularies(B, V, H):
-    """The sampler's noise formed between the load rounds (at most 32 rows) or behind the product (more), vocabularies that end
-    inside a 32-wide tile, and a k range too short for a load round."""
+@functools.lru_cache(maxsize=1)
+def _lm_weights(V, H):
+    return synth.make_weights(synth.ModelDims("x", 1, H, H // 64, 2 * H, V, 64, 1, 2, 3, "bf16", "gumbel"), seed=5)
+
+
+# The streamed form (slices of 32 rows, the noise formed between the load rounds): one slice or several, vocabularies that end
+# inside a 32-wide tile, a k range too short for a load round.  The tiled form (the noise behind the product): rows at the
+# edges of its 64-, 128- and 192-row tiles, a vocabulary that ends inside a 256-wide tile.
+@pytest.mark.parametrize("V,H,B,tile", [(V, H, B, 32) for V, H in ((31, 64), (257, 128), (2500, 512), (9000, 64))
+                                        for B in (1, 17, 32, 33, 65, 100, 130)] +
+                         [(50272, 512, B, t) for B, t in ((33, 64), (63, 64), (64, 64), (65, 128), (127, 128), (128, 128), (129, 192),
+                                                          (191, 192), (192, 192), (193, 128))])
+def test_lm_head_sampled_rows_and_vocabularies(V, H, B, tile):
     d = synth.ModelDims("x", 1, H, H // 64, 2 * H, V, 64, B, 2, 3, "bf16", "gumbel")
-    w = synth.make_weights(d, seed=5)
+    assert binding.he_plan_pass_gemm(binding.make_config(d), B, "lm_head").tile_rows == tile
+    w = _lm_weights(V, H)
     prompts = synth.make_prompts(d, seed=6)
     want = util.oracle_run(d, util.weights_f64(w), prompts, 3, "gumbel", 0.9, seed=3)
     eng = util.make_engine(d, w)
