@@ -349,7 +349,8 @@ __global__ void sample_kernel(const float* __restrict__ logits, int V, he_dev_st
     if (threadIdx.x == 0) {
         const size_t at = (size_t)b * out_stride + (out_at_step ? n : 0);
         ids_out[at] = besti;
-        lp_out[at] = z[besti] - (mx + logf(sum));
+        // (a row of nothing but NaN has no best token: besti is no vocabulary id then, and the sum is NaN)
+        lp_out[at] = (besti < V ? z[besti] : 0.f) - (mx + logf(sum));
         if (cur_ids) cur_ids[b] = besti;
     }
     if (advance) advance_state_by_last(st, advance, 1);

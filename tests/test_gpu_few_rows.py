@@ -131,6 +131,21 @@ def test_lm_head_nan_slice_reaches_the_logprob(B):
     eng.he_destroy()
 
 
+@pytest.mark.parametrize("dtype,impl", [("f32", 0), ("bf16", 1), ("bf16", 0)])
+def test_logits_of_nothing_but_nan(dtype, impl):
+    """No token is the best of such a row: NaN log-probabilities, and the id that stands for none is looked up nowhere -- the
+    following step clamps it like any id outside the vocabulary."""
+    import torch
+    d = synth.ModelDims("x", 1, 128, 2, 256, 2000, 64, 3, 3, 4, dtype, "greedy")
+    w = binding.upload_weights(synth.make_weights(d, seed=5, tied=False), dtype)
+    w["lm_head"][:] = float("nan")
+    eng = binding.Engine(binding.make_config(d, impl=impl), w)
+    ids, lp = eng.he_generate(torch.from_numpy(synth.make_prompts(d, seed=6)).cuda(), d.gen_len, binding.sampling("greedy"))
+    torch.cuda.synchronize()
+    assert torch.isnan(lp).all() and not ((ids >= 0) & (ids < d.vocab)).any()
+    eng.he_destroy()
+
+
 @pytest.mark.parametrize("B,S,H,nh", [(1, 32, 128, 2), (3, 129, 192, 3), (2, 257, 256, 2), (5, 400, 640, 5)])
 def test_prompt_attention_blocks_and_pairs(B, S, H, nh):
     """Query blocks of 128 with remainders, (sequence, head) pairs that do not divide over the eight XCDs, both head dimensions,
