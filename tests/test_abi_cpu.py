@@ -163,6 +163,36 @@ def test_lm_head_of_a_small_vocabulary_is_streamed():
             assert tile(50272, H, rows) == ({1: 64, 2: 128, 3: 192}[(rows + 63) // 64], 256)
 
 
+def test_pass_gemms_stay_inside_their_scratch():
+    """The k ranges of the many-row GEMMs write ksplit [rows, columns] sets of partial sums: whatever the planner picks, they fit
+    what he_create reserves -- every benchmark shape and a set of narrow ones, batches and lengths from one up, rows at the
+    edges of the tiles, three chip sizes; a scoring pass of few rows is never cut."""
+    import dataclasses
+    shapes = [synth.CONFIGS[n] for n in synth.CONFIGS]
+    for H, nh, F in ((64, 1, 64), (128, 2, 512), (320, 5, 1344), (1024, 8, 4096), (4480, 35, 8960)):
+        shapes.append(dataclasses.replace(synth.CONFIGS["tiny"], hidden=H, n_heads=nh, ffn=F))
+    tiles = set()
+    for d in shapes:
+        d = dataclasses.replace(d, dtype="bf16")
+        for max_batch, max_seq in ((1, 2), (1, 70), (3, 64), (16, 300), (64, 17), (96, 2), (256, 1), (300, 64), (8, 2048)):
+            cfg = binding.make_config(d, max_batch=max_batch, max_seq_len=max_seq)
+            most = max_batch * max_seq
+            for rows in sorted({r for r in (1, 33, 64, 65, 128, 129, 192, 193, 257, 385, 769, 1000, 1024, 2049, 8192, most) if r <= most}):
+                for which in ("qkv", "out_proj", "fc1", "fc2"):
+                    for cus in (64, 256, 304):
+                        for scoring in (False, True):
+                            a = binding.he_plan_pass_gemm(cfg, rows, which, scoring, cus)
+                            case = (d.hidden, d.ffn, max_batch, max_seq, rows, which, cus, scoring)
+                            assert 1 <= a.ksplit <= 16 and a.scratch_floats <= a.scratch_reserved, case
+                            assert not scoring or rows >= 1024 or a.ksplit == 1, case
+                            tiles.add((a.tile_rows, a.tile_cols))
+    assert tiles == {(64, 256), (128, 256), (192, 256), (256, 256), (256, 320)}
+    with pytest.raises(binding.HeError):
+        binding.he_plan_pass_gemm(cfg, most + 1, "qkv")
+    with pytest.raises(binding.HeError):
+        binding.he_plan_pass_gemm(binding.make_config(synth.CONFIGS["tiny"]), 8, "qkv")  # float
+
+
 def test_ksplit_hand_off_stays_inside_what_he_create_reserves():
     """The invariant the k-split hand-off of the decode out-projection / FC2 rests on.  Partial sums cross
     workgroups inside one launch through scratch, every (column group, row slice, split) in words of its own, with

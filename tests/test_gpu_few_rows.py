@@ -1,6 +1,7 @@
-"""GPU parity of the prompt and scoring passes of few rows (the deep-ring GEMM): row counts at the edges of its 64-, 128- and
-192-row tiles and of the 32-row blocks, column counts that end inside a 256-column tile, k ranges of different lengths, and
-wide decode steps, each against the oracle."""
+"""GPU parity of the prompt and scoring passes of few rows and of wide decode steps (the deep-ring GEMM), the LM head of many
+rows and the decode attention of few, each against the oracle.  The narrow shapes all take 64-row tiles: rows at the edges
+of those and of the 32-row blocks, columns that end inside a 256-column tile, k ranges of different lengths.
+test_passes_on_every_tile reaches the other tiles, by what the planner says."""
 import functools
 
 import numpy as np
@@ -26,6 +27,69 @@ def test_prompt_rows_at_tile_edges(H, nh, F, B, S):
     got = util.engine_teacher_forced(eng, prompts, want["ids"], 2, binding.sampling("greedy", 1.0, 3))
     eng.he_destroy()
     util.compare(got, want, BF16_TOL, MARGIN)
+
+
+@functools.lru_cache(maxsize=1)
+def _layers_4480():
+    d = synth.ModelDims("x", 2, 4480, 35, 8960, 300, 1024, 1, 2, 2, "bf16", "greedy")
+    w = synth.make_weights(d, seed=5)
+    return d, util.weights_f64(w), binding.upload_weights(w, "bf16")
+
+
+# rows B S of the prompt pass (70 and more sequences: B rows of the pass ahead of the last token, and of the wide step); tile rows x
+# tile columns / k ranges of the GEMMs it is there for.  65, 129, 193, 257, 385, 577, 769 and 1793 rows: one row in the last tile
+# of at least one of them, or one 32-row block and a row; 128, 192, 256, 384: full tiles; 127, 191, 255, 383: a row short.
+@pytest.mark.parametrize("ragged", [False, True])
+@pytest.mark.parametrize("B,S,plan", [
+    (5, 13, {"qkv": (128, 256, 4), "fc1": (128, 256, 7), "fc2": (128, 256, 14)}),
+    (1, 127, {"qkv": (128, 256, 4), "out_proj": (64, 256, 7)}),
+    (4, 32, {"qkv": (128, 256, 4), "out_proj": (64, 256, 7)}),
+    (3, 43, {"qkv": (192, 256, 4), "fc1": (192, 256, 5), "fc2": (128, 256, 7)}),
+    (1, 191, {"qkv": (192, 256, 4), "fc1": (128, 256, 3)}),
+    (4, 48, {"qkv": (192, 256, 4), "fc1": (128, 256, 3)}),
+    (1, 193, {"qkv": (128, 256, 2), "out_proj": (128, 256, 7)}),
+    (5, 51, {"qkv": (128, 256, 2), "fc1": (128, 256, 3), "fc2": (128, 256, 7)}),
+    (1, 257, {"qkv": (192, 256, 2), "out_proj": (128, 256, 4), "fc1": (192, 256, 3), "fc2": (192, 256, 7)}),
+    (1, 383, {"qkv": (192, 256, 2), "fc2": (192, 256, 7)}),
+    (6, 64, {"qkv": (192, 256, 2), "fc2": (192, 256, 7)}),
+    (7, 55, {"qkv": (128, 256, 1), "out_proj": (128, 256, 3), "fc2": (192, 256, 4)}),
+    (1, 577, {"qkv": (192, 256, 1), "fc1": (128, 256, 1), "fc2": (192, 256, 3)}),
+    (1, 769, {"qkv": (256, 256, 1), "fc2": (128, 256, 2)}),
+    (12, 75, {"qkv": (256, 256, 1), "fc1": (192, 256, 1), "fc2": (256, 256, 3)}),
+    (11, 163, {"qkv": (256, 256, 1), "fc1": (256, 320, 1), "fc2": (256, 320, 2)}),
+    (80, 2, {"qkv": (128, 256, 4), "fc1": (128, 256, 7), "fc2": (128, 256, 14)}),
+    (129, 2, {"qkv": (192, 256, 4), "fc1": (192, 256, 5), "fc2": (128, 256, 7)}),
+])
+def test_passes_on_every_tile(B, S, plan, ragged):
+    """Prompt pass and a decode step on its keys and values, the first, the last and a middle sequence against the oracle's run
+    of it alone; lengths that differ send a left-padded batch through QKV's finishing kernel as well."""
+    import torch
+    base, w64, w_dev = _layers_4480()
+    cfg = binding.make_config(base, max_batch=B, max_seq_len=S + 1)
+    rows = B * S if B <= 64 else B
+    for g, want in plan.items():
+        a = binding.he_plan_pass_gemm(cfg, rows, g)
+        assert (a.tile_rows, a.tile_cols, a.ksplit) == want, g
+    rng = np.random.default_rng(17 * B + S)
+    prompts = rng.integers(0, base.vocab, (B, S)).astype(np.int32)
+    lens = rng.integers(1, S + 1, B).astype(np.int32) if ragged else np.full(B, S, np.int32)
+    if ragged:
+        lens[0], lens[-1] = S, 1 if B > 1 else S - 37
+    some = sorted({0, B // 2, B - 1})
+    want = {b: O.generate(w64, prompts[b:b + 1, S - lens[b]:], 2, base.n_heads, mode="greedy", eps=base.ln_eps) for b in some}
+    feed = np.zeros(B, np.int32)
+    for b in some:
+        feed[b] = want[b]["ids"][0, 0]
+    eng = binding.Engine(cfg, w_dev)
+    p, samp = torch.from_numpy(prompts).cuda(), binding.sampling("greedy")
+    first = eng.he_prefill_ragged(p, torch.from_numpy(lens).cuda(), samp, True) if ragged else eng.he_prefill(p, samp, True)
+    second = eng.he_decode_step(torch.from_numpy(feed).cuda(), samp, True)
+    torch.cuda.synchronize()
+    got = [first[2].cpu().numpy(), second[2].cpu().numpy()]
+    eng.he_destroy()
+    for b in some:
+        for n in range(2):
+            assert float(np.abs(got[n][b] - want[b]["logits"][n, 0]).max()) <= BF16_TOL, (b, n)
 
 
 @pytest.mark.parametrize("B", [65, 96, 129, 200])
