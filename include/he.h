@@ -230,9 +230,13 @@ he_status he_acquire_arena(he_engine* e);
  * right-aligned behind padding, and an answer is over once the end-of-sequence token has come).
  * d_prompt_ids is [B, S] int32 row-major, LEFT-padded: row b's tokens are its last d_prompt_lens[b]
  * entries (1 <= len <= S; values outside are clamped), whatever stands before them is ignored.
- * Padding is not part of a sequence: sequence b is computed exactly as if it were run alone on its own
+ * Padding is not part of a sequence: sequence b is computed as if it were run alone on its own
  * tokens at positions 0, 1, 2, ... (only its row number b enters, through the sampling noise), and its
  * cache holds len[b] positions after the prompt.  Capacity is checked as for S tokens per sequence.
+ * What the batch does decide, here and in he_prefill, is the order of summation: how many rows a pass has sets the
+ * k ranges its GEMMs' sums are cut into and how many wavefronts share an attention row, so a sequence alone and in a
+ * batch agree to the rounding of the activations (HE_BF16: a few 1e-3 of the logits at most, HE_F32: a few 1e-6), not
+ * bit for bit.  The same batch gives the same bits every time.  (A scoring pass of few rows is not cut: he_score.)
  *
  * he_prefill_ragged is he_prefill for such a batch; he_decode_step then continues every sequence at
  * its own position.
@@ -246,7 +250,8 @@ he_status he_acquire_arena(he_engine* e);
  * dropped from the following steps whenever that makes a step cheaper (the row count falls to fewer 16-row
  * halves of the weight-streaming GEMMs' activation slices, up to 64 rows, or to fewer 128-row matrix-core
  * tiles above): the running sequences move up in order, every result still goes to its sequence's place,
- * and the sampling noise stays keyed by the sequence's number b -- results do not depend on it. */
+ * and the sampling noise stays keyed by the sequence's number b -- results do not depend on it beyond the order of
+ * summation described above. */
 he_status he_prefill_ragged(he_engine* e, const int32_t* d_prompt_ids, const int32_t* d_prompt_lens, int B, int S,
                             const he_sampling* sampling, int32_t* d_next_ids, float* d_logprobs, float* d_logits_opt);
 he_status he_generate_ragged(he_engine* e, const int32_t* d_prompt_ids, const int32_t* d_prompt_lens, int B, int S, int G,
@@ -262,7 +267,9 @@ he_status he_generate_ragged(he_engine* e, const int32_t* d_prompt_ids, const in
  *   out[b][t] = log_softmax(logits at position t of sequence b)[d_ids[b][t+1]],  t = 0 .. T-2.
  * All T positions go through the prompt-pass kernels at once; the LM head is fused with the
  * log-softmax and the gather, so the [B*T, V] logits are never stored.  Uses the KV arena as
- * scratch: the cache is emptied before and after (as by he_reset). */
+ * scratch: the cache is emptied before and after (as by he_reset).  HE_BF16: passes of too few rows for rounds of
+ * 256-row tiles keep every sum whole, so that a sequence scores the same in them and in a batch whose tiles are not cut
+ * along k either. */
 he_status he_score(he_engine* e, const int32_t* d_ids, int B, int T, float* d_out_logprobs);
 
 /* Empties the KV cache (lengths to zero; memory is kept). */

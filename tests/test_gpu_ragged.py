@@ -93,6 +93,34 @@ def test_bf16_ragged_teacher_forced(impl, H, nh, lens, S, G):
     print("bf16 ragged err", impl, _check_teacher_forced(d, lens, S, G, impl == 0, BF16_TOL, impl=impl))
 
 
+@pytest.mark.parametrize("dtype,bound", [("bf16", 4e-3), ("f32", 1e-5)])
+def test_sequence_alone_and_in_a_batch_differ_by_rounding_only(dtype, bound):
+    """The rows of a pass decide how its sums are cut (k ranges, wavefronts per attention row): a sequence alone and in a batch
+    agree to the rounding of the activations.  The bound is twice what either run is off the oracle at this width (2e-3 bf16,
+    5e-6 f32).  The same batch again: the same bits."""
+    import torch
+    S, lens, G = 90, [90, 1, 33, 64, 70], 3
+    d = synth.ModelDims("x", 2, 1024, 8, 4096, 1000, 128, len(lens), S, G, dtype, "greedy")
+    eng = util.make_engine(d, synth.make_weights(d, seed=5), max_batch=len(lens), max_seq_len=S + G)
+    ids, prompts, ln = _ragged_batch(d, lens, S, 6)
+    rng = np.random.default_rng(7)
+    forced = rng.integers(0, d.vocab, (len(lens), G)).astype(np.int32)
+    samp = binding.sampling("greedy")
+    batch, again = (_teacher_forced(eng, ids, ln, forced, G, samp) for _ in range(2))
+    if dtype == "bf16":  # the two really are cut differently
+        plans = [binding.he_plan_pass_gemm(eng.cfg, r, "fc2").ksplit for r in (len(lens) * S, 33, 90)]
+        assert len(set(plans)) > 1, plans
+    for n in range(G):
+        assert all(np.array_equal(x, y) for x, y in zip(batch[n], again[n]))
+    worst = 0.0
+    for b, p in enumerate(prompts):
+        alone = _teacher_forced(eng, p[None], np.asarray([len(p)], np.int32), forced[b:b + 1], G, samp)
+        worst = max(worst, max(float(np.abs(alone[n][2][0] - batch[n][2][b]).max()) for n in range(G)))
+    eng.he_destroy()
+    print("alone against batch", dtype, worst)
+    assert worst <= bound
+
+
 def _compare_generation(got_ids, got_lp, got_lens, want, tol, eos, pad):
     """Free-running: a sequence is compared up to its first step whose oracle margin is too thin to
     fix the token; what the engine itself reports must be consistent throughout."""
