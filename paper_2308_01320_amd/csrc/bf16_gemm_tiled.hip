@@ -56,7 +56,7 @@ __device__ __forceinline__ void lm_head_tile(const Epi& p, const f32x16 (&acc)[4
     const int mode = p.st->mode, step = p.st->step;
     const float temp = p.st->temperature;
     const uint32_t k0 = p.st->seed_lo, k1 = p.st->seed_hi;
-    const bool folded = p.ln_stats != nullptr;
+    const bool folded = MJ == 1 && p.ln_stats != nullptr;  // (more rows to a tile: never folded)
 #pragma unroll
     for (int j = 0; j < MJ; ++j) {
         if (m0 + j * 32 < p.M) {  // (wave-uniform)
@@ -572,11 +572,14 @@ __global__ __launch_bounds__(256, 1) void gemm_ring_kernel(const u32x4* __restri
     const int tn = rest % tiles_n, ks = rest / tiles_n;
     const int wn = wave & 1, wm = wave >> 1;  // this wavefront's 128 (n) x 32 MW (m) sub-tile
     [[maybe_unused]] const int cur_len = epilogue_len<MODE>(p);
-    [[maybe_unused]] LnLoads lnl[2 * MW];  // LM head with the final LayerNorm folded in: this wavefront's share of the rows' statistics
-    if constexpr (MODE == MODE_LMHEAD) {
+    // LM head with the final LayerNorm folded in (decode steps of up to 64 rows, whose rows are one tile of 64: MW = 1): this
+    // wavefront's share of the rows' statistics
+    constexpr bool FOLDS = MODE == MODE_LMHEAD && MW == 1;
+    [[maybe_unused]] LnLoads lnl[FOLDS ? 2 : 1];
+    if constexpr (FOLDS) {
         if (p.ln_stats) {
 #pragma unroll
-            for (int x = 0; x < 2 * MW; ++x) ln_issue<4>(lnl[x], p, min(tm * 2 * MW + x, MT32 - 1), wave, lane);
+            for (int x = 0; x < 2; ++x) ln_issue<4>(lnl[x], p, min(tm * 2 + x, MT32 - 1), wave, lane);
         }
     }
     f32x16 acc[4][MW];
@@ -695,14 +698,14 @@ __global__ __launch_bounds__(256, 1) void gemm_ring_kernel(const u32x4* __restri
         for (int j = 0; j < MW; ++j) fold[j] = make_float2(0.f, 1.f);
         float* lds = reinterpret_cast<float*>(&ring[0][0][0]);  // the ring is free: statistics and logits go through it
         __syncthreads();
-        if (p.ln_stats) {
-            float* lnp = lds + 4 * 64 * 64;
+        if constexpr (FOLDS) {
+            if (p.ln_stats) {
+                float* lnp = lds + 4 * 64 * 64;
 #pragma unroll
-            for (int x = 0; x < 2 * MW; ++x)
-                ln_partial<4>(lnl[x], p, min(tm * 2 * MW + x, MT32 - 1), wave, lane, lnp + x * 4 * 4 * 32);
-            __syncthreads();
-#pragma unroll
-            for (int j = 0; j < MW; ++j) fold[j] = ln_finish<4>(lnp + (wm * MW + j) * 4 * 4 * 32, lane & 31, p);
+                for (int x = 0; x < 2; ++x) ln_partial<4>(lnl[x], p, min(tm * 2 + x, MT32 - 1), wave, lane, lnp + x * 4 * 4 * 32);
+                __syncthreads();
+                fold[0] = ln_finish<4>(lnp + wm * 4 * 4 * 32, lane & 31, p);
+            }
         }
         lm_head_tile<MW>(p, acc, fold, tm * Sh::TM + wm * 32 * MW, tn * 256 + wn * 128, tn * 2 + wn, lane,
                          lds + wave * 64 * 64);
@@ -811,8 +814,9 @@ void launch_tiled(hipStream_t s, const void* Wp, const void* Xhi, int KB, int N,
         const int tiles_n = (N + 255) / 256, tiles_m = (M + 64 * tile - 1) / (64 * tile);
         const int grid = (tiles_n * tiles_m * ksplit + 7) / 8 * 8;
         if (tile == 1) gemm_ring_kernel<MODE, 1><<<grid, 256, 0, s>>>(W, X, bias8, KB, NT32, MT32, tiles_n, tiles_m, ksplit, p);
-        else if (tile == 2) gemm_ring_kernel<MODE, 2><<<grid, 256, 0, s>>>(W, X, bias8, KB, NT32, MT32, tiles_n, tiles_m, ksplit, p);
-        else gemm_ring_kernel<MODE, 3><<<grid, 256, 0, s>>>(W, X, bias8, KB, NT32, MT32, tiles_n, tiles_m, ksplit, p);
+        else if (MODE == MODE_SCORE || tile == 2)  // (score_tile knows no 192-row tile)
+            gemm_ring_kernel<MODE, 2><<<grid, 256, 0, s>>>(W, X, bias8, KB, NT32, MT32, tiles_n, tiles_m, ksplit, p);
+        else gemm_ring_kernel<MODE, MODE == MODE_SCORE ? 2 : 3><<<grid, 256, 0, s>>>(W, X, bias8, KB, NT32, MT32, tiles_n, tiles_m, ksplit, p);
         return;
     }
     if constexpr (MODE != MODE_SCORE && MODE != MODE_LMHEAD) {
@@ -892,8 +896,9 @@ static RingPlan fused_plan(int M, int N, int KB, size_t capacity_floats) {
     return ring_plan(M, N, KB, true, capacity_floats);
 }
 
-// The LM head's tiles (no scratch: whole k ranges; 192 rows at most to a tile)
-static RingPlan lm_head_plan(int M, int V, int K) { return ring_plan(M, V, K / 16, true, 0, 3); }
+// The LM head's tiles (no scratch: whole k ranges; 192 rows at most to a tile).  Up to 64 rows one row of 64-row tiles: there the
+// final LayerNorm may come folded in.
+static RingPlan lm_head_plan(int M, int V, int K) { return ring_plan(M, V, K / 16, true, 0, M <= 64 ? 1 : 3); }
 
 // The scoring head: 0 for gemm_score_kernel (two workgroups per CU: from two rounds of its tiles on), else the ring kernel's tile
 static int score_tile(int M, int V) {

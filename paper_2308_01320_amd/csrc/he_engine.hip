@@ -154,7 +154,8 @@ Sizes sizes_of(const he_config& c) {
     // prompt rows, or the decode step's k-split scratch: splits x rows padded to 32, twice (a
     // workgroup of eight wavefronts on a single tile leaves half of its slots unused)
     const size_t drow = (size_t)2 * kMaxKSplit * (((size_t)c.max_batch + 31) / 32 * 32);
-    // ... or, for decode steps of more than 32 rows, the k-split partial sums of the widest GEMM
+    // ... or, for batches of more than 32, eight sets of the widest GEMM's sums.  (What the decode plans of 33 .. 64 rows may
+    // count on, and the floor of what the wide decode steps' k ranges use below: smaller, both would cut some matrices otherwise.)
     const size_t wide = (size_t)(3 * c.hidden > c.ffn ? 3 * c.hidden : c.ffn);
     const size_t mrow = c.max_batch > 32 ? ((size_t)kMaxKSplit * c.max_batch * wide + c.hidden - 1) / c.hidden : 0;
     const size_t prow = std::max(std::max(rows, drow), mrow);
