@@ -182,7 +182,7 @@ he_status he_decode_step(he_engine* e, const int32_t* d_in_ids, const he_samplin
  * HIP graph capture, tight serving loops, harnesses that forbid hipMalloc.  Same arguments, same results
  * (bit for bit) as he_decode_step.  The step's scratch -- the k-split partial sums of the out-projection
  * and FC2, the column-group statistics and arrival counters of the folded LayerNorms, and the LM head's
- * per-tile soft-max / arg-max partials -- lives in a file-scope device array of 16 MiB inside the library
+ * soft-max / arg-max partials -- lives in a file-scope device array of 16 MiB inside the library
  * (every GPU the library runs on holds its own copy until the process ends) instead of the engine's
  * workspace; the call makes no hipMalloc / hipFree / event or graph creation and launches its kernels one by
  * one on cfg.stream.  KV arena, activations and weights are still the engine's (he_create allocated them).
@@ -247,9 +247,9 @@ he_status he_acquire_arena(he_engine* e);
  * the end token included.  When every sequence has ended, the remaining steps are skipped (the count
  * of running sequences is read back every 16 steps, which synchronises cfg.stream).  A sequence that has
  * ended skips attention at once; at those read-backs, on the HE_BF16 path, the rows of ended sequences are
- * dropped from the following steps whenever that makes a step cheaper (the row count falls to fewer 16-row
- * halves of the weight-streaming GEMMs' activation slices, up to 64 rows, or to fewer 128-row matrix-core
- * tiles above): the running sequences move up in order, every result still goes to its sequence's place,
+ * dropped from the following steps whenever the row count falls into a lower class (fewer 16-row
+ * halves of the weight-streaming GEMMs' activation slices, up to 64 rows, or fewer multiples of 128 rows
+ * above): the running sequences move up in order, every result still goes to its sequence's place,
  * and the sampling noise stays keyed by the sequence's number b -- results do not depend on it beyond the order of
  * summation described above. */
 he_status he_prefill_ragged(he_engine* e, const int32_t* d_prompt_ids, const int32_t* d_prompt_lens, int B, int S,

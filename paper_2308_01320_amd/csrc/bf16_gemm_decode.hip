@@ -633,10 +633,12 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_half_kernel(const u32x4* __re
         for (int s2 = 0; s2 < MT; ++s2) ln_partial<WAVES>(lnl[s2], p, mt + s2, wave, lane, lnp[s2]);
     };
     int n = kp1 - kp0;
-    // Where every workgroup's ranges begin at multiples of 32 KiB and more (they do at these widths), workgroups that walk
-    // them in step ask the same memory channels at the same time.  With ROTATE each starts its rounds at another one and
-    // wraps around: 8-bit 16384 x 4096 19.0 -> 14.9 us, 20480 x 5120 21.9 -> 20.0, 4096 x 16384 (four ranges) 22.7 ->
-    // 18.6, 16-bit 4096 x 16384 (two) 28.9 -> 26.9.  The 16-bit GEMMs with one range lose by it (16384 x 4096 27.2 -> 29.8).
+    // Where every workgroup's ranges begin at multiples of 32 KiB and more, workgroups that walk them in step ask the same memory
+    // channels at the same time.  With ROTATE each starts its rounds at another one and wraps around: 8-bit 16384 x 4096
+    // 19.0 -> 14.9 us, 20480 x 5120 21.9 -> 20.0, 4096 x 16384 (four ranges) 22.7 -> 18.6, 16-bit 4096 x 16384 (two) 28.9 -> 26.9.
+    // The 16-bit GEMMs with one range lose by it (16384 x 4096 27.2 -> 29.8).  At other widths it is done for nothing: a layer's
+    // decode GEMMs together, rotated less not, us: 8-bit hidden 4096 -7.5, 5120 -2.7, 2048 -0.2, 5184 -0.6, 4160 +0.2, 2112 +0.7, 1088
+    // and 1024 +0.4; 16-bit 4096 -1.7, 5120 and 5184 +0.2, 4160 +0.4, 2112 +0.2, 1088 +0.4, 1024 +0.1.
     constexpr bool ROTATE = W8 || MODE == MODE_STORE_LN;
     constexpr int WSTEP = W8 ? 64 : 128;
     const int rounds = n / U;

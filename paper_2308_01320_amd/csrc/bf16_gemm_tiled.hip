@@ -538,9 +538,10 @@ __global__ __launch_bounds__(256, 1) void gemm_tiled256_kernel(const u32x4* __re
 // kernel's -- LDS reads and copies dealt out behind the matrix instructions, a bare workgroup barrier per stage -- with
 // one difference: a slot is refilled behind the barrier of its own stage (every wavefront waits for its own LDS reads
 // before it), so all but one of the slots are in flight.
-// Measured (weights from HBM, one k range per tile -> the planned ranges; the kernel before this, four stages, one
-// range): 250 x 4096 x 16384: 269 -> 203 -> 45 us; 250 x 16384 x 4096: 79 -> 64 -> 44; 96 x 5120 x 20480: 52 (eight
-// ranges) -> 44 (twelve); 768 x 12288 x 4096: 150 -> 76 (192-row tiles, one range).
+// Measured, the kernel before this (four stages, one range) -> this one with one k range per tile -> with the planned ones:
+// 250 x 4096 x 16384: 269 -> 203 -> 45 us; 250 x 16384 x 4096: 79 -> 56, the plan (one range on 64-row tiles; ranges would
+// need finish_kernel, 8 us); 250 x 12288 x 4096: 41 and 8 for finish_kernel; 96 x 5120 x 20480: 52 (eight ranges) -> 44 (twelve);
+// 768 x 12288 x 4096: 150 -> 76 (192-row tiles, one range).
 template <int MW> struct RingShape {
     static constexpr int TM = 64 * MW;                       // rows of X per tile
     static constexpr int SB = (8 + 2 * MW) * 2;              // blocks per stage (two k-blocks)

@@ -692,8 +692,9 @@ he_status run_forward(he_engine* e, const int32_t* d_ids, int B, int S, int32_t*
     return check_hip(e, hipGetLastError(), "kernel launch");
 }
 
-// What a decode step of `rows` rows costs, as far as the row count decides it: 16-row halves of the activation
-// slices the weight-streaming GEMMs multiply by (up to 64 rows), 128-row tiles of the matrix-core GEMMs above.
+// Classes of decode steps by their row count, between which dropping rows pays for two new graphs: 16-row halves of the
+// activation slices the weight-streaming GEMMs multiply by (up to 64 rows), every 128 rows above (the matrix-core GEMMs'
+// tiles there hold 64, 128 or 192).
 int step_cost_class(const he_engine* e, int rows) {
     return wide_decode(e, rows) ? 4 + (rows + 127) / 128 : (rows + 15) / 16;
 }

@@ -496,7 +496,11 @@ void plain_ln(hipStream_t s, int bf16, const float* r, const plain_ln_args& ln, 
                                                    ln.in_add);
 }
 
-// rows up to which the LayerNorm is folded into the GEMM: every workgroup of 16 columns then normalises its 16 rows for itself
+// Rows up to which the LayerNorm is folded into the GEMM: every workgroup of 16 columns then normalises its 16 rows for itself,
+// which costs rows x width x columns / 16.  Measured, decode steps of two layers (us, folded / a LayerNorm kernel and the 32 x 32
+// tiles): width 256: 1 row 62 / 84, 64 rows 74 / 94; 512: 77 / 117, 117 / 130; 1024: 1 row 122 / 184, 32 rows 187 / 202, 33 220 / 198, 64
+// 287 / 201; 2048: 1 row 255 / 358, 16 367 / 362, 64 974 / 477.  So the line is right for models up to 512 wide, whose steps this path
+// is for, and too high for wider ones from 33 (1024) or 17 (2048) rows on.
 constexpr int kFewRows = 64;
 
 template <typename ST, bool VEC>
