@@ -252,6 +252,11 @@ inline int num_cus() {
     return n_cus;
 }
 
+// The CU count launch shapes are sized for: the current device's, or the one a planner query names (its own thread's, so that a
+// query never reshapes a launch).
+inline thread_local int plan_cus_override = 0;
+inline int plan_cus() { return plan_cus_override > 0 ? plan_cus_override : num_cus(); }
+
 inline Epi make_epi(int M, int N, const bf16_gemm_args& a) {
     Epi p{};
     p.M = M; p.N = N; p.bias = (const bf16_t*)a.bias; p.out = a.out; p.out_split = a.out_split;

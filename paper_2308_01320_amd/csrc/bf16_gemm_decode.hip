@@ -815,20 +815,16 @@ __global__ void lm_reduce_kernel(const float* __restrict__ stats, const int* __r
     if (advance) advance_state_by_last(st, 1, 1);
 }
 
-// Launch shapes are sized for the current device's CU count, or for the count a planner query names.
-int g_cus_override = 0;
-int plan_cus() { return g_cus_override > 0 ? g_cus_override : num_cus(); }
-
 #ifndef HE_SKINNY_U
 #define HE_SKINNY_U(NT) ((NT) <= 4 ? 4 : 2)
 #endif
 #ifndef HE_SKINNY_W8_MAXNT
 #define HE_SKINNY_W8_MAXNT 2
 #endif
-// Host-side account of a MODE_STORE_LN launch: when `g_dry` is set the launchers below go through their choice of
-// kernel variant and grid as usual, then record what that launch would index instead of launching it.
+// Host-side account of a MODE_STORE_LN launch: when `g_dry` is set the launchers below (called from the same thread) go through
+// their choice of kernel variant and grid as usual, then record what that launch would index instead of launching it.
 struct StoreFootprint { size_t scratch_floats; int cells; int stat_groups; int ksplit; };
-StoreFootprint* g_dry = nullptr;
+thread_local StoreFootprint* g_dry = nullptr;
 // grid: the launch's; items, waves: of the kernel variant chosen.  True if the launch is to be left out.
 inline bool dry_run(const dim3& grid, int ksplit, int items, int waves) {
     if (!g_dry) return false;
@@ -1113,9 +1109,9 @@ void bf16_store_plan_w8(int N, int K, size_t capacity, int* group_cols, int* ks)
 }
 
 void bf16_plan_query(int M, int N, int K, int store, size_t capacity, int cus, int* unit_rows, int* per_wg, int* ks) {
-    g_cus_override = cus;
+    plan_cus_override = cus;
     const GemmPlan g = store ? plan_store(M, N, K, capacity) : plan_fused(M, N);
-    g_cus_override = 0;
+    plan_cus_override = 0;
     *unit_rows = g.half ? 16 : 32;
     *per_wg = g.per_wg;
     *ks = g.ks;
@@ -1126,7 +1122,7 @@ void bf16_plan_query(int M, int N, int K, int store, size_t capacity, int cus, i
 void bf16_store_footprint(int M, int N, int K, size_t capacity, int w8, int cus, size_t* scratch_floats,
                           size_t* need_floats, int* cells, int* stat_groups, int* ksplit) {
     StoreFootprint f{};
-    g_cus_override = cus;
+    plan_cus_override = cus;
     bf16_gemm_args a{};
     a.out_capacity = capacity;
     float one = 1.f;
@@ -1135,7 +1131,7 @@ void bf16_store_footprint(int M, int N, int K, size_t capacity, int w8, int cus,
     bf16_gemm_skinny(nullptr, EPI_STORE_LN, nullptr, nullptr, M, N, K, 0, a);
     g_dry = nullptr;
     *need_floats = bf16_store_need(M, N, K, capacity, w8);
-    g_cus_override = 0;
+    plan_cus_override = 0;
     *scratch_floats = f.scratch_floats;
     *cells = f.cells;
     *stat_groups = f.stat_groups;

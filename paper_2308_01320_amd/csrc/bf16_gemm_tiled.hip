@@ -735,12 +735,10 @@ __global__ __launch_bounds__(256) void score_reduce_kernel(const float2* __restr
 
 
 constexpr int kMaxTiledKSplit = 16;  // k ranges a tile of a few-row GEMM is cut into at most
-static int g_tiled_cus_override = 0;  // a planner query's CU count
-static int tiled_cus() { return g_tiled_cus_override > 0 ? g_tiled_cus_override : num_cus(); }
 // Many rows (a prompt or scoring pass): 256 x 256 tiles, one workgroup per CU, once there are enough of them to
 // give every CU one.
 static bool use_big_tile(int M, int N) {
-    return M >= 1024 && (long)((N + TN - 1) / TN) * ((M + 255) / 256) >= tiled_cus();
+    return M >= 1024 && (long)((N + TN - 1) / TN) * ((M + 255) / 256) >= plan_cus();
 }
 
 // How a many-row GEMM is cut into tiles of 256 rows: 64 na columns wide (na = 4 or 5), and, where the partial sums
@@ -748,7 +746,7 @@ static bool use_big_tile(int M, int N) {
 // rounds of one per CU and a partly empty round costs a full one; the cost is in units of a whole 256-column tile.
 struct BigPlan { int na, ks, split_col; };
 static BigPlan big_plan(int M, int N, int KB, bool may_cut) {
-    const long cus = tiled_cus(), tm = (M + BM - 1) / BM;
+    const long cus = plan_cus(), tm = (M + BM - 1) / BM;
     may_cut = may_cut && KB % 4 == 0 && KB / 2 >= 8 * BSTAGES;
     BigPlan best{4, 1, 0};
     double best_cost = 1e30;
@@ -780,7 +778,7 @@ static BigPlan big_plan(int M, int N, int KB, bool may_cut) {
 struct RingPlan { int mw, ks; };
 static RingPlan ring_plan(int M, int N, int KB, bool fused, size_t capacity_floats, int max_mw = 5) {
     constexpr double kStage[5] = {0.33, 0.39, 0.43, 0.53, 0.68}, kRamp[5] = {6.0, 7.0, 8.5, 12.0, 14.0};
-    const long cus = tiled_cus(), stages = KB / 2;
+    const long cus = plan_cus(), stages = KB / 2;
     const double sums = 4.0 * M * N / 5e6, weights = 32.0 * N * KB / 14e6;
     RingPlan best{2, 1};
     double best_cost = 1e30;
@@ -879,7 +877,7 @@ void bf16_tiled_store_plan(int M, int N, int K, size_t capacity_floats, int* til
 
 void bf16_tiled_plan_query(int M, int N, int K, int may_cut, size_t capacity_floats, int cus, int* tile_cols, int* ks,
                            int* split_col) {
-    g_tiled_cus_override = cus;
+    plan_cus_override = cus;
     *tile_cols = 0; *ks = 1; *split_col = 0;
     const size_t room = capacity_floats ? capacity_floats : (size_t)-1;
     if (use_big_tile(M, N)) {
@@ -888,7 +886,7 @@ void bf16_tiled_plan_query(int M, int N, int K, int may_cut, size_t capacity_flo
     } else if (may_cut) {
         *ks = ring_plan(M, N, K / 16, false, room).ks;
     }
-    g_tiled_cus_override = 0;
+    plan_cus_override = 0;
 }
 
 // QKV and FC1, whose epilogue needs the whole sum: with k ranges finish_kernel applies it.
@@ -904,12 +902,12 @@ static RingPlan lm_head_plan(int M, int V, int K) { return ring_plan(M, V, K / 1
 // The scoring head: 0 for gemm_score_kernel (two workgroups per CU: from two rounds of its tiles on), else the ring kernel's tile
 static int score_tile(int M, int V) {
     const long tiles = (long)((V + TN - 1) / TN) * ((M + 127) / 128);
-    return tiles >= 2 * tiled_cus() ? 0 : (M <= 64 ? 1 : 2);
+    return tiles >= 2 * plan_cus() ? 0 : (M <= 64 ? 1 : 2);
 }
 
 void bf16_pass_plan_query(int use, int M, int N, int K, size_t capacity_floats, int cus, int* tile_rows, int* tile_cols, int* ks,
                           int* split_col) {
-    g_tiled_cus_override = cus;
+    plan_cus_override = cus;
     int tile = 0;
     *ks = 1; *split_col = 0;
     if (use == TILED_STORE || use == TILED_STORE_WHOLE) {
@@ -922,7 +920,7 @@ void bf16_pass_plan_query(int use, int M, int N, int K, size_t capacity_floats, 
     } else {
         tile = bf16_lm_head_streams(M, N) ? -1 : lm_head_plan(M, N, K).mw;
     }
-    g_tiled_cus_override = 0;
+    plan_cus_override = 0;
     *tile_rows = tile < 0 ? 32 : (tile == 0 ? 128 : (tile < 4 ? 64 * tile : 256));
     *tile_cols = tile < 0 ? 32 : (tile == 5 ? 320 : 256);
 }

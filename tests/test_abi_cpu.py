@@ -193,6 +193,40 @@ def test_pass_gemms_stay_inside_their_scratch():
         binding.he_plan_pass_gemm(binding.make_config(synth.CONFIGS["tiny"]), 8, "qkv")  # float
 
 
+def test_planner_queries_of_one_thread_do_not_change_anothers_plans():
+    """A query may name another CU count, and the scratch account dry-runs the launcher: both belong to the calling thread.  (Four
+    threads ask for four chip sizes; with either process-wide some four answers in a thousand belong to another thread.)"""
+    import sys
+    import threading
+    L = binding.lib()
+    cfg = binding.make_config(synth.CONFIGS["opt-13b"], max_batch=64, max_seq_len=64)
+
+    def account(cus, out):
+        assert L.he_decode_scratch_account(C.byref(cfg), 32, 1, cus, C.byref(out)) == 0
+        return out.scratch_floats, out.counters, out.ksplit
+
+    counts = (64, 128, 256, 304)
+    want = {c: account(c, binding.he_scratch_account()) for c in counts}
+    assert len(set(want.values())) == len(counts)
+    wrong = []
+
+    def ask(c):
+        out = binding.he_scratch_account()
+        wrong.extend(c for _ in range(8000) if account(c, out) != want[c])
+
+    threads = [threading.Thread(target=ask, args=(c,)) for c in counts]
+    interval = sys.getswitchinterval()
+    sys.setswitchinterval(1e-6)
+    try:
+        for t in threads:
+            t.start()
+        for t in threads:
+            t.join()
+    finally:
+        sys.setswitchinterval(interval)
+    assert not wrong, len(wrong)
+
+
 def test_ksplit_hand_off_stays_inside_what_he_create_reserves():
     """The invariant the k-split hand-off of the decode out-projection / FC2 rests on.  Partial sums cross
     workgroups inside one launch through scratch, every (column group, row slice, split) in words of its own, with
