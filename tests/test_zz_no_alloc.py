@@ -52,6 +52,25 @@ def test_static_scratch_decode_step_matches_the_allocating_one():
     eng.he_destroy()
 
 
+@pytest.mark.parametrize("V,H,nh", [(5000, 1024, 16), (50272, 512, 8)])
+@pytest.mark.parametrize("B", [33, 64])
+def test_static_scratch_decode_step_of_two_slices(B, V, H, nh):
+    """33 and 64 sequences: two activation slices per workgroup, the LM head streamed or (the larger vocabulary) in tiles with the
+    final LayerNorm folded in."""
+    d = synth.ModelDims("static-scratch", 2, H, nh, 4 * H, V, 64, B, 5, 4, "bf16", "gumbel")
+    cfg = binding.make_config(d)
+    assert binding.he_plan_pass_gemm(cfg, B, "lm_head").tile_rows == (32 if V == 5000 else 64)
+    eng = util.make_engine(d, synth.make_weights(d, seed=11))
+    samp = binding.sampling("gumbel", 1.0, 7)
+    prompts = synth.make_prompts(d, seed=13)
+    feeds = [np.random.default_rng(12 + n).integers(0, d.vocab, size=B, dtype=np.int32) for n in range(3)]
+    want = _steps(eng, prompts, feeds, samp, static=False)
+    got = _steps(eng, prompts, feeds, samp, static=True)
+    for n, (g, w_) in enumerate(zip(got, want)):
+        assert all(np.array_equal(x, y) for x, y in zip(g, w_)), n
+    eng.he_destroy()
+
+
 def test_static_scratch_limits_are_errors():
     import torch
     d = synth.CONFIGS["tiny"]
