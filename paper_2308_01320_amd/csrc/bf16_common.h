@@ -99,7 +99,7 @@ struct Epi {
     // over column group g (ln_gw columns, the last group may be short); c1 = W gamma, c2 = W beta.
     const float2* ln_stats;  // null: X is already normalised
     int ln_groups, ln_gw, ln_cols;
-    float ln_eps;
+    float ln_eps, ln_inv;   // ln_inv: 1 / ln_cols
     const float *c1, *c2;   // [N]
     // STORE_LN: the workgroup that finishes a column group last adds the k-split partial sums,
     // bias and residual, and hands the next GEMM gamma * x (out_blocks) and the
@@ -178,64 +178,69 @@ __device__ __forceinline__ void epilogue4(const Epi& p, int m, int n0, int ks, f
 // per-column-group statistics the producer left ([group][32 rows](mean, sum of squared deviations)).
 // Pairwise-update form, pivoted on the first group's mean so that the cross terms stay small.  The work is
 // spread over a workgroup and taken off the tail of the kernel: wavefront w takes the groups
-// g = 2w + lane/32 (mod 2 WAVES), a lane one row of them; the loads are issued (ln_issue) before the first
+// g = 2w + lane/32 (mod 2 WAVES; with at most 16 rows in use 4w + lane/16, mod 4 WAVES), a lane one row of them; the loads are issued (ln_issue) before the first
 // weight loads, the partial sums formed (ln_partial) while those weights are in flight and left in LDS ahead
 // of the barrier that ends the k loop; after it every lane adds the WAVES partial sums of the rows it needs in
 // wavefront order (ln_finish).
-constexpr int kLnBatch = 6;  // statistics a lane keeps in flight; more groups than 2 WAVES kLnBatch are loaded late
-struct LnLoads { float2 e[kLnBatch]; float pivot; };
-
+// Statistics a lane keeps in flight (what more groups need is loaded late, as many at a time, while no weights are requested):
+// four wavefronts have twice the registers and half the lanes.
+constexpr int ln_batch(int waves) { return waves == 4 ? 12 : 6; }
 template <int WAVES>
-__device__ __forceinline__ void ln_issue(LnLoads& L, const Epi& p, int mt, int wave, int lane) {
-    const float2* gs = p.ln_stats + (size_t)mt * p.ln_groups * 32 + (lane & 31);
-    L.pivot = gs[0].x;
-    const int g0 = 2 * wave + (lane >> 5);
+struct LnLoads { float2 e[ln_batch(WAVES)]; float pivot; };
+
+// ROWS: 32, or 16 where no more rows of the slice are in use (twice the groups per load)
+template <int WAVES, int ROWS = 32>
+__device__ __forceinline__ void ln_load(LnLoads<WAVES>& L, const Epi& p, const float2* gs, int g0, int from) {
+    constexpr int STEP = (64 / ROWS) * WAVES;
 #pragma unroll
-    for (int i = 0; i < kLnBatch; ++i) {
-        const int g = g0 + i * 2 * WAVES;
+    for (int i = 0; i < ln_batch(WAVES); ++i) {
+        if (from + i * STEP >= p.ln_groups) break;  // (the same for the whole workgroup)
+        const int g = g0 + i * STEP;
         L.e[i] = g < p.ln_groups ? gs[(size_t)g * 32] : make_float2(0.f, 0.f);
     }
 }
+template <int WAVES, int ROWS = 32>
+__device__ __forceinline__ void ln_issue(LnLoads<WAVES>& L, const Epi& p, int mt, int wave, int lane) {
+    const float2* gs = p.ln_stats + (size_t)mt * p.ln_groups * 32 + (lane & (ROWS - 1));
+    L.pivot = gs[0].x;
+    ln_load<WAVES, ROWS>(L, p, gs, (64 / ROWS) * wave + lane / ROWS, 0);
+}
 
-// lnp: [WAVES][4][32] floats of LDS
-template <int WAVES>
-__device__ __forceinline__ void ln_partial(const LnLoads& L, const Epi& p, int mt, int wave, int lane, float* lnp) {
-    const int g0 = 2 * wave + (lane >> 5);
+// lnp: [WAVES][32] float4 of LDS
+template <int WAVES, int ROWS = 32>
+__device__ __forceinline__ void ln_partial(LnLoads<WAVES>& L, const Epi& p, int mt, int wave, int lane, float4* lnp) {
+    constexpr int STEP = (64 / ROWS) * WAVES;
+    const int g0 = (64 / ROWS) * wave + lane / ROWS;
+    const float2* gs = p.ln_stats + (size_t)mt * p.ln_groups * 32 + (lane & (ROWS - 1));
     float s1 = 0.f, s2 = 0.f, sm = 0.f;
-    auto add = [&](int g, float2 e) {
-        const float cnt = (float)min(p.ln_gw, p.ln_cols - g * p.ln_gw), dlt = e.x - L.pivot;
-        s1 += cnt * dlt;
-        s2 += cnt * dlt * dlt;
-        sm += e.y;
-    };
+    for (int from = 0; from < p.ln_groups; from += ln_batch(WAVES) * STEP) {
+        if (from > 0) ln_load<WAVES, ROWS>(L, p, gs, g0 + from, from);
 #pragma unroll
-    for (int i = 0; i < kLnBatch; ++i) {
-        const int g = g0 + i * 2 * WAVES;
-        if (g < p.ln_groups) add(g, L.e[i]);
+        for (int i = 0; i < ln_batch(WAVES); ++i) {
+            if (from + i * STEP >= p.ln_groups) break;
+            // (of a group past the last one nothing is counted)
+            const float cnt = (float)max(min(p.ln_gw, p.ln_cols - (g0 + from + i * STEP) * p.ln_gw), 0), dlt = L.e[i].x - L.pivot;
+            const float cd = cnt * dlt;
+            s1 += cd;
+            s2 += cd * dlt;
+            sm += L.e[i].y;
+        }
     }
-    const float2* gs = p.ln_stats + (size_t)mt * p.ln_groups * 32 + (lane & 31);
-    for (int g = g0 + kLnBatch * 2 * WAVES; g < p.ln_groups; g += 2 * WAVES) add(g, gs[(size_t)g * 32]);
-    s1 += __shfl_xor(s1, 32);
-    s2 += __shfl_xor(s2, 32);
-    sm += __shfl_xor(sm, 32);
-    if (lane < 32) {
-        float* o = lnp + wave * 4 * 32 + lane;
-        o[0] = s1; o[32] = s2; o[64] = sm; o[96] = L.pivot;
-    }
+    if (ROWS == 16) { s1 = lane_sum16_apart(s1); s2 = lane_sum16_apart(s2); sm = lane_sum16_apart(sm); }
+    s1 = lane_sum32_apart(s1); s2 = lane_sum32_apart(s2); sm = lane_sum32_apart(sm);
+    if (lane < ROWS) lnp[wave * 32 + lane] = make_float4(s1, s2, sm, L.pivot);
 }
 
 template <int WAVES>
-__device__ __forceinline__ float2 ln_finish(const float* lnp, int row, const Epi& p) {
+__device__ __forceinline__ float2 ln_finish(const float4* lnp, int row, const Epi& p) {
+    float4 e[WAVES];
+#pragma unroll
+    for (int w = 0; w < WAVES; ++w) e[w] = lnp[w * 32 + row];
     float s1 = 0.f, s2 = 0.f, sm = 0.f;
 #pragma unroll
-    for (int w = 0; w < WAVES; ++w) {
-        const float* o = lnp + w * 4 * 32 + row;
-        s1 += o[0]; s2 += o[32]; sm += o[64];
-    }
-    const float pivot = lnp[96 + row];
-    const float inv = 1.0f / (float)p.ln_cols;
-    const float mean = pivot + s1 * inv;
-    const float var = fmaxf((sm + s2 - s1 * s1 * inv) * inv, 0.f);
+    for (int w = 0; w < WAVES; ++w) { s1 += e[w].x; s2 += e[w].y; sm += e[w].z; }
+    const float mean = e[0].w + s1 * p.ln_inv;
+    const float var = fmaxf((sm + s2 - s1 * s1 * p.ln_inv) * p.ln_inv, 0.f);
     return make_float2(mean, 1.0f / sqrtf(var + p.ln_eps));
 }
 
@@ -264,7 +269,7 @@ inline Epi make_epi(int M, int N, const bf16_gemm_args& a) {
     p.S = a.S; p.layer = a.layer; p.H = a.H; p.n_heads = a.n_heads; p.d = a.n_heads ? a.H / a.n_heads : 0;
     p.max_batch = a.max_batch; p.max_seq = a.max_seq; p.qscale = a.qscale;
     p.ln_stats = (const float2*)a.ln_stats; p.ln_groups = a.ln_groups; p.ln_gw = a.ln_gw; p.ln_cols = a.ln_cols;
-    p.ln_eps = a.ln_eps; p.c1 = a.c1; p.c2 = a.c2;
+    p.ln_eps = a.ln_eps; p.ln_inv = a.ln_cols ? 1.0f / (float)a.ln_cols : 0.f; p.c1 = a.c1; p.c2 = a.c2;
     p.resid = a.resid; p.gamma = (const bf16_t*)a.gamma; p.stats_out = (float2*)a.stats_out; p.counters = a.counters;
     p.wscale = a.wscale;
     return p;

@@ -576,7 +576,7 @@ __global__ __launch_bounds__(256, 1) void gemm_ring_kernel(const u32x4* __restri
     // LM head with the final LayerNorm folded in (decode steps of up to 64 rows, whose rows are one tile of 64: MW = 1): this
     // wavefront's share of the rows' statistics
     constexpr bool FOLDS = MODE == MODE_LMHEAD && MW == 1;
-    [[maybe_unused]] LnLoads lnl[FOLDS ? 2 : 1];
+    [[maybe_unused]] LnLoads<4> lnl[FOLDS ? 2 : 1];
     if constexpr (FOLDS) {
         if (p.ln_stats) {
 #pragma unroll
@@ -701,11 +701,11 @@ __global__ __launch_bounds__(256, 1) void gemm_ring_kernel(const u32x4* __restri
         __syncthreads();
         if constexpr (FOLDS) {
             if (p.ln_stats) {
-                float* lnp = lds + 4 * 64 * 64;
+                float4* lnp = reinterpret_cast<float4*>(lds + 4 * 64 * 64);
 #pragma unroll
-                for (int x = 0; x < 2; ++x) ln_partial<4>(lnl[x], p, min(tm * 2 + x, MT32 - 1), wave, lane, lnp + x * 4 * 4 * 32);
+                for (int x = 0; x < 2; ++x) ln_partial<4>(lnl[x], p, min(tm * 2 + x, MT32 - 1), wave, lane, lnp + x * 4 * 32);
                 __syncthreads();
-                fold[0] = ln_finish<4>(lnp + wm * 4 * 4 * 32, lane & 31, p);
+                fold[0] = ln_finish<4>(lnp + wm * 4 * 32, lane & 31, p);
             }
         }
         lm_head_tile<MW>(p, acc, fold, tm * Sh::TM + wm * 32 * MW, tn * 256 + wn * 128, tn * 2 + wn, lane,

@@ -204,27 +204,42 @@ __global__ __launch_bounds__(THREADS) void ln_row_kernel(float* __restrict__ r, 
 // weights and applies mean and rstd in its epilogue, and W gamma, W beta are vectors computed
 // once per weight update.
 
-// Row m of a decode step: x = tok_emb[id] + pos_emb[cur_len + pos_offset]; one wavefront per
-// (column group, row), four columns per lane (gw <= 256).
+// Row m of a decode step: x = tok_emb[id] + pos_emb[cur_len + pos_offset], four columns per lane.  A wavefront takes the
+// column groups that fit its lanes whole (gw <= 256; one lane group of gw / 4 lanes to each).  What bounds it is the chain
+// from the state and the ids to the table rows; the sums over a group's lanes are data-parallel moves where gw / 4 is a power of two.
+__device__ __forceinline__ float group_sum(float v, int lanes, int first) {
+    switch (lanes) {  // (the same for the whole launch)
+        case 4: return lane_sum<4>(v);
+        case 8: return lane_sum<8>(v);
+        case 16: return lane_sum<16>(v);
+        case 32: return lane_sum<32>(v);
+        case 64: return lane_sum<64>(v);
+    }
+    float t = 0.f;
+    for (int i = 0; i < lanes; ++i) t += __shfl(v, first + i);
+    return t;
+}
 __global__ __launch_bounds__(64) void embed_ln_kernel(const int32_t* __restrict__ ids, int id_stride,
                                                       const bf16_t* __restrict__ tok, const bf16_t* __restrict__ pos,
                                                       he_dev_state* __restrict__ st, int V, int pos_offset,
-                                                      int H, int gw, int groups, const bf16_t* __restrict__ gamma,
+                                                      int H, int gw, int groups, int per_wave, const bf16_t* __restrict__ gamma,
                                                       float* __restrict__ r, u32x4* __restrict__ xb,
                                                       float2* __restrict__ stats, he_step_sampling sp) {
     if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) store_sampling(st, sp);
-    const int g = blockIdx.x, m = blockIdx.y, lane = threadIdx.x;
+    const int m = blockIdx.y, lane = threadIdx.x, lanes = gw >> 2;
+    const int sub = min(lane / lanes, per_wave), in_group = lane - sub * lanes;  // (lanes past the last whole group: idle)
+    const int g = blockIdx.x * per_wave + sub, cols = g < groups ? min(gw, H - g * gw) : 0, c0 = g * gw + 4 * in_group;
+    const bool live = sub < per_wave && 4 * in_group < cols;
+    uint2 gg = make_uint2(0, 0);
+    if (live) gg = *reinterpret_cast<const uint2*>(gamma + c0);
     const int b = sp.start ? m : row_seq(st, m, 1);  // one row per running sequence here
     int id = ids[(size_t)b * id_stride];
     id = id < 0 ? 0 : (id >= V ? V - 1 : id);
     const size_t prow = (size_t)((sp.start ? 0 : seq_len(st, b)) + pos_offset);
-    const int cols = min(gw, H - g * gw), c0 = g * gw + 4 * lane;
-    const bool live = 4 * lane < cols;
     float x0 = 0.f, x1 = 0.f, x2 = 0.f, x3 = 0.f;
     if (live) {
         const uint2 t = *reinterpret_cast<const uint2*>(tok + (size_t)id * H + c0);
         const uint2 q = *reinterpret_cast<const uint2*>(pos + prow * H + c0);
-        const uint2 gg = *reinterpret_cast<const uint2*>(gamma + c0);
         x0 = bf_lo(t.x) + bf_lo(q.x);
         x1 = bf_hi(t.x) + bf_hi(q.x);
         x2 = bf_lo(t.y) + bf_lo(q.y);
@@ -234,16 +249,15 @@ __global__ __launch_bounds__(64) void embed_ln_kernel(const int32_t* __restrict_
         reinterpret_cast<uint2*>(xb + slot)[(c0 >> 2) & 1] =
             make_uint2(pack2(x0 * bf_lo(gg.x), x1 * bf_hi(gg.x)), pack2(x2 * bf_lo(gg.y), x3 * bf_hi(gg.y)));
     }
-    float s = (x0 + x1) + (x2 + x3);
-    for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o);
-    const float mean = s / (float)cols;
+    const int first = sub * lanes;
+    const float mean = group_sum((x0 + x1) + (x2 + x3), lanes, first) / (float)max(cols, 1);
     float q2 = 0.f;
     if (live) {
         const float d0 = x0 - mean, d1 = x1 - mean, d2 = x2 - mean, d3 = x3 - mean;
         q2 = (d0 * d0 + d1 * d1) + (d2 * d2 + d3 * d3);
     }
-    for (int o = 32; o > 0; o >>= 1) q2 += __shfl_xor(q2, o);
-    if (lane == 0) stats[((size_t)(m >> 5) * groups + g) * 32 + (m & 31)] = make_float2(mean, q2);
+    q2 = group_sum(q2, lanes, first);
+    if (live && in_group == 0) stats[((size_t)(m >> 5) * groups + g) * 32 + (m & 31)] = make_float2(mean, q2);
 }
 
 // c1[n] = sum_k W[n][k] gamma[k], c2[n] = sum_k W[n][k] beta[k] from the tiled weights: a workgroup per 32-row tile (lane =
@@ -323,9 +337,9 @@ void bf16_gather_last_rows(hipStream_t s, const float* r, const float* q, float*
 void bf16_embed_ln(hipStream_t s, const int32_t* ids, int id_stride, const void* tok, const void* pos,
                    he_dev_state* st, int B, int H, int V, int pos_offset, int gw, const void* gamma, float* r,
                    void* x_blocks, float* stats, const he_step_sampling& sp) {
-    const int groups = (H + gw - 1) / gw;
-    embed_ln_kernel<<<dim3(groups, B), 64, 0, s>>>(ids, id_stride, (const bf16_t*)tok, (const bf16_t*)pos, st, V,
-                                                   pos_offset, H, gw, groups, (const bf16_t*)gamma, r,
+    const int groups = (H + gw - 1) / gw, per_wave = 256 / gw;
+    embed_ln_kernel<<<dim3((groups + per_wave - 1) / per_wave, B), 64, 0, s>>>(ids, id_stride, (const bf16_t*)tok, (const bf16_t*)pos, st, V,
+                                                   pos_offset, H, gw, groups, per_wave, (const bf16_t*)gamma, r,
                                                    (u32x4*)x_blocks, (float2*)stats, sp);
 }
 

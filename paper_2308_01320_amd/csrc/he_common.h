@@ -76,6 +76,10 @@ __device__ __forceinline__ void advance_state(he_dev_state* st, int tokens, int 
 __device__ __forceinline__ void advance_state_by_last(he_dev_state* st, int tokens, int steps) {
     __shared__ int last;
     __syncthreads();
+    if (gridDim.x == 1) {  // nobody to wait for
+        advance_state(st, tokens, steps);
+        return;
+    }
     if (threadIdx.x == 0) {
         asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
         last = __hip_atomic_fetch_add(&st->arrivals, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (int)gridDim.x - 1;
@@ -84,6 +88,65 @@ __device__ __forceinline__ void advance_state_by_last(he_dev_state* st, int toke
     if (!last) return;
     advance_state(st, tokens, steps);
     if (threadIdx.x == 0) __hip_atomic_store(&st->arrivals, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// ---- sums and maxima over lanes
+//
+// Data-parallel moves inside the vector unit: some ten cycles a step, where a shuffle goes through LDS (a hundred).  The last
+// steps of the kernels are chains of these.  Every lane of the wavefront takes part.
+// The lane l ^ 8 of a row of 16, l ^ 16 and l ^ 32 for any values; xor_1/2 likewise; the two mirrors stand for l ^ 4 and l ^ 8 where
+// the four (eight) lanes below already hold the same value.
+template <int CTRL>
+__device__ __forceinline__ float lane_dpp(float v) {
+    return __uint_as_float((uint32_t)__builtin_amdgcn_mov_dpp((int)__float_as_uint(v), CTRL, 0xF, 0xF, false));
+}
+__device__ __forceinline__ float lane_xor1(float v) { return lane_dpp<0xB1>(v); }          // quad_perm [1, 0, 3, 2]
+__device__ __forceinline__ float lane_xor2(float v) { return lane_dpp<0x4E>(v); }          // quad_perm [2, 3, 0, 1]
+__device__ __forceinline__ float lane_mirror8(float v) { return lane_dpp<0x141>(v); }      // l ^ 7
+__device__ __forceinline__ float lane_mirror16(float v) { return lane_dpp<0x140>(v); }     // l ^ 15
+__device__ __forceinline__ float lane_xor8(float v) { return lane_dpp<0x128>(v); }         // row_ror 8
+// v of the lower and of the upper lane of the pair (l, l ^ 16) or (l, l ^ 32)
+struct LanePair { float lo, hi; };
+__device__ __forceinline__ LanePair lane_pair16(float v) {
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    return {__uint_as_float(r[0]), __uint_as_float(r[1])};
+}
+__device__ __forceinline__ LanePair lane_pair32(float v) {
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    return {__uint_as_float(r[0]), __uint_as_float(r[1])};
+}
+__device__ __forceinline__ float lane_sum16_apart(float v) { const LanePair p = lane_pair16(v); return p.lo + p.hi; }
+__device__ __forceinline__ float lane_sum32_apart(float v) { const LanePair p = lane_pair32(v); return p.lo + p.hi; }
+__device__ __forceinline__ float lane_max16_apart(float v) { const LanePair p = lane_pair16(v); return fmaxf(p.lo, p.hi); }
+__device__ __forceinline__ float lane_max32_apart(float v) { const LanePair p = lane_pair32(v); return fmaxf(p.lo, p.hi); }
+// over the N lanes of an aligned group (all of them get it)
+template <int N>
+__device__ __forceinline__ float lane_sum(float v) {
+    if (N >= 2) v += lane_xor1(v);
+    if (N >= 4) v += lane_xor2(v);
+    if (N >= 8) v += lane_mirror8(v);
+    if (N >= 16) v += lane_mirror16(v);
+    if (N >= 32) v = lane_sum16_apart(v);
+    if (N >= 64) v = lane_sum32_apart(v);
+    return v;
+}
+template <int N>
+__device__ __forceinline__ float lane_max(float v) {
+    if (N >= 2) v = fmaxf(v, lane_xor1(v));
+    if (N >= 4) v = fmaxf(v, lane_xor2(v));
+    if (N >= 8) v = fmaxf(v, lane_mirror8(v));
+    if (N >= 16) v = fmaxf(v, lane_mirror16(v));
+    if (N >= 32) v = lane_max16_apart(v);
+    if (N >= 64) v = lane_max32_apart(v);
+    return v;
+}
+// over the lanes N (8, 16 or 32) apart
+template <int N>
+__device__ __forceinline__ float lane_sum_apart(float v) {
+    if (N <= 8) v += lane_xor8(v);
+    if (N <= 16) v = lane_sum16_apart(v);
+    if (N <= 32) v = lane_sum32_apart(v);
+    return v;
 }
 
 __device__ __forceinline__ float bf16_to_f32(bf16_t v) { return __uint_as_float(((uint32_t)v) << 16); }

@@ -245,7 +245,7 @@ struct LaunchTimer {
 
 // 8-bit weights: where the row scales of layer l live, and the layer as bf16 blocks (dequantised into the
 // scratch layer, on the engine's stream, for the GEMMs that read 32x16 blocks: prompt rows, scoring,
-// decode steps of more than 32 rows).
+// decode steps of more than 64 rows).
 struct Scales { float *wqkv, *wo, *w1, *w2; };
 Scales scales_of(const he_engine* e, int l) {
     const size_t H = e->cfg.hidden, F = e->cfg.ffn;
@@ -355,13 +355,8 @@ void pass_decode_bf16(he_engine* e, const int32_t* d_ids, int id_stride, int B, 
     // residual row (the embedding, the out-projection, FC2) leaves gamma * x as half blocks
     // and statistics per group of columns; the column groups are the producer's workgroups.
     int gw1, ks1, gw2, ks2;  // column-group widths after the out-projection / after FC2 and the embedding
-    if (e->w8) {
-        bf16_store_plan_w8(H, H, e->part_floats, &gw1, &ks1);
-        bf16_store_plan_w8(H, F, e->part_floats, &gw2, &ks2);
-    } else {
-        bf16_store_plan(B, H, H, e->part_floats, &gw1, &ks1);
-        bf16_store_plan(B, H, F, e->part_floats, &gw2, &ks2);
-    }
+    bf16_store_plan(B, H, H, e->part_floats, e->w8, &gw1, &ks1);
+    bf16_store_plan(B, H, F, e->part_floats, e->w8, &gw2, &ks2);
     if (!L) gw2 = 128;
     const size_t split = (size_t)B * H;
     auto fold = [&](bf16_gemm_args& a, int gw, const CVec& cv) {
@@ -445,13 +440,8 @@ void pass_last_token_bf16(he_engine* e, int B, int S, int32_t* ids_out, float* l
     base.st = e->st; base.S = 1; base.H = H; base.n_heads = c.n_heads; base.max_batch = c.max_batch;
     base.max_seq = c.max_seq_len;
     int gw1, ks1, gw2, ks2;
-    if (e->w8) {
-        bf16_store_plan_w8(H, H, e->part_floats, &gw1, &ks1);
-        bf16_store_plan_w8(H, F, e->part_floats, &gw2, &ks2);
-    } else {
-        bf16_store_plan(B, H, H, e->part_floats, &gw1, &ks1);
-        bf16_store_plan(B, H, F, e->part_floats, &gw2, &ks2);
-    }
+    bf16_store_plan(B, H, H, e->part_floats, e->w8, &gw1, &ks1);
+    bf16_store_plan(B, H, F, e->part_floats, e->w8, &gw2, &ks2);
     const size_t split = (size_t)B * H;
     float *r_last = e->tail_buf, *q_last = e->tail_buf + (size_t)c.max_batch * H;
     bf16_gather_last_rows(s, e->resid, e->qbuf, r_last, q_last, B, S, H, e->st, S - 1);
@@ -505,7 +495,7 @@ void pass_last_token_bf16(he_engine* e, int B, int S, int32_t* ids_out, float* l
     e->step += 1;
 }
 
-// The same pass for more than 64 sequences (more than 32 with 8-bit weights): the rows no longer fit the
+// The same pass for more than 64 sequences: the rows no longer fit the
 // weight-streaming kernels, so the GEMMs are the prompt-pass tiles (weights shared through LDS by all rows), cut along k until they fill the
 // chip; LayerNorms are kernels of their own again and add the partial sums.
 void pass_decode_wide_bf16(he_engine* e, const int32_t* d_ids, int id_stride, int B, int32_t* ids_out, float* lp_out,
@@ -575,13 +565,14 @@ void pass_decode_wide_bf16(he_engine* e, const int32_t* d_ids, int id_stride, in
     e->step += 1;
 }
 
-// Decode steps of up to 32 sequences, and of up to 64 with bf16 weights (two 32-row slices per workgroup),
-// stream the weights through the decode GEMMs; larger ones take the prompt pass's tiles.
-bool wide_decode(const he_engine* e, int B) { return B > 64 || (B > 32 && e->w8); }
+// Decode steps of up to 64 sequences (two 32-row slices per workgroup) stream the weights through the decode GEMMs; larger ones
+// take the prompt pass's tiles.  (8-bit weights too: a step on the tiles dequantises every layer first, 157 us of a 13B layer, whose
+// four streamed GEMMs take 89 us with 48 rows.)
+bool wide_decode(int B) { return B > 64; }
 
 he_status run_forward_bf16(he_engine* e, const int32_t* d_ids, int B, int S, int32_t* ids_out, float* lp_out,
                            int out_stride, int out_at_step, float* d_logits_opt) {
-    if (S > 1 && e->cfg.n_layers > 0 && !wide_decode(e, B)) {
+    if (S > 1 && e->cfg.n_layers > 0 && !wide_decode(B)) {
         // every prompt token through the tiled GEMMs up to the last layer's keys and values, then the rest of
         // that layer for the last tokens alone
         pass_tiled_bf16(e, d_ids, S, B, S, false, nullptr, nullptr, true);
@@ -589,7 +580,7 @@ he_status run_forward_bf16(he_engine* e, const int32_t* d_ids, int B, int S, int
         return check_hip(e, hipGetLastError(), "kernel launch");
     }
     if (S > 1) pass_tiled_bf16(e, d_ids, S, B, S - 1);
-    if (wide_decode(e, B)) pass_decode_wide_bf16(e, d_ids + (S - 1), S, B, ids_out, lp_out, out_stride, out_at_step, d_logits_opt);
+    if (wide_decode(B)) pass_decode_wide_bf16(e, d_ids + (S - 1), S, B, ids_out, lp_out, out_stride, out_at_step, d_logits_opt);
     else pass_decode_bf16(e, d_ids + (S - 1), S, B, ids_out, lp_out, out_stride, out_at_step, d_logits_opt);
     return check_hip(e, hipGetLastError(), "kernel launch");
 }
@@ -695,8 +686,8 @@ he_status run_forward(he_engine* e, const int32_t* d_ids, int B, int S, int32_t*
 // Classes of decode steps by their row count, between which dropping rows pays for two new graphs: 16-row halves of the
 // activation slices the weight-streaming GEMMs multiply by (up to 64 rows), every 128 rows above (the matrix-core GEMMs'
 // tiles there hold 64, 128 or 192).
-int step_cost_class(const he_engine* e, int rows) {
-    return wide_decode(e, rows) ? 4 + (rows + 127) / 128 : (rows + 15) / 16;
+int step_cost_class(int rows) {
+    return wide_decode(rows) ? 4 + (rows + 127) / 128 : (rows + 15) / 16;
 }
 
 void drop_step_graph(he_engine* e) {
@@ -1033,7 +1024,7 @@ he_status he_decode_step_static(he_engine* e, const int32_t* d_in_ids, const he_
     if (e->cur_len == 0 || e->batch == 0) return fail(e, HE_ERR_STATE, "he_decode_step_static: no prompt has been prefilled");
     if (e->cur_len + 1 > e->cfg.max_seq_len) return fail(e, HE_ERR_CAPACITY, "he_decode_step_static: KV cache is full");
     if (e->cur_len + 1 > e->cfg.max_positions) return fail(e, HE_ERR_CAPACITY, "he_decode_step_static: position table exhausted");
-    if (wide_decode(e, e->batch))
+    if (wide_decode(e->batch) || (e->w8 && e->batch > 32))
         return fail(e, HE_ERR_CAPACITY, "he_decode_step_static: the batch is too large for the weight-streaming decode kernels "
                                         "(at most 64 sequences, 32 with 8-bit weights)");
     const StaticLayout L = static_layout(e, e->batch);
@@ -1128,7 +1119,7 @@ static he_status generate_impl(he_engine* e, const char* who, const int32_t* d_p
             rc = check_hip(e, r, "reading the active count");
             const int active = *e->host_active;
             if (rc == HE_OK && active == 0) break;
-            if (rc == HE_OK && e->fast && active < rows && step_cost_class(e, active) < step_cost_class(e, rows)) {
+            if (rc == HE_OK && e->fast && active < rows && step_cost_class(active) < step_cost_class(rows)) {
                 launch_compact_rows(e->stream, e->st, rows);
                 rows = active;
                 if (use_graph) rc = ensure_step_graph(e, rows, G);
@@ -1293,7 +1284,7 @@ he_status he_plan_pass_gemm(const he_config* cfg, int rows, int which, int scori
 he_status he_decode_scratch_account(const he_config* cfg, int B, int which, int cus, he_scratch_account* out) {
     if (!out || check_config(cfg) || check_shape(cfg) || !is_fast(*cfg)) return HE_ERR_INVALID_ARG;
     if (B < 1 || B > cfg->max_batch || B > 64 || (which != 0 && which != 1) || cus < 0) return HE_ERR_INVALID_ARG;
-    if (cfg->weights_fp8 && B > 32) return HE_ERR_INVALID_ARG;  // those steps take the wide path
+    if (cfg->weights_fp8 && B > 32) return HE_ERR_INVALID_ARG;  // (answered for one 32-row slice)
     const Sizes z = sizes_of(*cfg);
     const int H = cfg->hidden, K = which ? cfg->ffn : H;
     const size_t cap = z.part / sizeof(float);
@@ -1350,8 +1341,8 @@ he_status he_kernel_sweep(he_engine* e, int kernel_class, int reps) {
     for (int r = 0; r < reps; ++r)
         for (int l = 0; l < c.n_layers; ++l) {
             bf16_gemm_args a = base;
-            if (wide_decode(e, B)) {  // the GEMMs of the wide decode step
-                if (e->w8) return fail(e, HE_ERR_STATE, "he_kernel_sweep: with 8-bit weights only for batches up to 32");
+            if (e->w8 && B > 32) return fail(e, HE_ERR_STATE, "he_kernel_sweep: with 8-bit weights only for batches up to 32");
+            if (wide_decode(B)) {  // the GEMMs of the wide decode step
                 if (kernel_class == HE_K_FC1) {
                     a.bias = e->layers[l].b1; a.out_blocks = e->hblk;
                     bf16_gemm_tiled(e->stream, EPI_BIAS_RELU, e->tiled[l].w1, e->ablk, B, F, H, a, e->part, e->tiled_part_floats);
@@ -1367,8 +1358,7 @@ he_status he_kernel_sweep(he_engine* e, int kernel_class, int reps) {
             if (kernel_class == HE_K_FC1) {
                 a.bias = e->layers[l].b1; a.out_blocks = e->hblk;
                 int gw1, ks1;
-                if (e->w8) bf16_store_plan_w8(H, H, e->part_floats, &gw1, &ks1);
-                else bf16_store_plan(B, H, H, e->part_floats, &gw1, &ks1);
+                bf16_store_plan(B, H, H, e->part_floats, e->w8, &gw1, &ks1);
                 if (e->w8) a.wscale = scales_of(e, l).w1;
                 a.ln_stats = e->ln_stats; a.ln_gw = gw1; a.ln_groups = (H + a.ln_gw - 1) / a.ln_gw; a.ln_cols = H;
                 a.ln_eps = c.ln_eps; a.c1 = cvec_fc1(e, l).c1; a.c2 = cvec_fc1(e, l).c2;
@@ -1378,8 +1368,7 @@ he_status he_kernel_sweep(he_engine* e, int kernel_class, int reps) {
                 // into the residual rows and rewrites the blocks and statistics the next GEMM reads
                 const bool fc2 = kernel_class == HE_K_FC2;
                 int gw, ks;
-                if (e->w8) bf16_store_plan_w8(H, fc2 ? F : H, e->part_floats, &gw, &ks);
-                else bf16_store_plan(B, H, fc2 ? F : H, e->part_floats, &gw, &ks);
+                bf16_store_plan(B, H, fc2 ? F : H, e->part_floats, e->w8, &gw, &ks);
                 if (e->w8) a.wscale = fc2 ? scales_of(e, l).w2 : scales_of(e, l).wo;
                 a.out = e->part; a.out_split = split; a.out_capacity = e->part_floats; a.resid = e->resid;
                 a.bias = fc2 ? e->layers[l].b2 : e->layers[l].bo;

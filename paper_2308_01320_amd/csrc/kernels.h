@@ -76,11 +76,9 @@ void bf16_tile_rows(hipStream_t s, const void* src, void* dst, int R, int K);
 // dst = tiled bf16(src + scale * B A): A bf16 [rank, K], B bf16 [R, rank]
 void bf16_tile_rows_lora(hipStream_t s, const void* src, void* dst, int R, int K, const void* A, const void* B, int rank,
                          float scale);
-// decode-shaped STORE GEMM of M rows: weight tiles per workgroup (its column group is 32*nt wide) and k-splits
-void bf16_store_shape(int M, int N, int K, int* nt, int* ks);
-// EPI_STORE_LN GEMM of M <= 32 rows: columns per workgroup (= per group of LayerNorm statistics) and k-splits;
-// capacity = floats of k-split scratch available (the value passed as bf16_gemm_args.out_capacity)
-void bf16_store_plan(int M, int N, int K, size_t capacity, int* group_cols, int* ks);
+// EPI_STORE_LN GEMM of M <= 64 rows: columns per workgroup (= per group of LayerNorm statistics) and k-splits;
+// capacity = floats of k-split scratch available (the value passed as bf16_gemm_args.out_capacity); w8 != 0: 8-bit weights
+void bf16_store_plan(int M, int N, int K, size_t capacity, int w8, int* group_cols, int* ks);
 // floats of k-split scratch that launch may index (upper bound); w8 != 0: the 8-bit-weight plan
 size_t bf16_store_need(int M, int N, int K, size_t capacity, int w8);
 // What that launch indexes, from the launcher's own choice of kernel variant and grid (host logic, no launch).
@@ -100,6 +98,9 @@ void bf16_wvec(hipStream_t s, const void* Wp, int N, int K, const void* gamma, c
 // rows in slices of 32 (a decode step of up to 32 sequences): EPI_BIAS_RELU, EPI_QKV or EPI_STORE_LN;
 // X: the activations as tiled half blocks; ksplit is ignored (the plan decides)
 void bf16_gemm_skinny(hipStream_t s, int mode, const void* Wp, const void* X, int M, int N, int K, int ksplit,
+                      const bf16_gemm_args& a);
+// ... on 8-bit weights: Wp holds E4M3 units, `units` of them to a workgroup
+void bf16_gemm_units8(hipStream_t s, int mode, const void* Wp, const void* X, int M, int N, int K, int units, int ksplit,
                       const bf16_gemm_args& a);
 // Many rows (prompt and scoring passes, wide decode steps): EPI_BIAS_RELU or EPI_QKV.  part: scratch of part_floats
 // floats for the k ranges' sums where the tiles alone do not fill the chip (a second kernel then adds them and applies
@@ -130,7 +131,6 @@ void fp8_quant_rows(hipStream_t s, const void* src, const int* exps, void* codes
 void fp8_quant_units(hipStream_t s, const void* src, const int* exps, void* units, int R, int K);
 // units -> half 32x16 blocks (what the tiled GEMMs read)
 void fp8_dequant_units(hipStream_t s, const void* units, const float* scales, void* dst_blocks, int R, int K);
-void bf16_store_plan_w8(int N, int K, size_t capacity, int* group_cols, int* ks);
 // advance: the step ends here (else launch_advance_state follows)
 void bf16_lm_head(hipStream_t s, const void* Wp, const void* X, int B, int V, int K,
                   he_dev_state* st, float* logits_opt, float* stats, int* stats_idx, int32_t* ids_out,
