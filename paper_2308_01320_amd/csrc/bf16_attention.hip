@@ -13,17 +13,14 @@ namespace {
 // shuffles, kept in LDS, soft-maxed, then the same lanes accumulate p_j * V[j].
 // The output goes out as tiled half blocks for the out-projection GEMM.
 //
-// WAVES: with many (row, head) pairs a workgroup is four wavefronts, several share a CU and the launch runs at the HBM rate
-// (6.2 TB/s at 32 sequences x 40 heads x 384 positions).  With few, what bounds it is the serial chain of load rounds of one
-// workgroup, and more wavefronts shorten it: 16 where a CU has at most one pair, 8 where it has two, but no more than one
-// round over a full cache needs (waves without keys only lengthen the barriers).  Measured, 4 wavefronts -> the rule's:
-// 1 x 32 heads of 64, 516 keys: 12.7 -> 8.6 us; 7 x 32 heads of 128, 100-250 keys: 11.8 -> 9.0; 2 x 40 heads of 128,
-// 1999 keys: 71.7 -> 26.0; 16 x 32 heads of 64 in a cache of 64: 5.8 (8 wavefronts: 6.8).
-template <int D, int WAVES>
-__global__ __launch_bounds__(64 * WAVES) void attn_kernel(const float* __restrict__ q, const half_t* __restrict__ kv,
+// Two passes with a score buffer, four wavefronts, several workgroups to a CU: the form for many (row, head) pairs and long caches, which
+// run at the HBM rate (6.2 TB/s at 32 sequences x 40 heads x 384 positions).  attn_few_kernel below is the other.
+template <int D>
+__global__ __launch_bounds__(256) void attn_kernel(const float* __restrict__ q, const half_t* __restrict__ kv,
                                                    u32x4* __restrict__ o,
                                                    const he_dev_state* __restrict__ st, int S, int layer, int H,
                                                    int n_heads, int max_batch, int max_seq) {
+    constexpr int WAVES = 4;
     constexpr int LPK = D / 8;     // lanes per key
     constexpr int KPW = 64 / LPK;  // keys per wavefront load
     constexpr int KR = WAVES * KPW;  // keys per workgroup round
@@ -146,6 +143,119 @@ __global__ __launch_bounds__(64 * WAVES) void attn_kernel(const float* __restric
         }
         const size_t slot = block_slot(m, h * D + threadIdx.x * 8, H >> 4);
         o[slot] = u32x4{pack2(ov[0], ov[1]), pack2(ov[2], ov[3]), pack2(ov[4], ov[5]), pack2(ov[6], ov[7])};
+    }
+}
+
+// The same in one pass, for few (row, head) pairs and short caches: what bounds those is not the stream but the chain from the state
+// to the output, so there is one barrier and no score buffer.  Every group of D/8 lanes keeps the soft-max state of its own keys (largest
+// score, sum, weighted values), K and V of a round are on their way together, one round ahead; the groups of a wavefront are
+// merged with data-parallel moves, the wavefronts through LDS.  us, attn_kernel with the number of wavefronts that suited it -> this:
+// 1 x 32 heads of 64, 516 keys 8.3 -> 6.9, 130 keys 5.0 -> 3.9; 7 x 32 heads of 128, 180 keys 8.5 -> 7.0; 2 x 40 of 128, 1999 keys
+// 26.9 -> 24.5; 16 x 32 of 64, 56 keys 5.6 -> 4.6; 32 x 32 of 64, 64 keys 7.5 -> 5.9; 96 x 40 of 128, 80 keys 31.0 -> 29.0; but 32 x 40
+// of 128: 160 keys 19.6 -> 19.4, 384 keys 39.6 -> 41.2.
+template <int D, int WAVES>
+__global__ __launch_bounds__(64 * WAVES) void attn_few_kernel(const float* __restrict__ q, const half_t* __restrict__ kv,
+                                                       u32x4* __restrict__ o, const he_dev_state* __restrict__ st, int S, int layer,
+                                                       int H, int n_heads, int max_batch, int max_seq) {
+    constexpr int LPK = D / 8, KPW = 64 / LPK, KR = WAVES * KPW, U = 4, STEP = KR * U;
+    static_assert(D <= 64 * WAVES, "an output value per thread");
+    __shared__ float2 ml[WAVES];          // a wavefront's largest score and sum
+    __shared__ float ored[WAVES][D];      // ... and its weighted values
+    const int m = blockIdx.x, h = blockIdx.y;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int sub = lane % LPK, grp = lane / LPK;
+    const float4 qa = *reinterpret_cast<const float4*>(q + (size_t)m * H + h * D + sub * 8);
+    const float4 qb = *reinterpret_cast<const float4*>(q + (size_t)m * H + h * D + sub * 8 + 4);
+    const int b = row_seq(st, m, S), t = S == 1 ? 0 : m % S, T = seq_len(st, b) + t - row_pad(st, b) + 1;
+    if (seq_done(st, b)) return;  // the sequence has ended: its row's output is not used any more
+    if (T <= 0) {                 // a padding row: nothing to attend to, nothing reads the output; keep it finite
+        if (wave == 0 && grp == 0) o[block_slot(m, h * D + sub * 8, H >> 4)] = u32x4{0u, 0u, 0u, 0u};
+        return;
+    }
+    const u32x4* Kp = reinterpret_cast<const u32x4*>(kv + kv_index(layer, 0, b, h, 0, max_batch, n_heads, max_seq, D));
+    const u32x4* Vp = reinterpret_cast<const u32x4*>(kv + kv_index(layer, 1, b, h, 0, max_batch, n_heads, max_seq, D));
+    const int jw = wave * KPW + grp;
+    auto load_rows = [&](u32x4 (&dst)[U], const u32x4* src, int base) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int j = base + u * KR + jw;
+            dst[u] = j < T ? __builtin_nontemporal_load(src + (size_t)j * LPK + sub) : u32x4{0u, 0u, 0u, 0u};
+        }
+    };
+    float mx = -INFINITY, sum = 0.f, acc[8] = {};
+    u32x4 k[U], v[U];
+    load_rows(k, Kp, 0);
+    load_rows(v, Vp, 0);
+    for (int base = 0; base < T; base += STEP) {
+        float s[U];
+        float top = mx;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            float x = qa.x * half_lo(k[u].x);
+            x = fmaf(qa.y, half_hi(k[u].x), x);
+            x = fmaf(qa.z, half_lo(k[u].y), x);
+            x = fmaf(qa.w, half_hi(k[u].y), x);
+            x = fmaf(qb.x, half_lo(k[u].z), x);
+            x = fmaf(qb.y, half_hi(k[u].z), x);
+            x = fmaf(qb.z, half_lo(k[u].w), x);
+            x = fmaf(qb.w, half_hi(k[u].w), x);
+            x = lane_sum<LPK>(x);
+            s[u] = base + u * KR + jw < T ? x : -INFINITY;
+            top = fmaxf(top, s[u]);
+        }
+        const bool more = base + STEP < T;  // (the same for the whole workgroup)
+        if (more) load_rows(k, Kp, base + STEP);
+        // (nothing above -inf yet: the state stays what it is)
+        const float ref = top > -INFINITY ? top : 0.f, keep = expf(mx - ref);
+        float pr[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) pr[u] = base + u * KR + jw < T ? expf(s[u] - ref) : 0.f;
+        mx = top;
+        sum = fmaf(sum, keep, (pr[0] + pr[1]) + (pr[2] + pr[3]));
+#pragma unroll
+        for (int e = 0; e < 8; ++e) acc[e] *= keep;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            acc[0] = fmaf(pr[u], half_lo(v[u].x), acc[0]);
+            acc[1] = fmaf(pr[u], half_hi(v[u].x), acc[1]);
+            acc[2] = fmaf(pr[u], half_lo(v[u].y), acc[2]);
+            acc[3] = fmaf(pr[u], half_hi(v[u].y), acc[3]);
+            acc[4] = fmaf(pr[u], half_lo(v[u].z), acc[4]);
+            acc[5] = fmaf(pr[u], half_hi(v[u].z), acc[5]);
+            acc[6] = fmaf(pr[u], half_lo(v[u].w), acc[6]);
+            acc[7] = fmaf(pr[u], half_hi(v[u].w), acc[7]);
+        }
+        if (more) load_rows(v, Vp, base + STEP);
+    }
+    // the groups of the wavefront
+    float wmx = mx;
+    if (LPK <= 8) wmx = fmaxf(wmx, lane_xor8(wmx));
+    wmx = lane_max32_apart(lane_max16_apart(wmx));
+    const float own = mx > -INFINITY ? expf(mx - wmx) : 0.f;
+    sum = lane_sum_apart<LPK>(sum * own);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) acc[e] = lane_sum_apart<LPK>(acc[e] * own);
+    if (lane == 0) ml[wave] = make_float2(wmx, sum);
+    if (grp == 0) {
+        float4* dst = reinterpret_cast<float4*>(&ored[wave][sub * 8]);
+        dst[0] = make_float4(acc[0], acc[1], acc[2], acc[3]);
+        dst[1] = make_float4(acc[4], acc[5], acc[6], acc[7]);
+    }
+    __syncthreads();
+    if (threadIdx.x >= D) return;
+    // the wavefronts: lane i of 16 knows wavefront i's weight
+    const float2 e = ml[min(lane & 15, WAVES - 1)];
+    const bool counts = (lane & 15) < WAVES && e.x > -INFINITY;
+    const float all = lane_max<16>(e.x);
+    const float w = counts ? expf(e.x - all) : 0.f, total = lane_sum<16>(counts ? e.y * w : 0.f);
+    float out = 0.f;
+#pragma unroll
+    for (int x = 0; x < WAVES; ++x) out = fmaf(__uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(w), x)), ored[x][threadIdx.x], out);
+    out *= 1.0f / total;
+    const float next = lane_xor1(out);
+    if ((threadIdx.x & 1) == 0) {
+        const int i = threadIdx.x, n = h * D + i;
+        reinterpret_cast<uint32_t*>(o + block_slot(m, n & ~7, H >> 4))[(n & 7) >> 1] = pack2(out, next);
     }
 }
 
@@ -518,13 +628,16 @@ __global__ __launch_bounds__(256, 2) void attn_prompt_mfma_kernel(const float* _
 
 // ------------------------------------------------------------------ launchers
 
-// Wavefronts per (row, head): by the sizes of the launch and of the cache, never by how much of it is filled, so that a captured
-// step and the same step launched alone add up in the same order.
+// Wavefronts of a (row, head) in the one-pass form, or 0 for the two-pass one.  The rule looks at the cache's size and not at how far it
+// is filled: a captured step must add up like the eager one.  More than two pairs to a CU: from some 200 keys on the two-pass form is
+// ahead (measured between 160, even, and 200, 43.6 us against 44.2), below it two wavefronts.  Else as many as one round over a
+// full cache takes, at most four, or eight where a CU has at most one pair.
 static int attn_waves(long pairs, int max_seq, int d) {
     const long cus = num_cus();
-    int waves = pairs <= cus ? 16 : (pairs <= 2 * cus ? 8 : 4);
-    const int keys_per_wave = 4 * 64 / (d / 8);  // of one round
-    while (waves > 4 && (waves / 2) * keys_per_wave >= max_seq) waves /= 2;
+    if (pairs > 2 * cus) return max_seq > 192 ? 0 : 2;
+    const int keys_per_wave = 4 * 64 / (d / 8), most = pairs <= cus ? 8 : 4;  // of one round
+    int waves = 2;
+    while (waves < most && waves * keys_per_wave < max_seq) waves *= 2;
     return waves;
 }
 
@@ -532,14 +645,14 @@ template <int D>
 static void launch_attn(hipStream_t s, const float* q, const void* kv, void* o_blocks, const he_dev_state* st, int M, int S, int layer,
                         int H, int n_heads, int max_batch, int max_seq) {
     const dim3 grid(M, n_heads);
-    const size_t shm = (size_t)max_seq * sizeof(float);
-    const int waves = attn_waves((long)M * n_heads, max_seq, D);
-    if (waves == 16)
-        attn_kernel<D, 16><<<grid, 1024, shm, s>>>(q, (const half_t*)kv, (u32x4*)o_blocks, st, S, layer, H, n_heads, max_batch, max_seq);
-    else if (waves == 8)
-        attn_kernel<D, 8><<<grid, 512, shm, s>>>(q, (const half_t*)kv, (u32x4*)o_blocks, st, S, layer, H, n_heads, max_batch, max_seq);
-    else
-        attn_kernel<D, 4><<<grid, 256, shm, s>>>(q, (const half_t*)kv, (u32x4*)o_blocks, st, S, layer, H, n_heads, max_batch, max_seq);
+    const half_t* c = (const half_t*)kv;
+    u32x4* o = (u32x4*)o_blocks;
+    switch (attn_waves((long)M * n_heads, max_seq, D)) {
+        case 8: attn_few_kernel<D, 8><<<grid, 512, 0, s>>>(q, c, o, st, S, layer, H, n_heads, max_batch, max_seq); break;
+        case 4: attn_few_kernel<D, 4><<<grid, 256, 0, s>>>(q, c, o, st, S, layer, H, n_heads, max_batch, max_seq); break;
+        case 2: attn_few_kernel<D, 2><<<grid, 128, 0, s>>>(q, c, o, st, S, layer, H, n_heads, max_batch, max_seq); break;
+        default: attn_kernel<D><<<grid, 256, (size_t)max_seq * sizeof(float), s>>>(q, c, o, st, S, layer, H, n_heads, max_batch, max_seq);
+    }
 }
 
 void bf16_attn(hipStream_t s, const float* q, const void* kv, void* o_blocks, const he_dev_state* st, int M, int S, int layer, int H, int n_heads, int max_batch, int max_seq) {
