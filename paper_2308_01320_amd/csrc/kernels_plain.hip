@@ -20,24 +20,13 @@ template <typename ST>
 bool aligned4(const void* q) { return (uintptr_t)q % (4 * sizeof(ST)) == 0; }
 
 __device__ __forceinline__ float block_sum(float v, float* red) {
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
+    v = lane_sum<64>(v);
     const int w = threadIdx.x >> 6, nw = blockDim.x >> 6;
     __syncthreads();
     if ((threadIdx.x & 63) == 0) red[w] = v;
     __syncthreads();
     float t = 0.f;
     for (int i = 0; i < nw; ++i) t += red[i];
-    return t;
-}
-
-__device__ __forceinline__ float block_max(float v, float* red) {
-    for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o));
-    const int w = threadIdx.x >> 6, nw = blockDim.x >> 6;
-    __syncthreads();
-    if ((threadIdx.x & 63) == 0) red[w] = v;
-    __syncthreads();
-    float t = red[0];
-    for (int i = 1; i < nw; ++i) t = fmaxf(t, red[i]);
     return t;
 }
 
@@ -92,13 +81,11 @@ __global__ void ln_kernel(const float* __restrict__ r, const ST* __restrict__ ga
 // 16 bytes each, and instruction i of a step multiplies element i of both: the four lane groups' k values differ, but
 // by the same rule on both sides.  No LDS staging: the models of this path are small and their rows come out of L2.
 // What bounds it is the length of the dependent chain -- a launch, a load or two, a few matrix instructions -- so the k
-// range is split over KW wavefronts of a workgroup (partial sums added in wavefront order through LDS) and the few rows
-// of a decode step go 16 columns to a workgroup.  Measured on 4 rows (float, captured decode step): the 256 x 256 and
-// 256 x 1024 matrices together 139 -> 9.8 us, 768 x 256 with its LayerNorm 40 -> 6.1; the kernel before this gave a 64 x 64
-// tile to a workgroup and walked k alone.
-//   few rows (at most 64):      T = 1, KW = 8: 16 columns x 16 rows per workgroup, LayerNorm of the rows folded in
-//   many tiles (from 256 on):   T = 2, KW = 1: 64 x 64 per workgroup of four wavefronts
-//   else:                       T = 2, KW = 8: 32 x 32 per workgroup
+// range is split over the wavefronts of a workgroup (partial sums added in wavefront order through LDS) and the few rows
+// of a decode step go 16 columns to a workgroup.
+//   few rows (at most 64):      gemm_few_kernel: 16 columns x 16 rows per workgroup, LayerNorm of the rows folded in
+//   many tiles (from 256 on):   KW = 1: 64 x 64 per workgroup of four wavefronts
+//   else:                       KW = 8: 32 x 32 per workgroup
 // VEC: K is a multiple of four and the rows are aligned for 16-byte loads (8-byte ones for bf16 storage).
 template <bool VEC, typename ST>
 __device__ __forceinline__ f32x4 load_k4(const ST* row, int k, int K) {
@@ -157,14 +144,11 @@ __device__ __forceinline__ void plain_epilogue4(const PlainGemm& p, const ST* __
     }
 }
 
-template <typename ST, int T, int KW, int WN, int WM, bool VEC, bool LN>
+template <typename ST, int KW, int WN, int WM, bool VEC>
 __global__ __launch_bounds__(64 * KW * WN * WM) void gemm_kernel(const float* __restrict__ A, const ST* __restrict__ W,
-                                                                 const ST* __restrict__ bias, const ST* __restrict__ gamma,
-                                                                 const ST* __restrict__ beta, PlainGemm p) {
-    static_assert(!LN || (T == 1 && WM == 1), "the folded LayerNorm knows one 16-row tile");
-    constexpr int U = T == 1 ? 4 : 2;  // steps of 16 k requested together
+                                                                 const ST* __restrict__ bias, PlainGemm p) {
+    constexpr int T = 2, U = 2;  // U: steps of 16 k requested together
     __shared__ float red[KW > 1 ? KW : 1][T * T][4][64];
-    __shared__ float smean[16], srstd[16];
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, l16 = lane & 15, kq = 4 * (lane >> 4);
     const int kw = wave % KW, wn = (wave / KW) % WN, wm = wave / (KW * WN);
     const int n0 = (blockIdx.x * WN + wn) * 16 * T, m0 = (blockIdx.y * WM + wm) * 16 * T;
@@ -175,16 +159,15 @@ __global__ __launch_bounds__(64 * KW * WN * WM) void gemm_kernel(const float* __
 #pragma unroll
     for (int t = 0; t < T; ++t) {  // rows past the end: the last one (computed, never stored)
         wr[t] = W + (size_t)min(n0 + 16 * t + l16, p.N - 1) * p.K;
-        const size_t m = min(m0 + 16 * t + l16, p.M - 1);
-        ar[t] = A + (LN ? m * p.in_mul + p.in_add : m) * p.K;
+        ar[t] = A + (size_t)min(m0 + 16 * t + l16, p.M - 1) * p.K;
     }
     f32x4 acc[T][T];
 #pragma unroll
     for (int i = 0; i < T; ++i)
 #pragma unroll
         for (int j = 0; j < T; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-    f32x4 w[U][T], a[U][T], g[U], be[U];
-    auto load = [&](int s) {
+    f32x4 w[U][T], a[U][T];
+    for (int s = s0; s < s1; s += U) {
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const int k = s + u < s1 ? 16 * (s + u) + kq : p.K;  // (past this wavefront's range: zeros)
@@ -193,32 +176,9 @@ __global__ __launch_bounds__(64 * KW * WN * WM) void gemm_kernel(const float* __
                 w[u][t] = load_k4<VEC>(wr[t], k, p.K);
                 a[u][t] = load_k4<VEC>(ar[t], k, p.K);
             }
-            if (LN) { g[u] = load_k4<VEC>(gamma, k, p.K); be[u] = load_k4<VEC>(beta, k, p.K); }
         }
-    };
-    load(s0);
-    float mean = 0.f, rstd = 0.f;
-    if (LN) {  // mean and 1/sqrt(var + eps) of the tile's rows, a wavefront per row
-        for (int r = wave; r < 16 && m0 + r < p.M; r += KW * WN) {
-            const float* row = A + ((size_t)(m0 + r) * p.in_mul + p.in_add) * p.K;
-            float s = 0.f;
-            for (int k = lane; k < p.K; k += 64) s += row[k];
-            for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o);
-            const float mu = s / p.K;
-            float q = 0.f;
-            for (int k = lane; k < p.K; k += 64) { const float dlt = row[k] - mu; q += dlt * dlt; }
-            for (int o = 32; o > 0; o >>= 1) q += __shfl_xor(q, o);
-            if (lane == 0) { smean[r] = mu; srstd[r] = 1.0f / sqrtf(q / p.K + p.eps); }
-        }
-        __syncthreads();
-        const int r = min(l16, min(16, p.M - m0) - 1);
-        mean = smean[r]; rstd = srstd[r];
-    }
-    for (int s = s0; s < s1; s += U) {
-        if (s > s0) load(s);
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            if (LN) a[u][0] = (a[u][0] - mean) * rstd * g[u] + be[u];
+        for (int u = 0; u < U; ++u)
 #pragma unroll
             for (int e = 0; e < 4; ++e)
 #pragma unroll
@@ -226,7 +186,6 @@ __global__ __launch_bounds__(64 * KW * WN * WM) void gemm_kernel(const float* __
 #pragma unroll
                     for (int j = 0; j < T; ++j)
                         acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(w[u][i][e], a[u][j][e], acc[i][j], 0, 0, 0);
-        }
     }
     if (KW > 1) {
 #pragma unroll
@@ -252,105 +211,294 @@ __global__ __launch_bounds__(64 * KW * WN * WM) void gemm_kernel(const float* __
     }
 }
 
-// One block per (row m, head h): scores over keys 0..cur_len+t, softmax, weighted sum of values.  16 lanes share a key
-// (four of its dimensions at a time); a thread of the second part owns four output dimensions of a share of the keys.
+// The few rows of a decode step: 16 columns x 16 rows per workgroup of eight wavefronts, the LayerNorm of the rows folded in (LN).
+// Nothing here takes as long as a launch; what does is the chain of everything that waits for something else, so all that the
+// epilogue needs (bias, residual, where a key or value goes) is requested behind the first weights, a row's values are read
+// once and its sums are data-parallel moves.  4 rows, a captured decode step: 256 x 256 and 256 x 1024 5.2 -> 4.0 us,
+// 768 x 256 and 1024 x 256 with their LayerNorm 6.4 and 5.7 -> 4.1.
+template <typename ST, bool VEC, bool LN>
+__global__ __launch_bounds__(512) void gemm_few_kernel(const float* __restrict__ A, const ST* __restrict__ W, const ST* __restrict__ bias,
+                                                       const ST* __restrict__ gamma, const ST* __restrict__ beta, PlainGemm p) {
+    constexpr int KW = 8, U = 4, C = 4;  // U: steps of 16 k requested together; C: 256-value pieces of a row kept in registers
+    __shared__ f32x4 red[KW][64];
+    __shared__ float2 smr[16];
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, l16 = lane & 15, kq = 4 * (lane >> 4);
+    const int n0 = blockIdx.x * 16, m0 = blockIdx.y * 16;
+    const int steps = (p.K + 15) / 16, s0 = wave * steps / KW, s1 = (wave + 1) * steps / KW;
+    const ST* wr = W + (size_t)min(n0 + l16, p.N - 1) * p.K;  // rows past the end: the last one (computed, never stored)
+    auto a_row = [&](int m) { return A + (LN ? (size_t)m * p.in_mul + p.in_add : (size_t)m) * p.K; };
+    const float* ar = a_row(min(m0 + l16, p.M - 1));
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f}, w[U], a[U], g[U], be[U];
+    auto load = [&](int s) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int k = s + u < s1 ? 16 * (s + u) + kq : p.K;  // (past this wavefront's range: zeros)
+            w[u] = load_k4<VEC>(wr, k, p.K);
+            a[u] = load_k4<VEC>(ar, k, p.K);
+            if (LN) { g[u] = load_k4<VEC>(gamma, k, p.K); be[u] = load_k4<VEC>(beta, k, p.K); }
+        }
+    };
+    load(s0);
+    // rows of the tile: a wavefront takes row `wave` and row `wave` + 8
+    const int rows = min(16, p.M - m0);
+    f32x4 x[C];
+    auto load_row = [&](const float* row) {
+#pragma unroll
+        for (int c = 0; c < C; ++c) {
+            if (256 * c >= p.K) break;
+            x[c] = load_k4<VEC>(row, 256 * c + 4 * lane, p.K);
+        }
+    };
+    if (LN && wave < rows) load_row(a_row(m0 + wave));
+    // the first wavefront finishes the tile: lane -> row l16, columns n0 + kq .. + 3
+    const int m = m0 + l16, n = n0 + kq;
+    const bool live = wave == 0 && m < p.M && n < p.N;
+    f32x4 badd = {0.f, 0.f, 0.f, 0.f}, old = {0.f, 0.f, 0.f, 0.f};
+    float* dst = p.out + (size_t)m * p.N + n;
+    float scale = 1.f;
+    bool store = live;
+    if (live) {
+        if (p.epi != EPI_STORE) badd = load_k4<false>(bias, n, p.N);
+        if (p.epi == EPI_RESID) {
+            if (p.vec_out) old = *reinterpret_cast<const f32x4*>(dst);
+            else old = load_k4<false>(dst - n, n, p.N);
+        } else if (p.epi == EPI_QKV) {  // q scaled to `out`, k and v appended to the cache (H and the head dimension are multiples of 8)
+            if (n < p.H) {
+                dst = p.out + (size_t)m * p.H + n;
+                scale = p.qscale;
+            } else {
+                const int d = p.H / p.n_heads, which = n >= 2 * p.H, c = n - (which ? 2 * p.H : p.H);
+                const int b = row_seq(p.st, m, p.S), tr = (p.S == 1 ? 0 : m % p.S) - row_pad(p.st, b);
+                store = tr >= 0;  // padding rows append nothing
+                dst = p.kv + kv_index(p.layer, which, b, c / d, seq_len(p.st, b) + tr, p.max_batch, p.n_heads, p.max_seq, d) + (c % d);
+            }
+        }
+    }
+    float mean = 0.f, rstd = 0.f;
+    if (LN) {  // mean and 1/sqrt(var + eps) of the tile's rows
+        for (int r = wave; r < rows; r += KW) {
+            const float* row = a_row(m0 + r);
+            if (r != wave) load_row(row);
+            float t = 0.f;
+#pragma unroll
+            for (int c = 0; c < C; ++c) {
+                if (256 * c >= p.K) break;
+                t += (x[c][0] + x[c][1]) + (x[c][2] + x[c][3]);
+            }
+            for (int k = 256 * C + lane; k < p.K; k += 64) t += row[k];
+            const float mu = lane_sum<64>(t) / p.K;
+            float q = 0.f;
+#pragma unroll
+            for (int c = 0; c < C; ++c) {
+                if (256 * c >= p.K) break;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const float dlt = 256 * c + 4 * lane + e < p.K ? x[c][e] - mu : 0.f;
+                    q += dlt * dlt;
+                }
+            }
+            for (int k = 256 * C + lane; k < p.K; k += 64) { const float dlt = row[k] - mu; q += dlt * dlt; }
+            q = lane_sum<64>(q);
+            if (lane == 0) smr[r] = make_float2(mu, 1.0f / sqrtf(q / p.K + p.eps));
+        }
+        __syncthreads();
+        const float2 mr = smr[min(l16, rows - 1)];
+        mean = mr.x; rstd = mr.y;
+    }
+    for (int s = s0; s < s1; s += U) {
+        if (s > s0) load(s);
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (s + u >= s1) break;
+            if (LN) a[u] = (a[u] - mean) * rstd * g[u] + be[u];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(w[u][e], a[u][e], acc, 0, 0, 0);
+        }
+    }
+    red[wave][lane] = acc;
+    __syncthreads();
+    if (wave != 0) return;
+    f32x4 v = {0.f, 0.f, 0.f, 0.f}, part[KW];
+#pragma unroll
+    for (int i = 0; i < KW; ++i) part[i] = red[i][lane];
+#pragma unroll
+    for (int i = 0; i < KW; ++i) v += part[i];
+    v += badd;
+    if (p.epi == EPI_BIAS_RELU) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) v[i] = fmaxf(v[i], 0.f);
+    }
+    v = (v + old) * scale;
+    if (!store) return;
+    const int nv = min(4, p.N - n);
+    if (p.vec_out && nv == 4) {
+        *reinterpret_cast<f32x4*>(dst) = v;
+    } else {
+        for (int i = 0; i < nv; ++i) dst[i] = v[i];
+    }
+}
+
+// One block per (row m, head h).  16 lanes share a key, CH times four of its dimensions each, and keep the soft-max state of their
+// keys (largest score, sum, weighted values) in one pass; K and V are on their way together, a round ahead.  The lane groups of a
+// wavefront are merged with data-parallel moves, the four wavefronts through LDS behind the only barrier.  (4 rows x 4 heads of 64, up to
+// 48 keys: 3.3 us; with a score buffer, two block-wide reductions and serial sums 6.1.)
+template <int CH>
 __global__ __launch_bounds__(256) void attn_kernel(const float* __restrict__ q, const float* __restrict__ kv,
                                                    float* __restrict__ o, const he_dev_state* __restrict__ st, int S, int layer,
                                                    int H, int n_heads, int max_batch, int max_seq) {
-    extern __shared__ __align__(16) float smem[];
-    __shared__ float red[8];
-    const int d = H / n_heads, d4 = d / 4;  // (d is a multiple of 8)
-    f32x4* part = reinterpret_cast<f32x4*>(smem);  // [256] partial outputs
-    float* sc = smem + 4 * 256;                    // [max_seq] scores, then probabilities
+    constexpr int WAVES = 4, U = CH == 1 ? 4 : (CH == 2 ? 2 : 1), KR = WAVES * 4, STEP = KR * U;
+    __shared__ float2 ml[WAVES];             // a wavefront's largest score and sum
+    __shared__ f32x4 ored[WAVES][16 * CH];   // ... and its weighted values
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, sub = lane & 15, grp = lane >> 4;
+    const int d = H / n_heads, d4 = d / 4;  // (d is a multiple of 8, at most 256)
     const int m = blockIdx.x, h = blockIdx.y;
-    const int b = m / S, nkeys = seq_len(st, b) + (m % S) - row_pad(st, b) + 1;
-    if (nkeys <= 0 || seq_done(st, b)) {  // a padding row, or a sequence that has ended: nothing reads this output
-        for (int e = threadIdx.x; e < d; e += blockDim.x) o[(size_t)m * H + h * d + e] = 0.f;
+    const f32x4* Q = reinterpret_cast<const f32x4*>(q + (size_t)m * H + h * d);
+    f32x4 qv[CH];
+#pragma unroll
+    for (int c = 0; c < CH; ++c) qv[c] = sub + 16 * c < d4 ? Q[sub + 16 * c] : f32x4{0.f, 0.f, 0.f, 0.f};
+    const int b = S == 1 ? m : m / S, T = seq_len(st, b) + (S == 1 ? 0 : m % S) - row_pad(st, b) + 1;
+    f32x4* out = reinterpret_cast<f32x4*>(o + (size_t)m * H + h * d);
+    if (T <= 0 || seq_done(st, b)) {  // a padding row, or a sequence that has ended: nothing reads this output
+        for (int e = threadIdx.x; e < d4; e += 256) out[e] = f32x4{0.f, 0.f, 0.f, 0.f};
         return;
     }
-    const f32x4* Q = reinterpret_cast<const f32x4*>(q + (size_t)m * H + h * d);
     const f32x4* Kp = reinterpret_cast<const f32x4*>(kv + kv_index(layer, 0, b, h, 0, max_batch, n_heads, max_seq, d));
     const f32x4* Vp = reinterpret_cast<const f32x4*>(kv + kv_index(layer, 1, b, h, 0, max_batch, n_heads, max_seq, d));
-    const int sub = threadIdx.x & 15;
-    float mx = -INFINITY;
-    for (int j = threadIdx.x >> 4; j < nkeys; j += 16) {
-        float s = 0.f;
-        for (int e = sub; e < d4; e += 16) {
-            const f32x4 a = Q[e], c = Kp[(size_t)j * d4 + e];
-            s = fmaf(a[0], c[0], s); s = fmaf(a[1], c[1], s); s = fmaf(a[2], c[2], s); s = fmaf(a[3], c[3], s);
-        }
+    const int jw = wave * 4 + grp;
+    auto load_rows = [&](f32x4 (&dst)[U][CH], const f32x4* src, int base) {
 #pragma unroll
-        for (int x = 1; x < 16; x <<= 1) s += __shfl_xor(s, x);
-        if (sub == 0) sc[j] = s;
-        mx = fmaxf(mx, s);
-    }
-    mx = block_max(mx, red);
-    float sum = 0.f;
-    for (int j = threadIdx.x; j < nkeys; j += blockDim.x) {
-        const float p = expf(sc[j] - mx);
-        sc[j] = p;
-        sum += p;
-    }
-    sum = block_sum(sum, red);  // also orders the sc[] writes before the reads below
-    const int parts = 256 / d4, e = threadIdx.x % d4, part0 = threadIdx.x / d4;  // (d <= 256: at least four shares of the keys)
-    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-    if (part0 < parts) {
-        for (int j = part0; j < nkeys; j += parts) {
-            const f32x4 v = Vp[(size_t)j * d4 + e];
-            const float p = sc[j];
+        for (int u = 0; u < U; ++u)
 #pragma unroll
-            for (int i = 0; i < 4; ++i) acc[i] = fmaf(p, v[i], acc[i]);
+            for (int c = 0; c < CH; ++c) {
+                const int j = base + u * KR + jw;
+                dst[u][c] = j < T && sub + 16 * c < d4 ? src[(size_t)j * d4 + sub + 16 * c] : f32x4{0.f, 0.f, 0.f, 0.f};
+            }
+    };
+    float mx = -INFINITY, sum = 0.f;
+    f32x4 acc[CH], k[U][CH], v[U][CH];
+#pragma unroll
+    for (int c = 0; c < CH; ++c) acc[c] = f32x4{0.f, 0.f, 0.f, 0.f};
+    load_rows(k, Kp, 0);
+    load_rows(v, Vp, 0);
+    for (int base = 0; base < T; base += STEP) {
+        float s[U], top = mx;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            float x = 0.f;
+#pragma unroll
+            for (int c = 0; c < CH; ++c)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) x = fmaf(qv[c][e], k[u][c][e], x);
+            x = lane_sum<16>(x);
+            s[u] = base + u * KR + jw < T ? x : -INFINITY;
+            top = fmaxf(top, s[u]);
         }
-        part[threadIdx.x] = acc;
+        const bool more = base + STEP < T;  // (the same for the whole workgroup)
+        if (more) load_rows(k, Kp, base + STEP);
+        // (nothing above -inf yet: the state stays what it is)
+        const float ref = top > -INFINITY ? top : 0.f, keep = expf(mx - ref);
+        mx = top;
+        sum *= keep;
+#pragma unroll
+        for (int c = 0; c < CH; ++c) acc[c] *= keep;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const float pr = base + u * KR + jw < T ? expf(s[u] - ref) : 0.f;
+            sum += pr;
+#pragma unroll
+            for (int c = 0; c < CH; ++c)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) acc[c][e] = fmaf(pr, v[u][c][e], acc[c][e]);
+        }
+        if (more) load_rows(v, Vp, base + STEP);
+    }
+    const float wmx = lane_max32_apart(lane_max16_apart(mx)), own = mx > -INFINITY ? expf(mx - wmx) : 0.f;
+    sum = lane_sum_apart<16>(sum * own);
+    if (lane == 0) ml[wave] = make_float2(wmx, sum);
+#pragma unroll
+    for (int c = 0; c < CH; ++c) {
+        f32x4 t;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) t[e] = lane_sum_apart<16>(acc[c][e] * own);
+        if (grp == 0) ored[wave][sub + 16 * c] = t;
     }
     __syncthreads();
-    if ((int)threadIdx.x < d4) {
-        f32x4 t = part[threadIdx.x];
-        for (int x = 1; x < parts; ++x) t += part[threadIdx.x + x * d4];
-        reinterpret_cast<f32x4*>(o + (size_t)m * H + h * d)[threadIdx.x] = t / sum;
+    if ((int)threadIdx.x >= d4) return;
+    float2 e[WAVES];
+#pragma unroll
+    for (int w = 0; w < WAVES; ++w) e[w] = ml[w];
+    const float all = fmaxf(fmaxf(e[0].x, e[1].x), fmaxf(e[2].x, e[3].x));
+    float total = 0.f;
+    f32x4 t = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int w = 0; w < WAVES; ++w) {
+        const float f = e[w].x > -INFINITY ? expf(e[w].x - all) : 0.f;
+        total += e[w].x > -INFINITY ? e[w].y * f : 0.f;
+        t += ored[w][threadIdx.x] * f;
     }
+    out[threadIdx.x] = t / total;
 }
 
 // One block per sequence: token = argmax of z (greedy) or of z/temperature + Gumbel noise, ties
 // to the lowest id; logprob = z[token] - logsumexp(z).
 // advance > 0: the pass fed that many tokens per sequence and ends here.
-__global__ void sample_kernel(const float* __restrict__ logits, int V, he_dev_state* st,
+__global__ __launch_bounds__(kThreads) void sample_kernel(const float* __restrict__ logits, int V, he_dev_state* st,
                               int32_t* __restrict__ ids_out, float* __restrict__ lp_out, int out_stride,
                               int out_at_step, int32_t* __restrict__ cur_ids, int advance) {
-    __shared__ float red[8];
-    __shared__ float bs[kThreads / 64];
-    __shared__ int bi[kThreads / 64];
-    const int b = blockIdx.x;
+    constexpr int C = 8, WAVES = kThreads / 64;  // logits of a thread kept in registers, the rest read again
+    __shared__ float2 sms[WAVES];
+    __shared__ float bs[WAVES];
+    __shared__ int bi[WAVES];
+    const int b = blockIdx.x, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const float* z = logits + (size_t)b * V;
+    float zc[C];
+#pragma unroll
+    for (int c = 0; c < C; ++c) zc[c] = (int)threadIdx.x + c * kThreads < V ? z[threadIdx.x + c * kThreads] : -INFINITY;
     const int mode = st->mode, n = st->step;
     const float temp = st->temperature;
     const uint32_t k0 = st->seed_lo, k1 = st->seed_hi;
     float best = -INFINITY, mx = -INFINITY;
     int besti = 0x7FFFFFFF;
-    for (int v = threadIdx.x; v < V; v += blockDim.x) {
-        const float zv = z[v];
+    auto look = [&](float zv, int v) {
         mx = fmaxf(mx, zv);
         float s = zv;
         if (mode == 1) s = zv / temp + gumbel_from_word(philox_word0((uint32_t)v, (uint32_t)n, (uint32_t)b, k0, k1));
         if (s > best || (s == best && v < besti)) { best = s; besti = v; }
-    }
-    for (int o = 32; o > 0; o >>= 1) {
-        const float os = __shfl_xor(best, o);
-        const int oi = __shfl_xor(besti, o);
-        if (os > best || (os == best && oi < besti)) { best = os; besti = oi; }
-    }
-    if ((threadIdx.x & 63) == 0) { bs[threadIdx.x >> 6] = best; bi[threadIdx.x >> 6] = besti; }
-    mx = block_max(mx, red);  // contains the barriers that publish bs/bi
-    for (int w = 0; w < (int)(blockDim.x >> 6); ++w)
-        if (bs[w] > best || (bs[w] == best && bi[w] < besti)) { best = bs[w]; besti = bi[w]; }
+    };
+#pragma unroll
+    for (int c = 0; c < C; ++c)
+        if ((int)threadIdx.x + c * kThreads < V) look(zc[c], threadIdx.x + c * kThreads);
+    for (int v = threadIdx.x + C * kThreads; v < V; v += kThreads) look(z[v], v);
+    // a wavefront's exponentials against its own largest logit
+    mx = lane_max<64>(mx);
+    const float ref = mx > -INFINITY ? mx : 0.f;
     float sum = 0.f;
-    for (int v = threadIdx.x; v < V; v += blockDim.x) sum += expf(z[v] - mx);
-    sum = block_sum(sum, red);
+#pragma unroll
+    for (int c = 0; c < C; ++c) sum += expf(zc[c] - ref);  // (past the vocabulary: -inf, adds 0)
+    for (int v = threadIdx.x + C * kThreads; v < V; v += kThreads) sum += expf(z[v] - ref);
+    sum = lane_sum<64>(sum);
+    auto take = [&](float os, int oi) {
+        if (os > best || (os == best && oi < besti)) { best = os; besti = oi; }
+    };
+    take(lane_xor1(best), __builtin_amdgcn_mov_dpp(besti, 0xB1, 0xF, 0xF, false));
+    take(lane_xor2(best), __builtin_amdgcn_mov_dpp(besti, 0x4E, 0xF, 0xF, false));
+    take(lane_mirror8(best), __builtin_amdgcn_mov_dpp(besti, 0x141, 0xF, 0xF, false));
+    take(lane_mirror16(best), __builtin_amdgcn_mov_dpp(besti, 0x140, 0xF, 0xF, false));
+    take(__shfl_xor(best, 16), __shfl_xor(besti, 16));
+    take(__shfl_xor(best, 32), __shfl_xor(besti, 32));
+    if (lane == 0) { sms[wave] = make_float2(mx, sum); bs[wave] = best; bi[wave] = besti; }
+    __syncthreads();
     if (threadIdx.x == 0) {
+        sum = 0.f;
+#pragma unroll
+        for (int w = 0; w < WAVES; ++w) { mx = fmaxf(mx, sms[w].x); take(bs[w], bi[w]); }
+#pragma unroll
+        for (int w = 0; w < WAVES; ++w) sum += sms[w].x > -INFINITY ? sms[w].y * expf(sms[w].x - mx) : sms[w].y;
+        if (!(mx > -INFINITY)) sum = __builtin_nanf("");  // no logit above -inf: no probabilities
         const size_t at = (size_t)b * out_stride + (out_at_step ? n : 0);
         ids_out[at] = besti;
         // (a row of nothing but NaN has no best token: besti is no vocabulary id then, and the sum is NaN)
-        lp_out[at] = (besti < V ? z[besti] : 0.f) - (mx + logf(sum));
+        lp_out[at] = ((besti < V ? z[besti] : 0.f) - mx) - logf(sum);  // (in this order one rounding less of what is large)
         if (cur_ids) cur_ids[b] = besti;
     }
     if (advance) advance_state_by_last(st, advance, 1);
@@ -508,15 +656,15 @@ static void launch_gemm(hipStream_t s, const float* A, const ST* W, const ST* bi
     const ST *gamma = ln ? (const ST*)ln->gamma : nullptr, *beta = ln ? (const ST*)ln->beta : nullptr;
     if (p.M <= kFewRows) {
         const dim3 grid((p.N + 15) / 16, (p.M + 15) / 16);
-        if (ln) gemm_kernel<ST, 1, 8, 1, 1, VEC, true><<<grid, 512, 0, s>>>(A, W, bias, gamma, beta, p);
-        else gemm_kernel<ST, 1, 8, 1, 1, VEC, false><<<grid, 512, 0, s>>>(A, W, bias, gamma, beta, p);
+        if (ln) gemm_few_kernel<ST, VEC, true><<<grid, 512, 0, s>>>(A, W, bias, gamma, beta, p);
+        else gemm_few_kernel<ST, VEC, false><<<grid, 512, 0, s>>>(A, W, bias, gamma, beta, p);
         return;
     }
     const dim3 big((p.N + 63) / 64, (p.M + 63) / 64);
     if (big.x * big.y >= 256)
-        gemm_kernel<ST, 2, 1, 2, 2, VEC, false><<<big, 256, 0, s>>>(A, W, bias, gamma, beta, p);
+        gemm_kernel<ST, 1, 2, 2, VEC><<<big, 256, 0, s>>>(A, W, bias, p);
     else
-        gemm_kernel<ST, 2, 8, 1, 1, VEC, false><<<dim3((p.N + 31) / 32, (p.M + 31) / 32), 512, 0, s>>>(A, W, bias, gamma, beta, p);
+        gemm_kernel<ST, 8, 1, 1, VEC><<<dim3((p.N + 31) / 32, (p.M + 31) / 32), 512, 0, s>>>(A, W, bias, p);
 }
 
 template <typename ST>
@@ -546,9 +694,12 @@ void plain_gemm(hipStream_t s, int bf16, const float* A, const void* W, const vo
 void plain_attn(hipStream_t s, int bf16, const float* q, const void* kv, float* o, const he_dev_state* st, int M, int S,
                 int layer, int H, int n_heads, int max_batch, int max_seq) {
     dim3 grid(M, n_heads);
-    const size_t shm = (size_t)(4 * 256 + max_seq) * sizeof(float);
     (void)bf16;  // the plain kernels keep keys and values as floats whatever the weights' type
-    attn_kernel<<<grid, 256, shm, s>>>(q, (const float*)kv, o, st, S, layer, H, n_heads, max_batch, max_seq);
+    const float* c = (const float*)kv;
+    const int ch = (H / n_heads / 4 + 15) / 16;  // (1 to 4: heads of up to 256)
+    if (ch == 1) attn_kernel<1><<<grid, 256, 0, s>>>(q, c, o, st, S, layer, H, n_heads, max_batch, max_seq);
+    else if (ch == 2) attn_kernel<2><<<grid, 256, 0, s>>>(q, c, o, st, S, layer, H, n_heads, max_batch, max_seq);
+    else attn_kernel<4><<<grid, 256, 0, s>>>(q, c, o, st, S, layer, H, n_heads, max_batch, max_seq);
 }
 
 // one workgroup per row: log-sum-exp of the row's logits, then the next token's log-probability
