@@ -625,7 +625,8 @@ __device__ __forceinline__ void half_mma_some(const HalfRegs<HT, U, W8, MH>& r, 
 // 8-15: one contiguous 1 KiB load per unit, two matrix-instruction operands after conversion.
 template <int MODE, int HT, int U, int WAVES, bool W8, int MT = 1, int HALVES = 0>
 __global__ __launch_bounds__(WAVES * 64) void gemm_half_kernel(const u32x4* __restrict__ Wp, const u32x4* __restrict__ Xhi,
-                                                               int KB, int n_half, int ksplit, int kbase, int kmore, Epi p) {
+                                                               int KB, int n_half, int ksplit, int kbase, int kmore, int m_rows,
+                                                               Epi p) {
     // 16-row halves of the activation rows: both of every slice, or only the first HALVES of them when no more
     // are in use (at most 16 rows of one slice, at most 48 of two): the rest would be loaded and multiplied for nothing
     static_assert(HALVES == 0 || (HALVES < 2 * MT && HALVES > 2 * (MT - 1)), "HALVES ends inside the last slice");
@@ -650,7 +651,9 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_half_kernel(const u32x4* __re
         if (W8) w[t] = Wp + ((size_t)g * KP + kp0) * 64 + lane;
         else w[t] = Wp + ((size_t)(g >> 1) * KB + 2 * kp0) * 64 + in_pair + 16 * (g & 1);
     }
-    const u32x4* xh = Xhi + ((size_t)mt * KB + 2 * KU * kp0) * 64 + in_pair;
+    // (of the first 16 rows only those in use: a load then touches half the lines where they are at most eight)
+    const int x_in_pair = MH == 1 ? in_pair - (lane & 15) + min(lane & 15, m_rows - 1) : in_pair;
+    const u32x4* xh = Xhi + ((size_t)mt * KB + 2 * KU * kp0) * 64 + x_in_pair;
     constexpr int ITEMS = items_per_wave(NI, WAVES);  // item = wave + i*WAVES -> unit item/MH, row half item%MH
     // epilogue operands: requested right behind the first round of weight loads (see gemm_skinny_kernel)
     uint2 bias_w[ITEMS];
@@ -879,13 +882,13 @@ void launch_half_ht(hipStream_t s, const void* Wp, const void* Xhi, int KB, int 
                 constexpr size_t kStatic = (size_t)4 * HT * 3 * 4 * 64 * sizeof(float);
                 const size_t pad = kStatic >= kWant2 ? 0 : kWant2 - kStatic;
                 gemm_half_kernel<MODE, HT, U2, 4, W8, 2, 3><<<grid, 256, pad, s>>>(
-                    (const u32x4*)Wp, (const u32x4*)Xhi, KB, n_half, ksplit, steps / parts4, steps % parts4, p);
+                    (const u32x4*)Wp, (const u32x4*)Xhi, KB, n_half, ksplit, steps / parts4, steps % parts4, p.M, p);
                 return;
             }
             constexpr size_t kStatic = (size_t)4 * HT * 4 * 4 * 64 * sizeof(float);
             const size_t pad = kStatic >= kWant2 ? 0 : kWant2 - kStatic;
             gemm_half_kernel<MODE, HT, U2, 4, W8, 2><<<grid, 256, pad, s>>>((const u32x4*)Wp, (const u32x4*)Xhi,
-                                                                               KB, n_half, ksplit, steps / parts4, steps % parts4, p);
+                                                                               KB, n_half, ksplit, steps / parts4, steps % parts4, p.M, p);
             return;
         }
     }
@@ -904,12 +907,12 @@ void launch_half_ht(hipStream_t s, const void* Wp, const void* Xhi, int KB, int 
             constexpr size_t kStatic = (size_t)8 * HT * 4 * 64 * sizeof(float);
             const size_t pad = kStatic >= kWant ? 0 : kWant - kStatic;
             gemm_half_kernel<MODE, HT <= kEight ? HT : 2, U8, 8, W8, 1, 1><<<grid, 512, pad, s>>>(
-                (const u32x4*)Wp, (const u32x4*)Xhi, KB, n_half, ksplit, steps / parts8, steps % parts8, p);
+                (const u32x4*)Wp, (const u32x4*)Xhi, KB, n_half, ksplit, steps / parts8, steps % parts8, p.M, p);
         } else {
             constexpr size_t kStatic = (size_t)4 * HT * 4 * 64 * sizeof(float);
             const size_t pad = kStatic >= kWant ? 0 : kWant - kStatic;
             gemm_half_kernel<MODE, HT, U, 4, W8, 1, 1><<<grid, 256, pad, s>>>(
-                (const u32x4*)Wp, (const u32x4*)Xhi, KB, n_half, ksplit, steps / parts4, steps % parts4, p);
+                (const u32x4*)Wp, (const u32x4*)Xhi, KB, n_half, ksplit, steps / parts4, steps % parts4, p.M, p);
         }
         return;
     }
@@ -918,12 +921,12 @@ void launch_half_ht(hipStream_t s, const void* Wp, const void* Xhi, int KB, int 
         constexpr size_t kStatic = (size_t)8 * HT * 2 * 4 * 64 * sizeof(float);
         const size_t pad = kStatic >= kWant ? 0 : kWant - kStatic;
         gemm_half_kernel<MODE, HT <= kEight ? HT : 2, U8, 8, W8><<<grid, 512, pad, s>>>(
-            (const u32x4*)Wp, (const u32x4*)Xhi, KB, n_half, ksplit, steps / parts8, steps % parts8, p);
+            (const u32x4*)Wp, (const u32x4*)Xhi, KB, n_half, ksplit, steps / parts8, steps % parts8, p.M, p);
     } else {
         constexpr size_t kStatic = (size_t)4 * HT * 2 * 4 * 64 * sizeof(float);
         const size_t pad = kStatic >= kWant ? 0 : kWant - kStatic;
         gemm_half_kernel<MODE, HT, U, 4, W8><<<grid, 256, pad, s>>>((const u32x4*)Wp, (const u32x4*)Xhi,
-                                                                    KB, n_half, ksplit, steps / parts4, steps % parts4, p);
+                                                                    KB, n_half, ksplit, steps / parts4, steps % parts4, p.M, p);
     }
 }
 

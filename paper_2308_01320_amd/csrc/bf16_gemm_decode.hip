@@ -55,7 +55,7 @@ __global__ __launch_bounds__(256) void lm_reduce_kernel(const float4* __restrict
         if (!(mx > -INFINITY)) sum = __builtin_nanf("");  // no logit above -inf: no probabilities
         const size_t at = (size_t)q * out_stride + (out_at_step ? step : 0);
         ids_out[at] = best.id;
-        lp_out[at] = best.z - (mx + logf(sum));
+        lp_out[at] = (best.z - mx) - logf(sum);
         if (cur_ids) cur_ids[q] = best.id;
     }
     if (advance) advance_state_by_last(st, 1, 1);
