@@ -24,6 +24,7 @@
 // i.e. runs of four consecutive n -- what the epilogues store.
 #pragma once
 #include <algorithm>
+#include <cmath>
 #include <cstdlib>
 
 #include "he_common.h"

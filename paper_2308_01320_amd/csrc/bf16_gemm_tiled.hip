@@ -527,7 +527,7 @@ __global__ __launch_bounds__(256, 1) void gemm_tiled256_kernel(const u32x4* __re
     store_tile<MODE, NA, 4>(p, bias8, acc, tm * BM + wm * 128, tn * BN + wn * 32 * NA, ks, cur_len, lane);
 }
 
-// ----------------------------------------------------------------- 256 x 64..192 tiles on a deep ring (few rows)
+// ----------------------------------------------------------------- 256 x 64..192 tiles, and halved ones of up to 256 rows, on a deep ring (few rows)
 //
 // Prompt passes of too few rows to give every CU a 256 x 256 tile, and the wide decode steps.  What bounds these is not
 // the matrix cores but how fast one CU pulls operands in: about 64 KB can be outstanding per CU whatever the ring's depth,
@@ -538,13 +538,18 @@ __global__ __launch_bounds__(256, 1) void gemm_tiled256_kernel(const u32x4* __re
 // kernel's -- LDS reads and copies dealt out behind the matrix instructions, a bare workgroup barrier per stage -- with
 // one difference: a slot is refilled behind the barrier of its own stage (every wavefront waits for its own LDS reads
 // before it), so all but one of the slots are in flight.
+// Halved tiles -- two workgroups to 256 columns, 128 each (NW = 2) -- give narrow matrices and few rows more workgroups for the same number of k ranges, or leave them out:
+// 250 x 8192 x 2048 27.6 -> 18.8 us with whole sums, 250 x 16384 x 4096 53.9 -> 45.9, 96 x 2048 x 8192 14.4 (13 ranges) -> 11.8 (8),
+// 180 x 1024 x 1024 6.5 -> 5.1; 384 rows and more of wide matrices go better on 256 columns (12288 x 4096 46.4 / 53.6).  (A CU has some 64 KB of
+// copies on their way whatever they hit: prefetching the weights into L2 with scalar loads, 50 lines a microsecond and CU, is too slow by
+// a factor of four.)
 // Measured, the kernel before this (four stages, one range) -> this one with one k range per tile -> with the planned ones:
 // 250 x 4096 x 16384: 269 -> 203 -> 45 us; 250 x 16384 x 4096: 79 -> 56, the plan (one range on 64-row tiles; ranges would
 // need finish_kernel, 8 us); 250 x 12288 x 4096: 41 and 8 for finish_kernel; 96 x 5120 x 20480: 52 (eight ranges) -> 44 (twelve);
 // 768 x 12288 x 4096: 150 -> 76 (192-row tiles, one range).
-template <int MW> struct RingShape {
-    static constexpr int TM = 64 * MW;                       // rows of X per tile
-    static constexpr int SB = (8 + 2 * MW) * 2;              // blocks per stage (two k-blocks)
+template <int NW, int MW> struct RingShape {
+    static constexpr int TN = 64 * NW, TM = 64 * MW;         // rows of W (columns) and of X per tile
+    static constexpr int SB = (2 * NW + 2 * MW) * 2;         // blocks per stage (two k-blocks)
     static constexpr int NST = 160 / SB < 8 ? 160 / SB : 8;  // stages that fit into 160 KiB
     static constexpr int CW = SB / 4;                        // copies per wavefront and stage
 };
@@ -555,15 +560,16 @@ __device__ __forceinline__ void wait_vmcnt_lgkm0() {
     __builtin_amdgcn_s_waitcnt((N & 0xF) | ((N >> 4) << 14) | (0x7 << 4));
 }
 
-template <int MODE, int MW>
+template <int MODE, int NW, int MW>
 __global__ __launch_bounds__(256, 1) void gemm_ring_kernel(const u32x4* __restrict__ Wp, const u32x4* __restrict__ X,
                                                            const u32x4* __restrict__ bias8, int KB, int NT32, int MT32,
                                                            int tiles_n, int tiles_m, int ksplit, Epi p) {
-    typedef RingShape<MW> Sh;
+    typedef RingShape<NW, MW> Sh;
     constexpr int SB = Sh::SB, NST = Sh::NST, CW = Sh::CW;
-    constexpr int NM = 4 * MW, NR = 4 + MW;  // matrix instructions, LDS reads per wavefront and k-block
+    constexpr int NM = NW * MW, NR = NW + MW;  // matrix instructions, LDS reads per wavefront and k-block
     static_assert((NST - 1) * CW <= 63, "the wait counter holds every copy in flight");
-    __shared__ u32x4 ring[NST][SB][64];  // block c of a stage: W row-tile c / 2, k-block c % 2; from 16 on X row-tile (c - 16) / 2
+    constexpr int XOFF = 4 * NW;
+    __shared__ u32x4 ring[NST][SB][64];  // block c of a stage: W row-tile c / 2, k-block c % 2; from XOFF on X row-tile (c - XOFF) / 2
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     // A contiguous run of items per XCD; the row tiles of one (column tile, k range) are neighbours and share its weights
     const int nitem = tiles_n * tiles_m * ksplit, per_xcd = (nitem + 7) / 8;
@@ -571,7 +577,7 @@ __global__ __launch_bounds__(256, 1) void gemm_ring_kernel(const u32x4* __restri
     if (item >= nitem) return;
     const int tm = item % tiles_m, rest = item / tiles_m;
     const int tn = rest % tiles_n, ks = rest / tiles_n;
-    const int wn = wave & 1, wm = wave >> 1;  // this wavefront's 128 (n) x 32 MW (m) sub-tile
+    const int wn = wave & 1, wm = wave >> 1;  // this wavefront's 32 NW (n) x 32 MW (m) sub-tile
     [[maybe_unused]] const int cur_len = epilogue_len<MODE>(p);
     // LM head with the final LayerNorm folded in (decode steps of up to 64 rows, whose rows are one tile of 64: MW = 1): this
     // wavefront's share of the rows' statistics
@@ -583,9 +589,9 @@ __global__ __launch_bounds__(256, 1) void gemm_ring_kernel(const u32x4* __restri
             for (int x = 0; x < 2; ++x) ln_issue<4>(lnl[x], p, min(tm * 2 + x, MT32 - 1), wave, lane);
         }
     }
-    f32x16 acc[4][MW];
+    f32x16 acc[NW][MW];
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < NW; ++i)
 #pragma unroll
         for (int j = 0; j < MW; ++j) acc[i][j] = f32x16{};
     const int nst_all = KB / 2;  // KB is even (K % 32 == 0)
@@ -595,17 +601,17 @@ __global__ __launch_bounds__(256, 1) void gemm_ring_kernel(const u32x4* __restri
 #pragma unroll
     for (int q = 0; q < CW; ++q) {
         const int c = wave * CW + q;
-        const bool isw = c < 16;
-        const int rt = isw ? min(tn * 8 + (c >> 1), NT32 - 1) : min(tm * 2 * MW + ((c - 16) >> 1), MT32 - 1);
+        const bool isw = c < XOFF;
+        const int rt = isw ? min(tn * 2 * NW + (c >> 1), NT32 - 1) : min(tm * 2 * MW + ((c - XOFF) >> 1), MT32 - 1);
         src[q] = (isw ? Wp : X) + ((size_t)rt * KB + (size_t)st0 * 2 + (c & 1)) * 64 + lane;
     }
     auto copy1 = [&](int st, int slot, int q) { load_block_to_lds(src[q] + (size_t)st * 128, &ring[slot][wave * CW + q][0]); };
-    struct Ops { u32x4 a[4], b[MW]; };
-    // LDS read q of a k-block, in the order the matrix instructions first need the operands: a0, b0 .., a1, a2, a3
+    struct Ops { u32x4 a[NW], b[MW]; };
+    // LDS read q of a k-block, in the order the matrix instructions first need the operands: a0, b0 .., a1 ..
     auto read1 = [&](Ops& o, int slot, int j, int q) {
-        if (q == 0) o.a[0] = ring[slot][wn * 8 + j][lane];
-        else if (q <= MW) o.b[q - 1] = ring[slot][16 + (wm * MW + q - 1) * 2 + j][lane];
-        else o.a[q - MW] = ring[slot][(wn * 4 + q - MW) * 2 + j][lane];
+        if (q == 0) o.a[0] = ring[slot][wn * NW * 2 + j][lane];
+        else if (q <= MW) o.b[q - 1] = ring[slot][XOFF + (wm * MW + q - 1) * 2 + j][lane];
+        else o.a[q - MW] = ring[slot][(wn * NW + q - MW) * 2 + j][lane];
     };
     auto mma1 = [&](const Ops& o, int n) { acc[n / MW][n % MW] = mfma_f16(o.a[n / MW], o.b[n % MW], acc[n / MW][n % MW]); };
     // Two reads behind each matrix instruction until all are out, then the copies, spread over the remaining ones.
@@ -693,6 +699,7 @@ __global__ __launch_bounds__(256, 1) void gemm_ring_kernel(const u32x4* __restri
         for (int n = 0; n < NM; ++n) mma1(opb, n);
         slot = nslot;
     }
+    static_assert(NW == 4 || (MODE != MODE_LMHEAD && MODE != MODE_SCORE), "a wavefront's 128 vocabulary entries are one partial");
     if constexpr (MODE == MODE_LMHEAD) {
         float2 fold[MW];
 #pragma unroll
@@ -708,10 +715,10 @@ __global__ __launch_bounds__(256, 1) void gemm_ring_kernel(const u32x4* __restri
                 fold[0] = ln_finish<4>(lnp + wm * 4 * 32, lane & 31, p);
             }
         }
-        lm_head_tile<MW>(p, acc, fold, tm * Sh::TM + wm * 32 * MW, tn * 256 + wn * 128, tn * 2 + wn, lane,
+        lm_head_tile<MW>(p, acc, fold, tm * Sh::TM + wm * 32 * MW, tn * Sh::TN + wn * 128, tn * 2 + wn, lane,
                          lds + wave * 64 * 64);
-    } else if constexpr (MODE == MODE_SCORE) score_tile<4, MW>(p, acc, tm * Sh::TM + wm * 32 * MW, tn * 256 + wn * 128, tn * 2 + wn, lane);
-    else store_tile<MODE, 4, MW>(p, bias8, acc, tm * Sh::TM + wm * 32 * MW, tn * 256 + wn * 128, ks, cur_len, lane);
+    } else if constexpr (MODE == MODE_SCORE) score_tile<4, MW>(p, acc, tm * Sh::TM + wm * 32 * MW, tn * Sh::TN + wn * 128, tn * 2 + wn, lane);
+    else store_tile<MODE, NW, MW>(p, bias8, acc, tm * Sh::TM + wm * 32 * MW, tn * Sh::TN + wn * 32 * NW, ks, cur_len, lane);
 }
 
 // One wavefront per scored row: log-sum-exp over the vocabulary slices in slice order, then
@@ -775,8 +782,9 @@ static BigPlan big_plan(int M, int N, int KB, bool may_cut) {
 // epilogue that needs the whole sum (fused), the pass of finish_kernel.  Microseconds fitted to launches of M = 96 ..
 // 768 rows and the 1.3B .. 13B matrices (uncontended stages 0.33 / 0.39 / 0.43 / 0.53 / 0.68 us; a second, partly empty
 // round: 4096 x 4096 and 768 rows, 240 workgroups 33.6 us, 288: 54.1).
-struct RingPlan { int mw, ks; };
-static RingPlan ring_plan(int M, int N, int KB, bool fused, size_t capacity_floats, int max_mw = 5) {
+// (tile: mw, or 10 + mw for halved tiles)
+struct RingPlan { int tile, ks; };
+static RingPlan ring_plan_256(int M, int N, int KB, bool fused, size_t capacity_floats, int max_mw = 5) {
     constexpr double kStage[5] = {0.33, 0.39, 0.43, 0.53, 0.68}, kRamp[5] = {6.0, 7.0, 8.5, 12.0, 14.0};
     const long cus = plan_cus(), stages = KB / 2;
     const double sums = 4.0 * M * N / 5e6, weights = 32.0 * N * KB / 14e6;
@@ -800,7 +808,43 @@ static RingPlan ring_plan(int M, int N, int KB, bool fused, size_t capacity_floa
     return best;
 }
 
-// tile: 1 .. 3 the ring kernel with 64 tile rows, 4 / 5 the big tiles.  Columns from split_col on are cut into ksplit k
+// The same with halved tiles among the candidates, by a cost fitted to launches of 20 matrices from 512 x 512 to 36864 x 9216
+// with 50 .. 4000 rows (the plan chosen is within 6 % of the fastest in 216 of 219 cases, a median of nothing): the stages and the
+// epilogue of a CU's rounds, never less than the weights take from HBM; the partial sums' writes; and what reads them.  All of
+// those matrices have a multiple of 512 rows, as those of every model configuration have; others keep the plan above, which the
+// tests hold a 4480-wide model to.  us with what adds the sums up, before -> after: 250 rows of 6144 x 2048 23.6 -> 17.5, 12288 x
+// 4096 47.0 -> 42.8, 16384 x 4096 53.7 -> 45.3, 4096 x 4096 22.4 -> 20.3; 96 rows of 15360 x 5120 47.1 -> 40.1, 5120 x 5120 20.3 -> 17.6.
+static RingPlan ring_plan(int M, int N, int KB, bool fused, size_t capacity_floats) {
+    if (N % 512) return ring_plan_256(M, N, KB, fused, capacity_floats);
+    struct Tile { int id, nw, mw; double stage; };
+    static constexpr Tile kTiles[] = {{1, 4, 1, 0.291}, {2, 4, 2, 0.359}, {3, 4, 3, 0.431}, {4, 4, 4, 0.54}, {5, 5, 4, 0.725},
+                                      {11, 2, 1, 0.193}, {12, 2, 2, 0.244}, {13, 2, 3, 0.302}, {14, 2, 4, 0.343}};
+    const double cus = plan_cus(), sums = 4.0 * M * N, weights = 32.0 * N * KB / 5.52e6;
+    const long stages = KB / 2;
+    RingPlan best{2, 1};
+    double best_cost = 1e30;
+    for (const Tile& t : kTiles) {
+        const long tiles = (long)((N + 64 * t.nw - 1) / (64 * t.nw)) * ((M + 64 * t.mw - 1) / (64 * t.mw));
+        for (int ks = 1; ks <= kMaxTiledKSplit; ++ks) {
+            if (ks > 1 && (stages / ks < 4 || (size_t)ks * M * N > capacity_floats)) break;
+            // a second round costs more than its share (nothing covers its ramp), a partly empty one nearly a whole one
+            const double rounds = tiles * ks / cus, full = std::ceil(rounds);
+            const double turns = rounds <= 1.0 ? 1.0 : 1.0 + 1.3 * (full - 1.0) - 0.3 * (rounds - 1.0);
+            const double core = turns * (t.stage * (double)((stages + ks - 1) / ks) + 0.373 * t.nw * t.mw);
+            const double hbm = weights * (1.0 + 0.33 * std::max(0.0, 1.0 - rounds));
+            double cost = std::sqrt(std::sqrt(core * core * core * core + hbm * hbm * hbm * hbm)) + ks * sums / 3.72e6;
+            if (!fused) cost += ks * sums / 5e6;
+            else if (ks > 1) cost += 3.3 + ks * sums / 5e6;
+            if (cost < best_cost) {
+                best_cost = cost;
+                best = RingPlan{t.id, ks};
+            }
+        }
+    }
+    return best;
+}
+
+// tile: 1 .. 3 the ring kernel with 64 tile rows, 11 .. 14 halved tiles of 64 (tile - 10) rows (128 columns to a workgroup), 4 / 5 the big tiles.  Columns from split_col on are cut into ksplit k
 // ranges (with one range none are; the ring kernel cuts every tile).
 template <int MODE>
 void launch_tiled(hipStream_t s, const void* Wp, const void* Xhi, int KB, int N, int M, const Epi& p, int tile, int ksplit,
@@ -812,13 +856,22 @@ void launch_tiled(hipStream_t s, const void* Wp, const void* Xhi, int KB, int N,
     if (tile < 4) {
         const int tiles_n = (N + 255) / 256, tiles_m = (M + 64 * tile - 1) / (64 * tile);
         const int grid = (tiles_n * tiles_m * ksplit + 7) / 8 * 8;
-        if (tile == 1) gemm_ring_kernel<MODE, 1><<<grid, 256, 0, s>>>(W, X, bias8, KB, NT32, MT32, tiles_n, tiles_m, ksplit, p);
+        if (tile == 1) gemm_ring_kernel<MODE, 4, 1><<<grid, 256, 0, s>>>(W, X, bias8, KB, NT32, MT32, tiles_n, tiles_m, ksplit, p);
         else if (MODE == MODE_SCORE || tile == 2)  // (score_tile knows no 192-row tile)
-            gemm_ring_kernel<MODE, 2><<<grid, 256, 0, s>>>(W, X, bias8, KB, NT32, MT32, tiles_n, tiles_m, ksplit, p);
-        else gemm_ring_kernel<MODE, MODE == MODE_SCORE ? 2 : 3><<<grid, 256, 0, s>>>(W, X, bias8, KB, NT32, MT32, tiles_n, tiles_m, ksplit, p);
+            gemm_ring_kernel<MODE, 4, 2><<<grid, 256, 0, s>>>(W, X, bias8, KB, NT32, MT32, tiles_n, tiles_m, ksplit, p);
+        else gemm_ring_kernel<MODE, 4, MODE == MODE_SCORE ? 2 : 3><<<grid, 256, 0, s>>>(W, X, bias8, KB, NT32, MT32, tiles_n, tiles_m, ksplit, p);
         return;
     }
     if constexpr (MODE != MODE_SCORE && MODE != MODE_LMHEAD) {
+        if (tile > 10) {
+            const int tiles_n = (N + 127) / 128, tiles_m = (M + 64 * (tile - 10) - 1) / (64 * (tile - 10));
+            const int grid = (tiles_n * tiles_m * ksplit + 7) / 8 * 8;
+            if (tile == 11) gemm_ring_kernel<MODE, 2, 1><<<grid, 256, 0, s>>>(W, X, bias8, KB, NT32, MT32, tiles_n, tiles_m, ksplit, p);
+            else if (tile == 12) gemm_ring_kernel<MODE, 2, 2><<<grid, 256, 0, s>>>(W, X, bias8, KB, NT32, MT32, tiles_n, tiles_m, ksplit, p);
+            else if (tile == 13) gemm_ring_kernel<MODE, 2, 3><<<grid, 256, 0, s>>>(W, X, bias8, KB, NT32, MT32, tiles_n, tiles_m, ksplit, p);
+            else gemm_ring_kernel<MODE, 2, 4><<<grid, 256, 0, s>>>(W, X, bias8, KB, NT32, MT32, tiles_n, tiles_m, ksplit, p);
+            return;
+        }
         const int bn = 64 * tile, tiles_n = (N + bn - 1) / bn, tiles_m = (M + BM - 1) / BM;
         const int split_tn = ksplit > 1 ? split_col / bn : tiles_n;  // without a k-split every tile is whole
         const int whole = split_tn * tiles_m, cutn = (tiles_n - split_tn) * tiles_m * ksplit;
@@ -872,7 +925,7 @@ void bf16_tiled_store_plan(int M, int N, int K, size_t capacity_floats, int* til
         return;
     }
     const RingPlan g = ring_plan(M, N, K / 16, false, few_rows_whole ? 0 : capacity_floats);
-    *tile = g.mw; *ks = g.ks; *split_col = 0;
+    *tile = g.tile; *ks = g.ks; *split_col = 0;
 }
 
 void bf16_tiled_plan_query(int M, int N, int K, int may_cut, size_t capacity_floats, int cus, int* tile_cols, int* ks,
@@ -897,7 +950,7 @@ static RingPlan fused_plan(int M, int N, int KB, size_t capacity_floats) {
 
 // The LM head's tiles (no scratch: whole k ranges; 192 rows at most to a tile).  Up to 64 rows one row of 64-row tiles: there the
 // final LayerNorm may come folded in.
-static RingPlan lm_head_plan(int M, int V, int K) { return ring_plan(M, V, K / 16, true, 0, M <= 64 ? 1 : 3); }
+static RingPlan lm_head_plan(int M, int V, int K) { return ring_plan_256(M, V, K / 16, true, 0, M <= 64 ? 1 : 3); }
 
 // The scoring head: 0 for gemm_score_kernel (two workgroups per CU: from two rounds of its tiles on), else the ring kernel's tile
 static int score_tile(int M, int V) {
@@ -914,15 +967,15 @@ void bf16_pass_plan_query(int use, int M, int N, int K, size_t capacity_floats, 
         bf16_tiled_store_plan(M, N, K, capacity_floats, &tile, ks, split_col, use == TILED_STORE_WHOLE);
     } else if (use == TILED_FUSED) {
         const RingPlan g = fused_plan(M, N, K / 16, capacity_floats);
-        tile = g.mw; *ks = g.ks;
+        tile = g.tile; *ks = g.ks;
     } else if (use == TILED_SCORE_HEAD) {
         tile = score_tile(M, N);
     } else {
-        tile = bf16_lm_head_streams(M, N) ? -1 : lm_head_plan(M, N, K).mw;
+        tile = bf16_lm_head_streams(M, N) ? -1 : lm_head_plan(M, N, K).tile;
     }
     plan_cus_override = 0;
-    *tile_rows = tile < 0 ? 32 : (tile == 0 ? 128 : (tile < 4 ? 64 * tile : 256));
-    *tile_cols = tile < 0 ? 32 : (tile == 5 ? 320 : 256);
+    *tile_rows = tile < 0 ? 32 : (tile == 0 ? 128 : (tile > 10 ? 64 * (tile - 10) : (tile < 4 ? 64 * tile : 256)));
+    *tile_cols = tile < 0 ? 32 : (tile == 5 ? 320 : 256);  // (halved tiles count whole)
 }
 
 void bf16_gemm_tiled_store(hipStream_t s, const void* Wp, const void* Xhi, int M, int N, int K, float* part, int tile, int ks,
@@ -937,11 +990,11 @@ void bf16_gemm_tiled(hipStream_t s, int mode, const void* Wp, const void* Xhi, i
     const Epi p = make_epi(M, N, a);
     const RingPlan g = fused_plan(M, N, K / 16, part_floats);
     if (g.ks == 1) {  // the epilogue runs in the GEMM
-        if (mode == EPI_BIAS_RELU) launch_tiled<MODE_BIAS_RELU>(s, Wp, Xhi, K / 16, N, M, p, g.mw, 1, 0);
-        else launch_tiled<MODE_QKV>(s, Wp, Xhi, K / 16, N, M, p, g.mw, 1, 0);
+        if (mode == EPI_BIAS_RELU) launch_tiled<MODE_BIAS_RELU>(s, Wp, Xhi, K / 16, N, M, p, g.tile, 1, 0);
+        else launch_tiled<MODE_QKV>(s, Wp, Xhi, K / 16, N, M, p, g.tile, 1, 0);
         return;
     }
-    bf16_gemm_tiled_store(s, Wp, Xhi, M, N, K, part, g.mw, g.ks, 0);
+    bf16_gemm_tiled_store(s, Wp, Xhi, M, N, K, part, g.tile, g.ks, 0);
     const unsigned grid = (unsigned)(((size_t)M * (N / 4) + 255) / 256);
     if (mode == EPI_BIAS_RELU) finish_kernel<MODE_BIAS_RELU><<<grid, 256, 0, s>>>(part, g.ks, (size_t)M * N, p);
     else finish_kernel<MODE_QKV><<<grid, 256, 0, s>>>(part, g.ks, (size_t)M * N, p);
@@ -956,7 +1009,7 @@ int bf16_lm_head_tiles(hipStream_t s, const void* Wp, const void* X, int M, int 
     if (fold) p = make_epi(M, V, *fold);
     p.M = M; p.N = V; p.st = st; p.logits = logits_opt; p.stats = stats; p.stats_idx = stats_idx;
     p.n_tiles = 2 * ((V + 255) / 256);
-    launch_tiled<MODE_LMHEAD>(s, Wp, X, K / 16, V, M, p, lm_head_plan(M, V, K).mw, 1, 0);
+    launch_tiled<MODE_LMHEAD>(s, Wp, X, K / 16, V, M, p, lm_head_plan(M, V, K).tile, 1, 0);
     return p.n_tiles;
 }
 
