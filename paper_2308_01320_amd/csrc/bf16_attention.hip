@@ -624,6 +624,177 @@ __global__ __launch_bounds__(256, 2) void attn_prompt_mfma_kernel(const float* _
         }
 }
 
+// The same for passes that leave CUs idle: the four wavefronts of a workgroup take one block of 32 queries together, every
+// fourth tile of keys each, and merge their sums in LDS at the end.  What bounds such a pass is the serial chain of a block's
+// tiles (1.7 us each with the tile's way through registers, LDS and a barrier); here it is a quarter as long and has no barrier: a
+// wavefront reads its K operands straight from the cache (the register image of one is a row's 16 bytes per lane) and
+// transposes V in LDS of its own.  The keys are read by four times as many workgroups, out of L2.  us, one workgroup per 128 queries ->
+// this: 250 queries, 32 heads of 128 16.2 -> 11.9; 500, 32 of 64 19.1 -> 12.1; 1000, 16 of 64 33.0 -> 17.5; 4 x 879, 2 of 64 29.1 -> 12.0;
+// 11 x 113, 8 of 64 (88 workgroups) 8.1 -> 8.1; 1000, 32 of 128 (256) 50.4 -> 63.3.
+template <int D>
+__global__ __launch_bounds__(256, 1) void attn_prompt_split_kernel(const float* __restrict__ q, const half_t* __restrict__ kv,
+                                                                u32x4* __restrict__ o, const he_dev_state* __restrict__ st, int S, int layer,
+                                                                int H, int n_heads, int max_batch, int max_seq, int batch) {
+    constexpr int WAVES = 4;
+    constexpr int KBD = D / 16, DB = D / 32, VPITCH = 36, NV = D / 32;  // NV: groups of eight dimensions a lane transposes per tile
+    __shared__ __align__(16) half_t vt[WAVES][D * VPITCH];
+    __shared__ f32x16 red[WAVES][DB][64];
+    __shared__ float2 ml[WAVES][32];
+    const int qblocks = (S + 31) / 32, pairs = batch * n_heads, per_xcd = (pairs + 7) / 8, slot = blockIdx.x >> 3;
+    const int pair = (slot % per_xcd) * 8 + (blockIdx.x & 7), qblock = qblocks - 1 - slot / per_xcd;  // longest first
+    if (pair >= pairs) return;  // the whole workgroup
+    const int h = pair % n_heads, b = pair / n_heads;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int j = lane & 31, hh = lane >> 5, t0 = qblock * 32;
+    const bool ok = t0 + j < S;
+    float4 qa[KBD], qc[KBD];
+    const float* qp = q + (size_t)(b * S + (ok ? t0 + j : 0)) * H + h * D + hh * 8;
+#pragma unroll
+    for (int kb = 0; kb < KBD; ++kb) {
+        qa[kb] = *reinterpret_cast<const float4*>(qp + kb * 16);
+        qc[kb] = *reinterpret_cast<const float4*>(qp + kb * 16 + 4);
+    }
+    const int cur = seq_len(st, b) - row_pad(st, b);  // cache position of row 0: negative while rows are padding
+    const int T = cur + S;                          // keys in the cache once this pass is stored
+    const int qpos = max(cur + t0 + j, 0);          // last key this lane's query may see (a padding row looks at key 0)
+    const int n_tiles = min(T - 1, cur + t0 + 31) / 32 + 1;
+    const half_t* Kg = kv + kv_index(layer, 0, b, h, 0, max_batch, n_heads, max_seq, D);
+    const half_t* Vg = kv + kv_index(layer, 1, b, h, 0, max_batch, n_heads, max_seq, D);
+    const int vp = lane & 15, vc = lane >> 4;  // V: keys 2 vp, 2 vp + 1, dimensions 8 (vc + 4 n) .. + 7
+    u32x4 kreg[KBD], vreg[NV][2];
+    auto request_tile = [&](int kt) {
+        const int key = kt * 32 + j;
+#pragma unroll
+        for (int kb = 0; kb < KBD; ++kb) {
+            kreg[kb] = u32x4{0u, 0u, 0u, 0u};
+            if (key < T) kreg[kb] = *reinterpret_cast<const u32x4*>(Kg + (size_t)key * D + kb * 16 + hh * 8);
+        }
+#pragma unroll
+        for (int n = 0; n < NV; ++n)
+#pragma unroll
+            for (int e = 0; e < 2; ++e) {
+                const int kabs = kt * 32 + 2 * vp + e;
+                vreg[n][e] = u32x4{0u, 0u, 0u, 0u};
+                if (kabs < T) vreg[n][e] = *reinterpret_cast<const u32x4*>(Vg + (size_t)kabs * D + (vc + 4 * n) * 8);
+            }
+    };
+    if (wave < n_tiles) request_tile(wave);
+    u32x4 qhi[KBD], qlo[KBD];
+#pragma unroll
+    for (int kb = 0; kb < KBD; ++kb) {
+        float4 a = qa[kb], c = qc[kb];
+        if (!ok) a = c = make_float4(0.f, 0.f, 0.f, 0.f);
+        uint32_t h0, h1, h2, h3, l0, l1, l2, l3;
+        split2(a.x, a.y, h0, l0); split2(a.z, a.w, h1, l1);
+        split2(c.x, c.y, h2, l2); split2(c.z, c.w, h3, l3);
+        qhi[kb] = u32x4{h0, h1, h2, h3};
+        qlo[kb] = u32x4{l0, l1, l2, l3};
+    }
+    f32x16 oacc[DB];
+#pragma unroll
+    for (int i = 0; i < DB; ++i) oacc[i] = f32x16{};
+    constexpr float kLog2e = 1.44269504f;
+    float m_run = -INFINITY, l_run = 0.f;  // m_run: in units of log2
+    uint32_t* vw = reinterpret_cast<uint32_t*>(&vt[wave][0]);
+    for (int kt = wave; kt < n_tiles; kt += WAVES) {
+        f32x16 sacc = f32x16{};
+#pragma unroll
+        for (int kb = 0; kb < KBD; ++kb) {
+            sacc = mfma_f16(kreg[kb], qlo[kb], sacc);
+            sacc = mfma_f16(kreg[kb], qhi[kb], sacc);
+        }
+#pragma unroll
+        for (int n = 0; n < NV; ++n) {
+            const uint32_t a[4] = {vreg[n][0].x, vreg[n][0].y, vreg[n][0].z, vreg[n][0].w};
+            const uint32_t c[4] = {vreg[n][1].x, vreg[n][1].y, vreg[n][1].z, vreg[n][1].w};
+            uint32_t* dst = vw + (vc + 4 * n) * 8 * (VPITCH / 2) + vp;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {  // (key 2 vp, key 2 vp + 1) of dimensions 2 e and 2 e + 1
+                dst[(2 * e) * (VPITCH / 2)] = (a[e] & 0xFFFFu) | (c[e] << 16);
+                dst[(2 * e + 1) * (VPITCH / 2)] = (a[e] >> 16) | (c[e] & 0xFFFF0000u);
+            }
+        }
+        if (kt + WAVES < n_tiles) request_tile(kt + WAVES);
+        if (kt * 32 + 31 > cur + t0) {  // the tile reaches past the first query's last key: mask per query
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const int kabs = kt * 32 + 8 * (r >> 2) + 4 * hh + (r & 3);
+                if (kabs > qpos) sacc[r] = -INFINITY;
+            }
+        }
+        float mx = -INFINITY;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) mx = fmaxf(mx, sacc[r]);
+        mx = lane_max32_apart(mx);
+        const float m_new = fmaxf(m_run, mx * kLog2e);
+        const float ref = m_new > -INFINITY ? m_new : 0.f;  // (no key of this tile visible to the query, and none before)
+        const float alpha = __builtin_amdgcn_exp2f(m_run - ref);
+        float psum = 0.f, pr[16];
+#pragma unroll
+        for (int r = 0; r < 16; ++r) { pr[r] = __builtin_amdgcn_exp2f(fmaf(sacc[r], kLog2e, -ref)); psum += pr[r]; }
+        l_run = l_run * alpha + psum;
+        if (__any(m_new != m_run)) {
+#pragma unroll
+            for (int i = 0; i < DB; ++i)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) oacc[i][r] *= alpha;
+        }
+        m_run = m_new;
+        asm volatile("" ::: "memory");  // (the wavefront's own LDS accesses stay in this order)
+#pragma unroll
+        for (int s2 = 0; s2 < 2; ++s2) {
+            uint32_t ph[4], pl[4];
+#pragma unroll
+            for (int x = 0; x < 4; ++x) split2(pr[8 * s2 + 2 * x], pr[8 * s2 + 2 * x + 1], ph[x], pl[x]);
+            const u32x4 phi = u32x4{ph[0], ph[1], ph[2], ph[3]}, plo = u32x4{pl[0], pl[1], pl[2], pl[3]};
+            u32x4 vblk[DB];
+#pragma unroll
+            for (int i = 0; i < DB; ++i) {
+                const half_t* vrow = &vt[wave][(i * 32 + j) * VPITCH + s2 * 16 + 4 * hh];
+                const uint2 v0 = *reinterpret_cast<const uint2*>(vrow), v1 = *reinterpret_cast<const uint2*>(vrow + 8);
+                vblk[i] = u32x4{v0.x, v0.y, v1.x, v1.y};
+            }
+#pragma unroll
+            for (int i = 0; i < DB; ++i) oacc[i] = mfma_f16(vblk[i], plo, oacc[i]);
+#pragma unroll
+            for (int i = 0; i < DB; ++i) oacc[i] = mfma_f16(vblk[i], phi, oacc[i]);
+        }
+        asm volatile("" ::: "memory");
+    }
+    // the wavefronts' sums, each against the largest score of all
+    const float l_tot = lane_sum32_apart(l_run);
+    if (hh == 0) ml[wave][j] = make_float2(m_run, l_tot);
+    __syncthreads();
+    float2 e[WAVES];
+    float all = -INFINITY, total = 0.f;
+#pragma unroll
+    for (int w = 0; w < WAVES; ++w) { e[w] = ml[w][j]; all = fmaxf(all, e[w].x); }
+    const float ref = all > -INFINITY ? all : 0.f;
+#pragma unroll
+    for (int w = 0; w < WAVES; ++w) total = fmaf(e[w].y, __builtin_amdgcn_exp2f(e[w].x - ref), total);
+    const float own = __builtin_amdgcn_exp2f(m_run - ref);
+#pragma unroll
+    for (int i = 0; i < DB; ++i) {
+#pragma unroll
+        for (int r = 0; r < 16; ++r) oacc[i][r] *= own;
+        red[wave][i][lane] = oacc[i];
+    }
+    __syncthreads();
+    if (!ok || wave >= DB) return;
+    const float inv = total > 0.f ? 1.0f / total : 0.f;  // 0: a block of padding rows saw no tile
+    const int m = b * S + t0 + j;
+    f32x16 sum = red[0][wave][lane];
+#pragma unroll
+    for (int w = 1; w < WAVES; ++w) sum += red[w][wave][lane];
+#pragma unroll
+    for (int qd = 0; qd < 4; ++qd) {
+        const int dim = h * D + wave * 32 + 8 * qd + 4 * hh;  // four consecutive output dimensions
+        const size_t slot2 = block_slot(m, dim & ~7, H >> 4);
+        reinterpret_cast<uint2*>(o + slot2)[(dim >> 2) & 1] =
+            make_uint2(pack2(sum[qd * 4 + 0] * inv, sum[qd * 4 + 1] * inv), pack2(sum[qd * 4 + 2] * inv, sum[qd * 4 + 3] * inv));
+    }
+}
+
 }  // namespace
 
 // ------------------------------------------------------------------ launchers
@@ -658,7 +829,18 @@ static void launch_attn(hipStream_t s, const float* q, const void* kv, void* o_b
 void bf16_attn(hipStream_t s, const float* q, const void* kv, void* o_blocks, const he_dev_state* st, int M, int S, int layer, int H, int n_heads, int max_batch, int max_seq) {
     if (S >= 32) {  // prompt rows: 32 queries per wavefront on the matrix cores
         const int batch = M / S;
-        const unsigned fgrid = (unsigned)((S + 127) / 128) * ((batch * n_heads + 7) / 8) * 8;
+        const unsigned pairs8 = (unsigned)((batch * n_heads + 7) / 8) * 8, fgrid = (unsigned)((S + 127) / 128) * pairs8;
+        // half of the CUs or fewer with a workgroup of 128 queries, and more than one block of keys to share out: see the kernel
+        if (S > 64 && (long)((S + 127) / 128) * batch * n_heads * 2 <= num_cus()) {
+            const unsigned sgrid = (unsigned)((S + 31) / 32) * pairs8;
+            if (H / n_heads == 128)
+                attn_prompt_split_kernel<128><<<sgrid, 256, 0, s>>>(q, (const half_t*)kv, (u32x4*)o_blocks, st, S, layer, H, n_heads,
+                                                                    max_batch, max_seq, batch);
+            else
+                attn_prompt_split_kernel<64><<<sgrid, 256, 0, s>>>(q, (const half_t*)kv, (u32x4*)o_blocks, st, S, layer, H, n_heads,
+                                                                   max_batch, max_seq, batch);
+            return;
+        }
         if (H / n_heads == 128)
             attn_prompt_mfma_kernel<128><<<fgrid, 256, 0, s>>>(q, (const half_t*)kv, (u32x4*)o_blocks, st, S, layer, H, n_heads,
                                                                max_batch, max_seq, batch);
