@@ -614,28 +614,27 @@ void tile_weights(he_engine* e) {
         bf16_wvec(e->stream, e->lm_tiled, c.vocab, H, e->w.lnf_g, e->w.lnf_b, v.c1, v.c2);
         return;
     }
-    if (!c.weights_tiled) {  // else the caller's matrices are used in place
-        auto tile = [&](const void* src, void* dst, int R, int K, const he_lora* ad) {
-            if (ad && ad->a && ad->b && e->lora_rank > 0)
-                bf16_tile_rows_lora(e->stream, src, dst, R, K, ad->a, ad->b, e->lora_rank, e->lora_scale);
-            else
-                bf16_tile_rows(e->stream, src, dst, R, K);
-        };
-        for (int l = 0; l < c.n_layers; ++l) {
-            const he_lora_layer* ad = e->lora.empty() ? nullptr : &e->lora[l];
-            tile(e->layers[l].wqkv, e->tiled[l].wqkv, 3 * H, H, ad ? &ad->wqkv : nullptr);
-            tile(e->layers[l].wo, e->tiled[l].wo, H, H, ad ? &ad->wo : nullptr);
-            tile(e->layers[l].w1, e->tiled[l].w1, F, H, ad ? &ad->w1 : nullptr);
-            tile(e->layers[l].w2, e->tiled[l].w2, H, F, ad ? &ad->w2 : nullptr);
-        }
-        bf16_tile_rows(e->stream, e->w.lm_head, e->lm_tiled, c.vocab, H);
-    }
+    const bool own = !c.weights_tiled;  // else the caller's matrices are used in place
+    auto tile = [&](const void* src, void* dst, int R, int K, const he_lora* ad) {
+        if (!own) return;
+        if (ad && ad->a && ad->b && e->lora_rank > 0)
+            bf16_tile_rows_lora(e->stream, src, dst, R, K, ad->a, ad->b, e->lora_rank, e->lora_scale);
+        else
+            bf16_tile_rows(e->stream, src, dst, R, K);
+    };
+    // W gamma and W beta right behind the tiles they read: part of what was just written is still in the memory side's cache
     for (int l = 0; l < c.n_layers; ++l) {
         const he_layer_weights& lw = e->layers[l];
+        const he_lora_layer* ad = e->lora.empty() ? nullptr : &e->lora[l];
         const CVec q = cvec_qkv(e, l), f = cvec_fc1(e, l);
+        tile(lw.wqkv, e->tiled[l].wqkv, 3 * H, H, ad ? &ad->wqkv : nullptr);
         bf16_wvec(e->stream, e->tiled[l].wqkv, 3 * H, H, lw.ln1_g, lw.ln1_b, q.c1, q.c2);
+        tile(lw.wo, e->tiled[l].wo, H, H, ad ? &ad->wo : nullptr);
+        tile(lw.w1, e->tiled[l].w1, F, H, ad ? &ad->w1 : nullptr);
         bf16_wvec(e->stream, e->tiled[l].w1, F, H, lw.ln2_g, lw.ln2_b, f.c1, f.c2);
+        tile(lw.w2, e->tiled[l].w2, H, F, ad ? &ad->w2 : nullptr);
     }
+    tile(e->w.lm_head, e->lm_tiled, c.vocab, H, nullptr);
     const CVec v = cvec_lm(e);
     bf16_wvec(e->stream, e->lm_tiled, c.vocab, H, e->w.lnf_g, e->w.lnf_b, v.c1, v.c2);
 }
