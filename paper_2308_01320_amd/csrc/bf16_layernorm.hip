@@ -38,7 +38,7 @@ __global__ __launch_bounds__(1024) void ln_blocks_kernel(float* __restrict__ r, 
         reinterpret_cast<float4*>(row)[i] = v;
         s += (v.x + v.y) + (v.z + v.w);
     }
-    for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o);
+    s = lane_sum<64>(s);
     if (lane == 0) red[wave] = s;
     __syncthreads();
     float tot = 0.f;
@@ -46,7 +46,7 @@ __global__ __launch_bounds__(1024) void ln_blocks_kernel(float* __restrict__ r, 
     const float mean = tot / H;
     float q = 0.f;
     for (int i = threadIdx.x; i < H; i += blockDim.x) { const float dlt = row[i] - mean; q += dlt * dlt; }
-    for (int o = 32; o > 0; o >>= 1) q += __shfl_xor(q, o);
+    q = lane_sum<64>(q);
     __syncthreads();
     if (lane == 0) red[wave] = q;
     __syncthreads();
@@ -157,7 +157,7 @@ __global__ __launch_bounds__(THREADS) void ln_row_kernel(float* __restrict__ r, 
     }
 #pragma unroll
     for (int j = 0; j < NV; ++j) s += (v[j].x + v[j].y) + (v[j].z + v[j].w);  // lanes past the row hold zeros
-    for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o);
+    s = lane_sum<64>(s);
     if (lane == 0) red[0][wave] = s;
     __syncthreads();
     float tot = 0.f;
@@ -172,7 +172,7 @@ __global__ __launch_bounds__(THREADS) void ln_row_kernel(float* __restrict__ r, 
             q += (d0 * d0 + d1 * d1) + (d2 * d2 + d3 * d3);
         }
     }
-    for (int o = 32; o > 0; o >>= 1) q += __shfl_xor(q, o);
+    q = lane_sum<64>(q);
     if (lane == 0) red[1][wave] = q;
     __syncthreads();
     tot = 0.f;
