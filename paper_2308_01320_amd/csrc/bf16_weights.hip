@@ -38,9 +38,13 @@ __global__ void tile_rows_kernel(const bf16_t* __restrict__ src, u32x4* __restri
 // Bound by the vector units (two operations per element and rank, kept apart by the definition) and the memory rate
 // in about equal parts at rank 16.  A wavefront takes 64 rows x 8 KC columns, a lane per row: the adapter's A values are then
 // the same for all lanes, come through the scalar cache and enter the multiplications as scalar operands, and a lane's B
-// value serves 8 KC of them.  (A thread per 16 bytes of result, as before, loaded 18 bytes per eight products: 16384 x 4096,
-// rank 16: 318 -> 82 us; the plain tiling of a matrix of that size is 52.)
-template <int KC>
+// value serves 8 KC of them.  Where the rank is a multiple of eight and B so aligned (WIDE), a row of B comes in loads of 16 bytes,
+// requested ahead of the sums they enter: a value at a time, each a cache line per lane, was most of the time.  (16384 x 4096, rank 16: a
+// thread per 16 bytes of result 318 us, B a value at a time 80, this 59; the plain tiling of a matrix of that size is 52.  Back to
+// back, B a value at a time -> this: rank 8 47.6 -> 45.8, 16 62.9 -> 52.6, 32 99.7 -> 86.1, 64 183 -> 152; 4112 columns, rank 16
+// 89.9 -> 69.0.  Groups of four values of other ranks were slower from rank 16 on (unaligned 63.6 -> 93.4), loads of W past the
+// cache too (106: two wavefronts share a line), and 64 columns to a wavefront (62).)
+template <int KC, bool WIDE>
 __global__ __launch_bounds__(256) void tile_rows_lora_kernel(const bf16_t* __restrict__ src, u32x4* __restrict__ dst, int R, int K,
                                                              int kgroups, const bf16_t* __restrict__ A,
                                                              const bf16_t* __restrict__ B, int rank, float scale) {
@@ -57,9 +61,7 @@ __global__ __launch_bounds__(256) void tile_rows_lora_kernel(const bf16_t* __res
     for (int i = 0; i < 8 * KC; ++i) t[i] = 0.f;
     const uint32_t* a = reinterpret_cast<const uint32_t*>(A + k0);  // (wave-uniform addresses: scalar loads)
     const bf16_t* bp = B + (size_t)rr * rank;
-#pragma unroll 2
-    for (int j = 0; j < rank; ++j) {
-        const float b = bf16_to_f32(bp[j]);
+    auto add = [&](int j, float b) {
 #pragma unroll
         for (int i = 0; i < 4 * KC; ++i) {
             const uint32_t aw = a[(size_t)j * (K / 2) + i];
@@ -67,6 +69,21 @@ __global__ __launch_bounds__(256) void tile_rows_lora_kernel(const bf16_t* __res
             t[2 * i] = t[2 * i] + p0;
             t[2 * i + 1] = t[2 * i + 1] + p1;
         }
+    };
+    if constexpr (WIDE) {
+        u32x4 nxt = *reinterpret_cast<const u32x4*>(bp);
+        for (int j0 = 0; j0 < rank; j0 += 8) {
+            const uint32_t bw[4] = {nxt.x, nxt.y, nxt.z, nxt.w};
+            if (j0 + 8 < rank) nxt = *reinterpret_cast<const u32x4*>(bp + j0 + 8);
+#pragma unroll
+            for (int x = 0; x < 4; ++x) {
+                add(j0 + 2 * x, bf_lo(bw[x]));
+                add(j0 + 2 * x + 1, bf_hi(bw[x]));
+            }
+        }
+    } else {
+#pragma unroll 2
+        for (int j = 0; j < rank; ++j) add(j, bf16_to_f32(bp[j]));
     }
     if ((r >> 5) >= (R + 31) / 32) return;
 #pragma unroll
@@ -226,10 +243,10 @@ void bf16_tile_rows_lora(hipStream_t s, const void* src, void* dst, int R, int K
     const int kc = K % 32 == 0 ? 4 : 2;  // (K is a multiple of 16)
     const int kgroups = (K + 32 * kc - 1) / (32 * kc);
     const unsigned grid = (unsigned)((R + 63) / 64 * kgroups);
-    if (kc == 4)
-        tile_rows_lora_kernel<4><<<grid, 256, 0, s>>>((const bf16_t*)src, (u32x4*)dst, R, K, kgroups, (const bf16_t*)A, (const bf16_t*)B,
-                                                      rank, scale);
-    else
-        tile_rows_lora_kernel<2><<<grid, 256, 0, s>>>((const bf16_t*)src, (u32x4*)dst, R, K, kgroups, (const bf16_t*)A, (const bf16_t*)B,
-                                                      rank, scale);
+    const bool wide = rank % 8 == 0 && (reinterpret_cast<uintptr_t>(B) & 15) == 0;  // a row of B in loads of 16 bytes
+    auto launch = [&](auto kernel) {
+        kernel<<<grid, 256, 0, s>>>((const bf16_t*)src, (u32x4*)dst, R, K, kgroups, (const bf16_t*)A, (const bf16_t*)B, rank, scale);
+    };
+    if (kc == 4) wide ? launch(tile_rows_lora_kernel<4, true>) : launch(tile_rows_lora_kernel<4, false>);
+    else wide ? launch(tile_rows_lora_kernel<2, true>) : launch(tile_rows_lora_kernel<2, false>);
 }
