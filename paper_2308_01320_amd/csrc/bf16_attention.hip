@@ -800,12 +800,14 @@ __global__ __launch_bounds__(256, 1) void attn_prompt_split_kernel(const float* 
 // ------------------------------------------------------------------ launchers
 
 // Wavefronts of a (row, head) in the one-pass form, or 0 for the two-pass one.  The rule looks at the cache's size and not at how far it
-// is filled: a captured step must add up like the eager one.  More than two pairs to a CU: from some 200 keys on the two-pass form is
-// ahead (measured between 160, even, and 200, 43.6 us against 44.2), below it two wavefronts.  Else as many as one round over a
+// is filled: a captured step must add up like the eager one.  More than two pairs to a CU: from some size of the cache on the two-pass form
+// is ahead, below it two wavefronts.  A layer of a greedy job whose last third is generated, us per step, two passes / one: heads of 128, 1280 pairs, cache of
+// 144 96.5 / 96.2, 160 98.6 / 98.4, 192 100.3 / 100.4, 256 106.4 / 108.5; 768 pairs, 160 71.6 / 71.7, 192 72.4 / 73.2; heads of 64, a row of half the
+// bytes, 1024 pairs, 192 45.8 / 45.4, 256 50.7 / 48.9; 2048 pairs, 256 75.2 / 73.8 (the largest measured).  Else as many as one round over a
 // full cache takes, at most four, or eight where a CU has at most one pair.
 static int attn_waves(long pairs, int max_seq, int d) {
     const long cus = num_cus();
-    if (pairs > 2 * cus) return max_seq > 192 ? 0 : 2;
+    if (pairs > 2 * cus) return max_seq > (d == 128 ? 160 : 256) ? 0 : 2;
     const int keys_per_wave = 4 * 64 / (d / 8), most = pairs <= cus ? 8 : 4;  // of one round
     int waves = 2;
     while (waves < most && waves * keys_per_wave < max_seq) waves *= 2;

@@ -25,14 +25,15 @@ def _model(H, nh):
 
 
 # (B, S, cache): attention over S, S + 1 and S + 2 keys.  A round is 16 keys a wavefront with heads of 128, 32 with heads of 64.  On
-# 256 CUs two heads make 2, 4, 6 (at most eight wavefronts), 260 or 512 (four), 514 pairs (two, or two passes above 192)
+# 256 CUs two heads make 2, 4, 6 (at most eight wavefronts), 260 or 512 (four), 514 pairs (two, or two passes above a cache of 160 with
+# heads of 128, of 256 with heads of 64)
 @pytest.mark.parametrize("ragged", [False, True])
 @pytest.mark.parametrize("H,nh,B,S,cache", [
     (256, 2, 1, 1, 20), (256, 2, 1, 30, 32), (256, 2, 2, 31, 33), (256, 2, 3, 62, 64), (256, 2, 1, 63, 65), (256, 2, 2, 127, 200),
-    (256, 2, 1, 255, 260), (256, 2, 130, 63, 100), (256, 2, 256, 31, 40), (256, 2, 257, 31, 40), (256, 2, 257, 63, 192),
-    (256, 2, 257, 63, 193),
+    (256, 2, 1, 255, 260), (256, 2, 130, 63, 100), (256, 2, 256, 31, 40), (256, 2, 257, 31, 40), (256, 2, 257, 63, 160),
+    (256, 2, 257, 63, 161),
     (128, 2, 1, 1, 8), (128, 2, 1, 62, 64), (128, 2, 2, 126, 128), (128, 2, 3, 127, 129), (128, 2, 1, 255, 258), (128, 2, 130, 127, 200),
-    (128, 2, 257, 63, 100), (128, 2, 257, 63, 193),
+    (128, 2, 257, 63, 256), (128, 2, 257, 63, 257),
 ])
 def test_decode_attention_at_its_edges(H, nh, B, S, cache, ragged):
     import torch
