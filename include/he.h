@@ -378,6 +378,17 @@ typedef struct {
 } he_pass_plan;
 he_status he_plan_pass_gemm(const he_config* cfg, int rows, int which, int scoring, int cus, he_pass_plan* out);
 
+/* Test hook, host logic only: the kernel that computes the attention of B sequences with S rows each (S = 1: a decode step) in
+ * an engine created with cfg, and the wavefronts of its workgroups.  cus as in he_plan_prompt_gemm.  bf16, impl 0 only. */
+enum {
+    HE_ATTN_TWO_PASSES = 0,   /* a workgroup per (row, head): scores of all keys, then the weighted values */
+    HE_ATTN_ONE_PASS = 1,     /* the same with a running soft-max */
+    HE_ATTN_SHORT_PROMPT = 2, /* blocks of eight queries */
+    HE_ATTN_PROMPT = 3,       /* matrix cores, 32 queries to a wavefront */
+    HE_ATTN_PROMPT_SPLIT = 4  /* matrix cores, 32 queries to the four wavefronts of a workgroup */
+};
+he_status he_plan_attention(const he_config* cfg, int B, int S, int cus, int* form, int* wavefronts);
+
 /* Measurement hook: a plain copy kernel (reads `bytes`, writes `bytes`, a multiple of 16,
  * device pointers, on `stream`).  Hardware byte counters (rocprofv3 FETCH_SIZE /
  * WRITE_SIZE) are scaled by what they read for this kernel of known size. */

@@ -143,6 +143,8 @@ def lib() -> C.CDLL:
     L.he_plan_prompt_gemm.restype = C.c_int
     L.he_plan_prompt_gemm.argtypes = [C.c_int, C.c_int, C.c_int, C.c_int, C.c_size_t, C.c_int, C.POINTER(C.c_int),
                                       C.POINTER(C.c_int), C.POINTER(C.c_int)]
+    L.he_plan_attention.restype = C.c_int
+    L.he_plan_attention.argtypes = [C.POINTER(he_config), C.c_int, C.c_int, C.c_int, C.POINTER(C.c_int), C.POINTER(C.c_int)]
     L.he_kernel_sweep.restype = C.c_int
     L.he_kernel_sweep.argtypes = [vp, C.c_int, C.c_int]
     L.he_calibration_copy.restype = C.c_int
@@ -160,7 +162,7 @@ EXPORTS = ("he_workspace_bytes", "he_create", "he_refresh_weights", "he_prefill"
            "he_generate_ragged", "he_refresh_weights_lora", "he_release_arena", "he_acquire_arena",
            "he_tile_matrix_lora", "he_plan_decode_gemm", "he_fp8_quantize_rows", "he_decode_step_static",
            "he_decode_scratch_account", "he_arrival_counters_nonzero", "he_arrival_counters_set", "he_last_step_rows",
-           "he_plan_prompt_gemm", "he_plan_pass_gemm")
+           "he_plan_prompt_gemm", "he_plan_pass_gemm", "he_plan_attention")
 
 KERNEL_CLASSES = ("layernorm", "qkv", "attention", "out_proj", "fc1", "fc2", "lm_head", "empty")
 
@@ -431,6 +433,18 @@ def he_plan_pass_gemm(cfg: he_config, rows: int, which: str, scoring=False, cus:
     if rc != HE_OK:
         raise HeError(rc, "he_plan_pass_gemm")
     return out
+
+
+ATTENTION_FORMS = ("two passes", "one pass", "short prompt", "prompt", "prompt split")
+
+
+def he_plan_attention(cfg: he_config, B: int, S: int = 1, cus: int = 256):
+    """(form, wavefronts of a workgroup) of the attention over S rows of B sequences each; host logic only."""
+    f, w = C.c_int(), C.c_int()
+    rc = lib().he_plan_attention(C.byref(cfg), B, S, cus, C.byref(f), C.byref(w))
+    if rc != HE_OK:
+        raise HeError(rc, "he_plan_attention")
+    return ATTENTION_FORMS[f.value], w.value
 
 
 def he_decode_scratch_account(cfg: he_config, B: int, which: int, cus: int = 256) -> he_scratch_account:

@@ -1,4 +1,5 @@
 // bf16 path: attention over the KV cache of IEEE halves (decode rows, short prompts, prompt rows on the matrix cores).
+#include "../../include/he.h"
 #include "bf16_common.h"
 
 using namespace he_bf16;
@@ -806,7 +807,7 @@ __global__ __launch_bounds__(256, 1) void attn_prompt_split_kernel(const float* 
 // bytes, 1024 pairs, 192 45.8 / 45.4, 256 50.7 / 48.9; 2048 pairs, 256 75.2 / 73.8 (the largest measured).  Else as many as one round over a
 // full cache takes, at most four, or eight where a CU has at most one pair.
 static int attn_waves(long pairs, int max_seq, int d) {
-    const long cus = num_cus();
+    const long cus = plan_cus();
     if (pairs > 2 * cus) return max_seq > (d == 128 ? 160 : 256) ? 0 : 2;
     const int keys_per_wave = 4 * 64 / (d / 8), most = pairs <= cus ? 8 : 4;  // of one round
     int waves = 2;
@@ -816,11 +817,11 @@ static int attn_waves(long pairs, int max_seq, int d) {
 
 template <int D>
 static void launch_attn(hipStream_t s, const float* q, const void* kv, void* o_blocks, const he_dev_state* st, int M, int S, int layer,
-                        int H, int n_heads, int max_batch, int max_seq) {
+                        int H, int n_heads, int max_batch, int max_seq, int waves) {
     const dim3 grid(M, n_heads);
     const half_t* c = (const half_t*)kv;
     u32x4* o = (u32x4*)o_blocks;
-    switch (attn_waves((long)M * n_heads, max_seq, D)) {
+    switch (waves) {
         case 8: attn_few_kernel<D, 8><<<grid, 512, 0, s>>>(q, c, o, st, S, layer, H, n_heads, max_batch, max_seq); break;
         case 4: attn_few_kernel<D, 4><<<grid, 256, 0, s>>>(q, c, o, st, S, layer, H, n_heads, max_batch, max_seq); break;
         case 2: attn_few_kernel<D, 2><<<grid, 128, 0, s>>>(q, c, o, st, S, layer, H, n_heads, max_batch, max_seq); break;
@@ -828,40 +829,48 @@ static void launch_attn(hipStream_t s, const float* q, const void* kv, void* o_b
     }
 }
 
+// Prompt rows: half of the CUs or fewer with a workgroup of 128 queries, and more than one block of keys to share out: see the kernel
+static bool prompt_splits(int pairs, int S) { return S > 64 && (long)((S + 127) / 128) * pairs * 2 <= plan_cus(); }
+
+// The kernel that M rows of S per sequence take (HE_ATTN_ in he.h) and the wavefronts of its workgroups.
+struct AttnPlan { int form, waves; };
+static AttnPlan attn_plan(int M, int S, int n_heads, int d, int max_seq) {
+    if (S >= 32) return {prompt_splits(M / S * n_heads, S) ? HE_ATTN_PROMPT_SPLIT : HE_ATTN_PROMPT, 4};
+    if (S >= QB && (size_t)QB * max_seq * sizeof(float) <= 96 * 1024) return {HE_ATTN_SHORT_PROMPT, 4};
+    const int waves = attn_waves((long)M * n_heads, max_seq, d);
+    return waves ? AttnPlan{HE_ATTN_ONE_PASS, waves} : AttnPlan{HE_ATTN_TWO_PASSES, 4};
+}
+
+void bf16_attn_plan_query(int M, int S, int n_heads, int d, int max_seq, int cus, int* form, int* waves) {
+    plan_cus_override = cus;
+    const AttnPlan g = attn_plan(M, S, n_heads, d, max_seq);
+    plan_cus_override = 0;
+    *form = g.form;
+    *waves = g.waves;
+}
+
 void bf16_attn(hipStream_t s, const float* q, const void* kv, void* o_blocks, const he_dev_state* st, int M, int S, int layer, int H, int n_heads, int max_batch, int max_seq) {
-    if (S >= 32) {  // prompt rows: 32 queries per wavefront on the matrix cores
-        const int batch = M / S;
-        const unsigned pairs8 = (unsigned)((batch * n_heads + 7) / 8) * 8, fgrid = (unsigned)((S + 127) / 128) * pairs8;
-        // half of the CUs or fewer with a workgroup of 128 queries, and more than one block of keys to share out: see the kernel
-        if (S > 64 && (long)((S + 127) / 128) * batch * n_heads * 2 <= num_cus()) {
-            const unsigned sgrid = (unsigned)((S + 31) / 32) * pairs8;
-            if (H / n_heads == 128)
-                attn_prompt_split_kernel<128><<<sgrid, 256, 0, s>>>(q, (const half_t*)kv, (u32x4*)o_blocks, st, S, layer, H, n_heads,
-                                                                    max_batch, max_seq, batch);
-            else
-                attn_prompt_split_kernel<64><<<sgrid, 256, 0, s>>>(q, (const half_t*)kv, (u32x4*)o_blocks, st, S, layer, H, n_heads,
-                                                                   max_batch, max_seq, batch);
-            return;
-        }
-        if (H / n_heads == 128)
-            attn_prompt_mfma_kernel<128><<<fgrid, 256, 0, s>>>(q, (const half_t*)kv, (u32x4*)o_blocks, st, S, layer, H, n_heads,
-                                                               max_batch, max_seq, batch);
-        else
-            attn_prompt_mfma_kernel<64><<<fgrid, 256, 0, s>>>(q, (const half_t*)kv, (u32x4*)o_blocks, st, S, layer, H, n_heads,
-                                                              max_batch, max_seq, batch);
-        return;
+    const half_t* c = (const half_t*)kv;
+    u32x4* o = (u32x4*)o_blocks;
+    const int d = H / n_heads, batch = M / S;
+    const unsigned pairs8 = (unsigned)((batch * n_heads + 7) / 8) * 8;
+    const AttnPlan g = attn_plan(M, S, n_heads, d, max_seq);
+    if (g.form == HE_ATTN_PROMPT_SPLIT) {
+        const unsigned grid = (unsigned)((S + 31) / 32) * pairs8;
+        if (d == 128) attn_prompt_split_kernel<128><<<grid, 256, 0, s>>>(q, c, o, st, S, layer, H, n_heads, max_batch, max_seq, batch);
+        else attn_prompt_split_kernel<64><<<grid, 256, 0, s>>>(q, c, o, st, S, layer, H, n_heads, max_batch, max_seq, batch);
+    } else if (g.form == HE_ATTN_PROMPT) {  // 32 queries per wavefront on the matrix cores
+        const unsigned grid = (unsigned)((S + 127) / 128) * pairs8;
+        if (d == 128) attn_prompt_mfma_kernel<128><<<grid, 256, 0, s>>>(q, c, o, st, S, layer, H, n_heads, max_batch, max_seq, batch);
+        else attn_prompt_mfma_kernel<64><<<grid, 256, 0, s>>>(q, c, o, st, S, layer, H, n_heads, max_batch, max_seq, batch);
+    } else if (g.form == HE_ATTN_SHORT_PROMPT) {  // blocks of QB queries per workgroup
+        const size_t shm = (size_t)QB * max_seq * sizeof(float);
+        const dim3 grid((S + QB - 1) / QB, n_heads, batch);
+        if (d == 128) attn_prompt_kernel<128><<<grid, 256, shm, s>>>(q, c, o, st, S, layer, H, n_heads, max_batch, max_seq);
+        else attn_prompt_kernel<64><<<grid, 256, shm, s>>>(q, c, o, st, S, layer, H, n_heads, max_batch, max_seq);
+    } else {
+        const int waves = g.form == HE_ATTN_ONE_PASS ? g.waves : 0;
+        if (d == 128) launch_attn<128>(s, q, kv, o_blocks, st, M, S, layer, H, n_heads, max_batch, max_seq, waves);
+        else launch_attn<64>(s, q, kv, o_blocks, st, M, S, layer, H, n_heads, max_batch, max_seq, waves);
     }
-    const size_t prompt_shm = (size_t)QB * max_seq * sizeof(float);
-    if (S >= QB && prompt_shm <= 96 * 1024) {  // short prompts: blocks of QB queries per workgroup
-        dim3 pgrid((S + QB - 1) / QB, n_heads, M / S);
-        if (H / n_heads == 128)
-            attn_prompt_kernel<128><<<pgrid, 256, prompt_shm, s>>>(q, (const half_t*)kv, (u32x4*)o_blocks, st, S, layer, H, n_heads,
-                                                                   max_batch, max_seq);
-        else
-            attn_prompt_kernel<64><<<pgrid, 256, prompt_shm, s>>>(q, (const half_t*)kv, (u32x4*)o_blocks, st, S, layer, H, n_heads,
-                                                                  max_batch, max_seq);
-        return;
-    }
-    if (H / n_heads == 128) launch_attn<128>(s, q, kv, o_blocks, st, M, S, layer, H, n_heads, max_batch, max_seq);
-    else launch_attn<64>(s, q, kv, o_blocks, st, M, S, layer, H, n_heads, max_batch, max_seq);
 }

@@ -1280,6 +1280,13 @@ he_status he_plan_pass_gemm(const he_config* cfg, int rows, int which, int scori
     return HE_OK;
 }
 
+he_status he_plan_attention(const he_config* cfg, int B, int S, int cus, int* form, int* wavefronts) {
+    if (!form || !wavefronts || check_config(cfg) || check_shape(cfg) || !is_fast(*cfg)) return HE_ERR_INVALID_ARG;
+    if (B < 1 || B > cfg->max_batch || S < 1 || S > cfg->max_seq_len || (long)B * S > INT32_MAX || cus < 0) return HE_ERR_INVALID_ARG;
+    bf16_attn_plan_query(B * S, S, cfg->n_heads, cfg->hidden / cfg->n_heads, cfg->max_seq_len, cus, form, wavefronts);
+    return HE_OK;
+}
+
 he_status he_decode_scratch_account(const he_config* cfg, int B, int which, int cus, he_scratch_account* out) {
     if (!out || check_config(cfg) || check_shape(cfg) || !is_fast(*cfg)) return HE_ERR_INVALID_ARG;
     if (B < 1 || B > cfg->max_batch || B > 64 || (which != 0 && which != 1) || cus < 0) return HE_ERR_INVALID_ARG;

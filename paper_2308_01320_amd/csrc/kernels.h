@@ -154,3 +154,5 @@ void bf16_ln(hipStream_t s, float* r, const float* part, int ksplit, size_t part
              int writeback, int split_col = 0);
 void bf16_attn(hipStream_t s, const float* q, const void* kv, void* o_blocks, const he_dev_state* st, int M, int S,
                int layer, int H, int n_heads, int max_batch, int max_seq);
+// host logic: which kernel that launch is (HE_ATTN_ in he.h), wavefronts to a workgroup
+void bf16_attn_plan_query(int M, int S, int n_heads, int d, int max_seq, int cus, int* form, int* waves);

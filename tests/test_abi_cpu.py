@@ -193,6 +193,26 @@ def test_pass_gemms_stay_inside_their_scratch():
         binding.he_plan_pass_gemm(binding.make_config(synth.CONFIGS["tiny"]), 8, "qkv")  # float
 
 
+def _attention(H, nh, B, S, cache, cus=256):
+    import dataclasses
+    d = dataclasses.replace(synth.CONFIGS["tiny"], dtype="bf16", hidden=H, n_heads=nh)
+    return binding.he_plan_attention(binding.make_config(d, max_batch=B, max_seq_len=cache), B, S, cus)
+
+
+def test_attention_kernels_that_the_gpu_tests_name():
+    """The sizes of tests/test_gpu_decode_attention.py reach every wavefront count of the one-pass form and the two-pass one."""
+    for B, cache, waves in ((1, 20, 2), (1, 32, 2), (2, 33, 4), (3, 64, 4), (1, 65, 8), (2, 200, 8), (1, 260, 8), (130, 100, 4), (256, 40, 4),
+                            (257, 40, 2), (257, 160, 2)):
+        assert _attention(256, 2, B, 1, cache) == ("one pass", waves), (B, cache)
+    for B, cache, waves in ((1, 8, 2), (1, 64, 2), (2, 128, 4), (3, 129, 8), (1, 258, 8), (130, 200, 4), (257, 256, 2)):
+        assert _attention(128, 2, B, 1, cache) == ("one pass", waves), (B, cache)
+    assert _attention(256, 2, 257, 1, 161) == _attention(128, 2, 257, 1, 257) == ("two passes", 4)
+    assert _attention(512, 4, 3, 20, 40) == ("short prompt", 4) and _attention(512, 4, 3, 20, 8000) == ("one pass", 8)
+    assert _attention(512, 4, 1, 64, 64) == ("prompt", 4) and _attention(512, 4, 1, 65, 65) == ("prompt split", 4)
+    with pytest.raises(binding.HeError):
+        _attention(512, 4, 1, 9, 8)  # more rows than the cache holds
+
+
 def test_planner_queries_of_one_thread_do_not_change_anothers_plans():
     """A query may name another CU count, and the scratch account dry-runs the launcher: both belong to the calling thread.  (Four
     threads ask for four chip sizes; with either process-wide some four answers in a thousand belong to another thread.)"""
