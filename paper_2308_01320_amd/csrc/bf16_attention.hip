@@ -630,8 +630,8 @@ __global__ __launch_bounds__(256, 2) void attn_prompt_mfma_kernel(const float* _
 // tiles (1.7 us each with the tile's way through registers, LDS and a barrier); here it is a quarter as long and has no barrier: a
 // wavefront reads its K operands straight from the cache (the register image of one is a row's 16 bytes per lane) and
 // transposes V in LDS of its own.  The keys are read by four times as many workgroups, out of L2.  us, one workgroup per 128 queries ->
-// this: 250 queries, 32 heads of 128 16.2 -> 11.9; 500, 32 of 64 19.1 -> 12.1; 1000, 16 of 64 33.0 -> 17.5; 4 x 879, 2 of 64 29.1 -> 12.0;
-// 11 x 113, 8 of 64 (88 workgroups) 8.1 -> 8.1; 1000, 32 of 128 (256) 50.4 -> 63.3.
+// this: 250 queries, 32 heads of 128 16.2 -> 11.9; 500, 32 of 64 19.1 -> 12.1; 1000, 16 of 64 33.0 -> 17.5; 4 x 879, 2 of 64 29.1 -> 12.0.  (Where a second
+// round of workgroups loses: prompt_splits below.)
 template <int D>
 __global__ __launch_bounds__(256, 1) void attn_prompt_split_kernel(const float* __restrict__ q, const half_t* __restrict__ kv,
                                                                 u32x4* __restrict__ o, const he_dev_state* __restrict__ st, int S, int layer,
@@ -829,13 +829,25 @@ static void launch_attn(hipStream_t s, const float* q, const void* kv, void* o_b
     }
 }
 
-// Prompt rows: half of the CUs or fewer with a workgroup of 128 queries, and more than one block of keys to share out: see the kernel
-static bool prompt_splits(int pairs, int S) { return S > 64 && (long)((S + 127) / 128) * pairs * 2 <= plan_cus(); }
+// Prompt rows whose workgroups of 128 queries occupy half of the CUs or fewer, with more than one block of keys to share out: 32 queries
+// to a workgroup, as long as these do not come in rounds that cost more than a longer block does.  Heads of 128 leave room for one of
+// them to a CU (LDS), heads of 64 for three.  `blocks`: workgroups of an XCD, which takes every eighth (sequence, head) pair whole.  us a
+// launch, 128 queries to a workgroup -> 32, 256 CUs.  Heads of 128, one round: 96 queries x 64 pairs 10.9 -> 10.9, 250 x 32 17.9 -> 13.7, 1500 x 5 66.6 ->
+// 33.3; up to two: 96 x 96 11.1 -> 16.7, 192 x 48 14.4 -> 17.2, 250 x 48 18.0 -> 20.0, 320 x 40 20.0 -> 22.3, but of four pairs to an XCD 320 x 32
+// 17.7 -> 16.8, 500 x 32 28.4 -> 25.6, 1000 x 16 48.4 -> 34.1; beyond: 384 x 42 23.4 -> 30.0, 640 x 25 33.4 -> 36.4, but of three pairs to an XCD
+// 765 x 20 38.4 -> 36.9, 829 x 18 39.3 -> 41.0, 2000 x 8 86.7 -> 49.2.  Heads of 64, more than a round, difference: 65 queries +0.4, 96 +0.9,
+// 112 x 80 and 128 pairs -0.7 and -0.1, 128 +0.1, 160 0.0, 192 -0.8, 250 -2.4, 500 -6.8.
+static bool prompt_splits(int pairs, int S, int d) {
+    const long cus = plan_cus(), per_xcd = (pairs + 7) / 8, blocks = (S + 31) / 32 * per_xcd, round = cus / 8;
+    if (S <= 64 || (long)((S + 127) / 128) * pairs * 2 > cus) return false;
+    if (blocks <= round) return true;
+    return d == 128 ? per_xcd <= 3 || (per_xcd == 4 && blocks <= 2 * round) : S > 96;
+}
 
 // The kernel that M rows of S per sequence take (HE_ATTN_ in he.h) and the wavefronts of its workgroups.
 struct AttnPlan { int form, waves; };
 static AttnPlan attn_plan(int M, int S, int n_heads, int d, int max_seq) {
-    if (S >= 32) return {prompt_splits(M / S * n_heads, S) ? HE_ATTN_PROMPT_SPLIT : HE_ATTN_PROMPT, 4};
+    if (S >= 32) return {prompt_splits(M / S * n_heads, S, d) ? HE_ATTN_PROMPT_SPLIT : HE_ATTN_PROMPT, 4};
     if (S >= QB && (size_t)QB * max_seq * sizeof(float) <= 96 * 1024) return {HE_ATTN_SHORT_PROMPT, 4};
     const int waves = attn_waves((long)M * n_heads, max_seq, d);
     return waves ? AttnPlan{HE_ATTN_ONE_PASS, waves} : AttnPlan{HE_ATTN_TWO_PASSES, 4};

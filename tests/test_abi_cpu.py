@@ -213,6 +213,20 @@ def test_attention_kernels_that_the_gpu_tests_name():
         _attention(512, 4, 1, 9, 8)  # more rows than the cache holds
 
 
+def test_prompt_attention_in_blocks_of_32_queries_only_where_it_is_ahead():
+    """Measured on both kernels (256 CUs): more than a round of workgroups of 32 queries loses up to 1.5 times on short prompts of heads of
+    128, less on heads of 64, and gains on long ones."""
+    for S, pairs, split in ((64, 8, False), (65, 64, True), (65, 88, False), (70, 97, False), (96, 96, False), (128, 64, True), (128, 80, False), (129, 48, True),
+                            (129, 56, False), (192, 48, False), (250, 32, True), (250, 64, False), (320, 32, True), (320, 37, False), (384, 42, False),
+                            (500, 32, True), (640, 19, True), (640, 25, False), (1000, 16, True), (2000, 8, True), (2000, 9, False)):
+        assert _attention(128 * pairs, pairs, 1, S, S)[0] == ("prompt split" if split else "prompt"), (S, pairs)
+    for S, pairs, split in ((65, 80, True), (65, 96, False), (96, 80, True), (96, 81, False), (97, 128, True), (129, 64, True), (250, 64, True), (384, 42, True),
+                            (1000, 16, True), (1000, 18, False)):
+        assert _attention(64 * pairs, pairs, 1, S, S)[0] == ("prompt split" if split else "prompt"), (S, pairs)
+    # three sequences of 32 heads, and the same on 304 CUs (a round of 38 to an XCD)
+    assert _attention(4096, 32, 3, 96, 96)[0] == "prompt" and _attention(4096, 32, 3, 96, 96, 304)[0] == "prompt split"
+
+
 def test_planner_queries_of_one_thread_do_not_change_anothers_plans():
     """A query may name another CU count, and the scratch account dry-runs the launcher: both belong to the calling thread.  (Four
     threads ask for four chip sizes; with either process-wide some four answers in a thousand belong to another thread.)"""

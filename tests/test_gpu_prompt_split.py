@@ -21,13 +21,13 @@ def _model(H, nh):
     return d, util.weights_f64(w), binding.upload_weights(w, "bf16")
 
 
-# 64 rows: the kernel before; 65 .. 160: one to five tiles of keys (fewer than the wavefronts, as many, one more); 128 pairs of one
-# block of 128 queries are the most, 144 the kernel before
+# 64 rows: the kernel of 128 queries to a workgroup; 65 .. 160: one to five tiles of keys (fewer than the wavefronts, as many, one more); 500 x 32
+# and 161 x 64 pairs: more workgroups than CUs; 65 x 128 and more pairs: 128 queries again, 97 x 128: not with heads of 64
 @pytest.mark.parametrize("ragged", [False, True])
 @pytest.mark.parametrize("H,nh,B,S", [
     (512, 4, 1, 64), (512, 4, 1, 65), (512, 4, 2, 96), (512, 4, 3, 97), (512, 4, 1, 128), (512, 4, 1, 129), (512, 4, 5, 160), (512, 4, 2, 500),
-    (512, 4, 32, 65), (512, 4, 36, 65),
-    (512, 8, 1, 65), (512, 8, 3, 97), (512, 8, 1, 129), (512, 8, 2, 161), (512, 8, 1, 700), (512, 8, 16, 70), (512, 8, 18, 70),
+    (512, 4, 32, 65), (512, 4, 36, 65), (512, 4, 8, 500), (512, 4, 12, 96),
+    (512, 8, 1, 65), (512, 8, 3, 97), (512, 8, 1, 129), (512, 8, 2, 161), (512, 8, 1, 700), (512, 8, 16, 70), (512, 8, 18, 70), (512, 8, 8, 161), (512, 8, 16, 97),
 ])
 def test_prompt_pass_of_few_pairs(H, nh, B, S, ragged):
     """Prompt pass and a decode step over the cache it left, the first, a middle and the last sequence against the oracle's run of it
