@@ -14,14 +14,14 @@ namespace {
 // shuffles, kept in LDS, soft-maxed, then the same lanes accumulate p_j * V[j].
 // The output goes out as tiled half blocks for the out-projection GEMM.
 //
-// Two passes with a score buffer, four wavefronts, several workgroups to a CU: the form for many (row, head) pairs and long caches, which
-// run at the HBM rate (6.2 TB/s at 32 sequences x 40 heads x 384 positions).  attn_few_kernel below is the other.
-template <int D>
-__global__ __launch_bounds__(256) void attn_kernel(const float* __restrict__ q, const half_t* __restrict__ kv,
-                                                   u32x4* __restrict__ o,
-                                                   const he_dev_state* __restrict__ st, int S, int layer, int H,
-                                                   int n_heads, int max_batch, int max_seq) {
-    constexpr int WAVES = 4;
+// Two passes with a score buffer: the form for many (row, head) pairs and long caches, which run at the HBM rate (6.2 TB/s at 32
+// sequences x 40 heads x 384 positions) -- four wavefronts where several workgroups share a CU, eight where two do.  attn_few_kernel below is the
+// other.
+template <int D, int WAVES>
+__global__ __launch_bounds__(64 * WAVES) void attn_kernel(const float* __restrict__ q, const half_t* __restrict__ kv,
+                                                          u32x4* __restrict__ o,
+                                                          const he_dev_state* __restrict__ st, int S, int layer, int H,
+                                                          int n_heads, int max_batch, int max_seq) {
     constexpr int LPK = D / 8;     // lanes per key
     constexpr int KPW = 64 / LPK;  // keys per wavefront load
     constexpr int KR = WAVES * KPW;  // keys per workgroup round
@@ -153,7 +153,7 @@ __global__ __launch_bounds__(256) void attn_kernel(const float* __restrict__ q, 
 // merged with data-parallel moves, the wavefronts through LDS.  us, attn_kernel with the number of wavefronts that suited it -> this:
 // 1 x 32 heads of 64, 516 keys 8.3 -> 6.9, 130 keys 5.0 -> 3.9; 7 x 32 heads of 128, 180 keys 8.5 -> 7.0; 2 x 40 of 128, 1999 keys
 // 26.9 -> 24.5; 16 x 32 of 64, 56 keys 5.6 -> 4.6; 32 x 32 of 64, 64 keys 7.5 -> 5.9; 96 x 40 of 128, 80 keys 31.0 -> 29.0; but 32 x 40
-// of 128: 160 keys 19.6 -> 19.4, 384 keys 39.6 -> 41.2.
+// of 128: 160 keys 19.6 -> 19.4, 384 keys 39.6 -> 41.2.  (The line between the two: decode_attn_plan below.)
 template <int D, int WAVES>
 __global__ __launch_bounds__(64 * WAVES) void attn_few_kernel(const float* __restrict__ q, const half_t* __restrict__ kv,
                                                        u32x4* __restrict__ o, const he_dev_state* __restrict__ st, int S, int layer,
@@ -800,32 +800,52 @@ __global__ __launch_bounds__(256, 1) void attn_prompt_split_kernel(const float* 
 
 // ------------------------------------------------------------------ launchers
 
-// Wavefronts of a (row, head) in the one-pass form, or 0 for the two-pass one.  The rule looks at the cache's size and not at how far it
-// is filled: a captured step must add up like the eager one.  More than two pairs to a CU: from some size of the cache on the two-pass form
-// is ahead, below it two wavefronts.  A layer of a greedy job whose last third is generated, us per step, two passes / one: heads of 128, 1280 pairs, cache of
-// 144 96.5 / 96.2, 160 98.6 / 98.4, 192 100.3 / 100.4, 256 106.4 / 108.5; 768 pairs, 160 71.6 / 71.7, 192 72.4 / 73.2; heads of 64, a row of half the
-// bytes, 1024 pairs, 192 45.8 / 45.4, 256 50.7 / 48.9; 2048 pairs, 256 75.2 / 73.8 (the largest measured).  Else as many as one round over a
-// full cache takes, at most four, or eight where a CU has at most one pair.
-static int attn_waves(long pairs, int max_seq, int d) {
-    const long cus = plan_cus();
-    if (pairs > 2 * cus) return max_seq > (d == 128 ? 160 : 256) ? 0 : 2;
+// The form and the wavefronts of a (row, head).  The rule looks at the cache's size and not at how far it is filled: a captured
+// step must add up like the eager one.  us of a layer's step (attention, GEMMs of a short FFN) with the cache three quarters full, both
+// sides in turn on one engine, 256 CUs; a "row" is what a head caches of a sequence, in keys of 128 values (heads of 64: twice the keys):
+//   Up to a pair per CU: one pass, as many wavefronts as one round over a full cache takes, at most eight.  (32 to 256 pairs, rows of 64 to 2048:
+//   4 to 30 % less than two passes of 4 to 16.)
+//   Up to two: at most four, but two passes of eight (the launch is the HBM stream then, and wants more of it requested) where nearly
+//   every CU has two and the cache is long.  One pass of four / two passes of eight: 512 pairs, row 384 61.8 / 62.7, 512 64.6 / 64.3, 767 71.8 / 70.1, 1024 80.7 /
+//   77.5, 1536 94.0 / 92.3; 480, row 512 62.5 / 63.6, 640 65.2 / 65.0, 1536 90.4 / 89.0; 448, 511 63.3 / 63.7, 767 68.9 / 67.2, 1000 73.5 / 72.8; 400, 768 79.5 / 79.8, 1280 91.4 /
+//   90.7; 384, 768 65.1 / 65.4, 1024 72.3 / 70.9, 2048 93.0 / 91.8; 352, 1000 68.7 / 69.4, 1536 81.3 / 81.1; 320, 1280 73.0 / 74.3, 2048 87.6 / 88.9.  (Half
+//   full: 512 pairs, row 512 +1.1, 1000 -0.1, 1536 -0.7, 2500 -2.0; one size stands out, 512 pairs and a row of 1999: +0.3 and +0.8 where full.)
+//   More: one pass of two while the cache is short; four from 8 pairs per CU and a row of 128 on.  All three lie within 2 % of each other from rows of
+//   112 to 192.  One pass of two / four / two passes of four: 640 pairs, row 112 61.7 / 61.9 / 62.5, 160 61.9 / 61.1 / 62.2, 192 63.6 / 63.8 / 64.3;
+//   768, 136 63.0 / 62.1 / 62.4, 160 63.3 / 62.3 / 62.8, 192 65.6 / 66.2 / 65.2; 1280, 112 79.5 / 81.1 / 80.4, 160 83.3 / 83.0 / 82.9, 192 85.6 / 85.6 / 85.1; 1920,
+//   112 97.8 / 99.3 / 99.5, 160 102.7 / 102.2 / 102.5; 2560, 112 110.3 / 110.0 / 111.4, 128 112.4 / 110.6 / 113.0, 160 117.1 / 115.7 / 116.4, 192 122.1 / 120.5 / 122.3; 3840, 112
+//   137.5 / 138.5 / 139.9, 160 148.4 / 147.6 / 147.9; heads of 64, 1024 pairs, cache 224 41.2 / 42.4 / 42.0, 256 45.0 / 47.6 / 46.3, 320 45.0 / 44.7 / 44.8; 2048, 256 66.3 / 63.3 / 66.4,
+//   384 71.8 / 70.8 / 71.0.  (Heads of 64 could go on to a row of 160, 320 of theirs, within that 2 %.)
+struct AttnPlan { int form, waves; };  // form: HE_ATTN_ in he.h
+static AttnPlan decode_attn_plan(long pairs, int max_seq, int d) {
+    const long cus = plan_cus(), row = (long)max_seq * d;
+    if (pairs > 2 * cus) {
+        if (max_seq > (d == 128 ? 160 : 256)) return {HE_ATTN_TWO_PASSES, 4};
+        return {HE_ATTN_ONE_PASS, pairs >= 8 * cus && row >= 128 * 128 ? 4 : 2};
+    }
+    if (8 * pairs >= 11 * cus && (pairs - cus) * row >= 512 * 128 * cus) return {HE_ATTN_TWO_PASSES, 8};
     const int keys_per_wave = 4 * 64 / (d / 8), most = pairs <= cus ? 8 : 4;  // of one round
     int waves = 2;
     while (waves < most && waves * keys_per_wave < max_seq) waves *= 2;
-    return waves;
+    return {HE_ATTN_ONE_PASS, waves};
 }
 
 template <int D>
 static void launch_attn(hipStream_t s, const float* q, const void* kv, void* o_blocks, const he_dev_state* st, int M, int S, int layer,
-                        int H, int n_heads, int max_batch, int max_seq, int waves) {
+                        int H, int n_heads, int max_batch, int max_seq, AttnPlan g) {
     const dim3 grid(M, n_heads);
     const half_t* c = (const half_t*)kv;
     u32x4* o = (u32x4*)o_blocks;
-    switch (waves) {
+    if (g.form == HE_ATTN_TWO_PASSES) {
+        const size_t shm = (size_t)max_seq * sizeof(float);
+        if (g.waves == 8) attn_kernel<D, 8><<<grid, 512, shm, s>>>(q, c, o, st, S, layer, H, n_heads, max_batch, max_seq);
+        else attn_kernel<D, 4><<<grid, 256, shm, s>>>(q, c, o, st, S, layer, H, n_heads, max_batch, max_seq);
+        return;
+    }
+    switch (g.waves) {
         case 8: attn_few_kernel<D, 8><<<grid, 512, 0, s>>>(q, c, o, st, S, layer, H, n_heads, max_batch, max_seq); break;
         case 4: attn_few_kernel<D, 4><<<grid, 256, 0, s>>>(q, c, o, st, S, layer, H, n_heads, max_batch, max_seq); break;
-        case 2: attn_few_kernel<D, 2><<<grid, 128, 0, s>>>(q, c, o, st, S, layer, H, n_heads, max_batch, max_seq); break;
-        default: attn_kernel<D><<<grid, 256, (size_t)max_seq * sizeof(float), s>>>(q, c, o, st, S, layer, H, n_heads, max_batch, max_seq);
+        default: attn_few_kernel<D, 2><<<grid, 128, 0, s>>>(q, c, o, st, S, layer, H, n_heads, max_batch, max_seq);
     }
 }
 
@@ -844,13 +864,11 @@ static bool prompt_splits(int pairs, int S, int d) {
     return d == 128 ? per_xcd <= 3 || (per_xcd == 4 && blocks <= 2 * round) : S > 96;
 }
 
-// The kernel that M rows of S per sequence take (HE_ATTN_ in he.h) and the wavefronts of its workgroups.
-struct AttnPlan { int form, waves; };
+// The kernel that M rows of S per sequence take and the wavefronts of its workgroups.
 static AttnPlan attn_plan(int M, int S, int n_heads, int d, int max_seq) {
     if (S >= 32) return {prompt_splits(M / S * n_heads, S, d) ? HE_ATTN_PROMPT_SPLIT : HE_ATTN_PROMPT, 4};
     if (S >= QB && (size_t)QB * max_seq * sizeof(float) <= 96 * 1024) return {HE_ATTN_SHORT_PROMPT, 4};
-    const int waves = attn_waves((long)M * n_heads, max_seq, d);
-    return waves ? AttnPlan{HE_ATTN_ONE_PASS, waves} : AttnPlan{HE_ATTN_TWO_PASSES, 4};
+    return decode_attn_plan((long)M * n_heads, max_seq, d);
 }
 
 void bf16_attn_plan_query(int M, int S, int n_heads, int d, int max_seq, int cus, int* form, int* waves) {
@@ -881,8 +899,7 @@ void bf16_attn(hipStream_t s, const float* q, const void* kv, void* o_blocks, co
         if (d == 128) attn_prompt_kernel<128><<<grid, 256, shm, s>>>(q, c, o, st, S, layer, H, n_heads, max_batch, max_seq);
         else attn_prompt_kernel<64><<<grid, 256, shm, s>>>(q, c, o, st, S, layer, H, n_heads, max_batch, max_seq);
     } else {
-        const int waves = g.form == HE_ATTN_ONE_PASS ? g.waves : 0;
-        if (d == 128) launch_attn<128>(s, q, kv, o_blocks, st, M, S, layer, H, n_heads, max_batch, max_seq, waves);
-        else launch_attn<64>(s, q, kv, o_blocks, st, M, S, layer, H, n_heads, max_batch, max_seq, waves);
+        if (d == 128) launch_attn<128>(s, q, kv, o_blocks, st, M, S, layer, H, n_heads, max_batch, max_seq, g);
+        else launch_attn<64>(s, q, kv, o_blocks, st, M, S, layer, H, n_heads, max_batch, max_seq, g);
     }
 }

@@ -213,6 +213,22 @@ def test_attention_kernels_that_the_gpu_tests_name():
         _attention(512, 4, 1, 9, 8)  # more rows than the cache holds
 
 
+def test_decode_attention_of_one_to_two_pairs_per_cu_and_of_many():
+    """Two passes of eight wavefronts where nearly every CU has two (row, head) pairs and the cache is long; one pass of four, not two,
+    where each has eight and a head's row of a sequence is 128 keys of 128 (256 of 64) or more; 256 CUs."""
+    for pairs, cache, want in ((512, 511, ("one pass", 4)), (512, 512, ("two passes", 8)), (512, 2048, ("two passes", 8)), (480, 585, ("one pass", 4)),
+                               (480, 586, ("two passes", 8)), (384, 1023, ("one pass", 4)), (384, 1024, ("two passes", 8)), (352, 1366, ("two passes", 8)),
+                               (350, 8192, ("one pass", 4)), (320, 8192, ("one pass", 4)), (256, 8192, ("one pass", 8)), (514, 160, ("one pass", 2)),
+                               (514, 161, ("two passes", 4)), (2046, 128, ("one pass", 2)), (2048, 127, ("one pass", 2)), (2048, 128, ("one pass", 4)),
+                               (2560, 160, ("one pass", 4)), (2560, 161, ("two passes", 4))):
+        assert _attention(256, 2, pairs // 2, 1, cache) == want, (pairs, cache)
+    for pairs, cache, want in ((512, 1023, ("one pass", 4)), (512, 1024, ("two passes", 8)), (384, 2047, ("one pass", 4)), (384, 2048, ("two passes", 8)),
+                               (320, 8192, ("one pass", 4)), (2048, 255, ("one pass", 2)), (2048, 256, ("one pass", 4)), (2048, 257, ("two passes", 4))):
+        assert _attention(128, 2, pairs // 2, 1, cache) == want, (pairs, cache)
+    # 16 sequences of 32 heads of 128, prompts and answers of 256
+    assert _attention(4096, 32, 16, 1, 512) == ("two passes", 8)
+
+
 def test_prompt_attention_in_blocks_of_32_queries_only_where_it_is_ahead():
     """Measured on both kernels (256 CUs): more than a round of workgroups of 32 queries loses up to 1.5 times on short prompts of heads of
     128, less on heads of 64, and gains on long ones."""

@@ -1,5 +1,5 @@
 """GPU parity of decode attention at the edges of its one-pass form, against the oracle: two, four and eight wavefronts to a (row, head) and
-the two-pass form, on both sides of the rule's lines (pairs per CU, size of the cache), with one key, one short of a round of keys, a
+the two-pass form with four and eight, on both sides of the rule's lines (pairs per CU, size of the cache), with one key, one short of a round of keys, a
 whole round and one more, and sequences of different lengths."""
 import functools
 
@@ -26,14 +26,14 @@ def _model(H, nh):
 
 # (B, S, cache): attention over S, S + 1 and S + 2 keys.  A round is 16 keys a wavefront with heads of 128, 32 with heads of 64.  On
 # 256 CUs two heads make 2, 4, 6 (at most eight wavefronts), 260 or 512 (four), 514 pairs (two, or two passes above a cache of 160 with
-# heads of 128, of 256 with heads of 64)
+# heads of 128, of 256 with heads of 64); 512 pairs with a long cache two passes of eight wavefronts, 2050 one pass of four
 @pytest.mark.parametrize("ragged", [False, True])
 @pytest.mark.parametrize("H,nh,B,S,cache", [
     (256, 2, 1, 1, 20), (256, 2, 1, 30, 32), (256, 2, 2, 31, 33), (256, 2, 3, 62, 64), (256, 2, 1, 63, 65), (256, 2, 2, 127, 200),
     (256, 2, 1, 255, 260), (256, 2, 130, 63, 100), (256, 2, 256, 31, 40), (256, 2, 257, 31, 40), (256, 2, 257, 63, 160),
-    (256, 2, 257, 63, 161),
+    (256, 2, 257, 63, 161), (256, 2, 256, 1, 520), (256, 2, 256, 127, 520), (256, 2, 256, 255, 520), (256, 2, 1025, 63, 128),
     (128, 2, 1, 1, 8), (128, 2, 1, 62, 64), (128, 2, 2, 126, 128), (128, 2, 3, 127, 129), (128, 2, 1, 255, 258), (128, 2, 130, 127, 200),
-    (128, 2, 257, 63, 256), (128, 2, 257, 63, 257),
+    (128, 2, 257, 63, 256), (128, 2, 257, 63, 257), (128, 2, 256, 255, 1030), (128, 2, 1025, 127, 256),
 ])
 def test_decode_attention_at_its_edges(H, nh, B, S, cache, ragged):
     import torch

@@ -122,7 +122,7 @@ def test_score_few_rows(B, T):
 @pytest.mark.parametrize("B,S,max_seq,H,nh", [(1, 30, 40, 256, 4), (1, 200, 260, 256, 2), (2, 500, 1100, 128, 2), (9, 33, 300, 2048, 32),
                                               (9, 33, 130, 2048, 16), (3, 1, 600, 64, 1)])
 def test_decode_attention_wavefront_counts(B, S, max_seq, H, nh):
-    """4, 8 and 16 wavefronts per (row, head): caches below and above one round of keys, both head dimensions."""
+    """Few (row, head) pairs: caches below and above one round of keys, both head dimensions."""
     d = synth.ModelDims("x", 1, H, nh, 2 * H, 300, 1200, B, S, 4, "bf16", "greedy")
     w = synth.make_weights(d, seed=5)
     prompts = synth.make_prompts(d, seed=6)
