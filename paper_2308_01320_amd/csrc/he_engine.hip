@@ -1290,7 +1290,6 @@ he_status he_plan_attention(const he_config* cfg, int B, int S, int cus, int* fo
 he_status he_decode_scratch_account(const he_config* cfg, int B, int which, int cus, he_scratch_account* out) {
     if (!out || check_config(cfg) || check_shape(cfg) || !is_fast(*cfg)) return HE_ERR_INVALID_ARG;
     if (B < 1 || B > cfg->max_batch || B > 64 || (which != 0 && which != 1) || cus < 0) return HE_ERR_INVALID_ARG;
-    if (cfg->weights_fp8 && B > 32) return HE_ERR_INVALID_ARG;  // (answered for one 32-row slice)
     const Sizes z = sizes_of(*cfg);
     const int H = cfg->hidden, K = which ? cfg->ffn : H;
     const size_t cap = z.part / sizeof(float);

@@ -295,15 +295,15 @@ def test_ksplit_hand_off_stays_inside_what_he_create_reserves():
     for d in shapes:
         d = dataclasses.replace(d, dtype="bf16")
         for fp8 in (0, 1):
-            for max_batch in (1, 16, 32, 64):
-                cfg = binding.make_config(d, max_batch=max_batch, max_seq_len=64, weights_fp8=fp8)
+            for max_batch, max_seq in ((1, 64), (16, 64), (32, 64), (64, 64), (64, 2)):
+                cfg = binding.make_config(d, max_batch=max_batch, max_seq_len=max_seq, weights_fp8=fp8)
                 for B in sorted({1, 8, 16, 17, 32, 33, 48, 49, 64, max_batch}):
-                    if B > max_batch or (fp8 and B > 32):
+                    if B > max_batch:
                         continue
                     for which in (0, 1):
                         for cus in (64, 256, 304):
                             a = binding.he_decode_scratch_account(cfg, B, which, cus)
-                            case = (d.hidden, d.ffn, fp8, max_batch, B, which, cus)
+                            case = (d.hidden, d.ffn, fp8, max_batch, max_seq, B, which, cus)
                             assert 1 <= a.ksplit <= 8, case
                             assert a.scratch_floats <= a.scratch_reserved, case
                             assert a.scratch_floats <= a.static_floats, case
