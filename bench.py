@@ -278,7 +278,8 @@ def main():
                     runs.append(s0.elapsed_time(s1) * 1e3 / (sweep_reps * d.n_layers))
                 sweep_us[cls] = {"median": sorted(runs)[len(runs) // 2], "runs": runs}
             except binding.HeError as err:
-                # no sweep for this combination (8-bit matrices at more than 32 sequences): the per-launch event pairs of the decode steps above stand in
+                # no sweep for this combination (8-bit matrices at more than 64 sequences): the per-launch event pairs of the
+                # decode steps above stand in
                 if err.status != binding.HE_ERR_STATE:
                     raise
         # the scoring pass that follows generation: prompt + answer, all positions at once

@@ -1346,8 +1346,8 @@ he_status he_kernel_sweep(he_engine* e, int kernel_class, int reps) {
     for (int r = 0; r < reps; ++r)
         for (int l = 0; l < c.n_layers; ++l) {
             bf16_gemm_args a = base;
-            if (e->w8 && B > 32) return fail(e, HE_ERR_STATE, "he_kernel_sweep: with 8-bit weights only for batches up to 32");
             if (wide_decode(B)) {  // the GEMMs of the wide decode step
+                if (e->w8) return fail(e, HE_ERR_STATE, "he_kernel_sweep: with 8-bit weights only for batches up to 64");
                 if (kernel_class == HE_K_FC1) {
                     a.bias = e->layers[l].b1; a.out_blocks = e->hblk;
                     bf16_gemm_tiled(e->stream, EPI_BIAS_RELU, e->tiled[l].w1, e->ablk, B, F, H, a, e->part, e->tiled_part_floats);

@@ -110,6 +110,37 @@ def test_fp8_real_layer_shape_and_memory():
     eng.he_destroy()
 
 
+@pytest.mark.parametrize("B", [32, 33, 64])
+def test_kernel_sweep_of_8bit_steps(B):
+    """The sweep launches what a step of these rows launches, touches neither cache nor state, and leaves the counters at zero; steps on
+    the tiles dequantise first and have none."""
+    import torch
+    d = synth.ModelDims("x", 2, 1024, 8, 4096, 300, 64, B, 5, 4, "bf16", "greedy")
+    w = binding.upload_weights(synth.make_weights(d, seed=5), "bf16")
+    p, s = torch.from_numpy(synth.make_prompts(d, seed=6)).cuda(), binding.sampling("greedy")
+    out = []
+    for sweep in (False, True):
+        eng = binding.Engine(binding.make_config(d, weights_fp8=1), w)
+        ids, _, _ = eng.he_prefill(p, s, True)
+        if sweep:
+            for cls in ("out_proj", "fc1", "fc2"):
+                eng.he_kernel_sweep(cls, 2)
+        _, lp, lg = eng.he_decode_step(ids, s, True)
+        torch.cuda.synchronize()
+        assert eng.he_arrival_counters_nonzero() == 0
+        out.append((lp.cpu(), lg.cpu()))
+        eng.he_destroy()
+    assert all(torch.equal(a, b) for a, b in zip(*out))
+    if B == 64:
+        d = synth.ModelDims("x", 1, 128, 2, 128, 300, 64, 65, 2, 2, "bf16", "greedy")
+        eng = binding.Engine(binding.make_config(d, weights_fp8=1), binding.upload_weights(synth.make_weights(d, seed=1), "bf16"))
+        eng.he_prefill(torch.zeros(65, 2, dtype=torch.int32, device="cuda"), s)
+        with pytest.raises(binding.HeError) as err:
+            eng.he_kernel_sweep("fc1", 1)
+        assert err.value.status == binding.HE_ERR_STATE
+        eng.he_destroy()
+
+
 def test_fp8_config_errors():
     d = synth.ModelDims("x", 1, 128, 2, 128, 300, 64, 2, 8, 4, "f32", "greedy")
     with pytest.raises(binding.HeError):
