@@ -368,13 +368,14 @@ he_status he_plan_prompt_gemm(int M, int N, int K, int may_cut, size_t scratch_f
 /* Test hook, host logic only: how the launchers cut a GEMM of a pass of `rows` rows -- a prompt pass, a decode step on the
  * prompt pass's tiles (more than 64 sequences), with `scoring` a scoring pass -- in an engine created with cfg: which = 0 QKV,
  * 1 out-projection, 2 FC1, 3 FC2, 4 the LM head of a decode step of `rows` sequences (32 x 32: streamed once per 32 rows)
- * or, with `scoring`, the scoring head.  (A tile of 256 columns of a pass of few rows may be dealt out to two workgroups, half of
- * its columns each.)  The tiles of columns >= split_col come in ksplit k ranges; scratch_floats: what the launch
+ * or, with `scoring`, the scoring head.  tile_cols counts in whole tiles; workgroup_cols is what a workgroup takes of one: a tile of 256
+ * columns of a pass of few rows may be dealt out to two, 128 each.  The tiles of columns >= split_col come in ksplit k ranges; scratch_floats: what the launch
  * indexes of the scratch for partial sums, scratch_reserved: what he_create reserves.  cus as in he_plan_prompt_gemm.
  * bf16, impl 0 only. */
 typedef struct {
     int tile_rows, tile_cols, ksplit, split_col;
     size_t scratch_floats, scratch_reserved;
+    int workgroup_cols;
 } he_pass_plan;
 he_status he_plan_pass_gemm(const he_config* cfg, int rows, int which, int scoring, int cus, he_pass_plan* out);
 

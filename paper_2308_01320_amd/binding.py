@@ -59,7 +59,7 @@ class he_sampling(C.Structure):
 
 class he_pass_plan(C.Structure):
     _fields_ = [("tile_rows", C.c_int), ("tile_cols", C.c_int), ("ksplit", C.c_int), ("split_col", C.c_int),
-                ("scratch_floats", C.c_size_t), ("scratch_reserved", C.c_size_t)]
+                ("scratch_floats", C.c_size_t), ("scratch_reserved", C.c_size_t), ("workgroup_cols", C.c_int)]
 
 
 class HeError(RuntimeError):

@@ -958,7 +958,7 @@ static int score_tile(int M, int V) {
     return tiles >= 2 * plan_cus() ? 0 : (M <= 64 ? 1 : 2);
 }
 
-void bf16_pass_plan_query(int use, int M, int N, int K, size_t capacity_floats, int cus, int* tile_rows, int* tile_cols, int* ks,
+void bf16_pass_plan_query(int use, int M, int N, int K, size_t capacity_floats, int cus, int* tile_rows, int* tile_cols, int* wg_cols, int* ks,
                           int* split_col) {
     plan_cus_override = cus;
     int tile = 0;
@@ -975,7 +975,8 @@ void bf16_pass_plan_query(int use, int M, int N, int K, size_t capacity_floats, 
     }
     plan_cus_override = 0;
     *tile_rows = tile < 0 ? 32 : (tile == 0 ? 128 : (tile > 10 ? 64 * (tile - 10) : (tile < 4 ? 64 * tile : 256)));
-    *tile_cols = tile < 0 ? 32 : (tile == 5 ? 320 : 256);  // (halved tiles count whole)
+    *tile_cols = tile < 0 ? 32 : (tile == 5 ? 320 : 256);
+    *wg_cols = tile > 10 ? 128 : *tile_cols;
 }
 
 void bf16_gemm_tiled_store(hipStream_t s, const void* Wp, const void* Xhi, int M, int N, int K, float* part, int tile, int ks,

@@ -1273,8 +1273,8 @@ he_status he_plan_pass_gemm(const he_config* cfg, int rows, int which, int scori
     const size_t cap = sizes_of(*cfg).tiled_part / sizeof(float);
     const int use = which == 4 ? (scoring ? TILED_SCORE_HEAD : TILED_LM_HEAD)
                                : (store ? (scoring ? TILED_STORE_WHOLE : TILED_STORE) : TILED_FUSED);
-    bf16_pass_plan_query(use, rows, N[which], K, scoring && !store ? 0 : cap, cus, &out->tile_rows, &out->tile_cols, &out->ksplit,
-                         &out->split_col);
+    bf16_pass_plan_query(use, rows, N[which], K, scoring && !store ? 0 : cap, cus, &out->tile_rows, &out->tile_cols,
+                         &out->workgroup_cols, &out->ksplit, &out->split_col);
     out->scratch_floats = store || out->ksplit > 1 ? (size_t)out->ksplit * rows * N[which] : 0;
     out->scratch_reserved = cap;
     return HE_OK;

@@ -120,9 +120,9 @@ size_t bf16_tiled_scratch_floats(int rows, int widest);
 void bf16_tiled_plan_query(int M, int N, int K, int may_cut, size_t capacity_floats, int cus, int* tile_cols, int* ks,
                            int* split_col);
 // What the launchers choose for any of these GEMMs (capacity_floats: the scratch they are given): *tile_rows x *tile_cols tiles
-// (32 x 32: the LM head streamed in slices of 32 rows)
+// (32 x 32: the LM head streamed in slices of 32 rows), *wg_cols columns of one to a workgroup (128: a halved tile)
 enum { TILED_STORE = 0, TILED_STORE_WHOLE = 1, TILED_FUSED = 2, TILED_LM_HEAD = 3, TILED_SCORE_HEAD = 4 };
-void bf16_pass_plan_query(int use, int M, int N, int K, size_t capacity_floats, int cus, int* tile_rows, int* tile_cols, int* ks,
+void bf16_pass_plan_query(int use, int M, int N, int K, size_t capacity_floats, int cus, int* tile_rows, int* tile_cols, int* wg_cols, int* ks,
                           int* split_col);
 // ---- 8-bit weight storage: E4M3 codes with one power-of-two scale per row
 size_t fp8_units_bytes(int rows, int K);  // codes in the half-tile kernel's units: [rows/16][K/64][64 lanes][16 bytes]

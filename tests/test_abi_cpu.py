@@ -171,7 +171,7 @@ def test_pass_gemms_stay_inside_their_scratch():
     shapes = [synth.CONFIGS[n] for n in synth.CONFIGS]
     for H, nh, F in ((64, 1, 64), (128, 2, 512), (320, 5, 1344), (1024, 8, 4096), (4480, 35, 8960)):
         shapes.append(dataclasses.replace(synth.CONFIGS["tiny"], hidden=H, n_heads=nh, ffn=F))
-    tiles = set()
+    tiles, halved = set(), set()
     for d in shapes:
         d = dataclasses.replace(d, dtype="bf16")
         for max_batch, max_seq in ((1, 2), (1, 70), (3, 64), (16, 300), (64, 17), (96, 2), (256, 1), (300, 64), (8, 2048)):
@@ -186,7 +186,11 @@ def test_pass_gemms_stay_inside_their_scratch():
                             assert 1 <= a.ksplit <= 16 and a.scratch_floats <= a.scratch_reserved, case
                             assert not scoring or rows >= 1024 or a.ksplit == 1, case
                             tiles.add((a.tile_rows, a.tile_cols))
+                            assert a.workgroup_cols in (a.tile_cols, 128), case
+                            if a.workgroup_cols == 128:
+                                halved.add(a.tile_rows)
     assert tiles == {(64, 256), (128, 256), (192, 256), (256, 256), (256, 320)}
+    assert halved == {64, 128, 192, 256}
     with pytest.raises(binding.HeError):
         binding.he_plan_pass_gemm(cfg, most + 1, "qkv")
     with pytest.raises(binding.HeError):
