@@ -538,7 +538,8 @@ __global__ __launch_bounds__(256, 1) void gemm_tiled256_kernel(const u32x4* __re
 // kernel's -- LDS reads and copies dealt out behind the matrix instructions, a bare workgroup barrier per stage -- with
 // one difference: a slot is refilled behind the barrier of its own stage (every wavefront waits for its own LDS reads
 // before it), so all but one of the slots are in flight.
-// Halved tiles -- two workgroups to 256 columns, 128 each (NW = 2) -- give narrow matrices and few rows more workgroups for the same number of k ranges, or leave them out:
+// Halved tiles -- two workgroups to 256 columns, 128 each (NW = 2) -- give narrow matrices and few rows more workgroups for the same number of k ranges, or leave them out
+// (launches on one set of operands; inside the engine: ring_plan):
 // 250 x 8192 x 2048 27.6 -> 18.8 us with whole sums, 250 x 16384 x 4096 53.9 -> 45.9, 96 x 2048 x 8192 14.4 (13 ranges) -> 11.8 (8),
 // 180 x 1024 x 1024 6.5 -> 5.1; 384 rows and more of wide matrices go better on 256 columns (12288 x 4096 46.4 / 53.6).  (A CU has some 64 KB of
 // copies on their way whatever they hit: prefetching the weights into L2 with scalar loads, 50 lines a microsecond and CU, is too slow by
@@ -808,18 +809,23 @@ static RingPlan ring_plan_256(int M, int N, int KB, bool fused, size_t capacity_
     return best;
 }
 
-// The same with halved tiles among the candidates, by a cost fitted to launches of 20 matrices from 512 x 512 to 36864 x 9216
-// with 50 .. 4000 rows (the plan chosen is within 6 % of the fastest in 216 of 219 cases, a median of nothing): the stages and the
-// epilogue of a CU's rounds, never less than the weights take from HBM; the partial sums' writes; and what reads them.  All of
-// those matrices have a multiple of 512 rows, as those of every model configuration have; others keep the plan above, which the
-// tests hold a 4480-wide model to.  us with what adds the sums up, before -> after: 250 rows of 6144 x 2048 23.6 -> 17.5, 12288 x
-// 4096 47.0 -> 42.8, 16384 x 4096 53.7 -> 45.3, 4096 x 4096 22.4 -> 20.3; 96 rows of 15360 x 5120 47.1 -> 40.1, 5120 x 5120 20.3 -> 17.6.
+// The same with halved tiles among the candidates, by a cost fitted inside the engine: prompt passes of 33 .. 1000 rows through models of
+// hidden 1024 .. 9216 whose weights no cache holds, one GEMM's plan forced at a time (408 GEMMs, some 18 plans each: the plan chosen costs 0.2 us
+// more than the fastest on average, 4.6 at most).  The stages and the epilogue of a CU's rounds, and the weights' way from HBM, which they
+// cover in part; the partial sums' writes; and what reads them.  (A fit to launches that reuse one set of operands took those out of the
+// caches for nothing and priced whole sums too low: QKV of hidden 5120 and 80 rows in tiles of 64 x 128 47 us, in four ranges of 128 x 256 37 and
+// 6 for what adds them up.  A layer of a decode step, the plan above / that fit / this: hidden 5120, 80 rows 200.3 / 207.9 / 199.5 us, 112 rows
+// 215.8 / 221.9 / 216.9; 7168, 160 rows 398 / 400 / 379; 4096, 65 rows 146 / 146 / 143, 200 rows 204 / 193 / 192; 1024,
+// 160 rows 69 / 52 / 52.)
+// All of the fit's matrices have a multiple of 512 rows.  Others keep the plan above, which the tests' table of tiles (4480 wide) is drawn up for.
+// That is no crossing: this one is ahead there too, a prompt pass or a wide decode step by 6 to 25 % at hidden 768, 4 to 24 at 1344, -1 to 8 at 4480, 0 to 6 at
+// 4096 with an FFN of 10944.
 static RingPlan ring_plan(int M, int N, int KB, bool fused, size_t capacity_floats) {
     if (N % 512) return ring_plan_256(M, N, KB, fused, capacity_floats);
     struct Tile { int id, nw, mw; double stage; };
-    static constexpr Tile kTiles[] = {{1, 4, 1, 0.291}, {2, 4, 2, 0.359}, {3, 4, 3, 0.431}, {4, 4, 4, 0.54}, {5, 5, 4, 0.725},
-                                      {11, 2, 1, 0.193}, {12, 2, 2, 0.244}, {13, 2, 3, 0.302}, {14, 2, 4, 0.343}};
-    const double cus = plan_cus(), sums = 4.0 * M * N, weights = 32.0 * N * KB / 5.52e6;
+    static constexpr Tile kTiles[] = {{1, 4, 1, 0.372}, {2, 4, 2, 0.363}, {3, 4, 3, 0.40}, {4, 4, 4, 0.497}, {5, 5, 4, 0.85},
+                                      {11, 2, 1, 0.193}, {12, 2, 2, 0.243}, {13, 2, 3, 0.296}, {14, 2, 4, 0.348}};
+    const double cus = plan_cus(), sums = 4.0 * M * N, weights = 32.0 * N * KB / 6.8e6;
     const long stages = KB / 2;
     RingPlan best{2, 1};
     double best_cost = 1e30;
@@ -827,14 +833,14 @@ static RingPlan ring_plan(int M, int N, int KB, bool fused, size_t capacity_floa
         const long tiles = (long)((N + 64 * t.nw - 1) / (64 * t.nw)) * ((M + 64 * t.mw - 1) / (64 * t.mw));
         for (int ks = 1; ks <= kMaxTiledKSplit; ++ks) {
             if (ks > 1 && (stages / ks < 4 || (size_t)ks * M * N > capacity_floats)) break;
-            // a second round costs more than its share (nothing covers its ramp), a partly empty one nearly a whole one
+            // a second round costs more than its share (nothing covers its ramp), a partly empty one more than a whole one
             const double rounds = tiles * ks / cus, full = std::ceil(rounds);
-            const double turns = rounds <= 1.0 ? 1.0 : 1.0 + 1.3 * (full - 1.0) - 0.3 * (rounds - 1.0);
-            const double core = turns * (t.stage * (double)((stages + ks - 1) / ks) + 0.373 * t.nw * t.mw);
-            const double hbm = weights * (1.0 + 0.33 * std::max(0.0, 1.0 - rounds));
-            double cost = std::sqrt(std::sqrt(core * core * core * core + hbm * hbm * hbm * hbm)) + ks * sums / 3.72e6;
-            if (!fused) cost += ks * sums / 5e6;
-            else if (ks > 1) cost += 3.3 + ks * sums / 5e6;
+            const double turns = rounds <= 1.0 ? 1.0 : 1.0 + 2.1 * (full - 1.0) - 1.1 * (rounds - 1.0);
+            const double core = turns * (t.stage * (double)((stages + ks - 1) / ks) + 0.425 * t.nw * t.mw);
+            const double hbm = weights * (1.0 + 0.03 * std::max(0.0, 1.0 - rounds));
+            double cost = std::cbrt(core * core * core + hbm * hbm * hbm) + ks * sums / 3.7e6;
+            if (!fused) cost += ks * sums / 4.6e6;
+            else if (ks > 1) cost += 3.0 + ks * sums / 5.45e6;
             if (cost < best_cost) {
                 best_cost = cost;
                 best = RingPlan{t.id, ks};

@@ -247,6 +247,24 @@ def test_prompt_attention_in_blocks_of_32_queries_only_where_it_is_ahead():
     assert _attention(4096, 32, 3, 96, 96)[0] == "prompt" and _attention(4096, 32, 3, 96, 96, 304)[0] == "prompt split"
 
 
+def test_few_row_plans_where_whole_sums_lose():
+    """Passes of 65 to 112 rows on wide matrices whose weights come from HBM: tiles of whole sums measured 2 to 6 us behind k ranges and the
+    kernel that adds them up (QKV of hidden 5120; 4096 at 65 rows), FC1 of hidden 5120 up to 80 rows."""
+    import dataclasses
+
+    def plan(H, rows, which):
+        d = dataclasses.replace(synth.CONFIGS["opt-13b"], hidden=H, n_heads=H // 128, ffn=4 * H)
+        a = binding.he_plan_pass_gemm(binding.make_config(d, max_batch=1, max_seq_len=rows), rows, which)
+        return a.tile_rows, a.workgroup_cols, a.ksplit
+
+    for rows in (65, 80, 96, 112):
+        assert plan(5120, rows, "qkv") == (128, 128, 2)
+    for rows in (65, 80):
+        assert plan(5120, rows, "fc1") == (128, 256, 3)
+    assert plan(4096, 65, "qkv") == (128, 128, 2)
+    assert plan(5120, 250, "qkv") == (128, 128, 1) and plan(7168, 80, "fc1")[2] == 1  # (here whole sums are ahead)
+
+
 def test_planner_queries_of_one_thread_do_not_change_anothers_plans():
     """A query may name another CU count, and the scratch account dry-runs the launcher: both belong to the calling thread.  (Four
     threads ask for four chip sizes; with either process-wide some four answers in a thousand belong to another thread.)"""
