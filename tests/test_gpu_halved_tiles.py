@@ -21,7 +21,8 @@ def _model(H, nh, F):
     return d, util.weights_f64(w), binding.upload_weights(w, "bf16")
 
 
-# 1024 wide: 64-row tiles up to some 500 rows, 128 (750, 897), 192 (1495), 256 (2001, 2112); batches above 64: rows of the wide step as well
+# rows of QKV's halved tiles by the rows of the pass (else 64); batches above 64: rows of the wide step as well
+QKV_ROWS = {1500: 128, 750: 128, 897: 128, 1495: 192, 2001: 256, 2112: 256}
 @pytest.mark.parametrize("ragged", [False, True])
 @pytest.mark.parametrize("H,nh,F,B,S", [
     (512, 8, 1536, 1, 2), (512, 8, 1536, 1, 63), (512, 8, 1536, 2, 64), (512, 4, 1536, 7, 37), (512, 8, 1536, 30, 50),
@@ -33,11 +34,18 @@ def test_passes_on_halved_tiles(H, nh, F, B, S, ragged):
     """Prompt pass and a decode step, the first, a middle and the last sequence against the oracle's run of it alone."""
     import torch
     base, w64, w_dev = _model(H, nh, F)
+    cfg = binding.make_config(base, max_batch=B, max_seq_len=S + 1)
+    rows = B * S if B <= 64 else B * (S - 1)
+    for r in {rows, B if B > 64 else rows}:
+        plans = {g: binding.he_plan_pass_gemm(cfg, r, g) for g in binding.PASS_GEMMS[:4]}
+        assert all(a.workgroup_cols == 128 for g, a in plans.items() if (r, g) != (2112, "fc1"))
+        assert plans["qkv"].tile_rows == QKV_ROWS.get(r, 64)
+        assert r > 1024 or plans["fc2"].ksplit > 1  # (k ranges among them)
     rng = np.random.default_rng(17 * B + S)
     prompts = rng.integers(0, base.vocab, (B, S)).astype(np.int32)
     lens = rng.integers(1, S + 1, B).astype(np.int32) if ragged else np.full(B, S, np.int32)
     feed = rng.integers(0, base.vocab, B).astype(np.int32)
-    eng = binding.Engine(binding.make_config(base, max_batch=B, max_seq_len=S + 1), w_dev)
+    eng = binding.Engine(cfg, w_dev)
     p, samp = torch.from_numpy(prompts).cuda(), binding.sampling("greedy")
     first = eng.he_prefill_ragged(p, torch.from_numpy(lens).cuda(), samp, True) if ragged else eng.he_prefill(p, samp, True)
     second = eng.he_decode_step(torch.from_numpy(feed).cuda(), samp, True)
