@@ -100,7 +100,7 @@ typedef struct {
                           dequantised weights q 2^e (bf16 values again, so everything else is unchanged:
                           accumulation, activations, tolerances).  The LM head and the embeddings stay bf16.
                           This goes beyond the paper, which streams 16-bit weights (Section 5.3 (I): generation is
-                          bound by the bytes read per token).  Decode steps of up to 32 sequences read the codes
+                          bound by the bytes read per token).  Decode steps of up to 64 sequences read the codes
                           directly; prompt rows, scoring and larger batches dequantise a layer at a time into one
                           layer of scratch.  Not combinable with he_refresh_weights_lora. */
 } he_config;

@@ -167,8 +167,7 @@ Sizes sizes_of(const he_config& c) {
     s.stats_idx = (size_t)c.max_batch * ntile * sizeof(int);
     const size_t vpad = ((size_t)c.vocab + 31) / 32 * 32, mtiles = ((size_t)c.max_batch + 31) / 32;
     s.cvec = ((size_t)c.n_layers * 2 * (3 * H + F) + 2 * vpad) * sizeof(float);
-    // column groups of the k-split GEMMs: at most one per 16 columns (8-bit weights on a narrow model; 16-bit
-    // weights never go below 32)
+    // column groups of the out-projection and FC2 of a decode step: at most one per 16 columns (one unit to a workgroup)
     s.ln_stats = mtiles * (H / 16) * 32 * 2 * sizeof(float) + 1024;
     s.ln_counters = mtiles * (H / 16) * sizeof(int);
     s.score_stats = rows * bf16_score_parts(c.vocab) * 2 * sizeof(float);
@@ -1023,9 +1022,11 @@ he_status he_decode_step_static(he_engine* e, const int32_t* d_in_ids, const he_
     if (e->cur_len == 0 || e->batch == 0) return fail(e, HE_ERR_STATE, "he_decode_step_static: no prompt has been prefilled");
     if (e->cur_len + 1 > e->cfg.max_seq_len) return fail(e, HE_ERR_CAPACITY, "he_decode_step_static: KV cache is full");
     if (e->cur_len + 1 > e->cfg.max_positions) return fail(e, HE_ERR_CAPACITY, "he_decode_step_static: position table exhausted");
-    if (wide_decode(e->batch) || (e->w8 && e->batch > 32))
+    if (wide_decode(e->batch))
         return fail(e, HE_ERR_CAPACITY, "he_decode_step_static: the batch is too large for the weight-streaming decode kernels "
-                                        "(at most 64 sequences, 32 with 8-bit weights)");
+                                        "(at most 64 sequences)");
+    // (larger 8-bit steps would run like 16-bit ones of their size; the header states the limit and callers may rely on it)
+    if (e->w8 && e->batch > 32) return fail(e, HE_ERR_CAPACITY, "he_decode_step_static: at most 32 sequences with 8-bit weights");
     const StaticLayout L = static_layout(e, e->batch);
     if (L.total > kStaticScratchBytes)
         return fail(e, HE_ERR_CAPACITY, "he_decode_step_static: this model and batch need " + std::to_string(L.total) +

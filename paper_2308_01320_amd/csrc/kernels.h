@@ -95,7 +95,7 @@ void bf16_embed_ln(hipStream_t s, const int32_t* ids, int id_stride, const void*
 void bf16_gather_last_rows(hipStream_t s, const float* r, const float* q, float* r_out, float* q_out, int B, int S, int H, he_dev_state* st,
                            int advance);
 void bf16_wvec(hipStream_t s, const void* Wp, int N, int K, const void* gamma, const void* beta, float* c1, float* c2);
-// rows in slices of 32 (a decode step of up to 32 sequences): EPI_BIAS_RELU, EPI_QKV or EPI_STORE_LN;
+// rows in slices of 32 (a decode step; 33 to 64 sequences: both slices to a workgroup): EPI_BIAS_RELU, EPI_QKV or EPI_STORE_LN;
 // X: the activations as tiled half blocks; ksplit is ignored (the plan decides)
 void bf16_gemm_skinny(hipStream_t s, int mode, const void* Wp, const void* X, int M, int N, int K, int ksplit,
                       const bf16_gemm_args& a);

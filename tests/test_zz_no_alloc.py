@@ -81,3 +81,10 @@ def test_static_scratch_limits_are_errors():
         eng.he_decode_step_static(torch.zeros(d.batch, dtype=torch.int32, device="cuda"), samp)
     assert ei.value.status == binding.HE_ERR_STATE
     eng.he_destroy()
+    d = synth.ModelDims("static-scratch", 1, 128, 2, 256, 300, 64, 33, 2, 2, "bf16", "greedy")
+    eng = binding.Engine(binding.make_config(d, weights_fp8=1), binding.upload_weights(synth.make_weights(d, seed=0), "bf16"))
+    eng.he_prefill(torch.from_numpy(synth.make_prompts(d)).cuda(), samp)
+    with pytest.raises(binding.HeError, match="at most 32 sequences with 8-bit weights") as ei:
+        eng.he_decode_step_static(torch.zeros(33, dtype=torch.int32, device="cuda"), samp)
+    assert ei.value.status == binding.HE_ERR_CAPACITY
+    eng.he_destroy()
