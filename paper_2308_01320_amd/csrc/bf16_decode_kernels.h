@@ -23,11 +23,10 @@ constexpr size_t tail_floats_per_split(int items, int waves) { return (size_t)it
 
 // ----------------------------------------------------------------- k-split GEMM -> residual rows + next LayerNorm's input
 //
-// Tail of the decode-shaped out-projection / FC2 GEMMs (MODE_STORE_LN), shared by the 32-row and the
-// 16-row kernel.  On entry every thread holds ITEMS quads v[i][0..3]: this workgroup's k-split partial
-// sums of outputs n0[i]..n0[i]+3 of row mrow[i] (live[i]: the quad exists).  rslot[i] says which of the
-// lane's 32/LG rows the quad belongs to: lanes with equal lane % LG hold different columns of the same
-// rows (LG = 32: one row per lane; LG = 16: two).
+// Tail of the decode-shaped out-projection / FC2 GEMMs (MODE_STORE_LN).  On entry every thread holds ITEMS quads
+// v[i][0..3]: this workgroup's k-split partial sums of outputs n0[i]..n0[i]+3 of row mrow[i] (live[i]: the quad exists).
+// rslot[i] says which of the lane's two rows per slice the quad belongs to: lanes with equal lane % LG hold different
+// columns of the same rows.
 //
 // The partial sums cross workgroups (and XCDs, each with an L2 of its own) inside one launch.  They
 // travel as agent-scope atomic words -- written through to, and read from, the level every XCD shares
@@ -53,12 +52,12 @@ __device__ __forceinline__ void tail_request(TailOps<ITEMS>& t, const Epi& p, in
     t.bias[i] = *reinterpret_cast<const uint2*>(p.bias + nc);
     t.gamma[i] = *reinterpret_cast<const uint2*>(p.gamma + nc);
 }
-template <int ITEMS, int WAVES, int LG, int MT = 1, bool LONE = false>
+template <int ITEMS, int WAVES, int MT = 1, bool LONE = false>
 __device__ __forceinline__ void store_ln_tail(const Epi& p, int ksplit, int ks, int grp, int groups, int mt, float cnt,
                                               const float (&v)[ITEMS][4], const int (&mrow)[ITEMS],
                                               const int (&n0)[ITEMS], const bool (&live)[ITEMS],
                                               const int (&rslot)[ITEMS], TailOps<ITEMS>& ops, bool early) {
-    constexpr int NSLOT = 32 * MT / LG;
+    constexpr int LG = 16, NSLOT = 32 * MT / LG;
     __shared__ int s_last;
     __shared__ float sred[2][WAVES][32 * MT];
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
@@ -211,15 +210,14 @@ __device__ __forceinline__ void store_ln_tail(const Epi& p, int ksplit, int ks, 
 
 // ----------------------------------------------------------------- skinny GEMM (decode, LM head)
 //
-// At most 32 rows per grid.y slice: weights are streamed exactly once from HBM,
+// At most 32 rows per grid.z slice: weights are streamed exactly once from HBM,
 // straight from global memory into MFMA operand registers.  A workgroup of four
-// or eight wavefronts owns NT consecutive 32-row weight tiles and one k-split; its
+// or eight wavefronts owns NT consecutive 32-row weight tiles; its
 // wavefronts divide the k range, keep U blocks per stream in flight (NT weight
 // streams plus the activation stream out of L2, which every weight
-// tile reuses from registers), and combine their accumulators through LDS.  The
-// sum over k-splits (MODE_STORE_LN) is taken by the last-arriving workgroup (above).
+// tile reuses from registers), and combine their accumulators through LDS.
 //
-// The launcher picks NT (and the k-split) to put one equally loaded workgroup on
+// The launcher picks NT to put one equally loaded workgroup on
 // as many of the CUs as the shape allows: more workgroups than CUs double up
 // on some CUs and the whole launch waits for those.  Measured on the 13B shapes:
 // the stream itself runs at the HBM rate; what it competes for is the path from
@@ -256,8 +254,8 @@ __device__ __forceinline__ void skinny_mma(const SkinnyRegs<NT, U>& r, f32x16 (&
     }
 }
 
-// The k steps of a GEMM are dealt out to its wavefronts `kbase` to each and one more to the first `kmore`; column group, k range
-// and row slices are the grid's y, x and z.  All worked out by the launcher: divisions ahead of the first load are time in
+// The k steps of a GEMM are dealt out to its wavefronts `kbase` to each and one more to the first `kmore`; column group, k range (of the
+// 16-row units' kernel) and row slices are the grid's y, x and z.  All worked out by the launcher: divisions ahead of the first load are time in
 // which a short launch requests nothing.
 
 // Where the keys and values of a decode step's row go (QKV): cache position of its sequence, and the sequence; t < 0: nowhere
@@ -280,6 +278,7 @@ __device__ __forceinline__ void qkv_out(const Epi& p, int m, int n0, float v0, f
     }
 }
 
+// (one k range: ksplit is 1 and blockIdx.x 0.  Without the argument and the term a step of 7 rows, hidden 4096, measured 1.3 us longer.)
 template <int MODE, int NT, int U, int WAVES>
 __global__ __launch_bounds__(WAVES * 64) void gemm_skinny_kernel(const u32x4* __restrict__ Wp,
                                                                  const u32x4* __restrict__ Xhi, int KB, int n_tiles,
@@ -836,8 +835,8 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_half_kernel(const u32x4* __re
             live[i] = item < NI && g < n_half && mrow[i] < p.M;
             rslot[i] = item % MH;
         }
-        store_ln_tail<ITEMS, WAVES, 16, MT, NI <= WAVES && HT == 1>(p, ksplit, ks, grp, (n_half + HT - 1) / HT, mt,
-                                                                    16.f * (float)min(HT, n_half - grp * HT), v, mrow, n0, live, rslot,
+        store_ln_tail<ITEMS, WAVES, MT, NI <= WAVES && HT == 1>(p, ksplit, ks, grp, (n_half + HT - 1) / HT, mt,
+                                                                16.f * (float)min(HT, n_half - grp * HT), v, mrow, n0, live, rslot,
                                                                     tail_ops, EARLY && ksplit == 1);
         return;
     }

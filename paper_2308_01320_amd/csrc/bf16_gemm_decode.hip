@@ -69,45 +69,44 @@ __global__ __launch_bounds__(256) void lm_reduce_kernel(const float4* __restrict
 #endif
 template <int MODE, int NT>
 void launch_skinny_nt(hipStream_t s, const void* Wp, const void* Xhi, int KB, int n_tiles,
-                      int m_tiles, int ksplit, const Epi& p) {
+                      int m_tiles, const Epi& p) {
     constexpr int U = HE_SKINNY_U(NT);
-    dim3 grid(ksplit, (n_tiles + NT - 1) / NT, m_tiles);
+    dim3 grid(1, (n_tiles + NT - 1) / NT, m_tiles);
     if (MODE == MODE_LMHEAD && m_tiles > 1) grid.y = (grid.y + 7) / 8 * 8;  // see the kernel: slices of a tile group share an XCD
     // What bounds a wavefront is its serial chain of load rounds (K/16 blocks / wavefronts / U
     // rounds, about 1.7 us each under load): eight wavefronts halve the chain when K leaves each
     // of them two rounds (and their accumulators still fit in LDS for the final reduction).
-    const bool eight = NT <= HE_SKINNY_W8_MAXNT && KB / (ksplit * 8) >= 2 * U;
-    const int parts = ksplit * (eight ? 8 : 4);
+    const bool eight = NT <= HE_SKINNY_W8_MAXNT && KB / 8 >= 2 * U;
+    const int parts = eight ? 8 : 4;
     // Ask for more than half of a CU's LDS so that no two workgroups share a CU: with at most one
     // workgroup per CU the dispatcher has to spread a launch of <= #CUs workgroups evenly.
     constexpr size_t kWant = 84 * 1024;
-    if (dry_run(grid, ksplit, items_per_wave(NT * 4, eight ? 8 : 4), eight ? 8 : 4)) return;
     if (eight) {
         constexpr size_t kStatic = (size_t)8 * NT * 16 * 64 * sizeof(float);
         const size_t pad = kStatic >= kWant ? 0 : kWant - kStatic;
         gemm_skinny_kernel<MODE, NT <= HE_SKINNY_W8_MAXNT ? NT : 1, U, 8><<<grid, 512, pad, s>>>(
-            (const u32x4*)Wp, (const u32x4*)Xhi, KB, n_tiles, ksplit, KB / parts, KB % parts, p);
+            (const u32x4*)Wp, (const u32x4*)Xhi, KB, n_tiles, 1, KB / parts, KB % parts, p);
     } else {
         constexpr size_t kStatic = (size_t)4 * NT * 16 * 64 * sizeof(float);
         const size_t pad = kStatic >= kWant ? 0 : kWant - kStatic;
         gemm_skinny_kernel<MODE, NT, U, 4><<<grid, 256, pad, s>>>((const u32x4*)Wp, (const u32x4*)Xhi,
-                                                                  KB, n_tiles, ksplit, KB / parts, KB % parts, p);
+                                                                  KB, n_tiles, 1, KB / parts, KB % parts, p);
     }
 }
 
 // nt weight tiles per workgroup (1..8)
 template <int MODE>
 void launch_skinny(hipStream_t s, const void* Wp, const void* Xhi, int KB, int n_tiles, int m_tiles,
-                   int nt, int ksplit, const Epi& p) {
+                   int nt, const Epi& p) {
     switch (nt) {
-        case 1: launch_skinny_nt<MODE, 1>(s, Wp, Xhi, KB, n_tiles, m_tiles, ksplit, p); break;
-        case 2: launch_skinny_nt<MODE, 2>(s, Wp, Xhi, KB, n_tiles, m_tiles, ksplit, p); break;
-        case 3: launch_skinny_nt<MODE, 3>(s, Wp, Xhi, KB, n_tiles, m_tiles, ksplit, p); break;
-        case 4: launch_skinny_nt<MODE, 4>(s, Wp, Xhi, KB, n_tiles, m_tiles, ksplit, p); break;
-        case 5: launch_skinny_nt<MODE, 5>(s, Wp, Xhi, KB, n_tiles, m_tiles, ksplit, p); break;
-        case 6: launch_skinny_nt<MODE, 6>(s, Wp, Xhi, KB, n_tiles, m_tiles, ksplit, p); break;
-        case 7: launch_skinny_nt<MODE, 7>(s, Wp, Xhi, KB, n_tiles, m_tiles, ksplit, p); break;
-        default: launch_skinny_nt<MODE, 8>(s, Wp, Xhi, KB, n_tiles, m_tiles, ksplit, p); break;
+        case 1: launch_skinny_nt<MODE, 1>(s, Wp, Xhi, KB, n_tiles, m_tiles, p); break;
+        case 2: launch_skinny_nt<MODE, 2>(s, Wp, Xhi, KB, n_tiles, m_tiles, p); break;
+        case 3: launch_skinny_nt<MODE, 3>(s, Wp, Xhi, KB, n_tiles, m_tiles, p); break;
+        case 4: launch_skinny_nt<MODE, 4>(s, Wp, Xhi, KB, n_tiles, m_tiles, p); break;
+        case 5: launch_skinny_nt<MODE, 5>(s, Wp, Xhi, KB, n_tiles, m_tiles, p); break;
+        case 6: launch_skinny_nt<MODE, 6>(s, Wp, Xhi, KB, n_tiles, m_tiles, p); break;
+        case 7: launch_skinny_nt<MODE, 7>(s, Wp, Xhi, KB, n_tiles, m_tiles, p); break;
+        default: launch_skinny_nt<MODE, 8>(s, Wp, Xhi, KB, n_tiles, m_tiles, p); break;
     }
 }
 
@@ -256,10 +255,10 @@ void bf16_gemm_skinny(hipStream_t s, int mode, const void* Wp, const void* Xhi, 
     const GemmPlan g = plan_fused(M, N);
     if (mode == EPI_BIAS_RELU) {
         if (g.half) launch_half<MODE_BIAS_RELU, false>(s, Wp, Xhi, KB, N / 16, m_tiles, g.per_wg, 1, p);
-        else launch_skinny<MODE_BIAS_RELU>(s, Wp, Xhi, KB, n_tiles, m_tiles, g.per_wg, 1, p);
+        else launch_skinny<MODE_BIAS_RELU>(s, Wp, Xhi, KB, n_tiles, m_tiles, g.per_wg, p);
     } else {
         if (g.half) launch_half<MODE_QKV, false>(s, Wp, Xhi, KB, N / 16, m_tiles, g.per_wg, 1, p);
-        else launch_skinny<MODE_QKV>(s, Wp, Xhi, KB, n_tiles, m_tiles, g.per_wg, 1, p);
+        else launch_skinny<MODE_QKV>(s, Wp, Xhi, KB, n_tiles, m_tiles, g.per_wg, p);
     }
 }
 
@@ -296,7 +295,7 @@ void bf16_lm_head(hipStream_t s, const void* Wp, const void* Xhi, int B, int V, 
         const int tiles = (V + 31) / 32, m_tiles = (B + 31) / 32, nt = lm_stream_nt(tiles, m_tiles);
         p.M = B; p.N = V; p.st = st; p.logits = logits_opt; p.stats = stats; p.stats_idx = stats_idx;
         p.n_tiles = parts = (tiles + nt - 1) / nt;  // one per workgroup
-        launch_skinny<MODE_LMHEAD>(s, Wp, Xhi, K / 16, tiles, m_tiles, nt, 1, p);
+        launch_skinny<MODE_LMHEAD>(s, Wp, Xhi, K / 16, tiles, m_tiles, nt, p);
     }
     lm_reduce_kernel<<<B, 256, 0, s>>>((const float4*)stats, stats_idx, parts, st, ids_out, lp_out, out_stride, out_at_step,
                                        cur_ids, advance ? 1 : 0);
