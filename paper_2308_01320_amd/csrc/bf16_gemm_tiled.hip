@@ -825,24 +825,28 @@ static RingPlan ring_plan(int M, int N, int KB, bool fused, size_t capacity_floa
     struct Tile { int id, nw, mw; double stage; };
     static constexpr Tile kTiles[] = {{1, 4, 1, 0.372}, {2, 4, 2, 0.363}, {3, 4, 3, 0.40}, {4, 4, 4, 0.497}, {5, 5, 4, 0.85},
                                       {11, 2, 1, 0.193}, {12, 2, 2, 0.243}, {13, 2, 3, 0.296}, {14, 2, 4, 0.348}};
-    const double cus = plan_cus(), sums = 4.0 * M * N, weights = 32.0 * N * KB / 6.8e6;
-    const long stages = KB / 2;
+    const double sums = 4.0 * M * N, weights = 32.0 * N * KB / 6.8e6;
+    const double tail_of_range = sums / 3.7e6 + sums / (fused ? 5.45e6 : 4.6e6), idle = 0.03 * weights;
+    const int cus = plan_cus(), stages = KB / 2;
     RingPlan best{2, 1};
     double best_cost = 1e30;
     for (const Tile& t : kTiles) {
-        const long tiles = (long)((N + 64 * t.nw - 1) / (64 * t.nw)) * ((M + 64 * t.mw - 1) / (64 * t.mw));
+        const int tiles = ((N + 64 * t.nw - 1) / (64 * t.nw)) * ((M + 64 * t.mw - 1) / (64 * t.mw));
         for (int ks = 1; ks <= kMaxTiledKSplit; ++ks) {
-            if (ks > 1 && (stages / ks < 4 || (size_t)ks * M * N > capacity_floats)) break;
+            if (ks > 1 && (stages < 4 * ks || (size_t)ks * M * N > capacity_floats)) break;
+            const double tail = fused && ks == 1 ? sums / 3.7e6 : ks * tail_of_range + (fused ? 3.0 : 0.0), left = best_cost - tail;
+            if (left <= 0) break;  // (it grows with the ranges)
             // a second round costs more than its share (nothing covers its ramp), a partly empty one more than a whole one
-            const double rounds = tiles * ks / cus, full = std::ceil(rounds);
-            const double turns = rounds <= 1.0 ? 1.0 : 1.0 + 2.1 * (full - 1.0) - 1.1 * (rounds - 1.0);
-            const double core = turns * (t.stage * (double)((stages + ks - 1) / ks) + 0.425 * t.nw * t.mw);
-            const double hbm = weights * (1.0 + 0.03 * std::max(0.0, 1.0 - rounds));
-            double cost = std::cbrt(core * core * core + hbm * hbm * hbm) + ks * sums / 3.7e6;
-            if (!fused) cost += ks * sums / 4.6e6;
-            else if (ks > 1) cost += 3.0 + ks * sums / 5.45e6;
-            if (cost < best_cost) {
-                best_cost = cost;
+            const int full = (tiles * ks + cus - 1) / cus;
+            const double rounds = (double)(tiles * ks) / cus;
+            const double turns = full == 1 ? 1.0 : 1.0 + 2.1 * (full - 1) - 1.1 * (rounds - 1.0);
+            const double core = turns * (t.stage * ((stages + ks - 1) / ks) + 0.425 * t.nw * t.mw);
+            const double hbm = full == 1 ? weights + idle * (1.0 - rounds) : weights;
+            // (compared as cubes: a launch that no graph replays is planned anew, and a root for each candidate was most of what
+            // that costs the host: 96 rows of 5120 x 20480 5.0 us, so 1.6, 0.5 of it the measuring call)
+            const double cubes = core * core * core + hbm * hbm * hbm;
+            if (cubes < left * left * left) {
+                best_cost = std::cbrt(cubes) + tail;
                 best = RingPlan{t.id, ks};
             }
         }
