@@ -260,77 +260,6 @@ __global__ __launch_bounds__(64) void embed_ln_kernel(const int32_t* __restrict_
     if (live && in_group == 0) stats[((size_t)(m >> 5) * groups + g) * 32 + (m & 31)] = make_float2(mean, q2);
 }
 
-// c1[n] = sum_k W[n][k] gamma[k], c2[n] = sum_k W[n][k] beta[k] from the tiled weights: a workgroup per T 32-row tiles (lane =
-// row and k half), its eight wavefronts each with a share of k, float accumulation in k order, the shares' sums added in
-// wavefront order.  Bound by reading the matrix once: the next round of four blocks of each tile is on its way while one is
-// added up, and two tiles share their gamma and beta, where that leaves each CU a workgroup.  Right behind the kernel that
-// wrote the tiles part of them is read from the memory side's cache.  us with the matrix in its place in the pass over a model's
-// weights, one round of one tile after all matrices were written -> this:
-// 16384 x 4096 39.3 -> 28.0, 12288 x 4096 36.4 -> 22.1, 50272 x 4096 96 -> 83.
-constexpr int kWvecWaves = 8;
-template <int T>
-__global__ __launch_bounds__(64 * kWvecWaves) void wvec_kernel(const u32x4* __restrict__ Wp, int KB, int n_tiles,
-                                                               const bf16_t* __restrict__ gamma,
-                                                               const bf16_t* __restrict__ beta, float* __restrict__ c1,
-                                                               float* __restrict__ c2) {
-    __shared__ float red[2][kWvecWaves][T * 32];
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, tile = blockIdx.x * T;
-    const int kb0 = wave * KB / kWvecWaves, kb1 = (wave + 1) * KB / kWvecWaves;
-    constexpr int U = 4;
-    struct Round { u32x4 w[T][U], g[U], b[U]; };
-    auto load = [&](Round& r, int kb) {
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int k = min(kb + u, kb1 - 1);
-#pragma unroll
-            for (int t = 0; t < T; ++t)  // (past the last tile: it again, never stored)
-                r.w[t][u] = __builtin_nontemporal_load(Wp + ((size_t)min(tile + t, n_tiles - 1) * KB + k) * 64 + lane);
-            r.g[u] = *reinterpret_cast<const u32x4*>(gamma + k * 16 + (lane >> 5) * 8);
-            r.b[u] = *reinterpret_cast<const u32x4*>(beta + k * 16 + (lane >> 5) * 8);
-        }
-    };
-    float a1[T], a2[T];
-#pragma unroll
-    for (int t = 0; t < T; ++t) a1[t] = a2[t] = 0.f;
-    Round cur, nxt;
-    if (kb0 < kb1) load(cur, kb0);
-    for (int kb = kb0; kb < kb1; kb += U) {
-        if (kb + U < kb1) load(nxt, kb + U);
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            if (kb + u >= kb1) break;
-            const uint32_t gg[4] = {cur.g[u].x, cur.g[u].y, cur.g[u].z, cur.g[u].w}, bb[4] = {cur.b[u].x, cur.b[u].y, cur.b[u].z, cur.b[u].w};
-#pragma unroll
-            for (int t = 0; t < T; ++t) {
-                const uint32_t ww[4] = {cur.w[t][u].x, cur.w[t][u].y, cur.w[t][u].z, cur.w[t][u].w};
-#pragma unroll
-                for (int x = 0; x < 4; ++x) {
-                    const float w0 = half_lo(ww[x]), w1 = half_hi(ww[x]);
-                    a1[t] = fmaf(w0, bf_lo(gg[x]), a1[t]);
-                    a1[t] = fmaf(w1, bf_hi(gg[x]), a1[t]);
-                    a2[t] = fmaf(w0, bf_lo(bb[x]), a2[t]);
-                    a2[t] = fmaf(w1, bf_hi(bb[x]), a2[t]);
-                }
-            }
-        }
-        cur = nxt;
-    }
-#pragma unroll
-    for (int t = 0; t < T; ++t) {
-        a1[t] = lane_sum32_apart(a1[t]);
-        a2[t] = lane_sum32_apart(a2[t]);
-        if (lane < 32) { red[0][wave][t * 32 + lane] = a1[t]; red[1][wave][t * 32 + lane] = a2[t]; }
-    }
-    __syncthreads();
-    if (threadIdx.x < 64 * T) {  // rows past the matrix are zero blocks: their entries come out zero
-        const int which = threadIdx.x >= 32 * T, r = threadIdx.x - which * 32 * T;
-        float sum = 0.f;
-#pragma unroll
-        for (int x = 0; x < kWvecWaves; ++x) sum += red[which][x][r];
-        if (tile + (r >> 5) < n_tiles) (which ? c2 : c1)[tile * 32 + r] = sum;
-    }
-}
-
 // Rows b*S + S-1 (each sequence's last prompt row) of two [B*S][H] float arrays -> rows b of two [B][H] arrays.  Reads nothing of
 // the state, so the first workgroup also advances it (one launch less).
 __global__ __launch_bounds__(256) void gather_last_rows_kernel(const float* __restrict__ r, const float* __restrict__ q,
@@ -360,14 +289,6 @@ void bf16_embed_ln(hipStream_t s, const int32_t* ids, int id_stride, const void*
     embed_ln_kernel<<<dim3((groups + per_wave - 1) / per_wave, B), 64, 0, s>>>(ids, id_stride, (const bf16_t*)tok, (const bf16_t*)pos, st, V,
                                                    pos_offset, H, gw, groups, per_wave, (const bf16_t*)gamma, r,
                                                    (u32x4*)x_blocks, (float2*)stats, sp);
-}
-
-void bf16_wvec(hipStream_t s, const void* Wp, int N, int K, const void* gamma, const void* beta, float* c1, float* c2) {
-    const int tiles = (N + 31) / 32;  // two to a workgroup where every CU keeps one (12288 rows x 4096: 22.1 us with one each)
-    if (tiles >= 2 * num_cus())
-        wvec_kernel<2><<<(tiles + 1) / 2, 64 * kWvecWaves, 0, s>>>((const u32x4*)Wp, K / 16, tiles, (const bf16_t*)gamma, (const bf16_t*)beta, c1, c2);
-    else
-        wvec_kernel<1><<<tiles, 64 * kWvecWaves, 0, s>>>((const u32x4*)Wp, K / 16, tiles, (const bf16_t*)gamma, (const bf16_t*)beta, c1, c2);
 }
 
 void bf16_ln(hipStream_t s, float* r, const float* part, int ksplit, size_t part_split, const void* pbias,

@@ -17,89 +17,189 @@ __device__ __forceinline__ u32x4 bf16x8_to_half(const u32x4& w) {
 // two floats -> two bf16 in one word, round to nearest even (the LoRA merge rounds to the model's own format)
 __device__ __forceinline__ uint32_t pack2_bf16(float lo, float hi) { return f32x2_to_bf16x2(lo, hi); }
 
-__global__ void tile_rows_kernel(const bf16_t* __restrict__ src, u32x4* __restrict__ dst, int R, int K, size_t total) {
-    const size_t idx = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (idx >= total) return;
-    const int KB = K >> 4;
-    const int lane = (int)(idx & 63);
-    const int kb = (int)((idx >> 6) % KB);
-    const int rt = (int)((idx >> 6) / KB);
-    const int r = rt * 32 + (lane & 31), k = kb * 16 + (lane >> 5) * 8;
-    u32x4 v = u32x4{0u, 0u, 0u, 0u};
-    if (r < R) v = bf16x8_to_half(*reinterpret_cast<const u32x4*>(src + (size_t)r * K + k));
-    dst[idx] = v;
-}
-
 // The same with a low-rank adapter folded in: dst = tiled half(bf16(W + scale * B A)), A [rank, K], B [R, rank].
-// The sum fixes a bf16 rounding, so its order is part of the definition: products B[r][j] A[j][k]
-// (exact in float for bf16 inputs) are added one by one for j = 0..rank-1, then W + scale * that, every
-// operation a separate float rounding (no fused multiply-add).
+// The sum fixes a bf16 rounding, so its order is part of the definition: products B[r][j] A[j][k] are added one by one for
+// j = 0..rank-1, then W + scale * that, every operation a float rounding of its own.  The products of two bf16 values have 16
+// significant bits: they are floats, and adding one by a fused multiply-add rounds just as a separate addition does.  (Products
+// below 2^-134, which a float would round, leave a sum that is zero as a half for every scale below 2^75; products above 2^127
+// need adapter entries of 2^63.)  So the sums are formed on the matrix cores: a float instruction of depth one, a fused multiply-add
+// per element, for each rank.  scale * t is no such product: it and the addition to W round separately.
 //
-// Bound by the vector units (two operations per element and rank, kept apart by the definition) and the memory rate
-// in about equal parts at rank 16.  A wavefront takes 64 rows x 8 KC columns, a lane per row: the adapter's A values are then
-// the same for all lanes, come through the scalar cache and enter the multiplications as scalar operands, and a lane's B
-// value serves 8 KC of them.  Where the rank is a multiple of eight and B so aligned (WIDE), a row of B comes in loads of 16 bytes,
-// requested ahead of the sums they enter: a value at a time, each a cache line per lane, was most of the time.  (16384 x 4096, rank 16: a
-// thread per 16 bytes of result 318 us, B a value at a time 80, this 59; the plain tiling of a matrix of that size is 52.  Back to
-// back, B a value at a time -> this: rank 8 47.6 -> 45.8, 16 62.9 -> 52.6, 32 99.7 -> 86.1, 64 183 -> 152; 4112 columns, rank 16
-// 89.9 -> 69.0.  Groups of four values of other ranks were slower from rank 16 on (unaligned 63.6 -> 93.4), loads of W past the
-// cache too (106: two wavefronts share a line), and 64 columns to a wavefront (62).)
-template <int KC, bool WIDE>
-__global__ __launch_bounds__(256) void tile_rows_lora_kernel(const bf16_t* __restrict__ src, u32x4* __restrict__ dst, int R, int K,
-                                                             int kgroups, const bf16_t* __restrict__ A,
-                                                             const bf16_t* __restrict__ B, int rank, float scale) {
+// Where the matrix follows a LayerNorm (FOLD), W gamma and W beta of its rows are formed from the values on their way, or, TILED,
+// from tiles that are there already (the caller's, or dequantised ones), in one order whatever the weights came as: 64 columns
+// of a row to a wavefront -- the two halves of its blocks apart, k ascending, then added --, the eight wavefronts of a workgroup in
+// their order, and the workgroups of a row of tiles, which leave partial sums in `part`, in theirs (vec_sum_kernel).
+//
+// Bound by the memory rate: 32 rows x 512 columns to a workgroup, neighbours next to each other along k, so that the workgroups in
+// flight sweep source and destination in order; gamma and beta of the 512 columns go through LDS (a wavefront's own loads of them cost
+// as much as its weights').  The k side of the products is permuted so that a lane's accumulators are its own eight columns of
+// each block.  us, back to back, a kernel that tiles or merges on the vector units, then one that reads the tiles again for the
+// vectors -> this: 16384 x 4096 with vectors 70.5 -> 50.2 (5.4 TB/s), 50272 x 4096 225 -> 144, with an adapter of rank 16 as well 85 -> 68,
+// of rank 17 99 -> 86; without vectors, plain 52.6 -> 47.3, rank 16 (4096 x 16384) 61.4 -> 55, rank 64 157 -> 114.  (Workgroups of 32 rows
+// and all of k, no partial sums: 16384 x 4096 60.5, rank 16 66.)
+typedef float f32x32 __attribute__((ext_vector_type(32)));
+constexpr int kMergeBlocks = 4;                               // blocks of 16 columns to a wavefront: two accumulator tiles
+constexpr int kMergeWaves = 8;
+constexpr int kMergeSpan = kMergeBlocks * kMergeWaves;        // ... to a workgroup
+constexpr int kMergeRanks = 32;                               // ranks whose B values are in LDS at a time
+// LORA, how B's rows come: in loads of 16 bytes (rank a multiple of eight, B so aligned); a value at a time, up to eight; through
+// LDS, where the eight wavefronts would each wait for more than eight such loads.  16384 x 4096, rank 17: 81 us a value at a time, 67 through
+// LDS; rank 3: 48 and 57; rank 16: 53 by 16 bytes, 69 through LDS.
+enum { LORA_NONE = 0, LORA_WIDE = 1, LORA_FEW = 2, LORA_LDS = 3 };
+template <int LORA, bool FOLD, bool TILED>
+__global__ __launch_bounds__(64 * kMergeWaves) void tile_merge_kernel(const bf16_t* __restrict__ src, u32x4* __restrict__ dst, int R, int K,
+                                                                      const bf16_t* __restrict__ A, const bf16_t* __restrict__ B, int rank,
+                                                                      float scale, const bf16_t* __restrict__ gamma,
+                                                                      const bf16_t* __restrict__ beta, float* __restrict__ part, size_t part_half, int spans) {
 #pragma clang fp contract(off)  // scale * t and the addition to W round separately, as stated
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
-    const int k0 = ((int)(blockIdx.x % kgroups) * 4 + wave) * 8 * KC;
-    if (k0 >= K) return;  // (wave-uniform)
-    const int r = (int)(blockIdx.x / kgroups) * 64 + lane, rr = min(r, R - 1);
-    u32x4 w[KC];
+    constexpr int U = kMergeBlocks;
+    static_assert(!TILED || LORA == LORA_NONE, "tiles hold merged weights");
+    __shared__ float red[2][kMergeWaves][32];
+    __shared__ u32x4 vec[2][kMergeSpan * 2];  // the span's gamma and beta
+    __shared__ float bs[LORA == LORA_LDS ? 32 : 1][kMergeRanks + 1];
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, half = lane >> 5;
+    const int tile = blockIdx.x / spans, span = blockIdx.x % spans;
+    const int KB = K >> 4, kb = (span * kMergeWaves + wave) * U, nb = min(U, KB - kb);
+    const int r = tile * 32 + (lane & 31), rr = min(r, R - 1);
+    u32x4* out = dst + ((size_t)tile * KB + kb) * 64 + lane;
+    u32x4 w[U], v8;
+    if (nb > 0) {  // (the same for the whole wavefront; past the matrix: its last block, not used)
 #pragma unroll
-    for (int c = 0; c < KC; ++c) w[c] = *reinterpret_cast<const u32x4*>(src + (size_t)rr * K + k0 + 8 * c);
-    float t[8 * KC];
+        for (int u = 0; u < U; ++u)
+            w[u] = TILED ? out[min(u, nb - 1) * 64] : *reinterpret_cast<const u32x4*>(src + (size_t)rr * K + (kb + min(u, nb - 1)) * 16 + 8 * half);
+    }
+    if constexpr (FOLD) {
+        if (wave < 2) v8 = reinterpret_cast<const u32x4*>(wave ? beta : gamma)[min(span * kMergeSpan * 2 + lane, 2 * KB - 1)];
+    }
+    if constexpr (LORA == LORA_NONE && !FOLD) {  // (all four loads before the first of them is used)
 #pragma unroll
-    for (int i = 0; i < 8 * KC; ++i) t[i] = 0.f;
-    const uint32_t* a = reinterpret_cast<const uint32_t*>(A + k0);  // (wave-uniform addresses: scalar loads)
-    const bf16_t* bp = B + (size_t)rr * rank;
-    auto add = [&](int j, float b) {
+        for (int u = 0; u < U; ++u) asm volatile("" : "+v"(w[u]));
+    }
+    [[maybe_unused]] f32x32 t = {};
+    if constexpr (LORA != LORA_NONE) {
+        // accumulator 4 q + e of a lane belongs to column 8 q + 4 (lane / 32) + e of the instruction: that is fed column
+        // 16 (q / 2) + 8 (lane / 32) + 4 (q % 2) + e of the matrix
+        const int i = lane & 31, col = 32 * half + 16 * (i >> 4) + 8 * ((i >> 2) & 1) + 4 * ((i >> 3) & 1) + (i & 3);
+        const bf16_t* ap = A + min(kb * 16 + col, K - 1);  // (past the matrix: its last column, not used)
+        const bf16_t* bp = B + (size_t)rr * rank;
+        constexpr int G = 8;                               // ranks whose values are requested together
+        if constexpr (LORA == LORA_LDS) {
+            bf16_t aj[G], an[G];
+            auto load_a = [&](bf16_t (&v)[G], int j0) {
 #pragma unroll
-        for (int i = 0; i < 4 * KC; ++i) {
-            const uint32_t aw = a[(size_t)j * (K / 2) + i];
-            const float p0 = b * bf_lo(aw), p1 = b * bf_hi(aw);
-            t[2 * i] = t[2 * i] + p0;
-            t[2 * i + 1] = t[2 * i + 1] + p1;
-        }
-    };
-    if constexpr (WIDE) {
-        u32x4 nxt = *reinterpret_cast<const u32x4*>(bp);
-        for (int j0 = 0; j0 < rank; j0 += 8) {
-            const uint32_t bw[4] = {nxt.x, nxt.y, nxt.z, nxt.w};
-            if (j0 + 8 < rank) nxt = *reinterpret_cast<const u32x4*>(bp + j0 + 8);
+                for (int x = 0; x < G; ++x) v[x] = ap[(size_t)min(j0 + x, rank - 1) * K];
+            };
+            load_a(aj, 0);
+            for (int j0 = 0; j0 < rank; j0 += kMergeRanks) {
+                const int n = min(kMergeRanks, rank - j0);
+                if (j0) __syncthreads();
+                for (int x = threadIdx.x; x < 32 * kMergeRanks; x += 64 * kMergeWaves) {
+                    const int br = x / kMergeRanks, j = x % kMergeRanks;
+                    if (j < n) bs[br][j] = bf16_to_f32(B[(size_t)min(tile * 32 + br, R - 1) * rank + j0 + j]);
+                }
+                __syncthreads();
+                for (int j = 0; j < n; j += G) {
+                    if (j0 + j + G < rank) load_a(an, j0 + j + G);
 #pragma unroll
-            for (int x = 0; x < 4; ++x) {
-                add(j0 + 2 * x, bf_lo(bw[x]));
-                add(j0 + 2 * x + 1, bf_hi(bw[x]));
+                    for (int x = 0; x < G; ++x) {
+                        if (j + x >= n) break;
+                        t = __builtin_amdgcn_mfma_f32_32x32x1f32(bf16_to_f32(aj[x]), bs[lane & 31][j + x], t, 0, 0, 0);
+                    }
+#pragma unroll
+                    for (int x = 0; x < G; ++x) aj[x] = an[x];
+                }
+            }
+        } else if (nb > 0) {
+            for (int j0 = 0; j0 < rank; j0 += G) {
+                bf16_t aj[G], bj[G];
+                u32x4 b8;
+                if constexpr (LORA == LORA_WIDE) b8 = *reinterpret_cast<const u32x4*>(bp + j0);
+#pragma unroll
+                for (int x = 0; x < G; ++x) {
+                    const int j = min(j0 + x, rank - 1);
+                    aj[x] = ap[(size_t)j * K];
+                    if constexpr (LORA == LORA_FEW) bj[x] = bp[j];
+                }
+                const uint32_t bw[4] = {b8.x, b8.y, b8.z, b8.w};
+#pragma unroll
+                for (int x = 0; x < G; ++x) {
+                    if (LORA == LORA_FEW && j0 + x >= rank) break;
+                    const float bv = LORA == LORA_WIDE ? (x & 1 ? bf_hi(bw[x >> 1]) : bf_lo(bw[x >> 1])) : bf16_to_f32(bj[x]);
+                    t = __builtin_amdgcn_mfma_f32_32x32x1f32(bf16_to_f32(aj[x]), bv, t, 0, 0, 0);
+                }
             }
         }
-    } else {
-#pragma unroll 2
-        for (int j = 0; j < rank; ++j) add(j, bf16_to_f32(bp[j]));
     }
-    if ((r >> 5) >= (R + 31) / 32) return;
+    float a1 = 0.f, a2 = 0.f;
+    if constexpr (FOLD) {
+        if (wave < 2) vec[wave][lane] = v8;
+        __syncthreads();
+    }
 #pragma unroll
-    for (int c = 0; c < KC; ++c) {
-        const uint32_t ww[4] = {w[c].x, w[c].y, w[c].z, w[c].w};
-        uint32_t o[4];
+    for (int u = 0; u < U; ++u) {
+        if (u >= nb) break;
+        u32x4 h = w[u];
+        if constexpr (LORA != LORA_NONE) {
+            const uint32_t ww[4] = {h.x, h.y, h.z, h.w};
+            uint32_t o[4];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const float s0 = scale * t[8 * c + 2 * i], s1 = scale * t[8 * c + 2 * i + 1];  // plain operators: the pragma above covers them
-            const float lo = bf_lo(ww[i]) + s0;
-            const float hi = bf_hi(ww[i]) + s1;
-            o[i] = pack2_bf16(lo, hi);  // the merged weight is a bf16 value ...
+            for (int x = 0; x < 4; ++x) {
+                const float s0 = scale * t[8 * u + 2 * x], s1 = scale * t[8 * u + 2 * x + 1];  // plain operators: the pragma above covers them
+                const float lo = bf_lo(ww[x]) + s0;
+                const float hi = bf_hi(ww[x]) + s1;
+                o[x] = pack2_bf16(lo, hi);  // the merged weight is a bf16 value ...
+            }
+            h = u32x4{o[0], o[1], o[2], o[3]};
         }
-        // ... held as a half like every other weight; rows past the matrix are zeros
-        dst[block_slot(r, k0 + 8 * c, K >> 4)] = r < R ? bf16x8_to_half(u32x4{o[0], o[1], o[2], o[3]}) : u32x4{0u, 0u, 0u, 0u};
+        if constexpr (!TILED) {
+            h = bf16x8_to_half(h);  // ... held as a half like every other weight; rows past the matrix are zeros
+            if (r >= R) h = u32x4{0u, 0u, 0u, 0u};
+            out[u * 64] = h;
+        }
+        if constexpr (FOLD) {
+            const u32x4 g = vec[0][(wave * U + u) * 2 + half], b = vec[1][(wave * U + u) * 2 + half];
+            const uint32_t ww[4] = {h.x, h.y, h.z, h.w}, gg[4] = {g.x, g.y, g.z, g.w}, bb[4] = {b.x, b.y, b.z, b.w};
+#pragma unroll
+            for (int x = 0; x < 4; ++x) {
+                const float w0 = half_lo(ww[x]), w1 = half_hi(ww[x]);
+                a1 = fmaf(w0, bf_lo(gg[x]), a1);
+                a1 = fmaf(w1, bf_hi(gg[x]), a1);
+                a2 = fmaf(w0, bf_lo(bb[x]), a2);
+                a2 = fmaf(w1, bf_hi(bb[x]), a2);
+            }
+        }
     }
+    if constexpr (FOLD) {
+        a1 = lane_sum32_apart(a1);
+        a2 = lane_sum32_apart(a2);
+        if (lane < 32) { red[0][wave][lane] = a1; red[1][wave][lane] = a2; }
+        __syncthreads();
+        if (threadIdx.x < 64) {
+            float sum = 0.f;
+#pragma unroll
+            for (int x = 0; x < kMergeWaves; ++x) sum += red[half][x][lane & 31];
+            part[half * part_half + (size_t)span * (gridDim.x / spans) * 32 + tile * 32 + (lane & 31)] = sum;
+        }
+    }
+}
+
+// part [2][spans][rows] -> c1, c2 [rows]
+__global__ __launch_bounds__(256) void vec_sum_kernel(const float* __restrict__ part, int spans, int rows, float* __restrict__ c1,
+                                                      float* __restrict__ c2) {
+    const int i = blockIdx.x * 256 + threadIdx.x;
+    if (i >= 2 * rows) return;
+    const int which = i >= rows, r = i - which * rows;
+    const float* p = part + (size_t)which * spans * rows + r;
+    float sum = 0.f;
+    for (int g0 = 0; g0 < spans; g0 += 8) {
+        float v[8];
+#pragma unroll
+        for (int x = 0; x < 8; ++x) v[x] = p[(size_t)min(g0 + x, spans - 1) * rows];
+#pragma unroll
+        for (int x = 0; x < 8; ++x)
+            if (g0 + x < spans) sum += v[x];
+    }
+    (which ? c2 : c1)[r] = sum;
 }
 
 // ----------------------------------------------------------------- 8-bit weight storage
@@ -211,11 +311,6 @@ __global__ void dequant_units_kernel(const u32x4* __restrict__ units, const floa
 
 size_t bf16_tiled_bytes(int rows, int K) { return (size_t)((rows + 31) / 32) * (K / 16) * 1024; }
 
-void bf16_tile_rows(hipStream_t s, const void* src, void* dst, int R, int K) {
-    const size_t total = (size_t)((R + 31) / 32) * (K / 16) * 64;
-    tile_rows_kernel<<<(unsigned)((total + 255) / 256), 256, 0, s>>>((const bf16_t*)src, (u32x4*)dst, R, K, total);
-}
-
 size_t fp8_units_bytes(int rows, int K) { return (size_t)((rows + 15) / 16) * (K / 64) * 1024; }
 
 void fp8_row_exponents(hipStream_t s, const void* src, int R, int K, int* exps, float* scales) {
@@ -238,15 +333,48 @@ void fp8_dequant_units(hipStream_t s, const void* units, const float* scales, vo
                                                                         total);
 }
 
+// dst: the tiles, written, or (src null) read
+template <bool FOLD>
+static void launch_tile_merge(hipStream_t s, const void* src, void* dst, int R, int K, const void* A, const void* B, int rank, float scale,
+                              const void* gamma, const void* beta, float* part, size_t part_half) {
+    const int spans = (K / 16 + kMergeSpan - 1) / kMergeSpan, grid = (R + 31) / 32 * spans;
+    auto launch = [&](auto kernel) {
+        kernel<<<grid, 64 * kMergeWaves, 0, s>>>((const bf16_t*)src, (u32x4*)dst, R, K, (const bf16_t*)A, (const bf16_t*)B, rank, scale,
+                                                 (const bf16_t*)gamma, (const bf16_t*)beta, part, part_half, spans);
+    };
+    if (A && B && rank > 0) {
+        if (rank % 8 == 0 && (reinterpret_cast<uintptr_t>(B) & 15) == 0) launch(tile_merge_kernel<LORA_WIDE, FOLD, false>);
+        else if (rank <= 8) launch(tile_merge_kernel<LORA_FEW, FOLD, false>);
+        else launch(tile_merge_kernel<LORA_LDS, FOLD, false>);
+    } else if (!FOLD || src) launch(tile_merge_kernel<LORA_NONE, FOLD, false>);
+    else if constexpr (FOLD) launch(tile_merge_kernel<LORA_NONE, true, true>);
+}
+
+void bf16_tile_fold(hipStream_t s, const void* src, void* dst, int R, int K, const void* A, const void* B, int rank, float scale,
+                    const void* gamma, const void* beta, float* c1, float* c2, float* part, size_t part_floats) {
+    const int spans = (K / 16 + kMergeSpan - 1) / kMergeSpan;
+    const size_t row_bytes = (size_t)K * sizeof(bf16_t);
+    // as many rows at a time as the scratch holds partial sums for (one span: the sums themselves, written where they belong)
+    const int fit = spans == 1 ? R : (int)std::min<size_t>(R, part_floats / ((size_t)2 * spans) / 32 * 32);
+    for (int r0 = 0; r0 < R; r0 += fit) {
+        const int rows = std::min(fit, R - r0), padded = (rows + 31) / 32 * 32;
+        const void* from = src ? (const char*)src + r0 * row_bytes : nullptr;
+        void* tiles = (char*)dst + r0 * row_bytes;  // (whole row tiles: as many bytes as rows of the matrix)
+        const void* b = B ? (const bf16_t*)B + (size_t)r0 * rank : nullptr;
+        if (spans == 1) {
+            launch_tile_merge<true>(s, from, tiles, rows, K, A, b, rank, scale, gamma, beta, c1, (size_t)(c2 - c1));
+        } else {
+            launch_tile_merge<true>(s, from, tiles, rows, K, A, b, rank, scale, gamma, beta, part, (size_t)spans * padded);
+            vec_sum_kernel<<<(2 * padded + 255) / 256, 256, 0, s>>>(part, spans, padded, c1 + r0, c2 + r0);
+        }
+    }
+}
+
+void bf16_tile_rows(hipStream_t s, const void* src, void* dst, int R, int K) {
+    launch_tile_merge<false>(s, src, dst, R, K, nullptr, nullptr, 0, 0.f, nullptr, nullptr, nullptr, 0);
+}
+
 void bf16_tile_rows_lora(hipStream_t s, const void* src, void* dst, int R, int K, const void* A, const void* B, int rank,
                          float scale) {
-    const int kc = K % 32 == 0 ? 4 : 2;  // (K is a multiple of 16)
-    const int kgroups = (K + 32 * kc - 1) / (32 * kc);
-    const unsigned grid = (unsigned)((R + 63) / 64 * kgroups);
-    const bool wide = rank % 8 == 0 && (reinterpret_cast<uintptr_t>(B) & 15) == 0;  // a row of B in loads of 16 bytes
-    auto launch = [&](auto kernel) {
-        kernel<<<grid, 256, 0, s>>>((const bf16_t*)src, (u32x4*)dst, R, K, kgroups, (const bf16_t*)A, (const bf16_t*)B, rank, scale);
-    };
-    if (kc == 4) wide ? launch(tile_rows_lora_kernel<4, true>) : launch(tile_rows_lora_kernel<4, false>);
-    else wide ? launch(tile_rows_lora_kernel<2, true>) : launch(tile_rows_lora_kernel<2, false>);
+    launch_tile_merge<false>(s, src, dst, R, K, A, B, rank, scale, nullptr, nullptr, nullptr, 0);
 }

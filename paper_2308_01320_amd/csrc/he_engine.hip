@@ -589,53 +589,45 @@ he_status run_forward_bf16(he_engine* e, const int32_t* d_ids, int B, int S, int
 void tile_weights(he_engine* e) {
     const he_config& c = e->cfg;
     const int H = c.hidden, F = c.ffn;
-    if (e->w8) {
-        // E4M3 units and row scales of every layer matrix; the vectors W gamma, W beta from the dequantised
-        // layer (the weights the GEMMs really multiply by)
-        auto quant = [&](const void* src, void* units, float* scales, int R, int K) {
-            fp8_row_exponents(e->stream, src, R, K, e->exps_tmp, scales);
-            fp8_quant_units(e->stream, src, e->exps_tmp, units, R, K);
-        };
-        for (int l = 0; l < c.n_layers; ++l) {
-            const he_layer_weights& lw = e->layers[l];
+    const bool own = !c.weights_tiled;  // else the caller's matrices are used in place
+    auto factors = [&](const he_lora* ad) { return ad && ad->a && ad->b && e->lora_rank > 0; };
+    auto tile = [&](const void* src, void* dst, int R, int K, const he_lora* ad) {
+        if (!own) return;
+        if (factors(ad)) bf16_tile_rows_lora(e->stream, src, dst, R, K, ad->a, ad->b, e->lora_rank, e->lora_scale);
+        else bf16_tile_rows(e->stream, src, dst, R, K);
+    };
+    // ... of a matrix that follows a LayerNorm, with its W gamma and W beta; src null: from the tiles that are there
+    auto tile_fold = [&](const void* src, void* dst, int R, int K, const he_lora* ad, const void* gamma, const void* beta, const CVec& v) {
+        const bool merge = factors(ad);
+        bf16_tile_fold(e->stream, src, dst, R, K, merge ? ad->a : nullptr, merge ? ad->b : nullptr, e->lora_rank, e->lora_scale, gamma, beta,
+                       v.c1, v.c2, e->part, e->tiled_part_floats);
+    };
+    for (int l = 0; l < c.n_layers; ++l) {
+        const he_layer_weights& lw = e->layers[l];
+        const he_lora_layer* ad = e->lora.empty() ? nullptr : &e->lora[l];
+        if (e->w8) {
+            // E4M3 units and row scales of every layer matrix; the vectors W gamma, W beta from the dequantised
+            // layer (the weights the GEMMs really multiply by)
             const Scales sc = scales_of(e, l);
+            auto quant = [&](const void* src, void* units, float* scales, int R, int K) {
+                fp8_row_exponents(e->stream, src, R, K, e->exps_tmp, scales);
+                fp8_quant_units(e->stream, src, e->exps_tmp, units, R, K);
+            };
             quant(lw.wqkv, e->tiled[l].wqkv, sc.wqkv, 3 * H, H);
             quant(lw.wo, e->tiled[l].wo, sc.wo, H, H);
             quant(lw.w1, e->tiled[l].w1, sc.w1, F, H);
             quant(lw.w2, e->tiled[l].w2, sc.w2, H, F);
             const he_engine::Tiled blk = layer_blocks(e, l);
-            const CVec q = cvec_qkv(e, l), f = cvec_fc1(e, l);
-            bf16_wvec(e->stream, blk.wqkv, 3 * H, H, lw.ln1_g, lw.ln1_b, q.c1, q.c2);
-            bf16_wvec(e->stream, blk.w1, F, H, lw.ln2_g, lw.ln2_b, f.c1, f.c2);
+            tile_fold(nullptr, blk.wqkv, 3 * H, H, nullptr, lw.ln1_g, lw.ln1_b, cvec_qkv(e, l));
+            tile_fold(nullptr, blk.w1, F, H, nullptr, lw.ln2_g, lw.ln2_b, cvec_fc1(e, l));
+            continue;
         }
-        bf16_tile_rows(e->stream, e->w.lm_head, e->lm_tiled, c.vocab, H);
-        const CVec v = cvec_lm(e);
-        bf16_wvec(e->stream, e->lm_tiled, c.vocab, H, e->w.lnf_g, e->w.lnf_b, v.c1, v.c2);
-        return;
-    }
-    const bool own = !c.weights_tiled;  // else the caller's matrices are used in place
-    auto tile = [&](const void* src, void* dst, int R, int K, const he_lora* ad) {
-        if (!own) return;
-        if (ad && ad->a && ad->b && e->lora_rank > 0)
-            bf16_tile_rows_lora(e->stream, src, dst, R, K, ad->a, ad->b, e->lora_rank, e->lora_scale);
-        else
-            bf16_tile_rows(e->stream, src, dst, R, K);
-    };
-    // W gamma and W beta right behind the tiles they read: part of what was just written is still in the memory side's cache
-    for (int l = 0; l < c.n_layers; ++l) {
-        const he_layer_weights& lw = e->layers[l];
-        const he_lora_layer* ad = e->lora.empty() ? nullptr : &e->lora[l];
-        const CVec q = cvec_qkv(e, l), f = cvec_fc1(e, l);
-        tile(lw.wqkv, e->tiled[l].wqkv, 3 * H, H, ad ? &ad->wqkv : nullptr);
-        bf16_wvec(e->stream, e->tiled[l].wqkv, 3 * H, H, lw.ln1_g, lw.ln1_b, q.c1, q.c2);
+        tile_fold(own ? lw.wqkv : nullptr, e->tiled[l].wqkv, 3 * H, H, ad ? &ad->wqkv : nullptr, lw.ln1_g, lw.ln1_b, cvec_qkv(e, l));
         tile(lw.wo, e->tiled[l].wo, H, H, ad ? &ad->wo : nullptr);
-        tile(lw.w1, e->tiled[l].w1, F, H, ad ? &ad->w1 : nullptr);
-        bf16_wvec(e->stream, e->tiled[l].w1, F, H, lw.ln2_g, lw.ln2_b, f.c1, f.c2);
+        tile_fold(own ? lw.w1 : nullptr, e->tiled[l].w1, F, H, ad ? &ad->w1 : nullptr, lw.ln2_g, lw.ln2_b, cvec_fc1(e, l));
         tile(lw.w2, e->tiled[l].w2, H, F, ad ? &ad->w2 : nullptr);
     }
-    tile(e->w.lm_head, e->lm_tiled, c.vocab, H, nullptr);
-    const CVec v = cvec_lm(e);
-    bf16_wvec(e->stream, e->lm_tiled, c.vocab, H, e->w.lnf_g, e->w.lnf_b, v.c1, v.c2);
+    tile_fold(own ? e->w.lm_head : nullptr, e->lm_tiled, c.vocab, H, nullptr, e->w.lnf_g, e->w.lnf_b, cvec_lm(e));
 }
 
 // Plain kernels: every layer over the M = B*S rows of the residual stream, in place.

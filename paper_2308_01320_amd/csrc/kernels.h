@@ -76,6 +76,10 @@ void bf16_tile_rows(hipStream_t s, const void* src, void* dst, int R, int K);
 // dst = tiled bf16(src + scale * B A): A bf16 [rank, K], B bf16 [R, rank]
 void bf16_tile_rows_lora(hipStream_t s, const void* src, void* dst, int R, int K, const void* A, const void* B, int rank,
                          float scale);
+// The same (A null: without an adapter; src null: dst holds the tiles already), and c1 = W gamma, c2 = W beta of the R rows padded to 32
+// (c2 behind c1).  part: scratch, for 64 K / 512 floats at least
+void bf16_tile_fold(hipStream_t s, const void* src, void* dst, int R, int K, const void* A, const void* B, int rank, float scale,
+                    const void* gamma, const void* beta, float* c1, float* c2, float* part, size_t part_floats);
 // EPI_STORE_LN GEMM of M <= 64 rows: columns per workgroup (= per group of LayerNorm statistics) and k-splits;
 // capacity = floats of k-split scratch available (the value passed as bf16_gemm_args.out_capacity); w8 != 0: 8-bit weights
 void bf16_store_plan(int M, int N, int K, size_t capacity, int w8, int* group_cols, int* ks);
@@ -94,7 +98,6 @@ void bf16_embed_ln(hipStream_t s, const int32_t* ids, int id_stride, const void*
 // rows b*S + S-1 of r and q ([B*S][H] floats) -> rows b of r_out and q_out ([B][H]); the state advances by `advance` tokens
 void bf16_gather_last_rows(hipStream_t s, const float* r, const float* q, float* r_out, float* q_out, int B, int S, int H, he_dev_state* st,
                            int advance);
-void bf16_wvec(hipStream_t s, const void* Wp, int N, int K, const void* gamma, const void* beta, float* c1, float* c2);
 // rows in slices of 32 (a decode step; 33 to 64 sequences: both slices to a workgroup): EPI_BIAS_RELU, EPI_QKV or EPI_STORE_LN;
 // X: the activations as tiled half blocks; ksplit is ignored (the plan decides)
 void bf16_gemm_skinny(hipStream_t s, int mode, const void* Wp, const void* X, int M, int N, int K, int ksplit,
