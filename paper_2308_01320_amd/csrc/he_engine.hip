@@ -650,6 +650,48 @@ void plain_layers(he_engine* e, int M, int S) {
     }
 }
 
+// Whether a decode step of the float path runs as blocks (kernels_blocks.hip): a small model, few rows, every table and vector
+// aligned for four values at a time.  The partial sums go into the activation buffers such a step has no other use for.
+bool block_step(const he_engine* e, int B) {
+    const he_config& c = e->cfg;
+    const size_t rows = (size_t)c.max_batch * c.max_seq_len;
+    if (e->bf16 || !c.n_layers || !plain_blocks_fit(B, c.hidden, c.n_heads, c.ffn, rows * c.hidden, rows * c.ffn)) return false;
+    auto aligned = [](std::initializer_list<const void*> ps) {
+        for (const void* p : ps)
+            if ((uintptr_t)p % 16) return false;
+        return true;
+    };
+    if (!aligned({e->w.tok_emb, e->w.pos_emb, e->w.lnf_g, e->w.lnf_b, e->w.lm_head})) return false;
+    for (const he_layer_weights& lw : e->layers)
+        if (!aligned({lw.ln1_g, lw.ln1_b, lw.wqkv, lw.wo, lw.bo, lw.ln2_g, lw.ln2_b, lw.w1, lw.b1, lw.w2, lw.b2})) return false;
+    return true;
+}
+
+// ... its launches, the LM head's logits last.  Residual rows go to and fro between two buffers.
+void pass_blocks_f32(he_engine* e, const int32_t* d_ids, int id_stride, int B, float* logits) {
+    const he_config& c = e->cfg;
+    hipStream_t s = e->stream;
+    float *heads = e->abuf, *slices = e->hbuf, *x1 = e->obuf, *x2 = e->resid;
+    plain_block_args a{};
+    a.eps = c.ln_eps; a.H = c.hidden; a.n_heads = c.n_heads; a.max_batch = c.max_batch; a.max_seq = c.max_seq_len; a.V = c.vocab;
+    a.qscale = 1.0f / sqrtf((float)e->d);
+    a.ids = d_ids; a.id_stride = id_stride; a.tok = (const float*)e->w.tok_emb; a.pos = (const float*)e->w.pos_emb; a.pos_offset = c.pos_offset;
+    a.sp = take_sampling(e);
+    const float* pend = nullptr;  // bias that goes with the FFN's partial sums
+    for (int l = 0; l < c.n_layers; ++l) {
+        const he_layer_weights& lw = e->layers[l];
+        a.layer = l; a.pbias = pend; a.n_part = plain_ffn_slices(c.ffn); a.bqkv = (const float*)lw.bqkv;
+        a.gamma = (const float*)lw.ln1_g; a.beta = (const float*)lw.ln1_b; a.x_out = x1; a.part_out = heads;
+        plain_attn_block(s, l == 0, (const float*)lw.wqkv, (const float*)lw.wo, x2, slices, (float*)e->kv, e->st, B, a);
+        a.pbias = (const float*)lw.bo; a.n_part = c.n_heads;
+        a.gamma = (const float*)lw.ln2_g; a.beta = (const float*)lw.ln2_b; a.x_out = x2; a.part_out = slices;
+        plain_ffn_block(s, (const float*)lw.w1, (const float*)lw.w2, x1, heads, (const float*)lw.b1, B, c.ffn, a);
+        pend = (const float*)lw.b2;
+    }
+    a.pbias = pend; a.n_part = plain_ffn_slices(c.ffn); a.gamma = (const float*)e->w.lnf_g; a.beta = (const float*)e->w.lnf_b;
+    plain_head_block(s, (const float*)e->w.lm_head, x2, slices, logits, B, a);
+}
+
 // One pass of the decoder over M = B*S new rows (S = prompt length, or 1 for a
 // decode step) followed by the LM head on each sequence's last row and sampling.
 he_status run_forward(he_engine* e, const int32_t* d_ids, int B, int S, int32_t* ids_out, float* lp_out,
@@ -659,13 +701,17 @@ he_status run_forward(he_engine* e, const int32_t* d_ids, int B, int S, int32_t*
     hipStream_t s = e->stream;
     const int M = B * S, H = c.hidden, bf = e->bf16;
 
-    plain_embed(s, bf, d_ids, S, e->w.tok_emb, e->w.pos_emb, e->resid, e->st, M, S, H, c.vocab, c.pos_offset, take_sampling(e));
-    plain_layers(e, M, S);
-    // final LayerNorm on each sequence's last row only
     float* logits = d_logits_opt ? d_logits_opt : e->logits;
-    const plain_ln_args lnf{e->w.lnf_g, e->w.lnf_b, c.ln_eps, S, S - 1};
-    plain_gemm(s, bf, e->resid, e->w.lm_head, nullptr, B, c.vocab, H, EPI_STORE, logits, nullptr, e->st, S, 0, H, c.n_heads,
-               c.max_batch, c.max_seq_len, 1.f, &lnf, e->xf);
+    if (S == 1 && !e->next_sampling.start && block_step(e, B)) {  // (a pass that starts at position 0 whatever the state holds: below)
+        pass_blocks_f32(e, d_ids, S, B, logits);
+    } else {
+        plain_embed(s, bf, d_ids, S, e->w.tok_emb, e->w.pos_emb, e->resid, e->st, M, S, H, c.vocab, c.pos_offset, take_sampling(e));
+        plain_layers(e, M, S);
+        // final LayerNorm on each sequence's last row only
+        const plain_ln_args lnf{e->w.lnf_g, e->w.lnf_b, c.ln_eps, S, S - 1};
+        plain_gemm(s, bf, e->resid, e->w.lm_head, nullptr, B, c.vocab, H, EPI_STORE, logits, nullptr, e->st, S, 0, H, c.n_heads,
+                   c.max_batch, c.max_seq_len, 1.f, &lnf, e->xf);
+    }
     launch_sample(s, logits, B, c.vocab, e->st, ids_out, lp_out, out_stride, out_at_step, e->cur_ids, e->ragged_gen ? 0 : S);
     end_step(e, S, ids_out, lp_out, out_stride, B);
     e->cur_len += S;

@@ -3,8 +3,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
-struct he_dev_state;
-struct he_step_sampling;
+#include "he_common.h"
 
 enum { EPI_STORE = 0, EPI_BIAS_RELU = 1, EPI_QKV = 2, EPI_STORE_LN = 3, EPI_RESID = 4 };
 
@@ -21,6 +20,24 @@ void plain_gemm(hipStream_t s, int bf16, const float* A, const void* W, const vo
                 int max_seq, float qscale, const plain_ln_args* ln = nullptr, float* scratch = nullptr);
 void plain_attn(hipStream_t s, int bf16, const float* q, const void* kv, float* o, const he_dev_state* st, int M, int S,
                 int layer, int H, int n_heads, int max_batch, int max_seq);
+// ---- decode steps of small float models (kernels_blocks.hip): a launch per attention block and per FFN block
+struct plain_block_args {
+    // the rows: x + pbias + n_part partial sums (attention block of layer 0: embeddings), and the LayerNorm they go through
+    const float* pbias; const float *gamma, *beta; float eps; int n_part;
+    float* x_out;     // the rows themselves (the LM head: nowhere)
+    float* part_out;  // attention block: [n_heads][B][H], FFN block: [F / 32][B][H]
+    int H, n_heads, layer, max_batch, max_seq, V;
+    const float* bqkv; float qscale;
+    const int32_t* ids; int id_stride; const float *tok, *pos; int pos_offset;
+    he_step_sampling sp;
+};
+bool plain_blocks_fit(int B, int H, int n_heads, int F, size_t part_heads, size_t part_slices);
+void plain_attn_block(hipStream_t s, bool embed, const float* wqkv, const float* wo, const float* x, const float* part, float* kv, he_dev_state* st,
+                      int B, const plain_block_args& a);
+int plain_ffn_slices(int F);
+void plain_ffn_block(hipStream_t s, const float* w1, const float* w2, const float* x, const float* part, const float* b1, int B, int F,
+                     const plain_block_args& a);
+void plain_head_block(hipStream_t s, const float* w, const float* x, const float* part, float* logits, int B, const plain_block_args& a);
 // rows row0 .. row0+n-1 of the M = B*S positions, given their logits [n][V]: out[b][t] = log_softmax(z)[ids[m+1]]
 void plain_score_rows(hipStream_t s, const float* logits, const int32_t* ids, int row0, int n, int S, int V, float* out);
 

@@ -649,12 +649,16 @@ void plain_ln(hipStream_t s, int bf16, const float* r, const plain_ln_args& ln, 
 // tiles): width 256: 1 row 62 / 84, 64 rows 74 / 94; 512: 77 / 117, 117 / 130; 1024: 1 row 122 / 184, 32 rows 187 / 202, 33 220 / 198, 64
 // 287 / 201; 2048: 1 row 255 / 358, 16 367 / 362, 64 974 / 477.  So the line is right for models up to 512 wide, whose steps this path
 // is for, and too high for wider ones from 33 (1024) or 17 (2048) rows on.
-constexpr int kFewRows = 64;
+// Small matrices go this way up to 256 rows: the 32 x 32 tiles are too few workgroups there (128 rows: 32 of them for 256 columns).  A
+// prompt pass of two layers, tiles / this: width 256, FFN 1024: 128 rows 98 / 73, 256 rows 99 / 92, 272 106 / 104, 384 114 / 119, 512
+// 119 / 135; width 512, FFN 2048: 128 rows 128 / 112; width 128: 320 rows 139 / 73.
+constexpr int kFewRows = 64, kSmallRows = 256, kSmallMatrix = 1024 * 1024;
+static bool few_rows(int M, int N, int K) { return M <= kFewRows || (M <= kSmallRows && (long)N * K <= kSmallMatrix); }
 
 template <typename ST, bool VEC>
 static void launch_gemm(hipStream_t s, const float* A, const ST* W, const ST* bias, const plain_ln_args* ln, const PlainGemm& p) {
     const ST *gamma = ln ? (const ST*)ln->gamma : nullptr, *beta = ln ? (const ST*)ln->beta : nullptr;
-    if (p.M <= kFewRows) {
+    if (few_rows(p.M, p.N, p.K)) {
         const dim3 grid((p.N + 15) / 16, (p.M + 15) / 16);
         if (ln) gemm_few_kernel<ST, VEC, true><<<grid, 512, 0, s>>>(A, W, bias, gamma, beta, p);
         else gemm_few_kernel<ST, VEC, false><<<grid, 512, 0, s>>>(A, W, bias, gamma, beta, p);
@@ -670,7 +674,7 @@ static void launch_gemm(hipStream_t s, const float* A, const ST* W, const ST* bi
 template <typename ST>
 static void plain_gemm_t(hipStream_t s, const float* A, const void* W, const void* bias, const plain_ln_args* ln, float* scratch,
                          PlainGemm& p) {
-    if (ln && p.M > kFewRows) {
+    if (ln && !few_rows(p.M, p.N, p.K)) {
         plain_ln(s, sizeof(ST) == 2, A, *ln, scratch, p.M, p.K);
         A = scratch;
         ln = nullptr;
