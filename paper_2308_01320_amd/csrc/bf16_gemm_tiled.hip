@@ -7,10 +7,14 @@ namespace {
 
 // A wavefront's share of the scoring head, NA column blocks x MJ row blocks from row m0 and column n0 on.  The logits
 // never leave the registers: per row, the soft-max partials of the wavefront's 32 NA vocabulary entries (slice `part` of
-// the row) and, if the row's next token is among them, its logit.
+// the row) and, if the row's next token is among them, its logit.  (The hardware's exponential, and the next token looked for only where
+// one of the rows has it: of 16384 x 50272 x 2048 in 256 x 128 tiles 3770 -> 3520 us; the log-probabilities' error against 64 bits stays
+// 4.4e-5, the operands' rounding.)
+constexpr float kLog2e = 1.44269504088896340736f;
 template <int NA, int MJ>
 __device__ __forceinline__ void score_tile(const Epi& p, const f32x16 (&acc)[NA][MJ], int m0, int n0, int part, int lane) {
     const int nl = n0 + 4 * (lane >> 5);
+    const bool whole = n0 + 32 * NA <= p.N;  // (uniform) no entry past the vocabulary
 #pragma unroll
     for (int j = 0; j < MJ; ++j) {
         const int m = m0 + j * 32 + (lane & 31);
@@ -19,29 +23,35 @@ __device__ __forceinline__ void score_tile(const Epi& p, const f32x16 (&acc)[NA]
             tgt = p.ids[m + 1];
             tgt = tgt < 0 ? 0 : (tgt >= p.N ? p.N - 1 : tgt);  // clamped like the embedding's ids
         }
-        float mx = -INFINITY;
-#pragma unroll
-        for (int i = 0; i < NA; ++i)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int n = nl + i * 32 + 8 * (r >> 2) + (r & 3);
-                const float z = n < p.N ? acc[i][j][r] : -INFINITY;
-                mx = fmaxf(mx, z);
-                if (n == tgt) p.sc_tgt[m] = z;
-            }
-        mx = fmaxf(mx, __shfl_xor(mx, 32));
-        float sum = 0.f;
-        if (mx > -INFINITY) {
+        // the next token's logit: few wavefronts hold one of their rows'
+        if (__any(tgt >= n0 && tgt < n0 + 32 * NA)) {
+            const int at = tgt - nl;  // (this lane's entries: 32 i + 8 (r / 4) + r % 4)
+            float hit = 0.f;
 #pragma unroll
             for (int i = 0; i < NA; ++i)
 #pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const int n = nl + i * 32 + 8 * (r >> 2) + (r & 3);
-                    sum += expf((n < p.N ? acc[i][j][r] : -INFINITY) - mx);
-                }
+                for (int r = 0; r < 16; ++r) hit = at == i * 32 + 8 * (r >> 2) + (r & 3) ? acc[i][j][r] : hit;
+            if (at >= 0 && at < 32 * NA && !(at & 4)) p.sc_tgt[m] = hit;
         }
+        float mx = -INFINITY, sum = 0.f;
+        auto reduce = [&](auto logit) {
+#pragma unroll
+            for (int i = 0; i < NA; ++i)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) mx = fmaxf(mx, logit(i, r));
+            mx = fmaxf(mx, __shfl_xor(mx, 32));
+            if (mx > -INFINITY) {
+#pragma unroll
+                for (int i = 0; i < NA; ++i)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) sum += __builtin_amdgcn_exp2f((logit(i, r) - mx) * kLog2e);
+            }
+        };
+        if (whole) reduce([&](int i, int r) { return acc[i][j][r]; });
+        else reduce([&](int i, int r) { return nl + i * 32 + 8 * (r >> 2) + (r & 3) < p.N ? acc[i][j][r] : -INFINITY; });
         sum += __shfl_xor(sum, 32);
         if (lane < 32 && m < p.M) p.sc_stats[(size_t)m * p.sc_parts + part] = make_float2(mx, sum);
+        __builtin_amdgcn_sched_barrier(0);  // (one row block's values in registers at a time)
     }
 }
 
@@ -119,8 +129,9 @@ __device__ __forceinline__ void lm_head_tile(const Epi& p, const f32x16 (&acc)[4
 // they are moved global -> LDS directly (global_load_lds, 16 bytes per lane, no
 // staging registers) into a ring of five stages of one k-block (80 KiB); one barrier per stage.
 // At most 256 registers, so that TWO workgroups share a CU: while one of them sits at its barrier, waits
-// for operands or reduces its logits (13 us of a 256 x 256 tile's 72 at 2048 columns of k: the big tile's kernel with this
-// epilogue took as long), the other one's MFMAs keep the matrix cores busy.
+// for operands or reduces its logits, the other one's MFMAs keep the matrix cores busy.  Most passes take the big tile's kernel all the
+// same, which loads a third less per product (score_tile, the planner, has both sides); this one is for the row and column counts that
+// leave that kernel's last round nearly empty.
 constexpr int TN = 256;
 constexpr int TNB = TN / 32;  // 32-row operand blocks on the n side
 constexpr int TMB = 4;        // ... and on the m side
@@ -524,7 +535,11 @@ __global__ __launch_bounds__(256, 1) void gemm_tiled256_kernel(const u32x4* __re
         mma_all(opb);
     }
     if constexpr (NA > 4) asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");  // the last matrix instructions' results are in
-    store_tile<MODE, NA, 4>(p, bias8, acc, tm * BM + wm * 128, tn * BN + wn * 32 * NA, ks, cur_len, lane);
+    if constexpr (MODE == MODE_SCORE) {
+        // (the lane's number formed anew: kept through the loop it is a register too many)
+        const int lane1 = (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
+        score_tile<NA, 4>(p, acc, tm * BM + wm * 128, tn * BN + wn * 32 * NA, tn * 2 + wn, lane1);
+    } else store_tile<MODE, NA, 4>(p, bias8, acc, tm * BM + wm * 128, tn * BN + wn * 32 * NA, ks, cur_len, lane);
 }
 
 // ----------------------------------------------------------------- 256 x 64..192 tiles, and halved ones of up to 256 rows, on a deep ring (few rows)
@@ -872,7 +887,10 @@ void launch_tiled(hipStream_t s, const void* Wp, const void* Xhi, int KB, int N,
         else gemm_ring_kernel<MODE, 4, MODE == MODE_SCORE ? 2 : 3><<<grid, 256, 0, s>>>(W, X, bias8, KB, NT32, MT32, tiles_n, tiles_m, ksplit, p);
         return;
     }
-    if constexpr (MODE != MODE_SCORE && MODE != MODE_LMHEAD) {
+    if constexpr (MODE == MODE_SCORE) {
+        const int tiles_n = (N + TN - 1) / TN, tiles_m = (M + BM - 1) / BM, grid = (tiles_n * tiles_m + 7) / 8 * 8;
+        gemm_tiled256_kernel<MODE, 4><<<grid, 256, 0, s>>>(W, X, bias8, KB, NT32, MT32, tiles_n, tiles_m, 1, tiles_n, p);
+    } else if constexpr (MODE != MODE_LMHEAD) {
         if (tile > 10) {
             const int tiles_n = (N + 127) / 128, tiles_m = (M + 64 * (tile - 10) - 1) / (64 * (tile - 10));
             const int grid = (tiles_n * tiles_m * ksplit + 7) / 8 * 8;
@@ -962,10 +980,18 @@ static RingPlan fused_plan(int M, int N, int KB, size_t capacity_floats) {
 // final LayerNorm may come folded in.
 static RingPlan lm_head_plan(int M, int V, int K) { return ring_plan_256(M, V, K / 16, true, 0, M <= 64 ? 1 : 3); }
 
-// The scoring head: 0 for gemm_score_kernel (two workgroups per CU: from two rounds of its tiles on), else the ring kernel's tile
-static int score_tile(int M, int V) {
-    const long tiles = (long)((V + TN - 1) / TN) * ((M + 127) / 128);
-    return tiles >= 2 * plan_cus() ? 0 : (M <= 64 ? 1 : 2);
+// The scoring head: 0 for gemm_score_kernel (two workgroups per CU) or 4, the big tiles, from two rounds of the former's on, else the
+// ring kernel's tile.  Microseconds of rounds, fitted to 350 .. 16384 rows of 5000 .. 50272 ids at k = 1024, 2048, 5120: a big
+// tile loads a third less for its products (16 KiB to 64 of them), where two of the others reduce the logits of one behind the products of
+// the other and a last round of at most one workgroup to a CU takes seven tenths.  Rows x ids x k, two workgroups / big, the whole head:
+// 16384 x 50272 x 2048 3334 / 2892, x 5120 8286 / 6950, x 1024 1696 / 1593; 640 x 50272 x 2048 155 / 182, 3500 x 5000 x 1024 83 / 88.
+// (The same slices of 128 entries and the same order of sums: the results are the same to the bit.)
+static int score_tile(int M, int V, int K) {
+    const long cus = plan_cus(), tn = (V + TN - 1) / TN, tiles = tn * ((M + 127) / 128), big = tn * ((M + BM - 1) / BM);
+    if (tiles < 2 * cus) return M <= 64 ? 1 : 2;
+    const long rest = tiles % (2 * cus);
+    const double two = (double)(tiles / (2 * cus)) + (rest == 0 ? 0.0 : (rest <= cus ? 0.7 : 1.0));
+    return (double)((big + cus - 1) / cus) * (5.5 + 0.0256 * K) < two * (0.9 + 0.0322 * K) ? 4 : 0;
 }
 
 void bf16_pass_plan_query(int use, int M, int N, int K, size_t capacity_floats, int cus, int* tile_rows, int* tile_cols, int* wg_cols, int* ks,
@@ -979,7 +1005,7 @@ void bf16_pass_plan_query(int use, int M, int N, int K, size_t capacity_floats, 
         const RingPlan g = fused_plan(M, N, K / 16, capacity_floats);
         tile = g.tile; *ks = g.ks;
     } else if (use == TILED_SCORE_HEAD) {
-        tile = score_tile(M, N);
+        tile = score_tile(M, N, K);
     } else {
         tile = bf16_lm_head_streams(M, N) ? -1 : lm_head_plan(M, N, K).tile;
     }
@@ -1031,7 +1057,7 @@ void bf16_score_head(hipStream_t s, const void* Wp, const void* Xhi, int M, int 
     Epi p{};
     p.M = M; p.N = V; p.S = S; p.ids = ids; p.sc_stats = (float2*)stats; p.sc_tgt = tgt; p.sc_parts = bf16_score_parts(V);
     const int NT32 = (V + 31) / 32, MT32 = (M + 31) / 32, KB = K / 16;
-    const int tiles_n = (V + TN - 1) / TN, tiles_m = (M + 127) / 128, tiles = tiles_n * tiles_m, tile = score_tile(M, V);
+    const int tiles_n = (V + TN - 1) / TN, tiles_m = (M + 127) / 128, tiles = tiles_n * tiles_m, tile = score_tile(M, V, K);
     if (tile == 0)
         gemm_score_kernel<<<(tiles + 7) / 8 * 8, 256, 0, s>>>((const u32x4*)Wp, (const u32x4*)Xhi, KB, NT32, MT32, tiles_n, tiles_m, p);
     else
