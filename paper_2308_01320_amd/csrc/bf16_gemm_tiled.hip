@@ -11,8 +11,8 @@ namespace {
 // one of the rows has it: of 16384 x 50272 x 2048 in 256 x 128 tiles 3770 -> 3520 us; the log-probabilities' error against 64 bits stays
 // 4.4e-5, the operands' rounding.)
 constexpr float kLog2e = 1.44269504088896340736f;
-template <int NA, int MJ>
-__device__ __forceinline__ void score_tile(const Epi& p, const f32x16 (&acc)[NA][MJ], int m0, int n0, int part, int lane) {
+template <int NA, int MJ, bool BIG = false>
+__device__ __forceinline__ void score_tile(const Epi& p, f32x16 (&acc)[NA][MJ], int m0, int n0, int part, int lane) {
     const int nl = n0 + 4 * (lane >> 5);
     const bool whole = n0 + 32 * NA <= p.N;  // (uniform) no entry past the vocabulary
 #pragma unroll
@@ -22,6 +22,10 @@ __device__ __forceinline__ void score_tile(const Epi& p, const f32x16 (&acc)[NA]
         if (m < p.M && m % p.S != p.S - 1) {
             tgt = p.ids[m + 1];
             tgt = tgt < 0 ? 0 : (tgt >= p.N ? p.N - 1 : tgt);  // clamped like the embedding's ids
+        }
+        if constexpr (BIG) {  // (see store_tile)
+#pragma unroll
+            for (int i = 0; i < NA; ++i) asm volatile("" : "+a"(acc[i][j]));
         }
         // the next token's logit: few wavefronts hold one of their rows'
         if (__any(tgt >= n0 && tgt < n0 + 32 * NA)) {
@@ -264,89 +268,107 @@ __device__ __forceinline__ void store16(void* dst, float a, float b, float c, fl
 }
 
 // A wavefront's results, NA column blocks x MJ row blocks of 32 x 32 accumulators from row m0 and column n0 on.
-template <int MODE, int NA, int MJ>
-__device__ __forceinline__ void store_tile(const Epi& p, const u32x4* __restrict__ bias8, const f32x16 (&acc)[NA][MJ], int m0,
+// BIG: the big kernel's accumulators, which fill the accumulation registers (a fifth column block the vector registers) and are to
+// stay there until a block of them is turned into results: copied to vector registers all at once they push the next tile's addresses
+// into scratch memory.
+template <int MODE, int NA, int MJ, bool BIG = false>
+__device__ __forceinline__ void store_tile(const Epi& p, const u32x4* __restrict__ bias8, f32x16 (&acc)[NA][MJ], int m0,
                                            int n0, int ks, int cur_len, int lane) {
     // Epilogue.  The CU runs nothing else meanwhile, so it is written out per mode with everything that depends on
     // the row alone (sequence, cache position, row base address) computed once per 32-row block and everything
     // that depends on the column alone wave-uniform (the generic per-quad form recomputes both, with run-time
     // integer divisions, for each of a lane's 64 quads: 22 us per tile for FC1, 44 us for QKV, against 130 us of
     // matrix instructions).  N is a multiple of 32 here, so a 32-column block is inside or outside as a whole.
+    // Columns outside, rows inside: a column block's bias is fetched and unpacked once.
     const int hh = lane >> 5;
+    size_t row[MJ];                   // MODE_STORE: float index of (m, 4 hh); BIAS_RELU: 16-byte slot of (m, k half hh) in
+                                      // the first block of its row of blocks; QKV: float index into q
+    [[maybe_unused]] size_t kvrow[MJ];  // QKV: half index of (sequence, head 0, position, 0) inside one (layer, k|v) plane
+    bool live[MJ];
+    [[maybe_unused]] bool append[MJ];   // QKV: the row is a token (not padding): its key and value go into the cache
 #pragma unroll
     for (int j = 0; j < MJ; ++j) {
         const int m = m0 + j * 32 + (lane & 31);
-        if (m >= p.M) continue;
-        size_t row = 0;       // MODE_STORE: float index of (m, 4 hh); BIAS_RELU: 16-byte slot of (m, k half hh) in
-                              // the first block of its row of blocks; QKV: float index into q
-        size_t kvrow = 0;     // QKV: half index of (sequence, head 0, position, 0) inside one (layer, k|v) plane
-        bool append = true;   // QKV: the row is a token (not padding): its key and value go into the cache
+        live[j] = m < p.M;
         if (MODE == MODE_STORE) {
-            row = (size_t)ks * p.out_split + (size_t)m * p.N + 4 * hh;
+            row[j] = (size_t)ks * p.out_split + (size_t)m * p.N + 4 * hh;
         } else if (MODE == MODE_BIAS_RELU) {
-            row = (size_t)(m >> 5) * (p.N >> 4) * 64 + 32 * hh + (m & 31);
+            row[j] = (size_t)(m >> 5) * (p.N >> 4) * 64 + 32 * hh + (m & 31);
         } else {
-            row = (size_t)m * p.H + 4 * hh;
-            const int b = row_seq(p.st, m, p.S), r = m % p.S;
-            int t = cur_len + r;
-            if (cur_len < 0) {  // sequences of different lengths; padding rows append nothing
-                const int tr = r - row_pad(p.st, b);
-                append = tr >= 0;
-                t = seq_len(p.st, b) + tr;
+            row[j] = (size_t)m * p.H + 4 * hh;
+            append[j] = false;
+            kvrow[j] = 0;
+            if (live[j]) {
+                const int b = row_seq(p.st, m, p.S), r = m % p.S;
+                int t = cur_len + r;
+                append[j] = true;
+                if (cur_len < 0) {  // sequences of different lengths; padding rows append nothing
+                    const int tr = r - row_pad(p.st, b);
+                    append[j] = tr >= 0;
+                    t = seq_len(p.st, b) + tr;
+                }
+                kvrow[j] = ((size_t)b * p.n_heads * p.max_seq + t) * p.d;
             }
-            kvrow = ((size_t)b * p.n_heads * p.max_seq + t) * p.d;
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < NA; ++i) {
+        const int n32 = n0 + i * 32;  // wave-uniform
+        if (n32 >= p.N) break;
+        float bv[MODE == MODE_STORE ? 1 : 4][4];
+        if (MODE != MODE_STORE) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const u32x4 b8 = bias8[(n32 >> 3) + q];  // wave-uniform address: a scalar load
+                const uint2 bb = hh ? make_uint2(b8.z, b8.w) : make_uint2(b8.x, b8.y);
+                bv[q][0] = bf_lo(bb.x); bv[q][1] = bf_hi(bb.x); bv[q][2] = bf_lo(bb.y); bv[q][3] = bf_hi(bb.y);
+            }
+        }
+        const int part = MODE != MODE_QKV ? 0 : (n32 >= 2 * p.H ? 2 : (n32 >= p.H ? 1 : 0));  // query, key or value columns (uniform)
+        half_t* kvcol = nullptr;
+        if (part) {
+            const int c32 = n32 - part * p.H, head = c32 / p.d;
+            kvcol = p.kv + (((size_t)(p.layer * 2 + (part - 1)) * p.max_batch) * p.n_heads + head) * p.max_seq * (size_t)p.d +
+                    (c32 - head * p.d);
         }
 #pragma unroll
-        for (int i = 0; i < NA; ++i) {
-            const int n32 = n0 + i * 32;  // wave-uniform
-            if (n32 >= p.N) continue;
+        for (int j = 0; j < MJ; ++j) {
+            if constexpr (BIG) {
+                if (i < 4) asm volatile("" : "+a"(acc[i][j]));
+            }
+            if (!live[j]) continue;
             if (MODE == MODE_STORE) {
 #pragma unroll
                 for (int q = 0; q < 4; ++q)
-                    store16(p.out + row + n32 + 8 * q, acc[i][j][q * 4 + 0], acc[i][j][q * 4 + 1], acc[i][j][q * 4 + 2],
+                    store16(p.out + row[j] + n32 + 8 * q, acc[i][j][q * 4 + 0], acc[i][j][q * 4 + 1], acc[i][j][q * 4 + 2],
                             acc[i][j][q * 4 + 3]);
-            } else if (MODE == MODE_BIAS_RELU) {
-                u32x4* ob = p.out_blocks + row + (size_t)(n32 >> 4) * 64;
-                uint2 h4[4];
+                continue;
+            }
+            uint2 h4[4];
 #pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const u32x4 b8 = bias8[(n32 >> 3) + q];  // wave-uniform address: a scalar load
-                    const uint2 bb = hh ? make_uint2(b8.z, b8.w) : make_uint2(b8.x, b8.y);
-                    const float v0 = fmaxf(acc[i][j][q * 4 + 0] + bf_lo(bb.x), 0.f), v1 = fmaxf(acc[i][j][q * 4 + 1] + bf_hi(bb.x), 0.f);
-                    const float v2 = fmaxf(acc[i][j][q * 4 + 2] + bf_lo(bb.y), 0.f), v3 = fmaxf(acc[i][j][q * 4 + 3] + bf_hi(bb.y), 0.f);
-                    h4[q] = make_uint2(pack2(v0, v1), pack2(v2, v3));
+            for (int q = 0; q < 4; ++q) {
+                float v[4];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    v[e] = acc[i][j][q * 4 + e] + bv[MODE == MODE_STORE ? 0 : q][e];
+                    if (MODE == MODE_BIAS_RELU) v[e] = fmaxf(v[e], 0.f);
                 }
+                if (MODE == MODE_QKV && !part)
+                    store16(p.out + row[j] + n32 + 8 * q, v[0] * p.qscale, v[1] * p.qscale, v[2] * p.qscale, v[3] * p.qscale);
+                else
+                    h4[q] = make_uint2(pack2(v[0], v[1]), pack2(v[2], v[3]));
+            }
+            if (MODE == MODE_BIAS_RELU || part) {  // (uniform) halves: eight of a row per lane
+                u32x4* ob = p.out_blocks + row[j] + (size_t)(n32 >> 4) * 64;
 #pragma unroll
-                for (int qq = 0; qq < 2; ++qq) store16(ob + qq * 64, join_halves(h4[2 * qq], h4[2 * qq + 1]));
-            } else {
-                const int part = n32 >= 2 * p.H ? 2 : (n32 >= p.H ? 1 : 0);  // query, key or value columns (uniform)
-                half_t* kvcol = nullptr;
-                if (part) {
-                    const int c32 = n32 - part * p.H, head = c32 / p.d;
-                    kvcol = p.kv + (((size_t)(p.layer * 2 + (part - 1)) * p.max_batch) * p.n_heads + head) * p.max_seq * (size_t)p.d +
-                            (c32 - head * p.d);
-                }
-                uint2 h4[4];
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const u32x4 b8 = bias8[(n32 >> 3) + q];
-                    const uint2 bb = hh ? make_uint2(b8.z, b8.w) : make_uint2(b8.x, b8.y);
-                    const float v0 = acc[i][j][q * 4 + 0] + bf_lo(bb.x), v1 = acc[i][j][q * 4 + 1] + bf_hi(bb.x);
-                    const float v2 = acc[i][j][q * 4 + 2] + bf_lo(bb.y), v3 = acc[i][j][q * 4 + 3] + bf_hi(bb.y);
-                    if (!part)
-                        store16(p.out + row + n32 + 8 * q, v0 * p.qscale, v1 * p.qscale, v2 * p.qscale, v3 * p.qscale);
-                    else
-                        h4[q] = make_uint2(pack2(v0, v1), pack2(v2, v3));
-                }
-                if (part) {  // (uniform) keys / values: eight halves of a row per lane
-#pragma unroll
-                    for (int qq = 0; qq < 2; ++qq) {
-                        const u32x4 v8 = join_halves(h4[2 * qq], h4[2 * qq + 1]);
-                        if (append) store16(kvcol + kvrow + 8 * (2 * qq + hh), v8);
-                    }
+                for (int qq = 0; qq < 2; ++qq) {
+                    const u32x4 v8 = join_halves(h4[2 * qq], h4[2 * qq + 1]);
+                    if (MODE == MODE_BIAS_RELU) store16(ob + qq * 64, v8);
+                    else if (append[j]) store16(kvcol + kvrow[j] + 8 * (2 * qq + hh), v8);
                 }
             }
         }
+        __builtin_amdgcn_sched_barrier(0);  // (a column block's values in registers at a time)
     }
 }
 
@@ -382,48 +404,56 @@ __global__ __launch_bounds__(256, 1) void gemm_tiled256_kernel(const u32x4* __re
     constexpr int SB = 4 * NA + 16;   // blocks of a stage (two k-blocks of 2 NA W row-tiles and 8 X row-tiles)
     __shared__ u32x4 ring[BSTAGES][SB][64];
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
-    // Work items, in launch order: the tiles of the first split_tn columns of tiles with their whole k range, then
-    // the tiles of the other columns once per k range (k range after k range).  Each of the two parts is dealt out
-    // so that an XCD gets a contiguous run of it.
-    const int n_whole = split_tn * tiles_m, whole_pad = (n_whole + 7) / 8 * 8;
-    const bool cut = (int)blockIdx.x >= whole_pad;
-    const int idx = cut ? blockIdx.x - whole_pad : blockIdx.x;
-    const int cols = cut ? tiles_n - split_tn : split_tn;  // columns of tiles of this part
-    const int nblk = cols * tiles_m;
-    const int nitem = cut ? nblk * ksplit : nblk;
-    const int per_xcd = (nitem + 7) / 8;
-    const int item = (idx % 8) * per_xcd + idx / 8;
-    if (item >= nitem) return;
-    const int lin = item % nblk, ks = item / nblk;
-    const int nks = cut ? ksplit : 1;  // k ranges of this tile
-    constexpr int GROUP = 4;  // m-tiles per super-row: the 32 tiles an XCD works on at once share 4 X panels and 8 W panels
-    const int gsize = GROUP * cols;
-    const int g = lin / gsize, first_m = g * GROUP;
-    const int gm = min(GROUP, tiles_m - first_m);
-    const int tm = first_m + (lin % gsize) % gm, tn = (cut ? split_tn : 0) + (lin % gsize) / gm;
     const int wn = wave & 1, wm = wave >> 1;  // this wavefront's 32 NA (n) x 128 (m) sub-tile
     const int cur_len = epilogue_len<MODE>(p);
-    f32x16 acc[NA][4];
-#pragma unroll
-    for (int i = 0; i < NA; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = f32x16{};
-
-    const int nst_all = KB / 2;  // KB is even (K % 32 == 0)
-    const int st0 = (int)((long)ks * nst_all / nks);
-    const int nstage = (int)((long)(ks + 1) * nst_all / nks) - st0;
+    // Work items, in the order of `slot`: the tiles of the first split_tn columns of tiles with their whole k range, then
+    // the tiles of the other columns once per k range (k range after k range).  Each of the two parts is dealt out
+    // so that an XCD gets a contiguous run of it.  A workgroup takes every gridDim.x-th slot.
+    const int n_whole = split_tn * tiles_m, whole_pad = (n_whole + 7) / 8 * 8;
+    const int n_cut = (tiles_n - split_tn) * tiles_m * ksplit, slots = whole_pad + (n_cut + 7) / 8 * 8;
+    struct Item { int tm, tn, ks, st0, nstage; };
+    Item it;
+    auto decode = [&](int slot) {  // false: a slot of padding
+        const bool cut = slot >= whole_pad;
+        const int idx = cut ? slot - whole_pad : slot;
+        const int cols = cut ? tiles_n - split_tn : split_tn;  // columns of tiles of this part
+        const int nblk = cols * tiles_m;
+        const int nitem = cut ? n_cut : nblk;
+        const int per_xcd = (nitem + 7) / 8;
+        const int item = (idx % 8) * per_xcd + idx / 8;
+        if (item >= nitem) return false;
+        const int lin = item % nblk, ks = item / nblk;
+        const int nks = cut ? ksplit : 1;  // k ranges of this tile
+        constexpr int GROUP = 4;  // m-tiles per super-row: the 32 tiles an XCD works on at once share 4 X panels and 8 W panels
+        const int gsize = GROUP * cols;
+        const int g = lin / gsize, first_m = g * GROUP;
+        const int gm = min(GROUP, tiles_m - first_m);
+        const int nst_all = KB / 2;  // KB is even (K % 32 == 0)
+        const int st0 = (int)((long)ks * nst_all / nks);
+        it = Item{first_m + (lin % gsize) % gm, (cut ? split_tn : 0) + (lin % gsize) / gm, ks, st0,
+                  (int)((long)(ks + 1) * nst_all / nks) - st0};
+        return true;
+    };
+    int slot = blockIdx.x;
+    auto next_item = [&]() {  // the next slot from `slot` on that holds an item
+        while (slot < slots && !decode(slot)) slot += gridDim.x;
+        return slot < slots;
+    };
+    if (!next_item()) return;
     // The SB blocks of a stage are copied by the four wavefronts, CW each: wavefront w copies blocks w CW .. w CW + CW - 1
     // (block c < XOFF: W row-tile c / 2, k-block c % 2; else X row-tile (c - XOFF) / 2).  Row-tiles past the matrix:
     // the last one (computed, never stored).
     constexpr int CW = NA + 4;  // copies per wavefront and stage
     const u32x4* src[CW];
+    auto set_sources = [&]() {
 #pragma unroll
-    for (int q = 0; q < CW; ++q) {
-        const int c = wave * CW + q;
-        const bool isw = c < XOFF;
-        const int rt = isw ? min(tn * 2 * NA + (c >> 1), NT32 - 1) : min(tm * 8 + ((c - XOFF) >> 1), MT32 - 1);
-        src[q] = (isw ? Wp : X) + ((size_t)rt * KB + (size_t)st0 * 2 + (c & 1)) * 64 + lane;
-    }
+        for (int q = 0; q < CW; ++q) {
+            const int c = wave * CW + q;
+            const bool isw = c < XOFF;
+            const int rt = isw ? min(it.tn * 2 * NA + (c >> 1), NT32 - 1) : min(it.tm * 8 + ((c - XOFF) >> 1), MT32 - 1);
+            src[q] = (isw ? Wp : X) + ((size_t)rt * KB + (size_t)it.st0 * 2 + (c & 1)) * 64 + lane;
+        }
+    };
     auto copy1 = [&](int st, int q) {
         load_block_to_lds(src[q] + (size_t)st * 128, &ring[st & (BSTAGES - 1)][wave * CW + q][0]);
     };
@@ -432,6 +462,7 @@ __global__ __launch_bounds__(256, 1) void gemm_tiled256_kernel(const u32x4* __re
         for (int q = 0; q < CW; ++q) copy1(st, q);
     };
     constexpr int C2 = CW / 2;  // copies 0 .. C2-1 of a stage go out in the second half of stage t-3, the rest in the first of t-2
+    f32x16 acc[NA][4];
     struct Ops { u32x4 a[NA], b[4]; };
     // LDS read q (0 .. NA+3) of a k-block, in the order the matrix instructions below first need the operands:
     // a0, b0, b1, b2, b3, a1, a2, ...
@@ -462,84 +493,106 @@ __global__ __launch_bounds__(256, 1) void gemm_tiled256_kernel(const u32x4* __re
         for (int n = 0; n < 4 * NA; ++n) mma1(o, n);
     };
     // The prologue issues what would fall before stage 0.
-    issue(0);
-    if (nstage >= 2) issue(1);
-    if (nstage >= 3) {
+    auto prologue = [&]() {
+        issue(0);
+        if (it.nstage >= 2) issue(1);
+        if (it.nstage >= 3) {
 #pragma unroll
-        for (int q = 0; q < C2; ++q) copy1(2, q);
-        wait_vmcnt<CW + C2>();
-    } else if (nstage == 2) {
-        wait_vmcnt<CW>();
-    } else {
+            for (int q = 0; q < C2; ++q) copy1(2, q);
+        }
+    };
+    set_sources();
+    prologue();
+    if (it.nstage >= 3) wait_vmcnt<CW + C2>();
+    else if (it.nstage == 2) wait_vmcnt<CW>();
+    else wait_vmcnt<0>();
+    // One tile after another.  Between two of them nothing but this workgroup runs on the CU: the next tile's first stages are requested
+    // as soon as everybody has read the last stage, ahead of the epilogue that covers their way.  (A workgroup per tile before, and an
+    // epilogue of rows outside, columns inside: a four-layer prompt pass of 8192 rows, hidden 5120, 13.91 -> 13.68 ms, one of 2560
+    // rows 5.24 -> 5.15, twelve layers of 16384 rows, hidden 2048, and the scoring head 13.08 -> 12.42.)
+    for (;;) {
+        const int nstage = it.nstage, tm = it.tm, tn = it.tn, ks = it.ks;
+#pragma unroll
+        for (int i = 0; i < NA; ++i)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) acc[i][j] = f32x16{};
+        __syncthreads();
+        Ops opa, opb;
+        read_ops(opa, 0, 0);
+        int s = 0;
+        // Steady state: stage s+1 and the first copies of stage s+2 are in flight; the first half of stage s requests the
+        // rest of stage s+2 (into the slot stage s-2 left: everybody passed the barrier of stage s-1 since), the second
+        // half the first copies of stage s+3 (into the slot of stage s-1, behind this stage's barrier).  Scheduling
+        // barriers keep the order written here.  The workgroup barrier is the bare instruction: what it orders are the
+        // copies, which the wait before it covers -- the LDS reads in flight across it belong to the stage in use, not to
+        // the slot about to be refilled (a fence would wait for them).
+        // In each half of a stage (2 NA pairs of matrix instructions) the first pairs are followed by two LDS reads each
+        // (the operands of the other half: the last of them is at least eight matrix instructions old when the half
+        // ends, so the wait for the reads at the top of a half finds them done), the last ones by one copy each.
+        constexpr int NP = 2 * NA;  // pairs of matrix instructions per half
+        static_assert((NR + 1) / 2 + (CW - C2) <= NP, "reads and copies of a half fit behind its pairs");
+        for (; s + 3 < nstage; ++s) {
+#pragma unroll
+            for (int q = 0; q < NP; ++q) {
+                mma1(opa, 2 * q);
+                mma1(opa, 2 * q + 1);
+                if (2 * q < NR) {
+                    read1(opb, s, 1, 2 * q);
+                    if (2 * q + 1 < NR) read1(opb, s, 1, 2 * q + 1);
+                } else if (q >= NP - (CW - C2)) {
+                    copy1(s + 2, C2 + q - (NP - (CW - C2)));
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            wait_vmcnt<CW>();  // this wavefront's copies of stage s+1 have landed ...
+            asm volatile("" ::: "memory");
+            __builtin_amdgcn_s_barrier();  // ... and everybody's; everybody is done with stage s-1
+            asm volatile("" ::: "memory");
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int q = 0; q < NP; ++q) {
+                mma1(opb, 2 * q);
+                mma1(opb, 2 * q + 1);
+                if (2 * q < NR) {
+                    read1(opa, s + 1, 0, 2 * q);
+                    if (2 * q + 1 < NR) read1(opa, s + 1, 0, 2 * q + 1);
+                } else if (q >= NP - C2) {
+                    copy1(s + 3, q - (NP - C2));
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+        for (; s < nstage; ++s) {  // the last three stages: only the late copies of the last one are left to request
+            if (s + 2 < nstage) {
+#pragma unroll
+                for (int q = C2; q < CW; ++q) copy1(s + 2, q);
+            }
+            read_ops(opb, s, 1);
+            mma_all(opa);
+            if (s + 1 < nstage) {
+                if (s + 2 < nstage) wait_vmcnt<CW>();
+                else wait_vmcnt<0>();
+                __syncthreads();
+                read_ops(opa, s + 1, 0);
+            }
+            mma_all(opb);
+        }
+        slot += gridDim.x;
+        const bool more = next_item();
+        if (more) {
+            __syncthreads();  // (the reads of the last stage have been waited for: its matrix instructions are issued)
+            set_sources();
+            prologue();
+        }
+        if constexpr (NA > 4) asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");  // the last matrix instructions' results are in
+        if constexpr (MODE == MODE_SCORE) {
+            // (the lane's number formed anew: kept through the loop it is a register too many)
+            const int lane1 = (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
+            score_tile<NA, 4, true>(p, acc, tm * BM + wm * 128, tn * BN + wn * 32 * NA, tn * 2 + wn, lane1);
+        } else store_tile<MODE, NA, 4, true>(p, bias8, acc, tm * BM + wm * 128, tn * BN + wn * 32 * NA, ks, cur_len, lane);
+        if (!more) return;
         wait_vmcnt<0>();
     }
-    __syncthreads();
-    Ops opa, opb;
-    read_ops(opa, 0, 0);
-    int s = 0;
-    // Steady state: stage s+1 and the first copies of stage s+2 are in flight; the first half of stage s requests the
-    // rest of stage s+2 (into the slot stage s-2 left: everybody passed the barrier of stage s-1 since), the second
-    // half the first copies of stage s+3 (into the slot of stage s-1, behind this stage's barrier).  Scheduling
-    // barriers keep the order written here.  The workgroup barrier is the bare instruction: what it orders are the
-    // copies, which the wait before it covers -- the LDS reads in flight across it belong to the stage in use, not to
-    // the slot about to be refilled (a fence would wait for them).
-    // In each half of a stage (2 NA pairs of matrix instructions) the first pairs are followed by two LDS reads each
-    // (the operands of the other half: the last of them is at least eight matrix instructions old when the half
-    // ends, so the wait for the reads at the top of a half finds them done), the last ones by one copy each.
-    constexpr int NP = 2 * NA;  // pairs of matrix instructions per half
-    static_assert((NR + 1) / 2 + (CW - C2) <= NP, "reads and copies of a half fit behind its pairs");
-    for (; s + 3 < nstage; ++s) {
-#pragma unroll
-        for (int q = 0; q < NP; ++q) {
-            mma1(opa, 2 * q);
-            mma1(opa, 2 * q + 1);
-            if (2 * q < NR) {
-                read1(opb, s, 1, 2 * q);
-                if (2 * q + 1 < NR) read1(opb, s, 1, 2 * q + 1);
-            } else if (q >= NP - (CW - C2)) {
-                copy1(s + 2, C2 + q - (NP - (CW - C2)));
-            }
-            __builtin_amdgcn_sched_barrier(0);
-        }
-        wait_vmcnt<CW>();  // this wavefront's copies of stage s+1 have landed ...
-        asm volatile("" ::: "memory");
-        __builtin_amdgcn_s_barrier();  // ... and everybody's; everybody is done with stage s-1
-        asm volatile("" ::: "memory");
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int q = 0; q < NP; ++q) {
-            mma1(opb, 2 * q);
-            mma1(opb, 2 * q + 1);
-            if (2 * q < NR) {
-                read1(opa, s + 1, 0, 2 * q);
-                if (2 * q + 1 < NR) read1(opa, s + 1, 0, 2 * q + 1);
-            } else if (q >= NP - C2) {
-                copy1(s + 3, q - (NP - C2));
-            }
-            __builtin_amdgcn_sched_barrier(0);
-        }
-    }
-    for (; s < nstage; ++s) {  // the last three stages: only the late copies of the last one are left to request
-        if (s + 2 < nstage) {
-#pragma unroll
-            for (int q = C2; q < CW; ++q) copy1(s + 2, q);
-        }
-        read_ops(opb, s, 1);
-        mma_all(opa);
-        if (s + 1 < nstage) {
-            if (s + 2 < nstage) wait_vmcnt<CW>();
-            else wait_vmcnt<0>();
-            __syncthreads();
-            read_ops(opa, s + 1, 0);
-        }
-        mma_all(opb);
-    }
-    if constexpr (NA > 4) asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");  // the last matrix instructions' results are in
-    if constexpr (MODE == MODE_SCORE) {
-        // (the lane's number formed anew: kept through the loop it is a register too many)
-        const int lane1 = (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
-        score_tile<NA, 4>(p, acc, tm * BM + wm * 128, tn * BN + wn * 32 * NA, tn * 2 + wn, lane1);
-    } else store_tile<MODE, NA, 4>(p, bias8, acc, tm * BM + wm * 128, tn * BN + wn * 32 * NA, ks, cur_len, lane);
 }
 
 // ----------------------------------------------------------------- 256 x 64..192 tiles, and halved ones of up to 256 rows, on a deep ring (few rows)
@@ -869,6 +922,9 @@ static RingPlan ring_plan(int M, int N, int KB, bool fused, size_t capacity_floa
     return best;
 }
 
+// Workgroups of the big kernel: one per CU, each XCD the same number
+static int big_grid(int slots) { return std::min(slots, std::max(8, plan_cus() / 8 * 8)); }
+
 // tile: 1 .. 3 the ring kernel with 64 tile rows, 11 .. 14 halved tiles of 64 (tile - 10) rows (128 columns to a workgroup), 4 / 5 the big tiles.  Columns from split_col on are cut into ksplit k
 // ranges (with one range none are; the ring kernel cuts every tile).
 template <int MODE>
@@ -888,7 +944,7 @@ void launch_tiled(hipStream_t s, const void* Wp, const void* Xhi, int KB, int N,
         return;
     }
     if constexpr (MODE == MODE_SCORE) {
-        const int tiles_n = (N + TN - 1) / TN, tiles_m = (M + BM - 1) / BM, grid = (tiles_n * tiles_m + 7) / 8 * 8;
+        const int tiles_n = (N + TN - 1) / TN, tiles_m = (M + BM - 1) / BM, grid = big_grid((tiles_n * tiles_m + 7) / 8 * 8);
         gemm_tiled256_kernel<MODE, 4><<<grid, 256, 0, s>>>(W, X, bias8, KB, NT32, MT32, tiles_n, tiles_m, 1, tiles_n, p);
     } else if constexpr (MODE != MODE_LMHEAD) {
         if (tile > 10) {
@@ -903,7 +959,7 @@ void launch_tiled(hipStream_t s, const void* Wp, const void* Xhi, int KB, int N,
         const int bn = 64 * tile, tiles_n = (N + bn - 1) / bn, tiles_m = (M + BM - 1) / BM;
         const int split_tn = ksplit > 1 ? split_col / bn : tiles_n;  // without a k-split every tile is whole
         const int whole = split_tn * tiles_m, cutn = (tiles_n - split_tn) * tiles_m * ksplit;
-        const int grid = (whole + 7) / 8 * 8 + (cutn + 7) / 8 * 8;
+        const int grid = big_grid((whole + 7) / 8 * 8 + (cutn + 7) / 8 * 8);
         if (tile == 5) gemm_tiled256_kernel<MODE, 5><<<grid, 256, 0, s>>>(W, X, bias8, KB, NT32, MT32, tiles_n, tiles_m, ksplit, split_tn, p);
         else gemm_tiled256_kernel<MODE, 4><<<grid, 256, 0, s>>>(W, X, bias8, KB, NT32, MT32, tiles_n, tiles_m, ksplit, split_tn, p);
     }
