@@ -67,9 +67,11 @@ __device__ __forceinline__ size_t block_slot(int r, int k0, int KB) {
 }
 
 // 16 bytes per lane, global memory -> LDS with no staging registers: lane i's bytes land at lds_block + 16*i
+// (NT: non-temporal, for what is read once or by few at a time)
+template <bool NT = false>
 __device__ __forceinline__ void load_block_to_lds(const u32x4* gsrc_lane, u32x4* lds_block) {
     __builtin_amdgcn_global_load_lds((const void __attribute__((address_space(1)))*)gsrc_lane,
-                                     (void __attribute__((address_space(3)))*)lds_block, 16, 0, 0);
+                                     (void __attribute__((address_space(3)))*)lds_block, 16, 0, NT ? 2 : 0);
 }
 
 // s_waitcnt vmcnt(N) only (gfx9 encoding: vmcnt in bits 3:0 and 15:14; other counters left at their maxima)

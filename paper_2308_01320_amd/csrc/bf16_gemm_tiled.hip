@@ -629,7 +629,8 @@ __device__ __forceinline__ void wait_vmcnt_lgkm0() {
     __builtin_amdgcn_s_waitcnt((N & 0xF) | ((N >> 4) << 14) | (0x7 << 4));
 }
 
-template <int MODE, int NW, int MW>
+// STREAM: the weights' copies are non-temporal
+template <int MODE, int NW, int MW, bool STREAM>
 __global__ __launch_bounds__(256, 1) void gemm_ring_kernel(const u32x4* __restrict__ Wp, const u32x4* __restrict__ X,
                                                            const u32x4* __restrict__ bias8, int KB, int NT32, int MT32,
                                                            int tiles_n, int tiles_m, int ksplit, Epi p) {
@@ -666,15 +667,21 @@ __global__ __launch_bounds__(256, 1) void gemm_ring_kernel(const u32x4* __restri
     const int nst_all = KB / 2;  // KB is even (K % 32 == 0)
     const int st0 = (int)((long)ks * nst_all / ksplit);
     const int nstage = (int)((long)(ks + 1) * nst_all / ksplit) - st0;
+    // a wavefront's copies of a stage: NW blocks of W, then MW of X
+    auto block_of = [&](int q) { return q < NW ? wave * NW + q : XOFF + wave * MW + q - NW; };
     const u32x4* src[CW];  // row-tiles past the matrix: the last one (computed, never stored)
 #pragma unroll
     for (int q = 0; q < CW; ++q) {
-        const int c = wave * CW + q;
-        const bool isw = c < XOFF;
+        const bool isw = q < NW;
+        const int c = block_of(q);
         const int rt = isw ? min(tn * 2 * NW + (c >> 1), NT32 - 1) : min(tm * 2 * MW + ((c - XOFF) >> 1), MT32 - 1);
         src[q] = (isw ? Wp : X) + ((size_t)rt * KB + (size_t)st0 * 2 + (c & 1)) * 64 + lane;
     }
-    auto copy1 = [&](int st, int slot, int q) { load_block_to_lds(src[q] + (size_t)st * 128, &ring[slot][wave * CW + q][0]); };
+    auto copy1 = [&](int st, int slot, int q) {
+        u32x4* dst = &ring[slot][block_of(q)][0];
+        if (STREAM && q < NW) load_block_to_lds<true>(src[q] + (size_t)st * 128, dst);
+        else load_block_to_lds(src[q] + (size_t)st * 128, dst);
+    };
     struct Ops { u32x4 a[NW], b[MW]; };
     // LDS read q of a k-block, in the order the matrix instructions first need the operands: a0, b0 .., a1 ..
     auto read1 = [&](Ops& o, int slot, int j, int q) {
@@ -925,6 +932,18 @@ static RingPlan ring_plan(int M, int N, int KB, bool fused, size_t capacity_floa
 // Workgroups of the big kernel: one per CU, each XCD the same number
 static int big_grid(int slots) { return std::min(slots, std::max(8, plan_cus() / 8 * 8)); }
 
+// The weights' copies of the ring kernel are non-temporal where one row of tiles reads them, or, of halved tiles with whole sums, several do.
+// A copy of what comes from HBM then moves 6.6 - 7.1 TB/s on 256 CUs instead of 5.8, and the activations stay in L2.  Per launch inside the
+// engine (hidden 768 .. 7168, 40 .. 3000 rows): one row of tiles 1.02 - 1.18 times as fast (5120 x 20480 and 96 rows 43.6 -> 39.8 us, 7168 x
+// 28672 90.5 -> 76.7), several on halved tiles 1.03 - 1.21 at hidden 1024 (3072 x 1024 and 250 rows) and 4096 and 0.94 - 1.04 where they fill the chip; but
+// with k ranges 0.77 - 1.05 (1024 x 4096 and 100 rows in ten ranges 7.2 -> 9.2 us) and on 256 columns 0.93 - 1.03.
+template <int MODE, int NW, int MW>
+static void launch_ring(hipStream_t s, int grid, const u32x4* W, const u32x4* X, const u32x4* bias8, int KB, int NT32, int MT32, int tiles_n, int tiles_m,
+                        int ksplit, const Epi& p) {
+    if (tiles_m == 1 || (NW == 2 && ksplit == 1)) gemm_ring_kernel<MODE, NW, MW, true><<<grid, 256, 0, s>>>(W, X, bias8, KB, NT32, MT32, tiles_n, tiles_m, ksplit, p);
+    else gemm_ring_kernel<MODE, NW, MW, false><<<grid, 256, 0, s>>>(W, X, bias8, KB, NT32, MT32, tiles_n, tiles_m, ksplit, p);
+}
+
 // tile: 1 .. 3 the ring kernel with 64 tile rows, 11 .. 14 halved tiles of 64 (tile - 10) rows (128 columns to a workgroup), 4 / 5 the big tiles.  Columns from split_col on are cut into ksplit k
 // ranges (with one range none are; the ring kernel cuts every tile).
 template <int MODE>
@@ -937,10 +956,10 @@ void launch_tiled(hipStream_t s, const void* Wp, const void* Xhi, int KB, int N,
     if (tile < 4) {
         const int tiles_n = (N + 255) / 256, tiles_m = (M + 64 * tile - 1) / (64 * tile);
         const int grid = (tiles_n * tiles_m * ksplit + 7) / 8 * 8;
-        if (tile == 1) gemm_ring_kernel<MODE, 4, 1><<<grid, 256, 0, s>>>(W, X, bias8, KB, NT32, MT32, tiles_n, tiles_m, ksplit, p);
+        if (tile == 1) launch_ring<MODE, 4, 1>(s, grid, W, X, bias8, KB, NT32, MT32, tiles_n, tiles_m, ksplit, p);
         else if (MODE == MODE_SCORE || tile == 2)  // (score_tile knows no 192-row tile)
-            gemm_ring_kernel<MODE, 4, 2><<<grid, 256, 0, s>>>(W, X, bias8, KB, NT32, MT32, tiles_n, tiles_m, ksplit, p);
-        else gemm_ring_kernel<MODE, 4, MODE == MODE_SCORE ? 2 : 3><<<grid, 256, 0, s>>>(W, X, bias8, KB, NT32, MT32, tiles_n, tiles_m, ksplit, p);
+            launch_ring<MODE, 4, 2>(s, grid, W, X, bias8, KB, NT32, MT32, tiles_n, tiles_m, ksplit, p);
+        else launch_ring<MODE, 4, MODE == MODE_SCORE ? 2 : 3>(s, grid, W, X, bias8, KB, NT32, MT32, tiles_n, tiles_m, ksplit, p);
         return;
     }
     if constexpr (MODE == MODE_SCORE) {
@@ -950,10 +969,10 @@ void launch_tiled(hipStream_t s, const void* Wp, const void* Xhi, int KB, int N,
         if (tile > 10) {
             const int tiles_n = (N + 127) / 128, tiles_m = (M + 64 * (tile - 10) - 1) / (64 * (tile - 10));
             const int grid = (tiles_n * tiles_m * ksplit + 7) / 8 * 8;
-            if (tile == 11) gemm_ring_kernel<MODE, 2, 1><<<grid, 256, 0, s>>>(W, X, bias8, KB, NT32, MT32, tiles_n, tiles_m, ksplit, p);
-            else if (tile == 12) gemm_ring_kernel<MODE, 2, 2><<<grid, 256, 0, s>>>(W, X, bias8, KB, NT32, MT32, tiles_n, tiles_m, ksplit, p);
-            else if (tile == 13) gemm_ring_kernel<MODE, 2, 3><<<grid, 256, 0, s>>>(W, X, bias8, KB, NT32, MT32, tiles_n, tiles_m, ksplit, p);
-            else gemm_ring_kernel<MODE, 2, 4><<<grid, 256, 0, s>>>(W, X, bias8, KB, NT32, MT32, tiles_n, tiles_m, ksplit, p);
+            if (tile == 11) launch_ring<MODE, 2, 1>(s, grid, W, X, bias8, KB, NT32, MT32, tiles_n, tiles_m, ksplit, p);
+            else if (tile == 12) launch_ring<MODE, 2, 2>(s, grid, W, X, bias8, KB, NT32, MT32, tiles_n, tiles_m, ksplit, p);
+            else if (tile == 13) launch_ring<MODE, 2, 3>(s, grid, W, X, bias8, KB, NT32, MT32, tiles_n, tiles_m, ksplit, p);
+            else launch_ring<MODE, 2, 4>(s, grid, W, X, bias8, KB, NT32, MT32, tiles_n, tiles_m, ksplit, p);
             return;
         }
         const int bn = 64 * tile, tiles_n = (N + bn - 1) / bn, tiles_m = (M + BM - 1) / BM;

@@ -1,0 +1,27 @@
+"""Prompt passes on the ring kernel whose weights one row of tiles reads (non-temporal copies), and several do, on 128 and 256 columns,
+against the oracle."""
+import numpy as np
+import pytest
+
+from oracle import opt_oracle as O
+from paper_2308_01320_amd import binding, synth
+from tests import util
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("H,nh,F", [(768, 12, 3072), (1024, 16, 4096)])
+@pytest.mark.parametrize("S", [33, 64, 65, 127, 129, 257])
+def test_one_row_of_tiles_and_more(H, nh, F, S):
+    import torch
+    d = synth.ModelDims("x", 1, H, nh, F, 300, S + 1, 1, S, 1, "bf16", "greedy")
+    w = synth.make_weights(d, seed=13)
+    eng = binding.Engine(binding.make_config(d), binding.upload_weights(w, "bf16"))
+    ids = np.random.default_rng(S).integers(0, d.vocab, (1, S)).astype(np.int32)
+    scores = eng.he_score(torch.from_numpy(ids).cuda()).cpu().numpy()
+    last = eng.he_prefill(torch.from_numpy(ids).cuda(), binding.sampling("greedy"), True)[2].cpu().numpy()
+    eng.he_destroy()
+    z = O.forward_full(util.weights_f64(w), ids, nh, eps=d.ln_eps)[0]
+    want = O.log_softmax(z[:S - 1])[np.arange(S - 1), ids[0, 1:]]
+    assert float(np.abs(last[0] - z[S - 1]).max()) <= 2e-2  # (the other bfloat16 passes' bound)
+    assert float(np.abs(scores[0] - want).max()) <= 2e-2
