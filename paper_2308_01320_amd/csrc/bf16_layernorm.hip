@@ -69,11 +69,27 @@ __global__ __launch_bounds__(1024) void ln_blocks_kernel(float* __restrict__ r, 
     }
 }
 
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+template <bool ONCE>
+__device__ __forceinline__ float4 load4(const float* p) {
+    const f32x4* q = reinterpret_cast<const f32x4*>(p);
+    const f32x4 v = ONCE ? __builtin_nontemporal_load(q) : *q;
+    return make_float4(v.x, v.y, v.z, v.w);
+}
+template <bool ONCE>
+__device__ __forceinline__ void store4(float* p, const float4& a) {
+    const f32x4 v = {a.x, a.y, a.z, a.w};
+    if (ONCE) __builtin_nontemporal_store(v, reinterpret_cast<f32x4*>(p));
+    else *reinterpret_cast<f32x4*>(p) = v;
+}
+
 // The same operation with every value of the row held in registers (NV float4 per thread) and all
 // loads -- residual, k-split partials, bias, gamma, beta -- issued before the first reduction.
 // For the few rows of a decode step one 1024-thread workgroup per row (the kernel's time is then the
 // length of its dependent-load chain); for the many rows of a prompt pass 256 threads per row.
-template <int NV, int THREADS>
+// ONCE: the residual and the partial sums are loaded and stored non-temporally, so that the caches keep the blocks written here for the
+// GEMM that reads them.
+template <int NV, int THREADS, bool ONCE>
 __global__ __launch_bounds__(THREADS) void ln_row_kernel(float* __restrict__ r, const float* __restrict__ part, int ksplit,
                                                       size_t part_split, const bf16_t* __restrict__ pbias,
                                                       const bf16_t* __restrict__ gamma,
@@ -103,7 +119,7 @@ __global__ __launch_bounds__(THREADS) void ln_row_kernel(float* __restrict__ r, 
         v[j] = make_float4(0.f, 0.f, 0.f, 0.f);
         gg[j] = bb[j] = make_uint2(0, 0);
         if (i < nq) {
-            v[j] = *reinterpret_cast<const float4*>(r + src * H + 4 * i);
+            v[j] = load4<ONCE>(r + src * H + 4 * i);
             gg[j] = *reinterpret_cast<const uint2*>(gamma + 4 * i);
             bb[j] = *reinterpret_cast<const uint2*>(beta + 4 * i);
         }
@@ -117,9 +133,9 @@ __global__ __launch_bounds__(THREADS) void ln_row_kernel(float* __restrict__ r, 
             y0[j] = y1[j] = make_float4(0.f, 0.f, 0.f, 0.f);
             pb[j] = make_uint2(0, 0);
             if (i >= nq) continue;
-            y0[j] = *reinterpret_cast<const float4*>(part + src * H + 4 * i);
+            y0[j] = load4<ONCE>(part + src * H + 4 * i);
             // (columns before split_col have one whole sum; a multiple of 256 or 320)
-            if (ksplit == 2 && 4 * i >= split_col) y1[j] = *reinterpret_cast<const float4*>(part + part_split + src * H + 4 * i);
+            if (ksplit == 2 && 4 * i >= split_col) y1[j] = load4<ONCE>(part + part_split + src * H + 4 * i);
             pb[j] = *reinterpret_cast<const uint2*>(pbias + 4 * i);
         }
 #pragma unroll
@@ -130,7 +146,7 @@ __global__ __launch_bounds__(THREADS) void ln_row_kernel(float* __restrict__ r, 
             v[j].y += (y0[j].y + y1[j].y) + bf_hi(pb[j].x);
             v[j].z += (y0[j].z + y1[j].z) + bf_lo(pb[j].y);
             v[j].w += (y0[j].w + y1[j].w) + bf_hi(pb[j].y);
-            if (writeback) *reinterpret_cast<float4*>(r + src * H + 4 * i) = v[j];
+            if (writeback) store4<ONCE>(r + src * H + 4 * i, v[j]);
         }
     } else if (part) {
 #pragma unroll
@@ -296,10 +312,19 @@ void bf16_ln(hipStream_t s, float* r, const float* part, int ksplit, size_t part
              int writeback, int split_col) {
     if (ksplit != 2) split_col = 0;  // (only the two-range form knows partly cut rows)
     const int nv = (H / 4 + 1023) / 1024, nv256 = (H / 4 + 255) / 256;
-#define HE_LN_ROW(NV, T)                                                                                                \
-    ln_row_kernel<NV, T><<<(T == 256 ? (rows + 255) / 256 * 256 : rows), T, 0, s>>>(                                    \
+#define HE_LN_ROW_AS(NV, T, ONCE)                                                                                       \
+    ln_row_kernel<NV, T, ONCE><<<(T == 256 ? (rows + 255) / 256 * 256 : rows), T, 0, s>>>(                              \
         r, part, ksplit, part_split, (const bf16_t*)pbias, (const bf16_t*)gamma, (const bf16_t*)beta, (u32x4*)a_blocks, \
         H, eps, in_mul, in_add, writeback, rows, split_col)
+#define HE_LN_ROW(NV, T)                                                                                                \
+    do {                                                                                                                \
+        if (T == 256 && once) HE_LN_ROW_AS(NV, T, (T == 256));                                                          \
+        else HE_LN_ROW_AS(NV, T, false);                                                                                \
+    } while (0)
+    // From 96 MB of residual on nothing of it is left in the 256 MiB cache in front of memory by the time it is read again.  A pass of prompt
+    // rows, plain -> non-temporal: 9600 x 5120 6754 -> 6664 us, 6000 x 5120 4399 -> 4368, 9600 x 4096 8026 -> 7982, 6000 x 7168 1837 -> 1825;
+    // with less 9600 x 2048 5728 -> 5732, 3000 x 2048 1979 -> 2030, 9600 x 1024 5304 -> 5504.
+    const bool once = (size_t)rows * H >= 24000000;
     if (rows <= 256 && nv <= 3) {  // a decode step
         if (nv == 1) HE_LN_ROW(1, 1024);
         else if (nv == 2) HE_LN_ROW(2, 1024);
@@ -322,6 +347,7 @@ void bf16_ln(hipStream_t s, float* r, const float* part, int ksplit, size_t part
         return;
     }
 #undef HE_LN_ROW
+#undef HE_LN_ROW_AS
     ln_blocks_kernel<<<rows, 256, (size_t)H * sizeof(float), s>>>(
         r, part, ksplit, part_split, (const bf16_t*)pbias, (const bf16_t*)gamma, (const bf16_t*)beta, (u32x4*)a_blocks,
         H, eps, in_mul, in_add, writeback, split_col);

@@ -36,7 +36,9 @@ __device__ __forceinline__ uint32_t pack2_bf16(float lo, float hi) { return f32x
 // each block.  us, back to back, a kernel that tiles or merges on the vector units, then one that reads the tiles again for the
 // vectors -> this: 16384 x 4096 with vectors 70.5 -> 50.2 (5.4 TB/s), 50272 x 4096 225 -> 144, with an adapter of rank 16 as well 85 -> 68,
 // of rank 17 99 -> 86; without vectors, plain 52.6 -> 47.3, rank 16 (4096 x 16384) 61.4 -> 55, rank 64 157 -> 114.  (Workgroups of 32 rows
-// and all of k, no partial sums: 16384 x 4096 60.5, rank 16 66.)
+// and all of k, no partial sums: 16384 x 4096 60.5, rank 16 66.)  The tiles are stored non-temporally: four layers of hidden 4096 with adapters
+// and the head 1248 -> 1216 us, twelve of hidden 2048 650 -> 616, and with a decode step behind it 1061 -> 1025; the sources must not be loaded so (1248
+// -> 1434: four loads share a cache line).
 typedef float f32x32 __attribute__((ext_vector_type(32)));
 constexpr int kMergeBlocks = 4;                               // blocks of 16 columns to a wavefront: two accumulator tiles
 constexpr int kMergeWaves = 8;
@@ -154,7 +156,7 @@ __global__ __launch_bounds__(64 * kMergeWaves) void tile_merge_kernel(const bf16
         if constexpr (!TILED) {
             h = bf16x8_to_half(h);  // ... held as a half like every other weight; rows past the matrix are zeros
             if (r >= R) h = u32x4{0u, 0u, 0u, 0u};
-            out[u * 64] = h;
+            __builtin_nontemporal_store(h, out + u * 64);
         }
         if constexpr (FOLD) {
             const u32x4 g = vec[0][(wave * U + u) * 2 + half], b = vec[1][(wave * U + u) * 2 + half];

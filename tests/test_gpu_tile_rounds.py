@@ -1,5 +1,6 @@
 """Prompt passes whose GEMMs have more 256-row tiles than workgroups, each workgroup taking several: slots that hold no tile, a last round
-that not every workgroup has, and k ranges behind whole tiles, against the oracle."""
+that not every workgroup has, and k ranges behind whole tiles; the LayerNorms' two forms (of 96 MB of residual on, and below).  Against the
+oracle."""
 import numpy as np
 import pytest
 
