@@ -25,3 +25,19 @@ def test_one_row_of_tiles_and_more(H, nh, F, S):
     want = O.log_softmax(z[:S - 1])[np.arange(S - 1), ids[0, 1:]]
     assert float(np.abs(last[0] - z[S - 1]).max()) <= 2e-2  # (the other bfloat16 passes' bound)
     assert float(np.abs(scores[0] - want).max()) <= 2e-2
+
+
+@pytest.mark.parametrize("S", [193, 256])
+def test_one_row_of_256(S):
+    import torch
+    d = synth.ModelDims("x", 1, 4096, 32, 16384, 300, S + 1, 1, S, 1, "bf16", "greedy")
+    w = synth.make_weights(d, seed=17)
+    cfg = binding.make_config(d)
+    p = binding.he_plan_pass_gemm(cfg, S, "fc2")
+    assert (p.tile_rows, p.workgroup_cols, p.ksplit) == (256, 128, 8)
+    eng = binding.Engine(cfg, binding.upload_weights(w, "bf16"))
+    ids = np.random.default_rng(S).integers(0, d.vocab, (1, S)).astype(np.int32)
+    last = eng.he_prefill(torch.from_numpy(ids).cuda(), binding.sampling("greedy"), True)[2].cpu().numpy()
+    eng.he_destroy()
+    z = O.forward_full(util.weights_f64(w), ids, d.n_heads, eps=d.ln_eps)[0]
+    assert float(np.abs(last[0] - z[S - 1]).max()) <= 2e-2
