@@ -154,12 +154,43 @@ __global__ __launch_bounds__(64 * WAVES) void attn_kernel(const float* __restric
 // 1 x 32 heads of 64, 516 keys 8.3 -> 6.9, 130 keys 5.0 -> 3.9; 7 x 32 heads of 128, 180 keys 8.5 -> 7.0; 2 x 40 of 128, 1999 keys
 // 26.9 -> 24.5; 16 x 32 of 64, 56 keys 5.6 -> 4.6; 32 x 32 of 64, 64 keys 7.5 -> 5.9; 96 x 40 of 128, 80 keys 31.0 -> 29.0; but 32 x 40
 // of 128: 160 keys 19.6 -> 19.4, 384 keys 39.6 -> 41.2.  (The line between the two: decode_attn_plan below.)
+//
+// Behind the pairs' workgroups come those that fetch the out-projection's weights meanwhile (bf16_ahead): memory has little to do here, the
+// L2 caches keep what is read from one launch to the next, and workgroup j of every launch runs on XCD j mod 8.  A step, us, without ->
+// with: 16 x 32 heads of 64, 56 keys, hidden 2048 (attention 5.0 -> 5.2, the out-projection 5.2 -> 4.1) 230.3 -> 224.4; one row, 516 keys
+// 505.9 -> 501.7.  A cache that may hold more than 32 MiB is a stream of its own that this is in the way of: 16 x 32, 400 keys 268 -> 278.
+template <int THREADS>
+__device__ __forceinline__ void fetch_ahead(const bf16_ahead& a, int j) {
+    const int grp = j / a.ks, p0 = (j - grp * a.ks) * a.waves, p1 = p0 + a.waves;
+    const int k0 = p0 * a.kbase + min(p0, a.kmore), n = p1 * a.kbase + min(p1, a.kmore) - k0;  // steps of its k range
+    const int lines = a.units * n * 8;  // of 128 bytes, one to a lane
+    uint32_t got = 0;
+    for (int l0 = threadIdx.x; l0 < lines; l0 += 4 * THREADS) {
+        uint32_t v[4];
+#pragma unroll
+        for (int x = 0; x < 4; ++x) {
+            const int l = min(l0 + x * THREADS, lines - 1), q = l & 7, i = l >> 3, t = i / n, step = k0 + i - t * n;
+            const int g = min(grp * a.units + t, a.n_units - 1);
+            const size_t at = a.w8 ? ((size_t)g * (a.kb / 4) + step) * 1024 + q * 128
+                                   : (size_t)(g >> 1) * a.kb * 1024 + (size_t)step * 2048 + (q >> 1) * 512 + (g & 1) * 256 + (q & 1) * 128;
+            v[x] = *reinterpret_cast<const uint32_t*>((const char*)a.w + at);
+        }
+        got ^= (v[0] ^ v[1]) ^ (v[2] ^ v[3]);
+    }
+    asm volatile("" ::"v"(got));  // (all that matters is where the lines are now)
+}
+
 template <int D, int WAVES>
 __global__ __launch_bounds__(64 * WAVES) void attn_few_kernel(const float* __restrict__ q, const half_t* __restrict__ kv,
                                                        u32x4* __restrict__ o, const he_dev_state* __restrict__ st, int S, int layer,
-                                                       int H, int n_heads, int max_batch, int max_seq) {
+                                                       int H, int n_heads, int max_batch, int max_seq, bf16_ahead ahead) {
     constexpr int LPK = D / 8, KPW = 64 / LPK, KR = WAVES * KPW, U = 4, STEP = KR * U;
     static_assert(D <= 64 * WAVES, "an output value per thread");
+    if ((int)blockIdx.y >= n_heads) {  // (whole rows of the grid: the last workgroups of them have nothing to fetch)
+        const int j = (int)(blockIdx.y * gridDim.x + blockIdx.x) - (n_heads * (int)gridDim.x + 7) / 8 * 8;
+        if (j >= 0 && j < ahead.wgs) fetch_ahead<64 * WAVES>(ahead, j);
+        return;
+    }
     __shared__ float2 ml[WAVES];          // a wavefront's largest score and sum
     __shared__ float ored[WAVES][D];      // ... and its weighted values
     const int m = blockIdx.x, h = blockIdx.y;
@@ -832,8 +863,8 @@ static AttnPlan decode_attn_plan(long pairs, int max_seq, int d) {
 
 template <int D>
 static void launch_attn(hipStream_t s, const float* q, const void* kv, void* o_blocks, const he_dev_state* st, int M, int S, int layer,
-                        int H, int n_heads, int max_batch, int max_seq, AttnPlan g) {
-    const dim3 grid(M, n_heads);
+                        int H, int n_heads, int max_batch, int max_seq, AttnPlan g, const bf16_ahead* ahead) {
+    dim3 grid(M, n_heads);
     const half_t* c = (const half_t*)kv;
     u32x4* o = (u32x4*)o_blocks;
     if (g.form == HE_ATTN_TWO_PASSES) {
@@ -842,10 +873,13 @@ static void launch_attn(hipStream_t s, const float* q, const void* kv, void* o_b
         else attn_kernel<D, 4><<<grid, 256, shm, s>>>(q, c, o, st, S, layer, H, n_heads, max_batch, max_seq);
         return;
     }
+    bf16_ahead after;
+    if (ahead && (size_t)M * n_heads * max_seq * D * 4 <= (size_t)32 << 20) after = *ahead;
+    if (after.wgs) grid.y += (after.wgs + 7 + M - 1) / M;
     switch (g.waves) {
-        case 8: attn_few_kernel<D, 8><<<grid, 512, 0, s>>>(q, c, o, st, S, layer, H, n_heads, max_batch, max_seq); break;
-        case 4: attn_few_kernel<D, 4><<<grid, 256, 0, s>>>(q, c, o, st, S, layer, H, n_heads, max_batch, max_seq); break;
-        default: attn_few_kernel<D, 2><<<grid, 128, 0, s>>>(q, c, o, st, S, layer, H, n_heads, max_batch, max_seq);
+        case 8: attn_few_kernel<D, 8><<<grid, 512, 0, s>>>(q, c, o, st, S, layer, H, n_heads, max_batch, max_seq, after); break;
+        case 4: attn_few_kernel<D, 4><<<grid, 256, 0, s>>>(q, c, o, st, S, layer, H, n_heads, max_batch, max_seq, after); break;
+        default: attn_few_kernel<D, 2><<<grid, 128, 0, s>>>(q, c, o, st, S, layer, H, n_heads, max_batch, max_seq, after);
     }
 }
 
@@ -879,7 +913,8 @@ void bf16_attn_plan_query(int M, int S, int n_heads, int d, int max_seq, int cus
     *waves = g.waves;
 }
 
-void bf16_attn(hipStream_t s, const float* q, const void* kv, void* o_blocks, const he_dev_state* st, int M, int S, int layer, int H, int n_heads, int max_batch, int max_seq) {
+void bf16_attn(hipStream_t s, const float* q, const void* kv, void* o_blocks, const he_dev_state* st, int M, int S, int layer, int H, int n_heads, int max_batch, int max_seq,
+               const bf16_ahead* ahead) {
     const half_t* c = (const half_t*)kv;
     u32x4* o = (u32x4*)o_blocks;
     const int d = H / n_heads, batch = M / S;
@@ -899,7 +934,7 @@ void bf16_attn(hipStream_t s, const float* q, const void* kv, void* o_blocks, co
         if (d == 128) attn_prompt_kernel<128><<<grid, 256, shm, s>>>(q, c, o, st, S, layer, H, n_heads, max_batch, max_seq);
         else attn_prompt_kernel<64><<<grid, 256, shm, s>>>(q, c, o, st, S, layer, H, n_heads, max_batch, max_seq);
     } else {
-        if (d == 128) launch_attn<128>(s, q, kv, o_blocks, st, M, S, layer, H, n_heads, max_batch, max_seq, g);
-        else launch_attn<64>(s, q, kv, o_blocks, st, M, S, layer, H, n_heads, max_batch, max_seq, g);
+        if (d == 128) launch_attn<128>(s, q, kv, o_blocks, st, M, S, layer, H, n_heads, max_batch, max_seq, g, ahead);
+        else launch_attn<64>(s, q, kv, o_blocks, st, M, S, layer, H, n_heads, max_batch, max_seq, g, ahead);
     }
 }

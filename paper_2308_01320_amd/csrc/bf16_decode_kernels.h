@@ -9,6 +9,7 @@ namespace he_bf16 {
 // their choice of kernel variant and grid as usual, then record what that launch would index instead of launching it.
 struct StoreFootprint { size_t scratch_floats; int cells; int stat_groups; int ksplit; };
 inline thread_local StoreFootprint* g_dry = nullptr;
+inline thread_local bf16_ahead* g_dry_ahead = nullptr;  // the same for who reads which weights
 }  // namespace he_bf16
 using namespace he_bf16;
 
@@ -851,7 +852,13 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_half_kernel(const u32x4* __re
 }
 
 // grid: the launch's (k range, column group, row slices); items, waves: of the kernel variant chosen.  True if the launch is to be left out.
-inline bool dry_run(const dim3& grid, int ksplit, int items, int waves) {
+inline bool dry_run(const dim3& grid, int ksplit, int items, int waves, int units, int steps) {
+    if (bf16_ahead* a = g_dry_ahead) {
+        a->wgs = grid.x * grid.y;
+        a->ks = ksplit; a->units = units; a->waves = waves;
+        a->kbase = steps / (ksplit * waves); a->kmore = steps % (ksplit * waves);
+        return true;
+    }
     if (!g_dry) return false;
     g_dry->cells = grid.y * grid.z;
     g_dry->stat_groups = grid.y;
@@ -876,7 +883,7 @@ void launch_half_ht(hipStream_t s, const void* Wp, const void* Xhi, int KB, int 
             constexpr int U2 = !W8 && HT <= 6 ? 2 : 1;
             constexpr size_t kWant2 = 84 * 1024;
             grid.z = 1;
-            if (dry_run(grid, ksplit, items_per_wave(HT * (p.M <= 48 ? 3 : 4), 4), 4)) return;
+            if (dry_run(grid, ksplit, items_per_wave(HT * (p.M <= 48 ? 3 : 4), 4), 4, HT, steps)) return;
             if (p.M <= 48) {  // the last 16 of the 64 rows are not in use
                 constexpr size_t kStatic = (size_t)4 * HT * 3 * 4 * 64 * sizeof(float);
                 const size_t pad = kStatic >= kWant2 ? 0 : kWant2 - kStatic;
@@ -901,7 +908,7 @@ void launch_half_ht(hipStream_t s, const void* Wp, const void* Xhi, int KB, int 
     const bool eight = HT <= eight_most && (KB / (2 * KU)) / (ksplit * 8) >= 2 * U8;  // short chains per wavefront, as above
     constexpr size_t kWant = 84 * 1024;                                      // one workgroup per CU
     if (m_tiles == 1 && p.M <= 16) {  // the second half of the 32 activation rows is not in use: leave it out
-        if (dry_run(grid, ksplit, items_per_wave(HT, eight ? 8 : 4), eight ? 8 : 4)) return;
+        if (dry_run(grid, ksplit, items_per_wave(HT, eight ? 8 : 4), eight ? 8 : 4, HT, steps)) return;
         if (eight) {
             constexpr size_t kStatic = (size_t)8 * HT * 4 * 64 * sizeof(float);
             const size_t pad = kStatic >= kWant ? 0 : kWant - kStatic;
@@ -915,7 +922,7 @@ void launch_half_ht(hipStream_t s, const void* Wp, const void* Xhi, int KB, int 
         }
         return;
     }
-    if (dry_run(grid, ksplit, items_per_wave(HT * 2, eight ? 8 : 4), eight ? 8 : 4)) return;
+    if (dry_run(grid, ksplit, items_per_wave(HT * 2, eight ? 8 : 4), eight ? 8 : 4, HT, steps)) return;
     if (eight) {
         constexpr size_t kStatic = (size_t)8 * HT * 2 * 4 * 64 * sizeof(float);
         const size_t pad = kStatic >= kWant ? 0 : kWant - kStatic;

@@ -372,6 +372,7 @@ void pass_decode_bf16(he_engine* e, const int32_t* d_ids, int id_stride, int B, 
         bf16_embed_ln(s, d_ids, id_stride, e->w.tok_emb, e->w.pos_emb, e->st, B, H, c.vocab, c.pos_offset, gw2,
                       last ? e->w.lnf_g : e->layers[0].ln1_g, e->resid, last ? e->xfblk : e->ablk, e->ln_stats, take_sampling(e));
     }
+    bf16_ahead ahead = bf16_store_ahead(nullptr, B, H, H, e->part_floats, e->w8);
     for (int l = 0; l < L; ++l) {
         const he_layer_weights& lw = e->layers[l];
         const he_engine::Tiled& tw = e->tiled[l];  // bf16 blocks, or E4M3 units with 8-bit weights
@@ -386,7 +387,8 @@ void pass_decode_bf16(he_engine* e, const int32_t* d_ids, int id_stride, int B, 
         }
         {
             LaunchTimer t(e, HE_K_ATTENTION);
-            bf16_attn(s, e->qbuf, e->kv, e->oblk, e->st, B, 1, l, H, c.n_heads, c.max_batch, c.max_seq_len);
+            ahead.w = tw.wo;
+            bf16_attn(s, e->qbuf, e->kv, e->oblk, e->st, B, 1, l, H, c.n_heads, c.max_batch, c.max_seq_len, &ahead);
         }
         a = base;
         store_ln(a, lw.bo, lw.ln2_g, e->ablk);

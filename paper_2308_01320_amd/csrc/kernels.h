@@ -88,6 +88,13 @@ struct bf16_gemm_args {
     // 8-bit weights (bf16_gemm_skinny only): Wp holds E4M3 codes in 16-row units, wscale [N] the row scales 2^e
     const float* wscale = nullptr;
 };
+// The weights of an EPI_STORE_LN launch by the workgroups that read them, for the launch ahead of it to have them fetched into
+// the L2 caches (bf16_attn).  wgs 0: not worth it
+struct bf16_ahead {
+    const void* w = nullptr;
+    int wgs = 0, ks = 1, units = 1, n_units = 0, waves = 8, kbase = 0, kmore = 0, kb = 0, w8 = 0;  // as that kernel is launched
+};
+bf16_ahead bf16_store_ahead(const void* Wp, int M, int N, int K, size_t capacity, bool w8);
 size_t bf16_tiled_bytes(int rows, int K);
 void bf16_tile_rows(hipStream_t s, const void* src, void* dst, int R, int K);
 // dst = tiled bf16(src + scale * B A): A bf16 [rank, K], B bf16 [R, rank]
@@ -173,6 +180,6 @@ void bf16_ln(hipStream_t s, float* r, const float* part, int ksplit, size_t part
              const void* gamma, const void* beta, void* a_blocks, int rows, int H, float eps, int in_mul, int in_add,
              int writeback, int split_col = 0);
 void bf16_attn(hipStream_t s, const float* q, const void* kv, void* o_blocks, const he_dev_state* st, int M, int S,
-               int layer, int H, int n_heads, int max_batch, int max_seq);
+               int layer, int H, int n_heads, int max_batch, int max_seq, const bf16_ahead* ahead = nullptr);
 // host logic: which kernel that launch is (HE_ATTN_ in he.h), wavefronts to a workgroup
 void bf16_attn_plan_query(int M, int S, int n_heads, int d, int max_seq, int cus, int* form, int* waves);
