@@ -83,7 +83,8 @@ __global__ void ln_kernel(const float* __restrict__ r, const ST* __restrict__ ga
 // What bounds it is the length of the dependent chain -- a launch, a load or two, a few matrix instructions -- so the k
 // range is split over the wavefronts of a workgroup (partial sums added in wavefront order through LDS) and the few rows
 // of a decode step go 16 columns to a workgroup.
-//   few rows (at most 64):      gemm_few_kernel: 16 columns x 16 rows per workgroup, LayerNorm of the rows folded in
+//   few rows (at most 64, 256   gemm_few_kernel: 16 columns x 16 rows per workgroup, LayerNorm of the rows folded in
+//   of small matrices):
 //   many tiles (from 256 on):   KW = 1: 64 x 64 per workgroup of four wavefronts
 //   else:                       KW = 8: 32 x 32 per workgroup
 // VEC: K is a multiple of four and the rows are aligned for 16-byte loads (8-byte ones for bf16 storage).
