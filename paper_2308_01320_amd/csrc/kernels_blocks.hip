@@ -3,7 +3,8 @@
 // A step of a small model is nothing but launches: five a layer, 3.3 to 4.4 us each for a microsecond's work.  Here a workgroup
 // takes a whole head of a row (LayerNorm, its queries, keys and values, attention, and the head's share of the out-projection), or
 // 32 columns of the FFN's width (LayerNorm, FC1, and their share of FC2).  The shares are partial sums of the residual rows;
-// whoever reads the rows next adds them up, in order, with the bias: no hand-off inside a launch, none left over.  What the blocks
+// whoever reads the rows next adds them up, in order, with the bias, the row itself last (each of the others rounds at the sums' size, not
+// the row's): no hand-off inside a launch, none left over.  What the blocks
 // pay is work done more than once -- a row's sum and LayerNorm per head or slice, a head's weights per row -- so they are for models
 // a head of which one CU reads in two or three microseconds (plain_blocks_fit).  Weights and cached keys are requested behind the row
 // (loads return in order) and before anything that has to be waited for; sums over lanes are data-parallel moves; the products of an
@@ -59,7 +60,8 @@ __global__ __launch_bounds__(64 * kAttnWaves) void attn_block_kernel(const float
         id = id < 0 ? 0 : (id >= a.V ? a.V - 1 : id);  // out-of-range ids are clamped, never read out of bounds
         if (in) xv = ldv(a.tok + (size_t)id * H + 4 * lane) + ldv(a.pos + (size_t)(len + a.pos_offset) * H + 4 * lane);
     } else if (in) {
-        if (wave == 0) xv = ldv(x + (size_t)m * H + 4 * lane) + ldv(a.pbias + 4 * lane);
+        f32x4 pb = zero;
+        if (wave == 0) { xv = ldv(x + (size_t)m * H + 4 * lane); pb = ldv(a.pbias + 4 * lane); }
         f32x4 p[kMaxSlices / kAttnWaves];
 #pragma unroll
         for (int i = 0; i < kMaxSlices / kAttnWaves; ++i) {
@@ -67,7 +69,8 @@ __global__ __launch_bounds__(64 * kAttnWaves) void attn_block_kernel(const float
             p[i] = s < a.n_part ? ldv(part + ((size_t)s * B + m) * H + 4 * lane) : zero;
         }
 #pragma unroll
-        for (int i = 0; i < kMaxSlices / kAttnWaves; ++i) xv += p[i];
+        for (int i = 0; i < kMaxSlices / kAttnWaves; ++i) pb += p[i];
+        xv += pb;
     }
     if (in) { gv = ldv(a.gamma + 4 * lane); bv = ldv(a.beta + 4 * lane); }
     // weights and cached keys and values
@@ -98,9 +101,10 @@ __global__ __launch_bounds__(64 * kAttnWaves) void attn_block_kernel(const float
     if (!EMBED) {
         *reinterpret_cast<f32x4*>(&red[wave][4 * lane]) = xv;
         __syncthreads();
-        xv = zero;
+        xv = ldv(&red[1][4 * lane]);
 #pragma unroll
-        for (int i = 0; i < kAttnWaves; ++i) xv += ldv(&red[i][4 * lane]);
+        for (int i = 2; i < kAttnWaves; ++i) xv += ldv(&red[i][4 * lane]);
+        xv += ldv(&red[0][4 * lane]);
     }
     if (wave == 0) {
         *reinterpret_cast<f32x4*>(xs + 4 * lane) = norm_row(xv, H, lane, a.eps, gv, bv);  // (zeros past the row)
@@ -228,10 +232,10 @@ __device__ __forceinline__ void block_rows(BlockRows& L, RowRequest<NP>& q, cons
     for (int e = threadIdx.x - second * (kBlockThreads / 2); e < quads; e += kBlockThreads) {
         if (e >= kBlockThreads) request_quad(q, x, part, n, bias, B, H, e, two, second);
         const int m = e / c4, c = 4 * (e - m * c4);
-        f32x4 v = q.x + q.bias;
+        f32x4 v = q.bias;
 #pragma unroll
         for (int i = 0; i < NP; ++i) v += q.part[i];
-        *reinterpret_cast<f32x4*>((second ? L.half : L.xs)[m] + c) = v;
+        *reinterpret_cast<f32x4*>((second ? L.half : L.xs)[m] + c) = q.x + v;
     }
     __syncthreads();
     for (int m = wave; m < B; m += kBlockWaves) {
