@@ -54,7 +54,7 @@ __global__ __launch_bounds__(64 * kAttnWaves) void attn_block_kernel(const float
     const bool in = 4 * lane < H;
     const int len = seq_len(st, m) - row_pad(st, m);  // cached positions
     // the row: embedding, or residual row + bias + the FFN slices' shares
-    f32x4 xv = zero, gv = zero, bv = zero;
+    f32x4 xv = zero, gv = zero, bv = zero, first = zero;
     if (EMBED) {
         int id = a.ids[(size_t)m * a.id_stride];
         id = id < 0 ? 0 : (id >= a.V ? a.V - 1 : id);  // out-of-range ids are clamped, never read out of bounds
@@ -70,7 +70,8 @@ __global__ __launch_bounds__(64 * kAttnWaves) void attn_block_kernel(const float
         }
 #pragma unroll
         for (int i = 0; i < kMaxSlices / kAttnWaves; ++i) pb += p[i];
-        xv += pb;
+        if (wave) xv = pb;
+        else first = pb;
     }
     if (in) { gv = ldv(a.gamma + 4 * lane); bv = ldv(a.beta + 4 * lane); }
     // weights and cached keys and values
@@ -99,12 +100,13 @@ __global__ __launch_bounds__(64 * kAttnWaves) void attn_block_kernel(const float
 #pragma unroll
     for (int i = 0; i < NO; ++i) ow[i] = row0 + ROWS * i < H && dim ? ldv(wo + (size_t)(row0 + ROWS * i) * H + h * d + 4 * l16) : zero;
     if (!EMBED) {
-        *reinterpret_cast<f32x4*>(&red[wave][4 * lane]) = xv;
+        if (wave) *reinterpret_cast<f32x4*>(&red[wave][4 * lane]) = xv;
         __syncthreads();
-        xv = ldv(&red[1][4 * lane]);
+        if (wave == 0) {
 #pragma unroll
-        for (int i = 2; i < kAttnWaves; ++i) xv += ldv(&red[i][4 * lane]);
-        xv += ldv(&red[0][4 * lane]);
+            for (int i = 1; i < kAttnWaves; ++i) first += ldv(&red[i][4 * lane]);
+            xv += first;
+        }
     }
     if (wave == 0) {
         *reinterpret_cast<f32x4*>(xs + 4 * lane) = norm_row(xv, H, lane, a.eps, gv, bv);  // (zeros past the row)
@@ -195,7 +197,7 @@ __global__ __launch_bounds__(64 * kAttnWaves) void attn_block_kernel(const float
 // there are threads for that.  raw: where the rows themselves go (null: nowhere).  What a thread needs of its first quad comes from
 // request_rows, ahead of the weights: loads return in order.
 constexpr int kLdsRow = kMaxWidth + 4;
-struct BlockRows { float xs[kMaxRows][kLdsRow], half[kMaxRows][kLdsRow]; };
+struct BlockRows { float xs[kMaxRows][kLdsRow], half[2][kMaxRows][kLdsRow]; };
 template <int NP> struct RowRequest { f32x4 x, bias, part[NP]; };
 __device__ __forceinline__ bool rows_by_two(int B, int H) { return 2 * B * (H / 4) <= kBlockThreads; }
 template <int NP>
@@ -235,14 +237,15 @@ __device__ __forceinline__ void block_rows(BlockRows& L, RowRequest<NP>& q, cons
         f32x4 v = q.bias;
 #pragma unroll
         for (int i = 0; i < NP; ++i) v += q.part[i];
-        *reinterpret_cast<f32x4*>((second ? L.half : L.xs)[m] + c) = q.x + v;
+        if (two) *reinterpret_cast<f32x4*>(L.half[second][m] + c) = v;
+        if (!second) *reinterpret_cast<f32x4*>(L.xs[m] + c) = two ? q.x : q.x + v;
     }
     __syncthreads();
     for (int m = wave; m < B; m += kBlockWaves) {
         f32x4 v = zero;
         if (4 * lane < H) {
             v = ldv(L.xs[m] + 4 * lane);
-            if (two) v += ldv(L.half[m] + 4 * lane);
+            if (two) v += ldv(L.half[0][m] + 4 * lane) + ldv(L.half[1][m] + 4 * lane);
             if (raw) *reinterpret_cast<f32x4*>(raw + (size_t)m * H + 4 * lane) = v;
         }
         const f32x4 nv = norm_row(v, H, lane, eps, g, b);
