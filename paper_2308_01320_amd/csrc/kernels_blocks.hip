@@ -14,6 +14,7 @@
 // rows 910 -> 695, 16 rows 1022 -> 867; width 192, FFN 768, 16 rows 940 -> 730; width 128, FFN 512, 4 rows 802 -> 608.  A launch here is
 // 5 to 8 us, bound by what one CU reads (260 KB of weights for a head of 64 at width 256) and the chain behind it.  (FFN slices of 64 columns:
 // 8.5 us against 6; attention blocks of four or sixteen wavefronts: 738 and 745 us where eight take 695.)
+// Error against 64 bits, twelve models of width 128 to 256, a launch per matrix -> this: logits 2.45e-7 -> 2.40e-7, log-probabilities 7.7e-8 both.
 #include "he_common.h"
 #include "kernels.h"
 
@@ -273,11 +274,11 @@ __global__ __launch_bounds__(kBlockThreads) void ffn_block_kernel(const float* _
     const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
     RowRequest<kMaxHeads> q;
     request_rows(q, x, part, a.n_part, a.pbias, B, H);
-    // FC1: tiles of 16 columns, KW wavefronts to each, S1 steps of 16 k to a wavefront; FC2: tiles of 16 columns, a wavefront each
+    // FC1: tiles of 16 columns, KW wavefronts to each, every KW-th step of 16 k to a wavefront (S1 at most); FC2: tiles of 16 columns, a wavefront each
     f32x4 wa[S1], wb[T2][S2];
     const float* r1 = w1 + (size_t)(slice * kSlice + tile * 16 + l16) * H + kq;
 #pragma unroll
-    for (int i = 0; i < S1; ++i) wa[i] = 16 * (kw * S1 + i) < H ? ldv(r1 + 16 * (kw * S1 + i)) : zero;
+    for (int i = 0; i < S1; ++i) wa[i] = 16 * (kw + i * KW) < H ? ldv(r1 + 16 * (kw + i * KW)) : zero;
     const f32x4 bias = ldv(b1 + slice * kSlice + tile * 16 + kq);
 #pragma unroll
     for (int t = 0; t < T2; ++t) {
@@ -290,7 +291,7 @@ __global__ __launch_bounds__(kBlockThreads) void ffn_block_kernel(const float* _
     f32x4 acc = zero;
 #pragma unroll
     for (int i = 0; i < S1; ++i)
-        if (16 * (kw * S1 + i) < H) acc = mma4(wa[i], ldv(&L.xs[m][16 * (kw * S1 + i) + kq]), acc);
+        if (16 * (kw + i * KW) < H) acc = mma4(wa[i], ldv(&L.xs[m][16 * (kw + i * KW) + kq]), acc);
     red[kw][tile][lane] = acc;
     __syncthreads();
     if (kw == 0) {
