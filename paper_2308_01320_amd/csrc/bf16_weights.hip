@@ -26,23 +26,25 @@ __device__ __forceinline__ uint32_t pack2_bf16(float lo, float hi) { return f32x
 // per element, for each rank.  scale * t is no such product: it and the addition to W round separately.
 //
 // Where the matrix follows a LayerNorm (FOLD), W gamma and W beta of its rows are formed from the values on their way, or, TILED,
-// from tiles that are there already (the caller's, or dequantised ones), in one order whatever the weights came as: 64 columns
-// of a row to a wavefront -- the two halves of its blocks apart, k ascending, then added --, the eight wavefronts of a workgroup in
-// their order, and the workgroups of a row of tiles, which leave partial sums in `part`, in theirs (vec_sum_kernel).
+// from tiles that are there already (the caller's, or dequantised ones), in one order whatever the weights came as, part of the
+// definition too (a last bit of them can decide how an activation rounds, layers later): a workgroup has 32 rows, its eight wavefronts each
+// a share of k, in blocks of 16 columns; a wavefront adds up the two halves of its blocks apart, k ascending, then the one to the other,
+// and the wavefronts' sums are added in their order.
 //
-// Bound by the memory rate: 32 rows x 512 columns to a workgroup, neighbours next to each other along k, so that the workgroups in
-// flight sweep source and destination in order; gamma and beta of the 512 columns go through LDS (a wavefront's own loads of them cost
-// as much as its weights').  The k side of the products is permuted so that a lane's accumulators are its own eight columns of
-// each block.  us, back to back, a kernel that tiles or merges on the vector units, then one that reads the tiles again for the
-// vectors -> this: 16384 x 4096 with vectors 70.5 -> 50.2 (5.4 TB/s), 50272 x 4096 225 -> 144, with an adapter of rank 16 as well 85 -> 68,
-// of rank 17 99 -> 86; without vectors, plain 52.6 -> 47.3, rank 16 (4096 x 16384) 61.4 -> 55, rank 64 157 -> 114.  (Workgroups of 32 rows
-// and all of k, no partial sums: 16384 x 4096 60.5, rank 16 66.)  The tiles are stored non-temporally: four layers of hidden 4096 with adapters
-// and the head 1248 -> 1216 us, twelve of hidden 2048 650 -> 616, and with a decode step behind it 1061 -> 1025; the sources must not be loaded so (1248
-// -> 1434: four loads share a cache line).
+// Bound by the memory rate.  Without the vectors a workgroup takes 32 rows x 512 columns, neighbours next to each other along k, so that the
+// workgroups in flight sweep source and destination in order.  With them a wavefront goes over its share 64 columns at a time, whose
+// gamma and beta go through LDS (a wavefront's own loads of them cost as much as its weights').  The k side of the products is permuted so
+// that a lane's accumulators are its own eight columns of each block.
+// us a launch with others around it, a kernel that tiles or merges on the vector units, then one that reads the tiles again for the vectors -> this:
+// 16384 x 4096, rank 16 61.7 + 28.9 -> 66, 12288 x 4096 49.2 + 23.9 -> 62 (384 workgroups on 256 CUs), 50272 x 4096 without an adapter 152 + 82 -> 164;
+// without vectors, plain 52.6 -> 47.3, rank 16 (4096 x 16384) 61.4 -> 55, rank 64 157 -> 114.  (Workgroups of 32 rows x 512 columns that leave partial sums
+// for another kernel to add, 67, 54 and 146 us, sum in another order: outputs of whole models moved by 5e-4.  The next 64 columns requested
+// ahead: 68, 63 and 165.)  The tiles are stored non-temporally: four layers of hidden 4096 with adapters and the head 1248 -> 1216 us, twelve of hidden
+// 2048 650 -> 616, and with a decode step behind it 1061 -> 1025; the sources must not be loaded so (1248 -> 1434: four loads share a cache line).
 typedef float f32x32 __attribute__((ext_vector_type(32)));
-constexpr int kMergeBlocks = 4;                               // blocks of 16 columns to a wavefront: two accumulator tiles
+constexpr int kMergeBlocks = 4;                               // blocks of 16 columns at a time: two accumulator tiles
 constexpr int kMergeWaves = 8;
-constexpr int kMergeSpan = kMergeBlocks * kMergeWaves;        // ... to a workgroup
+constexpr int kMergeSpan = kMergeBlocks * kMergeWaves;        // ... to a workgroup without the vectors
 constexpr int kMergeRanks = 32;                               // ranks whose B values are in LDS at a time
 // LORA, how B's rows come: in loads of 16 bytes (rank a multiple of eight, B so aligned); a value at a time, up to eight; through
 // LDS, where the eight wavefronts would each wait for more than eight such loads.  16384 x 4096, rank 17: 81 us a value at a time, 67 through
@@ -52,124 +54,137 @@ template <int LORA, bool FOLD, bool TILED>
 __global__ __launch_bounds__(64 * kMergeWaves) void tile_merge_kernel(const bf16_t* __restrict__ src, u32x4* __restrict__ dst, int R, int K,
                                                                       const bf16_t* __restrict__ A, const bf16_t* __restrict__ B, int rank,
                                                                       float scale, const bf16_t* __restrict__ gamma,
-                                                                      const bf16_t* __restrict__ beta, float* __restrict__ part, size_t part_half, int spans) {
+                                                                      const bf16_t* __restrict__ beta, float* __restrict__ c1, float* __restrict__ c2,
+                                                                      int spans) {
 #pragma clang fp contract(off)  // scale * t and the addition to W round separately, as stated
     constexpr int U = kMergeBlocks;
     static_assert(!TILED || LORA == LORA_NONE, "tiles hold merged weights");
     __shared__ float red[2][kMergeWaves][32];
-    __shared__ u32x4 vec[2][kMergeSpan * 2];  // the span's gamma and beta
+    __shared__ u32x4 vec[kMergeWaves][4 * U];  // a wavefront's gamma, then beta, of the blocks at hand
     __shared__ float bs[LORA == LORA_LDS ? 32 : 1][kMergeRanks + 1];
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, half = lane >> 5;
-    const int tile = blockIdx.x / spans, span = blockIdx.x % spans;
-    const int KB = K >> 4, kb = (span * kMergeWaves + wave) * U, nb = min(U, KB - kb);
+    const int KB = K >> 4, tile = FOLD ? blockIdx.x : blockIdx.x / spans;
+    // the wavefront's blocks (the bounds are the same for all of its lanes; there may be none)
+    const int kb0 = FOLD ? (int)((long)wave * KB / kMergeWaves) : min(((int)(blockIdx.x % spans) * kMergeWaves + wave) * U, KB);
+    const int kb1 = FOLD ? (int)((long)(wave + 1) * KB / kMergeWaves) : min(kb0 + U, KB);
+    const int rounds = FOLD ? ((KB + kMergeWaves - 1) / kMergeWaves + U - 1) / U : 1;  // ... U at a time, the most that any wavefront has
     const int r = tile * 32 + (lane & 31), rr = min(r, R - 1);
-    u32x4* out = dst + ((size_t)tile * KB + kb) * 64 + lane;
-    u32x4 w[U], v8;
-    if (nb > 0) {  // (the same for the whole wavefront; past the matrix: its last block, not used)
+    u32x4* out = dst + (size_t)tile * KB * 64 + lane;
+    struct Round { u32x4 w[U], v; };
+    auto load = [&](Round& q, int kb) {  // (past the share: its last block, not used)
+        if (kb >= kb1) return;
 #pragma unroll
-        for (int u = 0; u < U; ++u)
-            w[u] = TILED ? out[min(u, nb - 1) * 64] : *reinterpret_cast<const u32x4*>(src + (size_t)rr * K + (kb + min(u, nb - 1)) * 16 + 8 * half);
-    }
-    if constexpr (FOLD) {
-        if (wave < 2) v8 = reinterpret_cast<const u32x4*>(wave ? beta : gamma)[min(span * kMergeSpan * 2 + lane, 2 * KB - 1)];
-    }
+        for (int u = 0; u < U; ++u) {
+            const int k = min(kb + u, kb1 - 1);
+            q.w[u] = TILED ? out[(size_t)k * 64] : *reinterpret_cast<const u32x4*>(src + (size_t)rr * K + k * 16 + 8 * half);
+        }
+        if (FOLD) q.v = reinterpret_cast<const u32x4*>(lane & 2 * U ? beta : gamma)[min(2 * kb + (lane & (2 * U - 1)), 2 * kb1 - 1)];
+    };
+    Round cur;
+    load(cur, kb0);
     if constexpr (LORA == LORA_NONE && !FOLD) {  // (all four loads before the first of them is used)
 #pragma unroll
-        for (int u = 0; u < U; ++u) asm volatile("" : "+v"(w[u]));
-    }
-    [[maybe_unused]] f32x32 t = {};
-    if constexpr (LORA != LORA_NONE) {
-        // accumulator 4 q + e of a lane belongs to column 8 q + 4 (lane / 32) + e of the instruction: that is fed column
-        // 16 (q / 2) + 8 (lane / 32) + 4 (q % 2) + e of the matrix
-        const int i = lane & 31, col = 32 * half + 16 * (i >> 4) + 8 * ((i >> 2) & 1) + 4 * ((i >> 3) & 1) + (i & 3);
-        const bf16_t* ap = A + min(kb * 16 + col, K - 1);  // (past the matrix: its last column, not used)
-        const bf16_t* bp = B + (size_t)rr * rank;
-        constexpr int G = 8;                               // ranks whose values are requested together
-        if constexpr (LORA == LORA_LDS) {
-            bf16_t aj[G], an[G];
-            auto load_a = [&](bf16_t (&v)[G], int j0) {
-#pragma unroll
-                for (int x = 0; x < G; ++x) v[x] = ap[(size_t)min(j0 + x, rank - 1) * K];
-            };
-            load_a(aj, 0);
-            for (int j0 = 0; j0 < rank; j0 += kMergeRanks) {
-                const int n = min(kMergeRanks, rank - j0);
-                if (j0) __syncthreads();
-                for (int x = threadIdx.x; x < 32 * kMergeRanks; x += 64 * kMergeWaves) {
-                    const int br = x / kMergeRanks, j = x % kMergeRanks;
-                    if (j < n) bs[br][j] = bf16_to_f32(B[(size_t)min(tile * 32 + br, R - 1) * rank + j0 + j]);
-                }
-                __syncthreads();
-                for (int j = 0; j < n; j += G) {
-                    if (j0 + j + G < rank) load_a(an, j0 + j + G);
-#pragma unroll
-                    for (int x = 0; x < G; ++x) {
-                        if (j + x >= n) break;
-                        t = __builtin_amdgcn_mfma_f32_32x32x1f32(bf16_to_f32(aj[x]), bs[lane & 31][j + x], t, 0, 0, 0);
-                    }
-#pragma unroll
-                    for (int x = 0; x < G; ++x) aj[x] = an[x];
-                }
-            }
-        } else if (nb > 0) {
-            for (int j0 = 0; j0 < rank; j0 += G) {
-                bf16_t aj[G], bj[G];
-                u32x4 b8;
-                if constexpr (LORA == LORA_WIDE) b8 = *reinterpret_cast<const u32x4*>(bp + j0);
-#pragma unroll
-                for (int x = 0; x < G; ++x) {
-                    const int j = min(j0 + x, rank - 1);
-                    aj[x] = ap[(size_t)j * K];
-                    if constexpr (LORA == LORA_FEW) bj[x] = bp[j];
-                }
-                const uint32_t bw[4] = {b8.x, b8.y, b8.z, b8.w};
-#pragma unroll
-                for (int x = 0; x < G; ++x) {
-                    if (LORA == LORA_FEW && j0 + x >= rank) break;
-                    const float bv = LORA == LORA_WIDE ? (x & 1 ? bf_hi(bw[x >> 1]) : bf_lo(bw[x >> 1])) : bf16_to_f32(bj[x]);
-                    t = __builtin_amdgcn_mfma_f32_32x32x1f32(bf16_to_f32(aj[x]), bv, t, 0, 0, 0);
-                }
-            }
-        }
+        for (int u = 0; u < U; ++u) asm volatile("" : "+v"(cur.w[u]));
     }
     float a1 = 0.f, a2 = 0.f;
-    if constexpr (FOLD) {
-        if (wave < 2) vec[wave][lane] = v8;
-        __syncthreads();
-    }
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-        if (u >= nb) break;
-        u32x4 h = w[u];
+    for (int round = 0; round < rounds; ++round) {
+        const int kb = kb0 + round * U, nb = min(U, kb1 - kb);
+        [[maybe_unused]] f32x32 t = {};
         if constexpr (LORA != LORA_NONE) {
-            const uint32_t ww[4] = {h.x, h.y, h.z, h.w};
-            uint32_t o[4];
+            // accumulator 4 q + e of a lane belongs to column 8 q + 4 (lane / 32) + e of the instruction: that is fed column
+            // 16 (q / 2) + 8 (lane / 32) + 4 (q % 2) + e of the matrix
+            const int i = lane & 31, col = 32 * half + 16 * (i >> 4) + 8 * ((i >> 2) & 1) + 4 * ((i >> 3) & 1) + (i & 3);
+            const bf16_t* ap = A + min(kb * 16 + col, K - 1);  // (past the matrix: its last column, not used)
+            const bf16_t* bp = B + (size_t)rr * rank;
+            constexpr int G = 8;                               // ranks whose values are requested together
+            if constexpr (LORA == LORA_LDS) {
+                bf16_t aj[G], an[G];
+                auto load_a = [&](bf16_t (&v)[G], int j0) {
 #pragma unroll
-            for (int x = 0; x < 4; ++x) {
-                const float s0 = scale * t[8 * u + 2 * x], s1 = scale * t[8 * u + 2 * x + 1];  // plain operators: the pragma above covers them
-                const float lo = bf_lo(ww[x]) + s0;
-                const float hi = bf_hi(ww[x]) + s1;
-                o[x] = pack2_bf16(lo, hi);  // the merged weight is a bf16 value ...
-            }
-            h = u32x4{o[0], o[1], o[2], o[3]};
-        }
-        if constexpr (!TILED) {
-            h = bf16x8_to_half(h);  // ... held as a half like every other weight; rows past the matrix are zeros
-            if (r >= R) h = u32x4{0u, 0u, 0u, 0u};
-            __builtin_nontemporal_store(h, out + u * 64);
-        }
-        if constexpr (FOLD) {
-            const u32x4 g = vec[0][(wave * U + u) * 2 + half], b = vec[1][(wave * U + u) * 2 + half];
-            const uint32_t ww[4] = {h.x, h.y, h.z, h.w}, gg[4] = {g.x, g.y, g.z, g.w}, bb[4] = {b.x, b.y, b.z, b.w};
+                    for (int x = 0; x < G; ++x) v[x] = ap[(size_t)min(j0 + x, rank - 1) * K];
+                };
+                load_a(aj, 0);
+                for (int j0 = 0; j0 < rank; j0 += kMergeRanks) {  // (every wavefront, with blocks left or not: there are barriers)
+                    const int n = min(kMergeRanks, rank - j0);
+                    if (round == 0 || rank > kMergeRanks) {
+                        if (round || j0) __syncthreads();
+                        for (int x = threadIdx.x; x < 32 * kMergeRanks; x += 64 * kMergeWaves) {
+                            const int br = x / kMergeRanks, j = x % kMergeRanks;
+                            if (j < n) bs[br][j] = bf16_to_f32(B[(size_t)min(tile * 32 + br, R - 1) * rank + j0 + j]);
+                        }
+                        __syncthreads();
+                    }
+                    for (int j = 0; j < n; j += G) {
+                        if (j0 + j + G < rank) load_a(an, j0 + j + G);
 #pragma unroll
-            for (int x = 0; x < 4; ++x) {
-                const float w0 = half_lo(ww[x]), w1 = half_hi(ww[x]);
-                a1 = fmaf(w0, bf_lo(gg[x]), a1);
-                a1 = fmaf(w1, bf_hi(gg[x]), a1);
-                a2 = fmaf(w0, bf_lo(bb[x]), a2);
-                a2 = fmaf(w1, bf_hi(bb[x]), a2);
+                        for (int x = 0; x < G; ++x) {
+                            if (j + x >= n) break;
+                            t = __builtin_amdgcn_mfma_f32_32x32x1f32(bf16_to_f32(aj[x]), bs[lane & 31][j + x], t, 0, 0, 0);
+                        }
+#pragma unroll
+                        for (int x = 0; x < G; ++x) aj[x] = an[x];
+                    }
+                }
+            } else if (nb > 0) {
+                for (int j0 = 0; j0 < rank; j0 += G) {
+                    bf16_t aj[G], bj[G];
+                    u32x4 b8;
+                    if constexpr (LORA == LORA_WIDE) b8 = *reinterpret_cast<const u32x4*>(bp + j0);
+#pragma unroll
+                    for (int x = 0; x < G; ++x) {
+                        const int j = min(j0 + x, rank - 1);
+                        aj[x] = ap[(size_t)j * K];
+                        if constexpr (LORA == LORA_FEW) bj[x] = bp[j];
+                    }
+                    const uint32_t bw[4] = {b8.x, b8.y, b8.z, b8.w};
+#pragma unroll
+                    for (int x = 0; x < G; ++x) {
+                        if (LORA == LORA_FEW && j0 + x >= rank) break;
+                        const float bv = LORA == LORA_WIDE ? (x & 1 ? bf_hi(bw[x >> 1]) : bf_lo(bw[x >> 1])) : bf16_to_f32(bj[x]);
+                        t = __builtin_amdgcn_mfma_f32_32x32x1f32(bf16_to_f32(aj[x]), bv, t, 0, 0, 0);
+                    }
+                }
             }
         }
+        if (FOLD && lane < 4 * U) vec[wave][lane] = cur.v;
+        __builtin_amdgcn_wave_barrier();  // (a wavefront's LDS operations are in order)
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (u < nb) {
+                u32x4 h = cur.w[u];
+                if constexpr (LORA != LORA_NONE) {
+                    const uint32_t ww[4] = {h.x, h.y, h.z, h.w};
+                    uint32_t o[4];
+#pragma unroll
+                    for (int x = 0; x < 4; ++x) {
+                        const float s0 = scale * t[8 * u + 2 * x], s1 = scale * t[8 * u + 2 * x + 1];  // plain operators: the pragma above covers them
+                        const float lo = bf_lo(ww[x]) + s0;
+                        const float hi = bf_hi(ww[x]) + s1;
+                        o[x] = pack2_bf16(lo, hi);  // the merged weight is a bf16 value ...
+                    }
+                    h = u32x4{o[0], o[1], o[2], o[3]};
+                }
+                if constexpr (!TILED) {
+                    h = bf16x8_to_half(h);  // ... held as a half like every other weight; rows past the matrix are zeros
+                    if (r >= R) h = u32x4{0u, 0u, 0u, 0u};
+                    __builtin_nontemporal_store(h, out + (size_t)(kb + u) * 64);
+                }
+                if constexpr (FOLD) {
+                    const u32x4 g = vec[wave][2 * u + half], b = vec[wave][2 * U + 2 * u + half];
+                    const uint32_t ww[4] = {h.x, h.y, h.z, h.w}, gg[4] = {g.x, g.y, g.z, g.w}, bb[4] = {b.x, b.y, b.z, b.w};
+#pragma unroll
+                    for (int x = 0; x < 4; ++x) {
+                        const float w0 = half_lo(ww[x]), w1 = half_hi(ww[x]);
+                        a1 = fmaf(w0, bf_lo(gg[x]), a1);
+                        a1 = fmaf(w1, bf_hi(gg[x]), a1);
+                        a2 = fmaf(w0, bf_lo(bb[x]), a2);
+                        a2 = fmaf(w1, bf_hi(bb[x]), a2);
+                    }
+                }
+            }
+        }
+        __builtin_amdgcn_wave_barrier();
+        if (FOLD) load(cur, kb + U);
     }
     if constexpr (FOLD) {
         a1 = lane_sum32_apart(a1);
@@ -180,28 +195,9 @@ __global__ __launch_bounds__(64 * kMergeWaves) void tile_merge_kernel(const bf16
             float sum = 0.f;
 #pragma unroll
             for (int x = 0; x < kMergeWaves; ++x) sum += red[half][x][lane & 31];
-            part[half * part_half + (size_t)span * (gridDim.x / spans) * 32 + tile * 32 + (lane & 31)] = sum;
+            (half ? c2 : c1)[tile * 32 + (lane & 31)] = sum;
         }
     }
-}
-
-// part [2][spans][rows] -> c1, c2 [rows]
-__global__ __launch_bounds__(256) void vec_sum_kernel(const float* __restrict__ part, int spans, int rows, float* __restrict__ c1,
-                                                      float* __restrict__ c2) {
-    const int i = blockIdx.x * 256 + threadIdx.x;
-    if (i >= 2 * rows) return;
-    const int which = i >= rows, r = i - which * rows;
-    const float* p = part + (size_t)which * spans * rows + r;
-    float sum = 0.f;
-    for (int g0 = 0; g0 < spans; g0 += 8) {
-        float v[8];
-#pragma unroll
-        for (int x = 0; x < 8; ++x) v[x] = p[(size_t)min(g0 + x, spans - 1) * rows];
-#pragma unroll
-        for (int x = 0; x < 8; ++x)
-            if (g0 + x < spans) sum += v[x];
-    }
-    (which ? c2 : c1)[r] = sum;
 }
 
 // ----------------------------------------------------------------- 8-bit weight storage
@@ -338,11 +334,11 @@ void fp8_dequant_units(hipStream_t s, const void* units, const float* scales, vo
 // dst: the tiles, written, or (src null) read
 template <bool FOLD>
 static void launch_tile_merge(hipStream_t s, const void* src, void* dst, int R, int K, const void* A, const void* B, int rank, float scale,
-                              const void* gamma, const void* beta, float* part, size_t part_half) {
-    const int spans = (K / 16 + kMergeSpan - 1) / kMergeSpan, grid = (R + 31) / 32 * spans;
+                              const void* gamma, const void* beta, float* c1, float* c2) {
+    const int spans = FOLD ? 1 : (K / 16 + kMergeSpan - 1) / kMergeSpan, grid = (R + 31) / 32 * spans;
     auto launch = [&](auto kernel) {
         kernel<<<grid, 64 * kMergeWaves, 0, s>>>((const bf16_t*)src, (u32x4*)dst, R, K, (const bf16_t*)A, (const bf16_t*)B, rank, scale,
-                                                 (const bf16_t*)gamma, (const bf16_t*)beta, part, part_half, spans);
+                                                 (const bf16_t*)gamma, (const bf16_t*)beta, c1, c2, spans);
     };
     if (A && B && rank > 0) {
         if (rank % 8 == 0 && (reinterpret_cast<uintptr_t>(B) & 15) == 0) launch(tile_merge_kernel<LORA_WIDE, FOLD, false>);
@@ -353,30 +349,15 @@ static void launch_tile_merge(hipStream_t s, const void* src, void* dst, int R, 
 }
 
 void bf16_tile_fold(hipStream_t s, const void* src, void* dst, int R, int K, const void* A, const void* B, int rank, float scale,
-                    const void* gamma, const void* beta, float* c1, float* c2, float* part, size_t part_floats) {
-    const int spans = (K / 16 + kMergeSpan - 1) / kMergeSpan;
-    const size_t row_bytes = (size_t)K * sizeof(bf16_t);
-    // as many rows at a time as the scratch holds partial sums for (one span: the sums themselves, written where they belong)
-    const int fit = spans == 1 ? R : (int)std::min<size_t>(R, part_floats / ((size_t)2 * spans) / 32 * 32);
-    for (int r0 = 0; r0 < R; r0 += fit) {
-        const int rows = std::min(fit, R - r0), padded = (rows + 31) / 32 * 32;
-        const void* from = src ? (const char*)src + r0 * row_bytes : nullptr;
-        void* tiles = (char*)dst + r0 * row_bytes;  // (whole row tiles: as many bytes as rows of the matrix)
-        const void* b = B ? (const bf16_t*)B + (size_t)r0 * rank : nullptr;
-        if (spans == 1) {
-            launch_tile_merge<true>(s, from, tiles, rows, K, A, b, rank, scale, gamma, beta, c1, (size_t)(c2 - c1));
-        } else {
-            launch_tile_merge<true>(s, from, tiles, rows, K, A, b, rank, scale, gamma, beta, part, (size_t)spans * padded);
-            vec_sum_kernel<<<(2 * padded + 255) / 256, 256, 0, s>>>(part, spans, padded, c1 + r0, c2 + r0);
-        }
-    }
+                    const void* gamma, const void* beta, float* c1, float* c2) {
+    launch_tile_merge<true>(s, src, dst, R, K, A, B, rank, scale, gamma, beta, c1, c2);
 }
 
 void bf16_tile_rows(hipStream_t s, const void* src, void* dst, int R, int K) {
-    launch_tile_merge<false>(s, src, dst, R, K, nullptr, nullptr, 0, 0.f, nullptr, nullptr, nullptr, 0);
+    launch_tile_merge<false>(s, src, dst, R, K, nullptr, nullptr, 0, 0.f, nullptr, nullptr, nullptr, nullptr);
 }
 
 void bf16_tile_rows_lora(hipStream_t s, const void* src, void* dst, int R, int K, const void* A, const void* B, int rank,
                          float scale) {
-    launch_tile_merge<false>(s, src, dst, R, K, A, B, rank, scale, nullptr, nullptr, nullptr, 0);
+    launch_tile_merge<false>(s, src, dst, R, K, A, B, rank, scale, nullptr, nullptr, nullptr, nullptr);
 }

@@ -602,7 +602,7 @@ void tile_weights(he_engine* e) {
     auto tile_fold = [&](const void* src, void* dst, int R, int K, const he_lora* ad, const void* gamma, const void* beta, const CVec& v) {
         const bool merge = factors(ad);
         bf16_tile_fold(e->stream, src, dst, R, K, merge ? ad->a : nullptr, merge ? ad->b : nullptr, e->lora_rank, e->lora_scale, gamma, beta,
-                       v.c1, v.c2, e->part, e->tiled_part_floats);
+                       v.c1, v.c2);
     };
     for (int l = 0; l < c.n_layers; ++l) {
         const he_layer_weights& lw = e->layers[l];

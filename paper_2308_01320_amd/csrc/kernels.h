@@ -101,9 +101,8 @@ void bf16_tile_rows(hipStream_t s, const void* src, void* dst, int R, int K);
 void bf16_tile_rows_lora(hipStream_t s, const void* src, void* dst, int R, int K, const void* A, const void* B, int rank,
                          float scale);
 // The same (A null: without an adapter; src null: dst holds the tiles already), and c1 = W gamma, c2 = W beta of the R rows padded to 32
-// (c2 behind c1).  part: scratch, for 64 K / 512 floats at least
 void bf16_tile_fold(hipStream_t s, const void* src, void* dst, int R, int K, const void* A, const void* B, int rank, float scale,
-                    const void* gamma, const void* beta, float* c1, float* c2, float* part, size_t part_floats);
+                    const void* gamma, const void* beta, float* c1, float* c2);
 // EPI_STORE_LN GEMM of M <= 64 rows: columns per workgroup (= per group of LayerNorm statistics) and k-splits;
 // capacity = floats of k-split scratch available (the value passed as bf16_gemm_args.out_capacity); w8 != 0: 8-bit weights
 void bf16_store_plan(int M, int N, int K, size_t capacity, int w8, int* group_cols, int* ks);

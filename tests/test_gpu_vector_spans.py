@@ -1,5 +1,5 @@
-"""GPU parity of the folded LayerNorm's vectors W gamma and W beta where their partial sums (one per 512 columns and row) do not fit the
-engine's scratch at once: a vocabulary of more rows than that, formed in two goes, and the vectors of rows at both sides of the cut."""
+"""GPU parity of the folded LayerNorm's vectors W gamma and W beta of a vocabulary of many rows, the last tile of 32 partly filled, from the caller's
+rows and from tiles: every logit of a decode step."""
 import numpy as np
 import pytest
 
@@ -11,13 +11,12 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("tiled", [0, 1])
-def test_vectors_formed_in_two_goes(tiled):
+def test_vectors_of_many_rows(tiled):
     import torch
-    H, V, cut = 576, 73901, 73728  # two partial sums to a row; 512 H floats of scratch hold them for 73728 rows
+    H, V = 576, 73901
     base = synth.ModelDims("x", 1, H, 9, 64, V, 8, 1, 2, 2, "bf16", "greedy")
     w = synth.make_weights(base, seed=13)
     cfg = binding.make_config(base, max_batch=1, max_seq_len=8, weights_tiled=tiled)
-    assert binding.he_plan_pass_gemm(cfg, 1, "qkv").scratch_reserved // 4 // 32 * 32 == cut
     dev = binding.upload_weights(w, "bf16")
     if tiled:
         dev = binding.tile_weights_in_place(dev)
@@ -29,4 +28,3 @@ def test_vectors_formed_in_two_goes(tiled):
     eng.he_destroy()
     want = O.forward_full(util.weights_f64(w), ids, 9, eps=base.ln_eps)[0][3]
     assert float(np.abs(got - want).max()) <= 2e-2
-    assert float(np.abs(got[cut - 64:cut + 64] - want[cut - 64:cut + 64]).max()) <= 2e-2
