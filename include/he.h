@@ -390,6 +390,16 @@ enum {
 };
 he_status he_plan_attention(const he_config* cfg, int B, int S, int cus, int* form, int* wavefronts);
 
+/* Test hook, host logic only: how the plain kernels (float, or impl 1) compute product `which` (as in he_plan_pass_gemm; 4 is the
+ * LM head, over B rows) of a pass of B sequences with S new tokens each in an engine created with cfg; S = 1: a decode step. */
+enum {
+    HE_PLAIN_BLOCKS = 0,   /* a step of a small float model: a launch per attention block and per FFN block (tables 16-byte aligned) */
+    HE_PLAIN_FEW_ROWS = 1, /* 16 rows x 16 columns to a workgroup, the LayerNorm ahead folded in */
+    HE_PLAIN_TILES_32 = 2, /* 32 x 32 */
+    HE_PLAIN_TILES_64 = 3  /* 64 x 64 */
+};
+he_status he_plan_plain_gemm(const he_config* cfg, int B, int S, int which, int* form);
+
 /* Measurement hook: a plain copy kernel (reads `bytes`, writes `bytes`, a multiple of 16,
  * device pointers, on `stream`).  Hardware byte counters (rocprofv3 FETCH_SIZE /
  * WRITE_SIZE) are scaled by what they read for this kernel of known size. */

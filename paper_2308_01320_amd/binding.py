@@ -145,6 +145,8 @@ def lib() -> C.CDLL:
                                       C.POINTER(C.c_int), C.POINTER(C.c_int)]
     L.he_plan_attention.restype = C.c_int
     L.he_plan_attention.argtypes = [C.POINTER(he_config), C.c_int, C.c_int, C.c_int, C.POINTER(C.c_int), C.POINTER(C.c_int)]
+    L.he_plan_plain_gemm.restype = C.c_int
+    L.he_plan_plain_gemm.argtypes = [C.POINTER(he_config), C.c_int, C.c_int, C.c_int, C.POINTER(C.c_int)]
     L.he_kernel_sweep.restype = C.c_int
     L.he_kernel_sweep.argtypes = [vp, C.c_int, C.c_int]
     L.he_calibration_copy.restype = C.c_int
@@ -162,7 +164,7 @@ EXPORTS = ("he_workspace_bytes", "he_create", "he_refresh_weights", "he_prefill"
            "he_generate_ragged", "he_refresh_weights_lora", "he_release_arena", "he_acquire_arena",
            "he_tile_matrix_lora", "he_plan_decode_gemm", "he_fp8_quantize_rows", "he_decode_step_static",
            "he_decode_scratch_account", "he_arrival_counters_nonzero", "he_arrival_counters_set", "he_last_step_rows",
-           "he_plan_prompt_gemm", "he_plan_pass_gemm", "he_plan_attention")
+           "he_plan_prompt_gemm", "he_plan_pass_gemm", "he_plan_attention", "he_plan_plain_gemm")
 
 KERNEL_CLASSES = ("layernorm", "qkv", "attention", "out_proj", "fc1", "fc2", "lm_head", "empty")
 
@@ -445,6 +447,18 @@ def he_plan_attention(cfg: he_config, B: int, S: int = 1, cus: int = 256):
     if rc != HE_OK:
         raise HeError(rc, "he_plan_attention")
     return ATTENTION_FORMS[f.value], w.value
+
+
+PLAIN_FORMS = ("blocks", "few rows", "32 x 32", "64 x 64")
+
+
+def he_plan_plain_gemm(cfg: he_config, B: int, S: int, which: str) -> str:
+    """How the plain kernels compute a product of a pass of S new tokens (1: a decode step) of B sequences; host logic only."""
+    f = C.c_int()
+    rc = lib().he_plan_plain_gemm(C.byref(cfg), B, S, PASS_GEMMS.index(which), C.byref(f))
+    if rc != HE_OK:
+        raise HeError(rc, "he_plan_plain_gemm")
+    return PLAIN_FORMS[f.value]
 
 
 def he_decode_scratch_account(cfg: he_config, B: int, which: int, cus: int = 256) -> he_scratch_account:

@@ -654,10 +654,12 @@ void plain_layers(he_engine* e, int M, int S) {
 
 // Whether a decode step of the float path runs as blocks (kernels_blocks.hip): a small model, few rows, every table and vector
 // aligned for four values at a time.  The partial sums go into the activation buffers such a step has no other use for.
-bool block_step(const he_engine* e, int B) {
-    const he_config& c = e->cfg;
+bool block_shape(const he_config& c, int B) {
     const size_t rows = (size_t)c.max_batch * c.max_seq_len;
-    if (e->bf16 || !c.n_layers || !plain_blocks_fit(B, c.hidden, c.n_heads, c.ffn, rows * c.hidden, rows * c.ffn)) return false;
+    return c.dtype == HE_F32 && c.n_layers && plain_blocks_fit(B, c.hidden, c.n_heads, c.ffn, rows * c.hidden, rows * c.ffn);
+}
+bool block_step(const he_engine* e, int B) {
+    if (!block_shape(e->cfg, B)) return false;
     auto aligned = [](std::initializer_list<const void*> ps) {
         for (const void* p : ps)
             if ((uintptr_t)p % 16) return false;
@@ -1325,6 +1327,14 @@ he_status he_plan_attention(const he_config* cfg, int B, int S, int cus, int* fo
     if (!form || !wavefronts || check_config(cfg) || check_shape(cfg) || !is_fast(*cfg)) return HE_ERR_INVALID_ARG;
     if (B < 1 || B > cfg->max_batch || S < 1 || S > cfg->max_seq_len || (long)B * S > INT32_MAX || cus < 0) return HE_ERR_INVALID_ARG;
     bf16_attn_plan_query(B * S, S, cfg->n_heads, cfg->hidden / cfg->n_heads, cfg->max_seq_len, cus, form, wavefronts);
+    return HE_OK;
+}
+
+he_status he_plan_plain_gemm(const he_config* cfg, int B, int S, int which, int* form) {
+    if (!form || check_config(cfg) || check_shape(cfg) || is_fast(*cfg)) return HE_ERR_INVALID_ARG;
+    if (B < 1 || B > cfg->max_batch || S < 1 || S > cfg->max_seq_len || (long)B * S > INT32_MAX || which < 0 || which > 4) return HE_ERR_INVALID_ARG;
+    const int H = cfg->hidden, F = cfg->ffn, N[] = {3 * H, H, F, H, cfg->vocab}, K[] = {H, H, H, F, H};
+    *form = S == 1 && block_shape(*cfg, B) ? (int)HE_PLAIN_BLOCKS : plain_gemm_form(which == 4 ? B : B * S, N[which], K[which]);
     return HE_OK;
 }
 

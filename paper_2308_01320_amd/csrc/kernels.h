@@ -18,6 +18,7 @@ void plain_ln(hipStream_t s, int bf16, const float* r, const plain_ln_args& ln, 
 void plain_gemm(hipStream_t s, int bf16, const float* A, const void* W, const void* bias, int M, int N, int K, int epi,
                 float* out, void* kv, const he_dev_state* st, int S, int layer, int H, int n_heads, int max_batch,
                 int max_seq, float qscale, const plain_ln_args* ln = nullptr, float* scratch = nullptr);
+int plain_gemm_form(int M, int N, int K);  // HE_PLAIN_ in he.h, of a product that is a launch of its own
 void plain_attn(hipStream_t s, int bf16, const float* q, const void* kv, float* o, const he_dev_state* st, int M, int S,
                 int layer, int H, int n_heads, int max_batch, int max_seq);
 // ---- decode steps of small float models (kernels_blocks.hip): a launch per attention block and per FFN block

@@ -2,6 +2,7 @@
 // a slow comparator for the tuned bf16 kernels).  One obvious kernel per step of
 // the decoder; activations are float, row-major [rows, features].
 #include "he_common.h"
+#include "../../include/he.h"
 #include "kernels.h"
 
 namespace {
@@ -83,7 +84,7 @@ __global__ void ln_kernel(const float* __restrict__ r, const ST* __restrict__ ga
 // What bounds it is the length of the dependent chain -- a launch, a load or two, a few matrix instructions -- so the k
 // range is split over the wavefronts of a workgroup (partial sums added in wavefront order through LDS) and the few rows
 // of a decode step go 16 columns to a workgroup.
-//   few rows (at most 64, 256   gemm_few_kernel: 16 columns x 16 rows per workgroup, LayerNorm of the rows folded in
+//   few rows (at most 64, 256   gemm_few_kernel: 16 columns x 16 rows per workgroup, LayerNorm of the rows folded in (plain_gemm_form)
 //   of small matrices):
 //   many tiles (from 256 on):   KW = 1: 64 x 64 per workgroup of four wavefronts
 //   else:                       KW = 8: 32 x 32 per workgroup
@@ -652,22 +653,29 @@ void plain_ln(hipStream_t s, int bf16, const float* r, const plain_ln_args& ln, 
 // is for, and too high for wider ones from 33 (1024) or 17 (2048) rows on.
 // Small matrices go this way up to 256 rows: the 32 x 32 tiles are too few workgroups there (128 rows: 32 of them for 256 columns).  A
 // prompt pass of two layers, tiles / this: width 256, FFN 1024: 128 rows 98 / 73, 256 rows 99 / 92, 272 106 / 104, 384 114 / 119, 512
-// 119 / 135; width 512, FFN 2048: 128 rows 128 / 112; width 128: 320 rows 139 / 73.
-constexpr int kFewRows = 64, kSmallRows = 256, kSmallMatrix = 1024 * 1024;
-static bool few_rows(int M, int N, int K) { return M <= kFewRows || (M <= kSmallRows && (long)N * K <= kSmallMatrix); }
+// 119 / 135; width 128: 320 rows 139 / 73.  Up to 2^27 multiply-adds: what a workgroup's 16 rows and 16 columns load for them is four
+// times what a tile loads.  Four layers, tiles / this: width 512, FFN 2048 (2^20 weights): 65 rows 233 / 170, 128 rows 244 / 208, 192 rows 298 / 303, 256
+// rows 314 / 353; width 1024, FFN 1024: 65 rows 299 / 252, 128 rows 325 / 295, 256 rows 416 / 490; 768, FFN 768: 128 rows 269 / 239, 256
+// rows 345 / 354.
+constexpr int kFewRows = 64, kSmallRows = 256, kSmallMatrix = 1024 * 1024, kSmallWork = 128 * kSmallMatrix;
+int plain_gemm_form(int M, int N, int K) {
+    if (M <= kFewRows) return HE_PLAIN_FEW_ROWS;
+    if (M <= kSmallRows && (long)N * K <= kSmallMatrix && (long)M * N * K <= kSmallWork) return HE_PLAIN_FEW_ROWS;
+    return (long)((N + 63) / 64) * ((M + 63) / 64) >= 256 ? HE_PLAIN_TILES_64 : HE_PLAIN_TILES_32;
+}
 
 template <typename ST, bool VEC>
 static void launch_gemm(hipStream_t s, const float* A, const ST* W, const ST* bias, const plain_ln_args* ln, const PlainGemm& p) {
     const ST *gamma = ln ? (const ST*)ln->gamma : nullptr, *beta = ln ? (const ST*)ln->beta : nullptr;
-    if (few_rows(p.M, p.N, p.K)) {
+    const int form = plain_gemm_form(p.M, p.N, p.K);
+    if (form == HE_PLAIN_FEW_ROWS) {
         const dim3 grid((p.N + 15) / 16, (p.M + 15) / 16);
         if (ln) gemm_few_kernel<ST, VEC, true><<<grid, 512, 0, s>>>(A, W, bias, gamma, beta, p);
         else gemm_few_kernel<ST, VEC, false><<<grid, 512, 0, s>>>(A, W, bias, gamma, beta, p);
         return;
     }
-    const dim3 big((p.N + 63) / 64, (p.M + 63) / 64);
-    if (big.x * big.y >= 256)
-        gemm_kernel<ST, 1, 2, 2, VEC><<<big, 256, 0, s>>>(A, W, bias, p);
+    if (form == HE_PLAIN_TILES_64)
+        gemm_kernel<ST, 1, 2, 2, VEC><<<dim3((p.N + 63) / 64, (p.M + 63) / 64), 256, 0, s>>>(A, W, bias, p);
     else
         gemm_kernel<ST, 8, 1, 1, VEC><<<dim3((p.N + 31) / 32, (p.M + 31) / 32), 512, 0, s>>>(A, W, bias, p);
 }
@@ -675,7 +683,7 @@ static void launch_gemm(hipStream_t s, const float* A, const ST* W, const ST* bi
 template <typename ST>
 static void plain_gemm_t(hipStream_t s, const float* A, const void* W, const void* bias, const plain_ln_args* ln, float* scratch,
                          PlainGemm& p) {
-    if (ln && !few_rows(p.M, p.N, p.K)) {
+    if (ln && plain_gemm_form(p.M, p.N, p.K) != HE_PLAIN_FEW_ROWS) {
         plain_ln(s, sizeof(ST) == 2, A, *ln, scratch, p.M, p.K);
         A = scratch;
         ln = nullptr;

@@ -1,4 +1,4 @@
-"""GPU parity of the plain path's passes of 65 to 256 rows, whose small matrices (at most 2^20 weights) go through the few-row kernel: the
+"""GPU parity of the plain path's passes of 65 to 256 rows, whose small matrices (at most 2^20 weights, 2^27 multiply-adds) go through the few-row kernel: the
 last row count it takes and the first it does not, a matrix of exactly that size, one above it between others below (its LayerNorm a
 launch of its own), and a width without whole quads."""
 import pytest
