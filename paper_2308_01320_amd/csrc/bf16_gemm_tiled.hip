@@ -7,10 +7,9 @@ namespace {
 
 // A wavefront's share of the scoring head, NA column blocks x MJ row blocks from row m0 and column n0 on.  The logits
 // never leave the registers: per row, the soft-max partials of the wavefront's 32 NA vocabulary entries (slice `part` of
-// the row) and, if the row's next token is among them, its logit.  (The hardware's exponential, and the next token looked for only where
-// one of the rows has it: of 16384 x 50272 x 2048 in 256 x 128 tiles 3770 -> 3520 us; the log-probabilities' error against 64 bits stays
-// 4.4e-5, the operands' rounding.)
-constexpr float kLog2e = 1.44269504088896340736f;
+// the row) and, if the row's next token is among them, its logit.  (The next token is looked for only where one of the rows has it.  The
+// hardware's 2^x of an argument multiplied by log2 e, 2976 us instead of 3161 for 16384 x 50272 x 2048, rounds the argument first: terms six
+// below the largest are off by up to five ulps, which many additions in one direction made 5e-6 of a sum.)
 template <int NA, int MJ, bool BIG = false>
 __device__ __forceinline__ void score_tile(const Epi& p, f32x16 (&acc)[NA][MJ], int m0, int n0, int part, int lane) {
     const int nl = n0 + 4 * (lane >> 5);
@@ -48,7 +47,7 @@ __device__ __forceinline__ void score_tile(const Epi& p, f32x16 (&acc)[NA][MJ], 
 #pragma unroll
                 for (int i = 0; i < NA; ++i)
 #pragma unroll
-                    for (int r = 0; r < 16; ++r) sum += __builtin_amdgcn_exp2f((logit(i, r) - mx) * kLog2e);
+                    for (int r = 0; r < 16; ++r) sum += expf(logit(i, r) - mx);
             }
         };
         if (whole) reduce([&](int i, int r) { return acc[i][j][r]; });
@@ -1062,17 +1061,17 @@ static RingPlan fused_plan(int M, int N, int KB, size_t capacity_floats) {
 static RingPlan lm_head_plan(int M, int V, int K) { return ring_plan_256(M, V, K / 16, true, 0, M <= 64 ? 1 : 3); }
 
 // The scoring head: 0 for gemm_score_kernel (two workgroups per CU) or 4, the big tiles, from two rounds of the former's on, else the
-// ring kernel's tile.  Microseconds of rounds, fitted to 350 .. 16384 rows of 5000 .. 50272 ids at k = 1024, 2048, 5120: a big
-// tile loads a third less for its products (16 KiB to 64 of them), where two of the others reduce the logits of one behind the products of
-// the other and a last round of at most one workgroup to a CU takes seven tenths.  Rows x ids x k, two workgroups / big, the whole head:
-// 16384 x 50272 x 2048 3334 / 2892, x 5120 8286 / 6950, x 1024 1696 / 1593; 640 x 50272 x 2048 155 / 182, 3500 x 5000 x 1024 83 / 88.
-// (The same slices of 128 entries and the same order of sums: the results are the same to the bit.)
+// ring kernel's tile.  Microseconds of rounds, fitted to 640 .. 16384 rows of 5000 .. 50272 ids at k = 1024 .. 5120: a big tile loads a
+// third less for its products (16 KiB to 64 of them), where two of the others reduce the logits of one behind the products of the other and
+// a last round of at most one workgroup to a CU takes seven tenths.  Rows x ids x k, two workgroups / big, us of the product: 16384 x 50272 x
+// 2048 3614 / 3161, x 5120 8265 / 6706, x 1024 1909 / 1944; 2048 x 50272 x 1024 245 / 277, x 2048 494 / 472; 1300 x 50272 x 1024 175 / 195; 700 x 50272
+// x 5120 487 / 398.  (The same slices of 128 entries and the same order of sums: the results are the same to the bit.)
 static int score_tile(int M, int V, int K) {
     const long cus = plan_cus(), tn = (V + TN - 1) / TN, tiles = tn * ((M + 127) / 128), big = tn * ((M + BM - 1) / BM);
     if (tiles < 2 * cus) return M <= 64 ? 1 : 2;
     const long rest = tiles % (2 * cus);
     const double two = (double)(tiles / (2 * cus)) + (rest == 0 ? 0.0 : (rest <= cus ? 0.7 : 1.0));
-    return (double)((big + cus - 1) / cus) * (5.5 + 0.0256 * K) < two * (0.9 + 0.0322 * K) ? 4 : 0;
+    return (double)((big + cus - 1) / cus) * (15.0 + 0.0238 * K) < two * (5.3 + 0.0335 * K) ? 4 : 0;
 }
 
 void bf16_pass_plan_query(int use, int M, int N, int K, size_t capacity_floats, int cus, int* tile_rows, int* tile_cols, int* wg_cols, int* ks,
