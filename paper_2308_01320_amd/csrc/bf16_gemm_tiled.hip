@@ -892,10 +892,6 @@ static RingPlan ring_plan_256(int M, int N, int KB, bool fused, size_t capacity_
 // 215.8 / 221.9 / 216.9; 7168, 160 rows 398 / 400 / 379; 4096, 65 rows 146 / 146 / 143, 200 rows 204 / 193 / 192; 1024,
 // 160 rows 69 / 52 / 52.)
 // All of the fit's matrices have a multiple of 512 rows.  Others keep the plan above, which the tests' table of tiles (4480 wide) is drawn up for.
-// (Fitted before the weights of one row of tiles were streamed past the caches (launch_ring).  What that gains shows in the choice where 256 rows
-// are such a row: a stage of its 0.30 us there, but for sums that finish_kernel adds up.  A prompt pass of 193 .. 256 rows then, us: hidden 4096, FC2 in eight
-// ranges of 256 x 128 instead of four of 128 x 128, 200 rows 501 -> 479, 250 rows 520 -> 502 (four layers); 5120, FC1 whole on 256 x 128, 200 rows 436 -> 410; 9216
-// 465 -> 432; 3072 as before.  Fewer rows: the same on 64, 128 and 192 tile rows moved nothing beyond what two runs differ by.)
 // That is no crossing: this one is ahead there too, a prompt pass or a wide decode step by 6 to 25 % at hidden 768, 4 to 24 at 1344, -1 to 8 at 4480, 0 to 6 at
 // 4096 with an FFN of 10944.
 static RingPlan ring_plan(int M, int N, int KB, bool fused, size_t capacity_floats) {
@@ -903,7 +899,6 @@ static RingPlan ring_plan(int M, int N, int KB, bool fused, size_t capacity_floa
     struct Tile { int id, nw, mw; double stage; };
     static constexpr Tile kTiles[] = {{1, 4, 1, 0.372}, {2, 4, 2, 0.363}, {3, 4, 3, 0.40}, {4, 4, 4, 0.497}, {5, 5, 4, 0.85},
                                       {11, 2, 1, 0.193}, {12, 2, 2, 0.243}, {13, 2, 3, 0.296}, {14, 2, 4, 0.348}};
-    constexpr double kStreamed256 = 0.30;
     const double sums = 4.0 * M * N, weights = 32.0 * N * KB / 6.8e6;
     const double tail_of_range = sums / 3.7e6 + sums / (fused ? 5.45e6 : 4.6e6), idle = 0.03 * weights;
     const int cus = plan_cus(), stages = KB / 2;
@@ -919,8 +914,7 @@ static RingPlan ring_plan(int M, int N, int KB, bool fused, size_t capacity_floa
             const int full = (tiles * ks + cus - 1) / cus;
             const double rounds = (double)(tiles * ks) / cus;
             const double turns = full == 1 ? 1.0 : 1.0 + 2.1 * (full - 1) - 1.1 * (rounds - 1.0);
-            const double stage = t.id == 14 && M <= 256 && !(fused && ks > 1) ? kStreamed256 : t.stage;
-            const double core = turns * (stage * ((stages + ks - 1) / ks) + 0.425 * t.nw * t.mw);
+            const double core = turns * (t.stage * ((stages + ks - 1) / ks) + 0.425 * t.nw * t.mw);
             const double hbm = full == 1 ? weights + idle * (1.0 - rounds) : weights;
             // (compared as cubes: a launch that no graph replays is planned anew, and a root for each candidate was most of what
             // that costs the host: 96 rows of 5120 x 20480 5.0 us, so 1.6, 0.5 of it the measuring call)

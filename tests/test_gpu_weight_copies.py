@@ -28,13 +28,13 @@ def test_one_row_of_tiles_and_more(H, nh, F, S):
 
 
 @pytest.mark.parametrize("S", [193, 256])
-def test_one_row_of_256(S):
+def test_k_ranges_of_up_to_256_rows(S):
     import torch
     d = synth.ModelDims("x", 1, 4096, 32, 16384, 300, S + 1, 1, S, 1, "bf16", "greedy")
     w = synth.make_weights(d, seed=17)
     cfg = binding.make_config(d)
     p = binding.he_plan_pass_gemm(cfg, S, "fc2")
-    assert (p.tile_rows, p.workgroup_cols, p.ksplit) == (256, 128, 8)
+    assert (p.tile_rows, p.workgroup_cols, p.ksplit) == (128, 128, 4)
     eng = binding.Engine(cfg, binding.upload_weights(w, "bf16"))
     ids = np.random.default_rng(S).integers(0, d.vocab, (1, S)).astype(np.int32)
     last = eng.he_prefill(torch.from_numpy(ids).cuda(), binding.sampling("greedy"), True)[2].cpu().numpy()
