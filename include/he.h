@@ -379,6 +379,9 @@ typedef struct {
 } he_pass_plan;
 he_status he_plan_pass_gemm(const he_config* cfg, int rows, int which, int scoring, int cus, he_pass_plan* out);
 
+/* Test hook, host logic only: whether that launch (which = 0 .. 3) is one of the few-row tiles and copies its weights past the caches. */
+he_status he_plan_weight_copies(const he_config* cfg, int rows, int which, int scoring, int cus, int* streamed);
+
 /* Test hook, host logic only: the kernel that computes the attention of B sequences with S rows each (S = 1: a decode step) in
  * an engine created with cfg, and the wavefronts of its workgroups.  cus as in he_plan_prompt_gemm.  bf16, impl 0 only. */
 enum {

@@ -145,6 +145,8 @@ def lib() -> C.CDLL:
                                       C.POINTER(C.c_int), C.POINTER(C.c_int)]
     L.he_plan_attention.restype = C.c_int
     L.he_plan_attention.argtypes = [C.POINTER(he_config), C.c_int, C.c_int, C.c_int, C.POINTER(C.c_int), C.POINTER(C.c_int)]
+    L.he_plan_weight_copies.restype = C.c_int
+    L.he_plan_weight_copies.argtypes = [C.POINTER(he_config), C.c_int, C.c_int, C.c_int, C.c_int, C.POINTER(C.c_int)]
     L.he_plan_plain_gemm.restype = C.c_int
     L.he_plan_plain_gemm.argtypes = [C.POINTER(he_config), C.c_int, C.c_int, C.c_int, C.POINTER(C.c_int)]
     L.he_kernel_sweep.restype = C.c_int
@@ -164,7 +166,7 @@ EXPORTS = ("he_workspace_bytes", "he_create", "he_refresh_weights", "he_prefill"
            "he_generate_ragged", "he_refresh_weights_lora", "he_release_arena", "he_acquire_arena",
            "he_tile_matrix_lora", "he_plan_decode_gemm", "he_fp8_quantize_rows", "he_decode_step_static",
            "he_decode_scratch_account", "he_arrival_counters_nonzero", "he_arrival_counters_set", "he_last_step_rows",
-           "he_plan_prompt_gemm", "he_plan_pass_gemm", "he_plan_attention", "he_plan_plain_gemm")
+           "he_plan_prompt_gemm", "he_plan_pass_gemm", "he_plan_attention", "he_plan_plain_gemm", "he_plan_weight_copies")
 
 KERNEL_CLASSES = ("layernorm", "qkv", "attention", "out_proj", "fc1", "fc2", "lm_head", "empty")
 
@@ -435,6 +437,15 @@ def he_plan_pass_gemm(cfg: he_config, rows: int, which: str, scoring=False, cus:
     if rc != HE_OK:
         raise HeError(rc, "he_plan_pass_gemm")
     return out
+
+
+def he_plan_weight_copies(cfg: he_config, rows: int, which: str, scoring=False, cus: int = 256) -> bool:
+    """Whether that launch is one of the few-row tiles and copies its weights past the caches; host logic only."""
+    out = C.c_int()
+    rc = lib().he_plan_weight_copies(C.byref(cfg), rows, PASS_GEMMS.index(which), 1 if scoring else 0, cus, C.byref(out))
+    if rc != HE_OK:
+        raise HeError(rc, "he_plan_weight_copies")
+    return bool(out.value)
 
 
 ATTENTION_FORMS = ("two passes", "one pass", "short prompt", "prompt", "prompt split")

@@ -931,15 +931,25 @@ static RingPlan ring_plan(int M, int N, int KB, bool fused, size_t capacity_floa
 // Workgroups of the big kernel: one per CU, each XCD the same number
 static int big_grid(int slots) { return std::min(slots, std::max(8, plan_cus() / 8 * 8)); }
 
-// The weights' copies of the ring kernel are non-temporal where one row of tiles reads them, or, of halved tiles with whole sums, several do.
-// A copy of what comes from HBM then moves 6.6 - 7.1 TB/s on 256 CUs instead of 5.8, and the activations stay in L2.  Per launch inside the
-// engine (hidden 768 .. 7168, 40 .. 3000 rows): one row of tiles 1.02 - 1.18 times as fast (5120 x 20480 and 96 rows 43.6 -> 39.8 us, 7168 x
-// 28672 90.5 -> 76.7), several on halved tiles 1.03 - 1.21 at hidden 1024 (3072 x 1024 and 250 rows) and 4096 and 0.94 - 1.04 where they fill the chip; but
-// with k ranges 0.77 - 1.05 (1024 x 4096 and 100 rows in ten ranges 7.2 -> 9.2 us) and on 256 columns 0.93 - 1.03.
+// Whether the weights' copies of the ring kernel are non-temporal.  A copy of what comes from HBM then moves 6.6 - 7.1 TB/s on 256 CUs instead
+// of 5.8, and the activations stay in L2.  One row of tiles: always, 1.02 - 1.18 times as fast per launch inside the engine (5120 x 20480 and 96 rows
+// 43.6 -> 39.8 us, 7168 x 28672 90.5 -> 76.7).  Several rows of halved tiles with whole sums share what one of them fetched only while they keep
+// together.  Measured alternately in one process, hidden 512 .. 7168, 66 .. 2000 rows, plain / streamed:
+//   64 tile rows, from 64 tiles of columns on    0.98 - 1.32 (12288 x 4096 and 96 rows 1.23, 14336 x 3584 and 120 rows 1.31), mean 1.09;
+//     fewer columns                              0.92 - 1.1 (60 tiles of columns 0.92 - 0.99, 36 0.94 - 0.99, 24 to 48 about 1);
+//   128 to 256, the last row of tiles at least   0.98 - 1.09 (8192 x 2048 and 512 rows 1.06), mean 1.01;
+//     seven eighths full, or less                0.81 - 1.07: a row of padding runs ahead of the others (14336 x 3584 and 160 rows 34.4 / 42.3 us).
+// With k ranges 0.77 - 1.05 (1024 x 4096 and 100 rows in ten ranges 7.2 -> 9.2 us), on 256 columns 0.93 - 1.03: plain.
+static bool ring_streams(int M, int N, int tile_rows, int wg_cols, int ksplit) {
+    const int tiles_m = (M + tile_rows - 1) / tile_rows;
+    if (tiles_m == 1) return true;
+    if (wg_cols != 128 || ksplit > 1) return false;
+    return tile_rows == 64 ? N > 63 * 128 : 8 * (M - (tiles_m - 1) * tile_rows) >= 7 * tile_rows;
+}
 template <int MODE, int NW, int MW>
 static void launch_ring(hipStream_t s, int grid, const u32x4* W, const u32x4* X, const u32x4* bias8, int KB, int NT32, int MT32, int tiles_n, int tiles_m,
                         int ksplit, const Epi& p) {
-    if (tiles_m == 1 || (NW == 2 && ksplit == 1)) gemm_ring_kernel<MODE, NW, MW, true><<<grid, 256, 0, s>>>(W, X, bias8, KB, NT32, MT32, tiles_n, tiles_m, ksplit, p);
+    if (ring_streams(p.M, p.N, 64 * MW, 64 * NW, ksplit)) gemm_ring_kernel<MODE, NW, MW, true><<<grid, 256, 0, s>>>(W, X, bias8, KB, NT32, MT32, tiles_n, tiles_m, ksplit, p);
     else gemm_ring_kernel<MODE, NW, MW, false><<<grid, 256, 0, s>>>(W, X, bias8, KB, NT32, MT32, tiles_n, tiles_m, ksplit, p);
 }
 
@@ -1067,6 +1077,8 @@ static int score_tile(int M, int V, int K) {
     const double two = (double)(tiles / (2 * cus)) + (rest == 0 ? 0.0 : (rest <= cus ? 0.7 : 1.0));
     return (double)((big + cus - 1) / cus) * (15.0 + 0.0238 * K) < two * (5.3 + 0.0335 * K) ? 4 : 0;
 }
+
+bool bf16_ring_streams(int M, int N, int tile_rows, int wg_cols, int ksplit) { return ring_streams(M, N, tile_rows, wg_cols, ksplit); }
 
 void bf16_pass_plan_query(int use, int M, int N, int K, size_t capacity_floats, int cus, int* tile_rows, int* tile_cols, int* wg_cols, int* ks,
                           int* split_col) {

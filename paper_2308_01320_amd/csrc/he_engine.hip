@@ -1323,6 +1323,17 @@ he_status he_plan_pass_gemm(const he_config* cfg, int rows, int which, int scori
     return HE_OK;
 }
 
+he_status he_plan_weight_copies(const he_config* cfg, int rows, int which, int scoring, int cus, int* streamed) {
+    he_pass_plan p;
+    if (!streamed || which > 3) return HE_ERR_INVALID_ARG;
+    const he_status r = he_plan_pass_gemm(cfg, rows, which, scoring, cus, &p);
+    if (r != HE_OK) return r;
+    const int H = cfg->hidden, F = cfg->ffn, N[] = {3 * H, H, F, H};
+    const bool few = p.workgroup_cols == 128 || p.tile_rows < 256;
+    *streamed = few && bf16_ring_streams(rows, N[which], p.tile_rows, p.workgroup_cols, p.ksplit);
+    return HE_OK;
+}
+
 he_status he_plan_attention(const he_config* cfg, int B, int S, int cus, int* form, int* wavefronts) {
     if (!form || !wavefronts || check_config(cfg) || check_shape(cfg) || !is_fast(*cfg)) return HE_ERR_INVALID_ARG;
     if (B < 1 || B > cfg->max_batch || S < 1 || S > cfg->max_seq_len || (long)B * S > INT32_MAX || cus < 0) return HE_ERR_INVALID_ARG;

@@ -1,5 +1,5 @@
-"""The k ranges of the products of 193 to 256 rows: their number is the order of the sums, by which activations round, so it is part of what a pass
-returns and not only of how fast it is (host logic, no GPU)."""
+"""Plans of the few-row tiles (host logic, no GPU): the k ranges of the products of 193 to 256 rows, whose number is the order of the sums, by which
+activations round, so part of what a pass returns and not only of how fast it is; and which launches copy their weights past the caches."""
 import dataclasses
 
 import pytest
@@ -17,3 +17,26 @@ def test_k_ranges(H, rows, ranges):
         d = dataclasses.replace(synth.CONFIGS["opt-13b"], hidden=H, n_heads=H // 128, ffn=4 * H)
         cfg = binding.make_config(d, max_batch=1, max_seq_len=256)
         assert tuple(binding.he_plan_pass_gemm(cfg, m, g).ksplit for g in binding.PASS_GEMMS[:4]) == ranges, m
+
+
+def _plan(H, rows, which, scoring=False):
+    d = dataclasses.replace(synth.CONFIGS["opt-13b"], hidden=H, n_heads=H // 64, ffn=4 * H)
+    cfg = binding.make_config(d, max_batch=1, max_seq_len=rows)
+    p = binding.he_plan_pass_gemm(cfg, rows, which, scoring=scoring)
+    return (p.tile_rows, p.workgroup_cols, p.ksplit), binding.he_plan_weight_copies(cfg, rows, which, scoring)
+
+
+@pytest.mark.parametrize("H,rows,which,plan,streamed", [
+    (4096, 96, "qkv", (128, 128, 2), True), (5120, 96, "fc1", (128, 128, 1), True),         # one row of tiles
+    (4096, 128, "qkv", (64, 128, 1), True), (3584, 120, "fc1", (64, 128, 1), True),         # two of 64 rows, many columns
+    (2048, 256, "fc1", (64, 128, 1), True), (2560, 130, "qkv", (64, 128, 1), False),       # 64 tiles of columns, 60
+    (1536, 200, "qkv", (64, 128, 1), False),
+    (3584, 160, "fc1", (128, 128, 1), False), (2560, 260, "qkv", (128, 128, 1), False),    # a last row of tiles a quarter full, 4 rows
+    (3584, 260, "qkv", (128, 128, 1), False), (3584, 240, "qkv", (128, 128, 1), True),     # 112 of 128 rows, 111
+    (3584, 239, "qkv", (128, 128, 1), False), (4096, 250, "qkv", (128, 128, 1), True),
+    (4096, 256, "fc2", (128, 128, 4), False), (1024, 100, "fc2", None, False),             # k ranges
+    (4096, 4096, "fc1", (256, 256, 1), False),                                             # the big tiles
+])
+def test_weight_copies(H, rows, which, plan, streamed):
+    got = _plan(H, rows, which)
+    assert (plan is None or got[0] == plan) and got[1] == streamed, got
