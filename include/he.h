@@ -382,6 +382,11 @@ he_status he_plan_pass_gemm(const he_config* cfg, int rows, int which, int scori
 /* Test hook, host logic only: whether that launch (which = 0 .. 3) is one of the few-row tiles and copies its weights past the caches. */
 he_status he_plan_weight_copies(const he_config* cfg, int rows, int which, int scoring, int cus, int* streamed);
 
+/* Test hook, host logic only: what the attention launch of a decode step of B sequences fetches of the out-projection's weights for
+ * workgroup `workgroup` of the launch behind it, as byte offsets / 128 into the engine's copy of the matrix (the first `capacity` of them;
+ * *n_lines: all).  *workgroups: workgroups of that launch, 0 if nothing is fetched.  bf16, impl 0, B <= 64. */
+he_status he_plan_fetch_ahead(const he_config* cfg, int B, int workgroup, uint32_t* lines, int capacity, int* n_lines, int* workgroups);
+
 /* Test hook, host logic only: the kernel that computes the attention of B sequences with S rows each (S = 1: a decode step) in
  * an engine created with cfg, and the wavefronts of its workgroups.  cus as in he_plan_prompt_gemm.  bf16, impl 0 only. */
 enum {

@@ -147,6 +147,8 @@ def lib() -> C.CDLL:
     L.he_plan_attention.argtypes = [C.POINTER(he_config), C.c_int, C.c_int, C.c_int, C.POINTER(C.c_int), C.POINTER(C.c_int)]
     L.he_plan_weight_copies.restype = C.c_int
     L.he_plan_weight_copies.argtypes = [C.POINTER(he_config), C.c_int, C.c_int, C.c_int, C.c_int, C.POINTER(C.c_int)]
+    L.he_plan_fetch_ahead.restype = C.c_int
+    L.he_plan_fetch_ahead.argtypes = [C.POINTER(he_config), C.c_int, C.c_int, C.POINTER(C.c_uint32), C.c_int, C.POINTER(C.c_int), C.POINTER(C.c_int)]
     L.he_plan_plain_gemm.restype = C.c_int
     L.he_plan_plain_gemm.argtypes = [C.POINTER(he_config), C.c_int, C.c_int, C.c_int, C.POINTER(C.c_int)]
     L.he_kernel_sweep.restype = C.c_int
@@ -166,7 +168,8 @@ EXPORTS = ("he_workspace_bytes", "he_create", "he_refresh_weights", "he_prefill"
            "he_generate_ragged", "he_refresh_weights_lora", "he_release_arena", "he_acquire_arena",
            "he_tile_matrix_lora", "he_plan_decode_gemm", "he_fp8_quantize_rows", "he_decode_step_static",
            "he_decode_scratch_account", "he_arrival_counters_nonzero", "he_arrival_counters_set", "he_last_step_rows",
-           "he_plan_prompt_gemm", "he_plan_pass_gemm", "he_plan_attention", "he_plan_plain_gemm", "he_plan_weight_copies")
+           "he_plan_prompt_gemm", "he_plan_pass_gemm", "he_plan_attention", "he_plan_plain_gemm", "he_plan_weight_copies",
+           "he_plan_fetch_ahead")
 
 KERNEL_CLASSES = ("layernorm", "qkv", "attention", "out_proj", "fc1", "fc2", "lm_head", "empty")
 
@@ -446,6 +449,21 @@ def he_plan_weight_copies(cfg: he_config, rows: int, which: str, scoring=False, 
     if rc != HE_OK:
         raise HeError(rc, "he_plan_weight_copies")
     return bool(out.value)
+
+
+def he_plan_fetch_ahead(cfg: he_config, B: int):
+    """For each workgroup of a decode step's out-projection the lines of 128 bytes of its weights that the attention launch fetches."""
+    n, wgs = C.c_int(), C.c_int()
+    cap = cfg.hidden * cfg.hidden * 2 // 128
+    buf = (C.c_uint32 * cap)()
+    out = []
+    while True:
+        rc = lib().he_plan_fetch_ahead(C.byref(cfg), B, len(out), buf, cap, C.byref(n), C.byref(wgs))
+        if rc != HE_OK:
+            raise HeError(rc, "he_plan_fetch_ahead")
+        if len(out) >= wgs.value:
+            return out
+        out.append(buf[:n.value])
 
 
 ATTENTION_FORMS = ("two passes", "one pass", "short prompt", "prompt", "prompt split")

@@ -508,7 +508,7 @@ __global__ __launch_bounds__(256, 1) void gemm_tiled256_kernel(const u32x4* __re
     // One tile after another.  Between two of them nothing but this workgroup runs on the CU: the next tile's first stages are requested
     // as soon as everybody has read the last stage, ahead of the epilogue that covers their way.  (A workgroup per tile before, and an
     // epilogue of rows outside, columns inside: a four-layer prompt pass of 8192 rows, hidden 5120, 13.91 -> 13.68 ms, one of 2560
-    // rows 5.24 -> 5.15, twelve layers of 16384 rows, hidden 2048, and the scoring head 13.08 -> 12.42.)
+    // rows 5.24 -> 5.15, six layers of 16384 rows, hidden 2048, and the scoring head 13.08 -> 12.42.)
     for (;;) {
         const int nstage = it.nstage, tm = it.tm, tn = it.tn, ks = it.ks;
 #pragma unroll

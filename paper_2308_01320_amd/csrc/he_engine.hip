@@ -1334,6 +1334,19 @@ he_status he_plan_weight_copies(const he_config* cfg, int rows, int which, int s
     return HE_OK;
 }
 
+he_status he_plan_fetch_ahead(const he_config* cfg, int B, int workgroup, uint32_t* lines, int capacity, int* n_lines, int* workgroups) {
+    if (!n_lines || !workgroups || capacity < 0 || (capacity && !lines) || check_config(cfg) || check_shape(cfg) || !is_fast(*cfg)) return HE_ERR_INVALID_ARG;
+    if (B < 1 || B > cfg->max_batch || B > 64 || workgroup < 0) return HE_ERR_INVALID_ARG;
+    const bf16_ahead a = bf16_store_ahead(nullptr, B, cfg->hidden, cfg->hidden, sizes_of(*cfg).part / sizeof(float), cfg->weights_fp8);
+    *workgroups = a.wgs;
+    *n_lines = 0;
+    if (workgroup >= a.wgs) return HE_OK;
+    const bf16_ahead_share s = bf16_ahead_of(a, workgroup);
+    *n_lines = s.lines;
+    for (int l = 0; l < std::min(s.lines, capacity); ++l) lines[l] = (uint32_t)(bf16_ahead_line(a, s, l) / 128);
+    return HE_OK;
+}
+
 he_status he_plan_attention(const he_config* cfg, int B, int S, int cus, int* form, int* wavefronts) {
     if (!form || !wavefronts || check_config(cfg) || check_shape(cfg) || !is_fast(*cfg)) return HE_ERR_INVALID_ARG;
     if (B < 1 || B > cfg->max_batch || S < 1 || S > cfg->max_seq_len || (long)B * S > INT32_MAX || cus < 0) return HE_ERR_INVALID_ARG;

@@ -95,6 +95,19 @@ struct bf16_ahead {
     const void* w = nullptr;
     int wgs = 0, ks = 1, units = 1, n_units = 0, waves = 8, kbase = 0, kmore = 0, kb = 0, w8 = 0;  // as that kernel is launched
 };
+// workgroup j's share: units of column group grp, steps k0 .. k0 + n - 1 of k, in lines of 128 bytes; where line l of it lies
+struct bf16_ahead_share { int grp, k0, n, lines; };
+__host__ __device__ inline bf16_ahead_share bf16_ahead_of(const bf16_ahead& a, int j) {
+    const int grp = j / a.ks, p0 = (j - grp * a.ks) * a.waves, p1 = p0 + a.waves;
+    const int k0 = p0 * a.kbase + (p0 < a.kmore ? p0 : a.kmore), n = p1 * a.kbase + (p1 < a.kmore ? p1 : a.kmore) - k0;
+    return {grp, k0, n, a.units * n * 8};
+}
+__host__ __device__ inline size_t bf16_ahead_line(const bf16_ahead& a, const bf16_ahead_share& s, int l) {
+    const int q = l & 7, i = l >> 3, t = i / s.n, step = s.k0 + i - t * s.n;
+    const int u = s.grp * a.units + t, g = u < a.n_units - 1 ? u : a.n_units - 1;  // (past the last unit: it again)
+    return a.w8 ? ((size_t)g * (a.kb / 4) + step) * 1024 + q * 128
+                : (size_t)(g >> 1) * a.kb * 1024 + (size_t)step * 2048 + (q >> 1) * 512 + (g & 1) * 256 + (q & 1) * 128;
+}
 bf16_ahead bf16_store_ahead(const void* Wp, int M, int N, int K, size_t capacity, bool w8);
 size_t bf16_tiled_bytes(int rows, int K);
 void bf16_tile_rows(hipStream_t s, const void* src, void* dst, int R, int K);
