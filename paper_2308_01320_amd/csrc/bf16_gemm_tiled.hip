@@ -932,24 +932,27 @@ static RingPlan ring_plan(int M, int N, int KB, bool fused, size_t capacity_floa
 static int big_grid(int slots) { return std::min(slots, std::max(8, plan_cus() / 8 * 8)); }
 
 // Whether the weights' copies of the ring kernel are non-temporal.  A copy of what comes from HBM then moves 6.6 - 7.1 TB/s on 256 CUs instead
-// of 5.8, and the activations stay in L2.  One row of tiles: always, 1.02 - 1.18 times as fast per launch inside the engine (5120 x 20480 and 96 rows
-// 43.6 -> 39.8 us, 7168 x 28672 90.5 -> 76.7).  Several rows of halved tiles with whole sums share what one of them fetched only while they keep
-// together.  Measured alternately in one process, hidden 512 .. 7168, 66 .. 2000 rows, plain / streamed:
-//   64 tile rows, from 64 tiles of columns on    0.98 - 1.32 (12288 x 4096 and 96 rows 1.23, 14336 x 3584 and 120 rows 1.31), mean 1.09;
-//     fewer columns                              0.92 - 1.1 (60 tiles of columns 0.92 - 0.99, 36 0.94 - 0.99, 24 to 48 about 1);
-//   128 to 256, the last row of tiles at least   0.98 - 1.09 (8192 x 2048 and 512 rows 1.06), mean 1.01;
-//     seven eighths full, or less                0.81 - 1.07: a row of padding runs ahead of the others (14336 x 3584 and 160 rows 34.4 / 42.3 us).
-// With k ranges 0.77 - 1.05 (1024 x 4096 and 100 rows in ten ranges 7.2 -> 9.2 us), on 256 columns 0.93 - 1.03: plain.
-static bool ring_streams(int M, int N, int tile_rows, int wg_cols, int ksplit) {
+// of 5.8, and the activations stay in L2.  Matrices of 96 MB and more: a layer of such is more than the 256 MiB cache in front of memory holds,
+// while a model of narrower layers may be in there as a whole (two layers of hidden 2048, 384 rows: 155 us, streamed 169; twelve of 768, 64 rows 581 and
+// 608).  And several rows of tiles share what one of them fetched only while they keep together.  Plain / streamed per launch, measured
+// alternately in one process, such matrices of hidden 3584 .. 7168, 34 .. 1000 rows:
+//   one row of tiles                                  0.92 - 1.26, mean 1.07 (28672 x 7168 and 80 rows 88.5 / 75.4 us, 4096 x 16384 and 100 rows 33.4 / 25.7);
+//   several, 128 columns to a workgroup, whole sums:
+//     64 tile rows                                    0.95 - 1.32, mean 1.17 (12288 x 4096 and 96 rows 1.23, 14336 x 3584 and 120 rows 1.31);
+//     128 to 256, the last row of tiles at least seven eighths full  0.98 - 1.06, mean 1.01;
+//       or less                                       0.81 - 1.07: a row of padding runs ahead of the others (14336 x 3584 and 160 rows 34.4 / 42.3);
+//   several, k ranges or 256 columns                  0.77 - 1.05.
+static bool ring_streams(int M, int N, int KB, int tile_rows, int wg_cols, int ksplit) {
+    if ((size_t)N * KB * 32 < 96000000) return false;
     const int tiles_m = (M + tile_rows - 1) / tile_rows;
     if (tiles_m == 1) return true;
     if (wg_cols != 128 || ksplit > 1) return false;
-    return tile_rows == 64 ? N > 63 * 128 : 8 * (M - (tiles_m - 1) * tile_rows) >= 7 * tile_rows;
+    return tile_rows == 64 ? N > 63 * 128 : 8 * (M - (tiles_m - 1) * tile_rows) >= 7 * tile_rows;  // (columns: fewer lost, of smaller matrices)
 }
 template <int MODE, int NW, int MW>
 static void launch_ring(hipStream_t s, int grid, const u32x4* W, const u32x4* X, const u32x4* bias8, int KB, int NT32, int MT32, int tiles_n, int tiles_m,
                         int ksplit, const Epi& p) {
-    if (ring_streams(p.M, p.N, 64 * MW, 64 * NW, ksplit)) gemm_ring_kernel<MODE, NW, MW, true><<<grid, 256, 0, s>>>(W, X, bias8, KB, NT32, MT32, tiles_n, tiles_m, ksplit, p);
+    if (ring_streams(p.M, p.N, KB, 64 * MW, 64 * NW, ksplit)) gemm_ring_kernel<MODE, NW, MW, true><<<grid, 256, 0, s>>>(W, X, bias8, KB, NT32, MT32, tiles_n, tiles_m, ksplit, p);
     else gemm_ring_kernel<MODE, NW, MW, false><<<grid, 256, 0, s>>>(W, X, bias8, KB, NT32, MT32, tiles_n, tiles_m, ksplit, p);
 }
 
@@ -1078,7 +1081,7 @@ static int score_tile(int M, int V, int K) {
     return (double)((big + cus - 1) / cus) * (15.0 + 0.0238 * K) < two * (5.3 + 0.0335 * K) ? 4 : 0;
 }
 
-bool bf16_ring_streams(int M, int N, int tile_rows, int wg_cols, int ksplit) { return ring_streams(M, N, tile_rows, wg_cols, ksplit); }
+bool bf16_ring_streams(int M, int N, int K, int tile_rows, int wg_cols, int ksplit) { return ring_streams(M, N, K / 16, tile_rows, wg_cols, ksplit); }
 
 void bf16_pass_plan_query(int use, int M, int N, int K, size_t capacity_floats, int cus, int* tile_rows, int* tile_cols, int* wg_cols, int* ks,
                           int* split_col) {

@@ -1328,9 +1328,9 @@ he_status he_plan_weight_copies(const he_config* cfg, int rows, int which, int s
     if (!streamed || which > 3) return HE_ERR_INVALID_ARG;
     const he_status r = he_plan_pass_gemm(cfg, rows, which, scoring, cus, &p);
     if (r != HE_OK) return r;
-    const int H = cfg->hidden, F = cfg->ffn, N[] = {3 * H, H, F, H};
+    const int H = cfg->hidden, F = cfg->ffn, N[] = {3 * H, H, F, H}, K = which == 3 ? F : H;
     const bool few = p.workgroup_cols == 128 || p.tile_rows < 256;
-    *streamed = few && bf16_ring_streams(rows, N[which], p.tile_rows, p.workgroup_cols, p.ksplit);
+    *streamed = few && bf16_ring_streams(rows, N[which], K, p.tile_rows, p.workgroup_cols, p.ksplit);
     return HE_OK;
 }
 

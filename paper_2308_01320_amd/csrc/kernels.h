@@ -165,7 +165,7 @@ enum { TILED_STORE = 0, TILED_STORE_WHOLE = 1, TILED_FUSED = 2, TILED_LM_HEAD = 
 void bf16_pass_plan_query(int use, int M, int N, int K, size_t capacity_floats, int cus, int* tile_rows, int* tile_cols, int* wg_cols, int* ks,
                           int* split_col);
 // whether a launch of the few-row tiles copies its weights past the caches
-bool bf16_ring_streams(int M, int N, int tile_rows, int wg_cols, int ksplit);
+bool bf16_ring_streams(int M, int N, int K, int tile_rows, int wg_cols, int ksplit);
 // ---- 8-bit weight storage: E4M3 codes with one power-of-two scale per row
 size_t fp8_units_bytes(int rows, int K);  // codes in the half-tile kernel's units: [rows/16][K/64][64 lanes][16 bytes]
 void fp8_row_exponents(hipStream_t s, const void* src, int R, int K, int* exps, float* scales);  // e[n], 2^e[n]

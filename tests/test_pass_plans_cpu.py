@@ -27,15 +27,16 @@ def _plan(H, rows, which, scoring=False):
 
 
 @pytest.mark.parametrize("H,rows,which,plan,streamed", [
-    (4096, 96, "qkv", (128, 128, 2), True), (5120, 96, "fc1", (128, 128, 1), True),         # one row of tiles
-    (4096, 128, "qkv", (64, 128, 1), True), (3584, 120, "fc1", (64, 128, 1), True),         # two of 64 rows, many columns
-    (2048, 256, "fc1", (64, 128, 1), True), (2560, 130, "qkv", (64, 128, 1), False),       # 64 tiles of columns, 60
-    (1536, 200, "qkv", (64, 128, 1), False),
-    (3584, 160, "fc1", (128, 128, 1), False), (2560, 260, "qkv", (128, 128, 1), False),    # a last row of tiles a quarter full, 4 rows
-    (3584, 260, "qkv", (128, 128, 1), False), (3584, 240, "qkv", (128, 128, 1), True),     # 112 of 128 rows, 111
-    (3584, 239, "qkv", (128, 128, 1), False), (4096, 250, "qkv", (128, 128, 1), True),
-    (4096, 256, "fc2", (128, 128, 4), False), (1024, 100, "fc2", None, False),             # k ranges
-    (4096, 4096, "fc1", (256, 256, 1), False),                                             # the big tiles
+    (5120, 96, "fc1", (128, 128, 1), True), (4096, 96, "qkv", (128, 128, 2), True),         # one row of tiles; k ranges of 101 MB
+    (3584, 64, "qkv", (64, 128, 3), False), (5120, 64, "out_proj", (64, 128, 5), False),    # of 77, 52
+    (3072, 140, "fc2", (192, 128, 10), False), (768, 64, "fc1", (64, 128, 1), False),       # of 75; 5 MB
+    (4096, 128, "qkv", (64, 128, 1), True), (3584, 120, "fc1", (64, 128, 1), True),         # two of 64 rows, 101 and 103 MB
+    (2048, 256, "fc1", (64, 128, 1), False), (2560, 130, "qkv", (64, 128, 1), False),       # 34, 39 MB
+    (3584, 160, "fc1", (128, 128, 1), False), (4096, 239, "qkv", (128, 128, 1), False),     # a last row of tiles a quarter full, 111 of 128 rows
+    (4096, 240, "qkv", (128, 128, 1), True), (4096, 250, "fc1", (128, 128, 1), True),
+    (3584, 240, "qkv", (128, 128, 1), False), (2048, 512, "fc1", (128, 128, 1), False),     # 77, 34 MB
+    (4096, 256, "fc2", (128, 128, 4), False), (1024, 100, "fc2", None, False),              # k ranges
+    (4096, 4096, "fc1", (256, 256, 1), False),                                              # the big tiles
 ])
 def test_weight_copies(H, rows, which, plan, streamed):
     got = _plan(H, rows, which)
