@@ -36,10 +36,10 @@ __device__ __forceinline__ uint32_t pack2_bf16(float lo, float hi) { return f32x
 // gamma and beta go through LDS (a wavefront's own loads of them cost as much as its weights').  The k side of the products is permuted so
 // that a lane's accumulators are its own eight columns of each block.
 // us a launch with others around it, a kernel that tiles or merges on the vector units, then one that reads the tiles again for the vectors -> this:
-// 16384 x 4096, rank 16 61.7 + 28.9 -> 66, 12288 x 4096 49.2 + 23.9 -> 62 (384 workgroups on 256 CUs), 50272 x 4096 without an adapter 152 + 82 -> 164;
-// without vectors, plain 52.6 -> 47.3, rank 16 (4096 x 16384) 61.4 -> 55, rank 64 157 -> 114.  (Workgroups of 32 rows x 512 columns that leave partial sums
+// 16384 x 4096, rank 16 61.7 + 28.9 -> 64.5, 12288 x 4096 49.2 + 23.9 -> 61 (384 workgroups on 256 CUs), 50272 x 4096 without an adapter 152 + 82 -> 164;
+// without vectors, plain 52.6 -> 47.3, rank 16 (4096 x 16384) 61.4 -> 50, (4096 x 4096) 21 -> 15.5.  (Workgroups of 32 rows x 512 columns that leave partial sums
 // for another kernel to add, 67, 54 and 146 us, sum in another order: outputs of whole models moved by 5e-4.  The next 64 columns requested
-// ahead: 68, 63 and 165.)  The tiles are stored non-temporally: four layers of hidden 4096 with adapters and the head 1248 -> 1216 us, twelve of hidden
+// ahead, then the adapter's values: 68, 63 and 165.)  The tiles are stored non-temporally: four layers of hidden 4096 with adapters and the head 1248 -> 1216 us, twelve of hidden
 // 2048 650 -> 616, and with a decode step behind it 1061 -> 1025; the sources must not be loaded so (1248 -> 1434: four loads share a cache line).
 typedef float f32x32 __attribute__((ext_vector_type(32)));
 constexpr int kMergeBlocks = 4;                               // blocks of 16 columns at a time: two accumulator tiles
@@ -81,15 +81,16 @@ __global__ __launch_bounds__(64 * kMergeWaves) void tile_merge_kernel(const bf16
         if (FOLD) q.v = reinterpret_cast<const u32x4*>(lane & 2 * U ? beta : gamma)[min(2 * kb + (lane & (2 * U - 1)), 2 * kb1 - 1)];
     };
     Round cur;
-    load(cur, kb0);
-    if constexpr (LORA == LORA_NONE && !FOLD) {  // (all four loads before the first of them is used)
-#pragma unroll
-        for (int u = 0; u < U; ++u) asm volatile("" : "+v"(cur.w[u]));
-    }
     float a1 = 0.f, a2 = 0.f;
     for (int round = 0; round < rounds; ++round) {
         const int kb = kb0 + round * U, nb = min(U, kb1 - kb);
         [[maybe_unused]] f32x32 t = {};
+        // (the adapter's first values ahead of the weights: loads return in order, and its products need not wait for them)
+        if constexpr (LORA == LORA_NONE) load(cur, kb);
+        if constexpr (LORA == LORA_NONE && !FOLD) {  // (all four loads before the first of them is used)
+#pragma unroll
+            for (int u = 0; u < U; ++u) asm volatile("" : "+v"(cur.w[u]));
+        }
         if constexpr (LORA != LORA_NONE) {
             // accumulator 4 q + e of a lane belongs to column 8 q + 4 (lane / 32) + e of the instruction: that is fed column
             // 16 (q / 2) + 8 (lane / 32) + 4 (q % 2) + e of the matrix
@@ -104,6 +105,7 @@ __global__ __launch_bounds__(64 * kMergeWaves) void tile_merge_kernel(const bf16
                     for (int x = 0; x < G; ++x) v[x] = ap[(size_t)min(j0 + x, rank - 1) * K];
                 };
                 load_a(aj, 0);
+                load(cur, kb);
                 for (int j0 = 0; j0 < rank; j0 += kMergeRanks) {  // (every wavefront, with blocks left or not: there are barriers)
                     const int n = min(kMergeRanks, rank - j0);
                     if (round == 0 || rank > kMergeRanks) {
@@ -136,6 +138,7 @@ __global__ __launch_bounds__(64 * kMergeWaves) void tile_merge_kernel(const bf16
                         aj[x] = ap[(size_t)j * K];
                         if constexpr (LORA == LORA_FEW) bj[x] = bp[j];
                     }
+                    if (j0 == 0) load(cur, kb);
                     const uint32_t bw[4] = {b8.x, b8.y, b8.z, b8.w};
 #pragma unroll
                     for (int x = 0; x < G; ++x) {
@@ -184,7 +187,6 @@ __global__ __launch_bounds__(64 * kMergeWaves) void tile_merge_kernel(const bf16
             }
         }
         __builtin_amdgcn_wave_barrier();
-        if (FOLD) load(cur, kb + U);
     }
     if constexpr (FOLD) {
         a1 = lane_sum32_apart(a1);
